@@ -33,4 +33,5 @@ void dev_launch_n12(DevLaunch &t)
     t.fwd_blocks = launch_fwd_blocks<12>;
     t.inv_blocks = launch_inv_blocks<12>;
     t.inner = launch_inner<12>;
+    t.inner_fin = launch_inner_fin<12>;
 }

@@ -6,4 +6,5 @@ void dev_launch_n17_blocks(DevLaunch &t)
     t.fwd_blocks = launch_fwd_blocks<17>;
     t.inv_blocks = launch_inv_blocks<17>;
     t.inner = launch_inner<17>;
+    t.inner_fin = launch_inner_fin<17>;
 }

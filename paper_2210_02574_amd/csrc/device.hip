@@ -6,11 +6,12 @@
 //   1. inverse NTT of d, its column pass also multiplying limb i by (D/q_i)^-1      -> y  (ws.x)
 //   2. forward NTT of every raised limb (digit j, modulus t outside the digit), the
 //      column pass summing y_i (D/q_i mod t) on the fly (ModUp)                     -> raised
-//   3. inner product with the key, reading the digits through the index map of g
-//      and the digit's own limbs straight from d                                     -> u
-//   4. inverse NTT of the special limbs of u, scaled by (P/p_k)^-1                   (in place)
-//   5. forward NTT of the 2*level ModDown corrections, column pass summing
-//      y_k (P/p_k mod q_i) over centred digits y_k, block pass finishing out = (u - ntt) P^-1 + addend       -> out
+//   3. inner product with the key on the special limbs, reading the digits through the index map of g -> u
+//   4. inverse NTT of these, scaled by (P/p_k)^-1                                    (in place)
+//   5. column pass of the forward NTT of the 2*level ModDown corrections, summing
+//      y_k (P/p_k mod q_i) over centred digits y_k                                     -> r
+//   6. inner product on the ciphertext limbs (the digit's own limbs straight from d), block pass of r and
+//      out = (u - r) P^-1 + addend, in one kernel                                      -> out
 // Hoisted rotations share steps 1-2.
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
@@ -82,7 +83,7 @@ int32_t dev_upload_tables(he_ctx *c)
 #define UP(field)                                                                                                    \
     if ((rc = upload(c, c->field, &c->dev.field)) != HE_OK) return rc;
     if ((rc = upload(c, c->modc, &c->dev.mod)) != HE_OK) return rc;
-    UP(tw_fwd) UP(tw_inv) UP(ninv) UP(twd_fwd) UP(twd_inv) UP(ninvd)
+    UP(tw_fwd) UP(tw_inv) UP(ninv) UP(twd_fwd) UP(twd_blk) UP(twd_inv) UP(ninvd)
     UP(up_inv) UP(up_hat) UP(up_inv_d) UP(up_hat_d) UP(up_hat_dh) UP(rq) UP(up_dmod) UP(up_dmod_d) UP(up_hat_p) UP(dn_r50_d)
     UP(dn_inv) UP(dn_hat) UP(dn_pinv) UP(dn_inv_d) UP(dn_hat_d) UP(dn_hat_dh) UP(dn_pinv_d) UP(dn_pmod) UP(dn_pmod_d)
     UP(rs_inv) UP(rs_inv_d) UP(rsp_inv) UP(rsp_inv_d)
@@ -176,7 +177,7 @@ extern "C" int32_t he_evk_to_host(const he_evk *evk, uint64_t *h_out)
 static const char *const kKernelNames[KID_COUNT] = {
     "k_ntt_fwd_cols", "k_ntt_fwd_cols_modup", "k_ntt_fwd_cols_moddown", "k_ntt_fwd_cols_rescale", "k_ntt_fwd_cols_moddown_rescale",
     "k_ntt_fwd_blocks",
-    "k_ntt_fwd_blocks_fin", "k_ntt_inv_blocks", "k_ntt_inv_cols", "k_limbwise", "k_cmult", "k_tensor", "k_inner_blocks"};
+    "k_ntt_fwd_blocks_fin", "k_ntt_inv_blocks", "k_ntt_inv_cols", "k_limbwise", "k_cmult", "k_tensor", "k_inner_blocks", "k_inner_fin"};
 
 bool prof_events(he_ctx *c, int kid, double bytes, ProfRecord &r)
 {
@@ -326,21 +327,8 @@ static ConvArgs conv_args(const he_ctx *c, const u64 *src, int level, int dst_st
     return cv;
 }
 
-static FinArgs fin_args(const u64 *u, u64 *out, const u64 *add, const ShoupConst *cst, const double *cst_d, int u_cstride,
-                        int nl, int mode, unsigned g, int dst_stride, int u_stride, int out_stride, int add_stride)
-{
-    FinArgs fa;
-    fa.u = u, fa.out = out, fa.add = add, fa.self = nullptr;
-    fa.cst = cst, fa.cst_d = cst_d, fa.cst2 = nullptr, fa.cst2_d = nullptr;
-    fa.u_cstride = u_cstride, fa.out_cstride = nl, fa.add_cstride = nl, fa.self_stride = 0, fa.nl = nl, fa.mode = mode;
-    fa.g = g;
-    fa.hoisted = 0;
-    fa.dst_stride = dst_stride, fa.u_stride = u_stride, fa.out_stride = out_stride, fa.add_stride = add_stride;
-    return fa;
-}
-static const HoistOuts kNoHoistOuts = {};
-static const HoistKeys kNoHoistKeys = {};
-static const FinArgs kNoFin = fin_args(nullptr, nullptr, nullptr, nullptr, nullptr, 0, 1, 0, 1u, 1 << 30, 0, 0, 0);
+static const FinArgs kNoFin = {nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, 0, 1, 1 << 30, 0, 0, 0};
+static const OpArgs kNoOps = {};
 
 // Forward NTT of the listed limbs of `data`.  pro selects what the column pass transforms (the
 // limb's own content, or a base conversion of cv.src); with fin != nullptr the block pass writes
@@ -349,10 +337,8 @@ static const FinArgs kNoFin = fin_args(nullptr, nullptr, nullptr, nullptr, nullp
 // int_blocks_only: the block pass runs only for limbs on the integer path (the others are finished by the
 // kernel that consumes them).
 static int32_t ntt_forward(he_ctx *c, hipStream_t st, u64 *data, const LimbList &l, int pro, const ConvArgs &cv,
-                           const FinArgs *fin, int src_limbs, bool int_blocks_only = false,
-                           const HoistOuts *hoist = nullptr)
+                           const FinArgs *fin, int src_limbs, bool int_blocks_only = false)
 {
-    const HoistOuts &ho = hoist ? *hoist : kNoHoistOuts;
     const bool wide = std::max(c->alpha, c->K) > 4;
     const double N8 = (double)c->N * 8.0;
     const DevLaunch &dl = dev_launch(c);
@@ -366,10 +352,9 @@ static int32_t ntt_forward(he_ctx *c, hipStream_t st, u64 *data, const LimbList 
         (cv.exact && dl.fwd_cols_ex[pro] ? dl.fwd_cols_ex[pro] : dl.fwd_cols[pro])(c, st, kid_cols, cols_bytes, wide, data, lb, nb, cv);
         if (fin) {
             // reads the transform's input, the minuend and the addend, writes the result
-            const double b = (double)nb * N8 * (3.0 + (fin->mode == 1 || fin->mode == 3 ? 1.0 : fin->mode == 2 ? 0.5 : fin->mode == 4 ? 1.5 : 0.0));
-            dl.fwd_blocks(c, st, b, true, data, lb, nb, *fin, ho);
+            dl.fwd_blocks(c, st, (double)nb * N8 * (fin->add ? 4.0 : 3.0), true, data, lb, nb, *fin);
         } else if (!int_blocks_only)
-            dl.fwd_blocks(c, st, 2.0 * nb * N8, false, data, lb, nb, kNoFin, kNoHoistOuts);
+            dl.fwd_blocks(c, st, 2.0 * nb * N8, false, data, lb, nb, kNoFin);
     });
     if (rc != HE_OK || !int_blocks_only) return rc;
     // block pass of the integer-path limbs alone, after all column passes: few launches, each as large as possible
@@ -377,7 +362,7 @@ static int32_t ntt_forward(he_ctx *c, hipStream_t st, u64 *data, const LimbList 
     for (int b = 0; b < l.size(); b++)
         if (c->modc[l.mod[b]].qd == 0.0) li.add(l.slot[b], l.src[b], l.mod[b]);
     return for_batches(c, li, [&](const LimbBatch &lb, int nb) {
-        dl.fwd_blocks(c, st, 2.0 * nb * N8, false, data, lb, nb, kNoFin, kNoHoistOuts);
+        dl.fwd_blocks(c, st, 2.0 * nb * N8, false, data, lb, nb, kNoFin);
     });
 }
 
@@ -645,64 +630,112 @@ static int32_t ks_raise(he_ctx *c, const u64 *d_ntt, int d_stride, u64 *ws, cons
     return ntt_forward(c, st, ws + w.raised * N, r, PRO_MODUP, cv, nullptr, level * count, true);
 }
 
-// Step 3 and the inverse transform of step 4: u and, in its special limbs, the scaled coefficient-domain digits.
-// hoist != nullptr: `count` rotations of one raised input (operation 0's workspace), operation o with key hoist->evk[o].
-// shared_raised = false: per-operation keys as well, but every operation has its own raised input.
-static int32_t ks_inner(he_ctx *c, const he_evk *evk, const u64 *d_ntt, int d_stride, u64 *ws, const WsLayout &w,
-                        int level, int count, hipStream_t st, const HoistKeys *hoist = nullptr, bool shared_raised = true)
+static InnerArgs inner_args(const he_ctx *c, const he_evk *evk, const u64 *d_ntt, int d_stride, u64 *ws, const WsLayout &w,
+                            int level, int count, const OpArgs *oa, bool shared_raised)
+{
+    InnerArgs ia;
+    ia.raised = ws + w.raised * c->N, ia.d = d_ntt, ia.evk = evk->dev, ia.u = ws + w.u * c->N;
+    ia.level = level, ia.L = c->L, ia.K = c->K, ia.alpha = c->alpha, ia.first = level;
+    ia.g = (unsigned)evk->galois;
+    ia.raised_stride = shared_raised ? 0 : (int)w.total, ia.u_stride = (int)w.total, ia.d_stride = d_stride;
+    ia.per_op = oa ? 1 : 0, ia.count = count;
+    return ia;
+}
+// Words per index that the inner product has to move on the active limbs [lo, hi), by the definition of the step and
+// each operand once per launch: per operation its digits (once for all if they share them), and 2 key words per digit
+// for each distinct key, up to the highest level it is used at.
+static double inner_words(const he_ctx *c, const InnerArgs &ia, const OpArgs *oa, int lo, int hi)
+{
+    auto limbs = [&](int level) { // active limbs of an operation at `level` within [lo, hi)
+        return std::max(0, std::min(hi, level) - lo) + std::max(0, hi - std::max(lo, ia.level));
+    };
+    double words = 0.0;
+    std::vector<std::pair<const u64 *, int>> keys;
+    for (int o = 0; o < ia.count; o++) {
+        const int level = oa && oa->level[o] ? oa->level[o] : ia.level, beta = (level + c->alpha - 1) / c->alpha;
+        const u64 *key = oa ? oa->evk[o] : ia.evk;
+        if (o == 0 || ia.raised_stride != 0) words += (double)beta * limbs(level);
+        auto k = std::find_if(keys.begin(), keys.end(), [&](const std::pair<const u64 *, int> &e) { return e.first == key; });
+        if (k == keys.end())
+            keys.push_back({key, level});
+        else
+            k->second = std::max(k->second, level);
+    }
+    for (const auto &k : keys) words += 2.0 * ((k.second + c->alpha - 1) / c->alpha) * limbs(k.second);
+    return words;
+}
+
+// Steps 3 and 4: the scaled coefficient-domain digits of the special limbs, in u.  ia.first < level: also u on the
+// limbs from there on.
+static int32_t ks_special(he_ctx *c, const InnerArgs &ia, const OpArgs *oa, const WsLayout &w, hipStream_t st)
 {
     const size_t N = c->N;
-    const int K = c->K, Ma = level + K, beta = (level + c->alpha - 1) / c->alpha, W = (int)w.total;
-    const unsigned g = (unsigned)evk->galois;
-    if (misaligned16(ws) || misaligned16(d_ntt) || misaligned16(evk->dev)) return HE_EINVAL; // entry points check first
-    dim3 grid(inner_grid((unsigned)(N / INNER_TILE), (unsigned)Ma, (unsigned)count));
-    InnerArgs ia;
-    ia.raised = ws + w.raised * N, ia.d = d_ntt, ia.evk = evk->dev, ia.u = ws + w.u * N;
-    ia.level = level, ia.L = c->L, ia.K = K, ia.alpha = c->alpha, ia.beta = beta;
-    ia.g = g, ia.raised_stride = hoist && shared_raised ? 0 : W, ia.u_stride = W, ia.d_stride = d_stride, ia.inv_special = 1;
-    ia.hoisted = hoist ? 1 : 0, ia.count = count;
-    const HoistKeys &hk = hoist ? *hoist : kNoHoistKeys;
-    // Bytes by the definition of the step, each operand once per launch: every operation writes 2 limbs per active
-    // modulus; beta digits per active modulus are read once per raised input (one for hoisted rotations, else one
-    // per operation); 2 beta key limbs per active modulus are read once per distinct key of the launch.
-    int keys = 1;
-    if (hoist) {
-        std::vector<const u64 *> seen(hoist->evk, hoist->evk + count);
-        std::sort(seen.begin(), seen.end());
-        keys = (int)(std::unique(seen.begin(), seen.end()) - seen.begin());
-    }
-    const int inputs = hoist && shared_raised ? 1 : count;
-    const double inner_bytes = ((double)inputs * beta + 2.0 * count + 2.0 * beta * keys) * Ma * N * 8.0;
-    dev_launch(c).inner(c, st, inner_bytes, grid.x, ia, hk);
+    const int K = c->K, Ma = ia.level + K, W = (int)w.total;
+    if (misaligned16(ia.raised) || misaligned16(ia.d) || misaligned16(ia.evk)) return HE_EINVAL; // entry points check first
+    const double bytes = (inner_words(c, ia, oa, ia.first, Ma) + 2.0 * ia.count * (Ma - ia.first)) * N * 8.0;
+    dev_launch(c).inner(c, st, bytes, inner_grid((unsigned)(N / INNER_TILE), (unsigned)(Ma - ia.first), (unsigned)ia.count), ia,
+                        oa ? *oa : kNoOps);
     int32_t rc = launch_ok(c);
     if (rc != HE_OK) return rc;
     LimbList sp;
-    for (int o = 0; o < count; o++)
+    for (int o = 0; o < ia.count; o++)
         for (int cc = 0; cc < 2; cc++)
-            for (int k = 0; k < K; k++) sp.add(o * W + cc * Ma + level + k, c->L + k);
-    const ConvArgs cv = conv_args(c, ws + w.u * N, level, W, W);
-    return ntt_inverse(c, st, ws + w.u * N, ws + w.u * N, sp, SCALE_MODDOWN, cv, true);
+            for (int k = 0; k < K; k++) sp.add(o * W + cc * Ma + ia.level + k, c->L + k);
+    const ConvArgs cv = conv_args(c, ia.u, ia.level, W, W);
+    return ntt_inverse(c, st, ia.u, ia.u, sp, SCALE_MODDOWN, cv, true);
 }
 
-// Steps 3-5.  Operation o writes out + o*out_stride limbs; mode / c0 (+ o*c0_stride): the addend of
-// the final step (see FinArgs).
-static int32_t ks_apply(he_ctx *c, const he_evk *evk, const u64 *d_ntt, int d_stride, u64 *ws, const WsLayout &w,
-                        int level, int count, u64 *out, int out_stride, const u64 *c0, int c0_stride, int mode,
-                        hipStream_t st)
+// Steps 5 and 6 on the first fa.nl limbs of every operation (those that it has): pro is the prologue of the
+// corrections' column pass, `extra` the source limbs it reads besides the special ones.
+static int32_t ks_finish(he_ctx *c, const InnerArgs &ia, const OpArgs *oa, const WsLayout &w, u64 *ws, FinishArgs fa, int mode, int pro,
+                         const ConvArgs &cv, int extra, hipStream_t st)
 {
     const size_t N = c->N;
-    const int Ma = level + c->K, W = (int)w.total;
-    int32_t rc = ks_inner(c, evk, d_ntt, d_stride, ws, w, level, count, st);
-    if (rc != HE_OK) return rc;
-    const ConvArgs cv = conv_args(c, ws + w.u * N, level, W, W);
-    LimbList r;
-    for (int o = 0; o < count; o++)
+    const int W = (int)w.total;
+    u64 *r = ws + w.r * N;
+    LimbList l;
+    double words = inner_words(c, ia, oa, 0, fa.nl);
+    for (int o = 0; o < ia.count; o++) {
+        const int limbs = std::min(oa && oa->level[o] ? oa->level[o] : ia.level, fa.nl);
         for (int cc = 0; cc < 2; cc++)
-            for (int i = 0; i < level; i++) r.add(o * W + cc * level + i, i);
-    FinArgs fa = fin_args(ws + w.u * N, out, c0, c->dev.dn_pinv, c->dev.dn_pinv_d, Ma, level, mode,
-                          (unsigned)evk->galois, W, W, out_stride, c0_stride);
-    if (mode == 4) fa.self = c0, fa.self_stride = c0_stride; // c0 points at the whole input ciphertext [2][level][N]
-    return ntt_forward(c, st, ws + w.r * N, r, PRO_MODDOWN, cv, &fa, 2 * c->K * count);
+            for (int i = 0; i < limbs; i++) l.add(o * W + cc * ia.level + i, i);
+        words += limbs * (4.0 + (mode == FIN_ADD ? 2.0 : mode == FIN_ROT ? 1.0 : 3.0)); // r, results, addends
+    }
+    int32_t rc = ntt_forward(c, st, r, l, pro, cv, nullptr, 2 * c->K * ia.count + extra, true);
+    if (rc != HE_OK) return rc;
+    fa.r = r, fa.r_stride = W;
+    const unsigned grid = inner_grid((unsigned)(N / INNER_TILE), (unsigned)fa.nl, (unsigned)ia.count);
+    int n_int = 0;
+    for (int i = 0; i < fa.nl; i++) n_int += c->modc[i].qd == 0.0 ? 1 : 0;
+    const OpArgs &ops = oa ? *oa : kNoOps;
+    for (int integer = 1; integer >= 0; integer--) {
+        const int limbs = integer ? n_int : fa.nl - n_int;
+        if (!limbs) continue;
+        dev_launch(c).inner_fin(c, st, words * N * 8.0 * limbs / fa.nl, grid, mode, integer != 0, ia, fa, ops);
+        if ((rc = launch_ok(c)) != HE_OK) return rc;
+    }
+    return HE_OK;
+}
+
+static FinishArgs finish_args(const he_ctx *c, u64 *out, int out_stride, const u64 *add, int add_stride, int add_cstride, int level)
+{
+    FinishArgs fa;
+    fa.r = nullptr, fa.out = out, fa.add = add;
+    fa.cst = c->dev.dn_pinv, fa.cst2 = nullptr, fa.cst_d = c->dev.dn_pinv_d, fa.cst2_d = nullptr;
+    fa.nl = level, fa.r_stride = 0, fa.out_stride = out_stride, fa.out_cstride = level;
+    fa.add_stride = add_stride, fa.add_cstride = add_cstride;
+    return fa;
+}
+
+// Steps 3-6 of one or more key switches that keep their level.
+static int32_t ks_apply(he_ctx *c, const InnerArgs &ia, const OpArgs *oa, u64 *ws, const WsLayout &w, const FinishArgs &fa, int mode,
+                        hipStream_t st)
+{
+    const int W = (int)w.total;
+    int32_t rc = ks_special(c, ia, oa, w, st);
+    if (rc != HE_OK) return rc;
+    const ConvArgs cv = conv_args(c, ws + w.u * c->N, ia.level, W, W);
+    return ks_finish(c, ia, oa, w, ws, fa, mode, PRO_MODDOWN, cv, 0, st);
 }
 
 static int32_t ks_guard(he_ctx *c, const he_evk *evk, int level, int count, void *ws, size_t ws_bytes)
@@ -735,7 +768,9 @@ extern "C" int32_t he_hmult_relin_batch(he_ctx *ctx, const he_evk *relin, const 
             level, ctx->logN, W, 2 * level);
     if ((rc = launch_ok(ctx)) != HE_OK) return rc;
     if ((rc = ks_raise(ctx, ws + w.d * N, W, ws, w, level, count, st)) != HE_OK) return rc;
-    return ks_apply(ctx, relin, ws + w.d * N, W, ws, w, level, count, d_out, 2 * level, nullptr, 0, 1, st);
+    // d0 and d1 wait in d_out
+    return ks_apply(ctx, inner_args(ctx, relin, ws + w.d * N, W, ws, w, level, count, nullptr, false), nullptr, ws, w,
+                    finish_args(ctx, d_out, 2 * level, d_out, 2 * level, level, level), FIN_ADD, st);
 }
 
 extern "C" int32_t he_hmult_relin(he_ctx *ctx, const he_evk *relin, const uint64_t *d_a, const uint64_t *d_b,
@@ -767,7 +802,9 @@ extern "C" int32_t he_hmult_relin_rescale_batch(he_ctx *ctx, const he_evk *relin
             level, ctx->logN, W, W);
     if ((rc = launch_ok(ctx)) != HE_OK) return rc;
     if ((rc = ks_raise(ctx, ws + w.d * N, W, ws, w, level, count, st)) != HE_OK) return rc;
-    if ((rc = ks_inner(ctx, relin, ws + w.d * N, W, ws, w, level, count, st)) != HE_OK) return rc;
+    InnerArgs ia = inner_args(ctx, relin, ws + w.d * N, W, ws, w, level, count, nullptr, false);
+    ia.first = level - 1; // the dropped limb as well
+    if ((rc = ks_special(ctx, ia, nullptr, w, st)) != HE_OK) return rc;
     u64 *rbuf = ws + w.r * N;
     ConvArgs cv = conv_args(ctx, ws + w.u * N, level, W, W);
     cv.src2 = rbuf;
@@ -776,20 +813,15 @@ extern "C" int32_t he_hmult_relin_rescale_batch(he_ctx *ctx, const he_evk *relin
     LimbList last;
     for (int o = 0; o < count; o++)
         for (int cc = 0; cc < 2; cc++) last.add(o * W + cc * level + level - 1, level - 1);
-    FinArgs fl = fin_args(ws + w.u * N, rbuf, d01, ctx->dev.dn_pinv, ctx->dev.dn_pinv_d, Ma, level, 3, 1u, W, W, W, W);
+    const FinArgs fl = {ws + w.u * N, rbuf, d01, ctx->dev.dn_pinv, ctx->dev.dn_pinv_d, Ma, level, level, level, W, W, W, W};
     if ((rc = ntt_forward(ctx, st, rbuf, last, PRO_MODDOWN, cv, &fl, 2 * K * count)) != HE_OK) return rc;
     if ((rc = ntt_inverse(ctx, st, rbuf, rbuf, last, SCALE_NONE, cv)) != HE_OK) return rc;
     // every other limb: ModDown and rescale corrections in one transform
-    LimbList rest;
-    for (int o = 0; o < count; o++)
-        for (int cc = 0; cc < 2; cc++)
-            for (int i = 0; i < level - 1; i++) rest.add(o * W + cc * level + i, i);
-    FinArgs fa = fin_args(ws + w.u * N, d_out, d01, ctx->dev.rsp_inv + (size_t)(level - 1) * L,
-                          ctx->dev.rsp_inv_d + (size_t)(level - 1) * L, Ma, level, 3, 1u, W, W, 2 * (level - 1), W);
-    fa.out_cstride = level - 1;
-    fa.cst2 = ctx->dev.rs_inv + (size_t)(level - 1) * L;
-    fa.cst2_d = ctx->dev.rs_inv_d + (size_t)(level - 1) * L;
-    return ntt_forward(ctx, st, rbuf, rest, PRO_MODDOWN_RS, cv, &fa, (2 * K + 2) * count);
+    FinishArgs fa = finish_args(ctx, d_out, 2 * (level - 1), d01, W, level, level);
+    fa.nl = fa.out_cstride = level - 1;
+    fa.cst = ctx->dev.rsp_inv + (size_t)(level - 1) * L, fa.cst_d = ctx->dev.rsp_inv_d + (size_t)(level - 1) * L;
+    fa.cst2 = ctx->dev.rs_inv + (size_t)(level - 1) * L, fa.cst2_d = ctx->dev.rs_inv_d + (size_t)(level - 1) * L;
+    return ks_finish(ctx, ia, nullptr, w, ws, fa, FIN_ADD, PRO_MODDOWN_RS, cv, 2 * count, st);
 }
 
 extern "C" int32_t he_hmult_relin_rescale(he_ctx *ctx, const he_evk *relin, const uint64_t *d_a, const uint64_t *d_b,
@@ -814,35 +846,22 @@ extern "C" int32_t he_hrot_many(he_ctx *ctx, const he_evk *const *rots, int32_t 
     const WsLayout w = ws_layout(ctx, level);
     const u64 *c1 = d_ct + (size_t)level * ctx->N;
     if ((rc = ks_raise(ctx, c1, 0, ws, w, level, 1, st)) != HE_OK) return rc;
-    const size_t N = ctx->N;
-    const int W = (int)w.total, Ma = level + ctx->K;
     // With workspace for several operations the rotations share every launch: operation o keeps its inner
     // products and ModDown corrections in workspace o, all read the raised digits of workspace 0.
-    const int fit = (int)std::min<size_t>(ws_bytes / (w.total * N * sizeof(u64)), HOIST_MAX);
-    int r = 0;
-    while (fit >= 2 && count - r >= 2 && batch_fits(w, std::min(fit, count - r))) {
+    int fit = (int)std::min<size_t>(ws_bytes / (w.total * ctx->N * sizeof(u64)), HE_OPS_MAX);
+    while (fit > 1 && !batch_fits(w, fit)) fit--;
+    for (int r = 0; r < count;) {
         const int nb = std::min(fit, count - r);
-        HoistKeys hk = {};
-        HoistOuts ho = {};
+        OpArgs oa = {};
         for (int o = 0; o < nb; o++) {
-            hk.evk[o] = rots[r + o]->dev;
-            hk.g[o] = ho.g[o] = (unsigned)rots[r + o]->galois;
-            ho.out[o] = h_d_outs[r + o];
+            oa.evk[o] = rots[r + o]->dev, oa.g[o] = (unsigned)rots[r + o]->galois;
+            oa.d[o] = c1, oa.add[o] = d_ct, oa.out[o] = h_d_outs[r + o];
         }
-        if ((rc = ks_inner(ctx, rots[r], c1, 0, ws, w, level, nb, st, &hk)) != HE_OK) return rc;
-        const ConvArgs cv = conv_args(ctx, ws + w.u * N, level, W, W);
-        LimbList lr;
-        for (int o = 0; o < nb; o++)
-            for (int cc = 0; cc < 2; cc++)
-                for (int i = 0; i < level; i++) lr.add(o * W + cc * level + i, i);
-        FinArgs fa = fin_args(ws + w.u * N, nullptr, d_ct, ctx->dev.dn_pinv, ctx->dev.dn_pinv_d, Ma, level, 2, 1u, W, W, 0, 0);
-        fa.hoisted = 1;
-        if ((rc = ntt_forward(ctx, st, ws + w.r * N, lr, PRO_MODDOWN, cv, &fa, 2 * ctx->K * nb, false, &ho)) != HE_OK)
+        if ((rc = ks_apply(ctx, inner_args(ctx, rots[r], c1, 0, ws, w, level, nb, &oa, true), &oa, ws, w,
+                           finish_args(ctx, nullptr, 0, d_ct, 0, level, level), FIN_ROT, st)) != HE_OK)
             return rc;
         r += nb;
     }
-    for (; r < count; r++)
-        if ((rc = ks_apply(ctx, rots[r], c1, 0, ws, w, level, 1, h_d_outs[r], 0, d_ct, 0, 2, st)) != HE_OK) return rc;
     return HE_OK;
 }
 
@@ -859,7 +878,8 @@ static int32_t hrot_batch_to(he_ctx *ctx, const he_evk *rot, const u64 *d_ct, in
     const WsLayout w = ws_layout(ctx, level);
     const u64 *c1 = d_ct + (size_t)level * ctx->N;
     if ((rc = ks_raise(ctx, c1, in_stride, ws, w, level, count, st)) != HE_OK) return rc;
-    return ks_apply(ctx, rot, c1, in_stride, ws, w, level, count, d_out, out_stride, d_ct, in_stride, plus_input ? 4 : 2, st);
+    return ks_apply(ctx, inner_args(ctx, rot, c1, in_stride, ws, w, level, count, nullptr, false), nullptr, ws, w,
+                    finish_args(ctx, d_out, out_stride, d_ct, in_stride, level, level), plus_input ? FIN_ROTSUM : FIN_ROT, st);
 }
 
 extern "C" int32_t he_hrot_batch(he_ctx *ctx, const he_evk *rot, const uint64_t *d_ct, uint64_t *d_out, int32_t level,
@@ -900,29 +920,20 @@ extern "C" int32_t he_hrot_batch_keys(he_ctx *ctx, const he_evk *const *rots, co
     u64 *ws = (u64 *)d_ws;
     const WsLayout w = ws_layout(ctx, level);
     const size_t N = ctx->N;
-    const int W = (int)w.total, Ma = level + ctx->K, ct_limbs = 2 * level;
-    int fit = (int)std::min<size_t>(ws_bytes / (w.total * N * sizeof(u64)), HOIST_MAX);
+    const int ct_limbs = 2 * level;
+    int fit = (int)std::min<size_t>(ws_bytes / (w.total * N * sizeof(u64)), HE_OPS_MAX);
     while (fit > 1 && !batch_fits(w, fit)) fit--;
     for (int r = 0; r < count;) {
         const int nb = std::min(fit, count - r);
         const u64 *in = d_ct + (size_t)r * ct_limbs * N, *c1 = in + (size_t)level * N;
         if ((rc = ks_raise(ctx, c1, ct_limbs, ws, w, level, nb, st)) != HE_OK) return rc;
-        HoistKeys hk = {};
-        HoistOuts ho = {};
+        OpArgs oa = {};
         for (int o = 0; o < nb; o++) {
-            hk.evk[o] = rots[r + o]->dev;
-            hk.g[o] = ho.g[o] = (unsigned)rots[r + o]->galois;
-            ho.out[o] = d_out + (size_t)(r + o) * ct_limbs * N;
+            oa.evk[o] = rots[r + o]->dev, oa.g[o] = (unsigned)rots[r + o]->galois;
+            oa.out[o] = d_out + (size_t)(r + o) * ct_limbs * N;
         }
-        if ((rc = ks_inner(ctx, rots[r], c1, ct_limbs, ws, w, level, nb, st, &hk, false)) != HE_OK) return rc;
-        const ConvArgs cv = conv_args(ctx, ws + w.u * N, level, W, W);
-        LimbList lr;
-        for (int o = 0; o < nb; o++)
-            for (int cc = 0; cc < 2; cc++)
-                for (int i = 0; i < level; i++) lr.add(o * W + cc * level + i, i);
-        FinArgs fa = fin_args(ws + w.u * N, nullptr, in, ctx->dev.dn_pinv, ctx->dev.dn_pinv_d, Ma, level, 2, 1u, W, W, 0, ct_limbs);
-        fa.hoisted = 1;
-        if ((rc = ntt_forward(ctx, st, ws + w.r * N, lr, PRO_MODDOWN, cv, &fa, 2 * ctx->K * nb, false, &ho)) != HE_OK)
+        if ((rc = ks_apply(ctx, inner_args(ctx, rots[r], c1, ct_limbs, ws, w, level, nb, &oa, false), &oa, ws, w,
+                           finish_args(ctx, nullptr, 0, in, ct_limbs, level, level), FIN_ROT, st)) != HE_OK)
             return rc;
         r += nb;
     }
@@ -955,7 +966,7 @@ extern "C" int32_t he_hrot_batch_levels(he_ctx *ctx, const he_evk *const *rots, 
     for (int r = 0; r < count;) {
         // group: as many operations as the workspace holds at the layout of their largest level
         int nb = 0, lmax = 0;
-        while (r + nb < count && nb < HOIST_MAX) {
+        while (r + nb < count && nb < HE_OPS_MAX) {
             const int lm = std::max(lmax, (int)h_levels[r + nb]);
             const WsLayout wl = ws_layout(ctx, lm);
             if (!batch_fits(wl, nb + 1) || wl.total * (size_t)(nb + 1) * N * sizeof(u64) > ws_bytes) break;
@@ -970,16 +981,14 @@ extern "C" int32_t he_hrot_batch_levels(he_ctx *ctx, const he_evk *const *rots, 
         for (int o = 0; o < nb; o++) off[o + 1] = off[o] + 2 * (size_t)h_levels[r + o];
         if (off[nb] > 65535) return HE_EINVAL;
         ConvArgs cv = conv_args(ctx, ws + w.x * N, lmax, W, W);
-        HoistKeys hk = {};
-        HoistOuts ho = {};
+        OpArgs oa = {};
         for (int o = 0; o < nb; o++) {
             const int lo = h_levels[r + o];
-            cv.op_level[o] = hk.level[o] = ho.cstride[o] = (uint8_t)lo;
-            hk.evk[o] = rots[r + o]->dev;
-            hk.g[o] = ho.g[o] = (unsigned)rots[r + o]->galois;
-            hk.d[o] = in0 + (off[o] + lo) * N; // c1
-            ho.add[o] = in0 + off[o] * N;      // c0
-            ho.out[o] = out0 + off[o] * N;
+            cv.op_level[o] = oa.level[o] = (uint8_t)lo;
+            oa.evk[o] = rots[r + o]->dev, oa.g[o] = (unsigned)rots[r + o]->galois;
+            oa.d[o] = in0 + (off[o] + lo) * N; // c1
+            oa.add[o] = in0 + off[o] * N;      // c0
+            oa.out[o] = out0 + off[o] * N;
         }
         // 1. inverse transform of every c1 limb, scaled for its digit's conversion
         LimbList l;
@@ -1001,40 +1010,11 @@ extern "C" int32_t he_hrot_batch_levels(he_ctx *ctx, const he_evk *const *rots, 
             }
         }
         if ((rc = ntt_forward(ctx, st, ws + w.raised * N, rl, PRO_MODUP, cv, nullptr, src_limbs, true)) != HE_OK) return rc;
-        // 3. inner products (block pass of the special limbs' inverse transform included) and 4. its column pass
+        // 3 - 6
         if (misaligned16(ws)) return HE_EINVAL;
-        InnerArgs ia;
-        ia.raised = ws + w.raised * N, ia.d = in0, ia.evk = rots[r]->dev, ia.u = ws + w.u * N;
-        ia.level = lmax, ia.L = L, ia.K = K, ia.alpha = alpha, ia.beta = (lmax + alpha - 1) / alpha;
-        ia.g = 1u, ia.raised_stride = W, ia.u_stride = W, ia.d_stride = 0, ia.inv_special = 1, ia.hoisted = 1, ia.count = nb;
-        // bytes by definition: digits and results per operation, each distinct key once at the largest level it serves
-        double inner_bytes = 0.0;
-        std::vector<std::pair<const u64 *, int>> key_level;
-        for (int o = 0; o < nb; o++) {
-            const int lo = h_levels[r + o], beta = (lo + alpha - 1) / alpha;
-            inner_bytes += (double)(beta + 2) * (lo + K) * N * 8.0;
-            bool found = false;
-            for (auto &kl : key_level)
-                if (kl.first == hk.evk[o]) kl.second = std::max(kl.second, lo), found = true;
-            if (!found) key_level.push_back({hk.evk[o], lo});
-        }
-        for (const auto &kl : key_level) inner_bytes += 2.0 * ((kl.second + alpha - 1) / alpha) * (kl.second + K) * N * 8.0;
-        dev_launch(ctx).inner(ctx, st, inner_bytes, inner_grid((unsigned)(N / INNER_TILE), (unsigned)Ma, (unsigned)nb), ia, hk);
-        if ((rc = launch_ok(ctx)) != HE_OK) return rc;
-        LimbList sp;
-        for (int o = 0; o < nb; o++)
-            for (int cc = 0; cc < 2; cc++)
-                for (int k = 0; k < K; k++) sp.add(o * W + cc * Ma + lmax + k, L + k);
-        const ConvArgs cu = conv_args(ctx, ws + w.u * N, lmax, W, W);
-        if ((rc = ntt_inverse(ctx, st, ws + w.u * N, ws + w.u * N, sp, SCALE_MODDOWN, cu, true)) != HE_OK) return rc;
-        // 5. ModDown: corrections transformed and applied, plus the rotated c0
-        LimbList lr;
-        for (int o = 0; o < nb; o++)
-            for (int cc = 0; cc < 2; cc++)
-                for (int i = 0; i < h_levels[r + o]; i++) lr.add(o * W + cc * lmax + i, i);
-        FinArgs fa = fin_args(ws + w.u * N, nullptr, in0, ctx->dev.dn_pinv, ctx->dev.dn_pinv_d, Ma, lmax, 2, 1u, W, W, 0, 0);
-        fa.hoisted = 1;
-        if ((rc = ntt_forward(ctx, st, ws + w.r * N, lr, PRO_MODDOWN, cu, &fa, 2 * K * nb, false, &ho)) != HE_OK) return rc;
+        if ((rc = ks_apply(ctx, inner_args(ctx, rots[r], in0, 0, ws, w, lmax, nb, &oa, false), &oa, ws, w,
+                           finish_args(ctx, nullptr, 0, in0, 0, lmax, lmax), FIN_ROT, st)) != HE_OK)
+            return rc;
         done_limbs += off[nb];
         r += nb;
     }
@@ -1111,9 +1091,8 @@ extern "C" int32_t he_rescale_batch(he_ctx *ctx, const uint64_t *d_ct, uint64_t 
     for (int o = 0; o < count; o++)
         for (int c = 0; c < 2; c++)
             for (int i = 0; i < level - 1; i++) l.add(o * W + c * (level - 1) + i, i);
-    const FinArgs fa = fin_args(d_ct, d_out, nullptr, ctx->dev.rs_inv + (size_t)(level - 1) * ctx->L,
-                                ctx->dev.rs_inv_d + (size_t)(level - 1) * ctx->L, level, level - 1, 0, 1u, W, 2 * level,
-                                2 * (level - 1), 0);
+    const FinArgs fa = {d_ct, d_out, nullptr, ctx->dev.rs_inv + (size_t)(level - 1) * ctx->L,
+                        ctx->dev.rs_inv_d + (size_t)(level - 1) * ctx->L, level, level - 1, 0, level - 1, W, 2 * level, 2 * (level - 1), 0};
     return ntt_forward(ctx, st, r, l, PRO_RESCALE, cv, &fa, 2 * count);
 }
 

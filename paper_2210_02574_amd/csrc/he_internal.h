@@ -34,6 +34,9 @@ struct DevTables {
     const ShoupConst *ninv;    // [M][2]  N^-1 and psi^-brv(1) * N^-1 (last inverse stage)
     // the same three tables as balanced residues in (-q/2, q/2) stored as doubles (moduli < 2^50)
     const double *twd_fwd;     // [M][N]
+    // forward twiddles of the last eight stages by block of 256 elements: entry 256 G + 2^m - 1 + i is the one of
+    // block G, local stage m, group i < 2^m (entry 255 of a block is unused)
+    const double *twd_blk;     // [M][N]
     const double *twd_inv;     // [M][N]
     const double *ninvd;       // [M][2]
     // ModUp constants for digit j holding a active limbs (1 <= a <= alpha), slot (j*alpha + a-1):
@@ -87,7 +90,7 @@ struct he_ctx {
     std::vector<ShoupConst> tw_fwd;  // [M][N]
     std::vector<ShoupConst> tw_inv;  // [M][N]
     std::vector<ShoupConst> ninv;    // [M][2]
-    std::vector<double> twd_fwd, twd_inv, ninvd;
+    std::vector<double> twd_fwd, twd_inv, twd_blk, ninvd;
     std::vector<ShoupConst> up_inv;
     std::vector<u64> up_hat;
     std::vector<double> up_inv_d, up_hat_d, up_hat_dh, dn_inv_d, dn_hat_d, dn_hat_dh, dn_pinv_d, dn_pmod_d, rs_inv_d, rsp_inv_d;

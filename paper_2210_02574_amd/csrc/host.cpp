@@ -217,6 +217,7 @@ extern "C" int32_t he_ctx_create(const he_params *p, int32_t device, he_ctx **ou
         c->ninv.resize((size_t)M * 2);
         c->twd_fwd.assign((size_t)M * N, 0.0);
         c->twd_inv.assign((size_t)M * N, 0.0);
+        c->twd_blk.assign((size_t)M * N, 0.0);
         c->ninvd.assign((size_t)M * 2, 0.0);
     } catch (...) {
         delete c;
@@ -259,6 +260,12 @@ extern "C" int32_t he_ctx_create(const he_params *p, int32_t device, he_ctx **ou
                 c->twd_fwd[(size_t)i * N + e] = bal(c->tw_fwd[(size_t)i * N + e].w);
                 c->twd_inv[(size_t)i * N + e] = bal(c->tw_inv[(size_t)i * N + e].w);
             }
+            const int s0 = c->logN - 8; // first stage of the block pass
+            for (u64 G = 0; G < N / 256; G++)
+                for (int m = 0; m < 8; m++)
+                    for (u64 x = 0; x < ((u64)1 << m); x++)
+                        c->twd_blk[(size_t)i * N + 256 * G + ((u64)1 << m) - 1 + x] =
+                            c->twd_fwd[(size_t)i * N + ((u64)1 << (s0 + m)) + (G << m) + x];
             c->ninvd[(size_t)i * 2 + 0] = bal(c->ninv[(size_t)i * 2 + 0].w);
             c->ninvd[(size_t)i * 2 + 1] = bal(c->ninv[(size_t)i * 2 + 1].w);
         }

@@ -2,7 +2,7 @@
 #pragma once
 #include "kernels_ntt.h"
 
-// ---- inner product with the evaluation key, block pass of the raised digits' forward NTT fused in -----------
+// ---- inner product with the evaluation key, fused with the transforms on both sides of it -----------------------
 //
 // u[c][a][n] = sum_j D_j[a][pi_g(n)] * evk[j][c][mod(a)][n] on every active limb a, where D_j[a] is the
 // raised digit outside digit j and the NTT-domain input d[a] inside it.
@@ -12,8 +12,14 @@
 // these outputs are the indices of one input tile of that size.  For a limb on the floating-point path the raised
 // digits arrive as the column pass left them; each is finished here (stages logN-8 .. logN-1) into LDS
 // and read back through the index map, so the transformed digits never travel to memory.  Limbs on
-// the integer path read digits that the block-pass kernel has finished.  With inv_special the special
-// limbs of u leave this kernel with the block pass of their inverse transform already applied.
+// the integer path read digits that the block-pass kernel has finished.
+//
+// Two launches make a key switch's inner product.  The first (k_inner_blocks8) takes the special limbs, whose
+// results leave it with the block pass of their inverse transform already applied.  The second (k_inner_fin) runs
+// after the ModDown corrections r have been through their column pass: it forms u on the ciphertext limbs, finishes
+// the transform of r the way it finishes a digit, and writes (u - r) * const + addend, so that u never travels to
+// memory either.  As one inner product over all limbs and a finishing block pass, u was written and read back:
+// 4 level limbs of traffic per operation, a tenth of a key switch's total.
 
 typedef u64 u64x2 __attribute__((ext_vector_type(2)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
@@ -21,21 +27,37 @@ typedef double f64x2 __attribute__((ext_vector_type(2)));
 struct InnerArgs {
     const u64 *raised, *d, *evk;
     u64 *u;
-    int level, L, K, alpha, beta;
+    int level, L, K, alpha;
+    int first; // k_inner_blocks8: the lowest active limb it works on (level: the special limbs alone)
     unsigned g;
     int raised_stride, u_stride, d_stride; // limbs between two operations of a batch in each buffer
-    int inv_special;
-    int hoisted; // operation z uses key and Galois element z of the HoistKeys argument (one raised input for all)
-    int count;   // operations in this launch
+    int per_op; // operation z uses entry z of the OpArgs argument
+    int count;  // operations in this launch
 };
-#define HOIST_MAX HE_OPS_MAX
-struct HoistKeys {
-    const u64 *evk[HOIST_MAX];
-    unsigned g[HOIST_MAX];
+// What differs between the operations of one launch, when anything but their place in the buffers does.
+struct OpArgs {
+    const u64 *evk[HE_OPS_MAX];
+    // the operation's NTT-domain input polynomial and its addend (null: InnerArgs.d + operation * d_stride,
+    // FinishArgs.add + operation * add_stride), its output
+    const u64 *d[HE_OPS_MAX];
+    const u64 *add[HE_OPS_MAX];
+    u64 *out[HE_OPS_MAX];
+    unsigned g[HE_OPS_MAX];
     // mixed-level rotations: the operation's level (0: InnerArgs.level, which always gives the buffer layout)
-    // and its NTT-domain input polynomial (null: InnerArgs.d + operation * d_stride)
-    const u64 *d[HOIST_MAX];
-    uint8_t level[HOIST_MAX];
+    uint8_t level[HE_OPS_MAX];
+};
+// The finishing step on ciphertext limb i, component c: out = (u - NTT(r)) * cst + addend.
+// FIN_ADD: the addend is limb i of component c of `add`, times cst2 unless that is null; FIN_ROT: sigma_g of limb i
+// of `add` (c0 of the rotated ciphertext) on component 0; FIN_ROTSUM: as FIN_ROT plus limb i of component c of `add`.
+enum { FIN_ADD = 0, FIN_ROT = 1, FIN_ROTSUM = 2 };
+struct FinishArgs {
+    const u64 *r; // [2][level] limbs per operation; floating-point limbs as the column pass left them, others finished
+    u64 *out;
+    const u64 *add;
+    const ShoupConst *cst, *cst2;
+    const double *cst_d, *cst2_d;
+    int nl; // output limbs per component (level, or level - 1 when a rescale is folded in)
+    int r_stride, out_stride, out_cstride, add_stride, add_cstride;
 };
 
 // One-dimensional grid of inner_grid() work-groups; every buffer is 16-byte aligned.  Work-groups go to the
@@ -59,6 +81,8 @@ __host__ __device__ inline unsigned inner_grid(unsigned tiles, unsigned limbs, u
 // With one pad word per 16 elements every 16 consecutive lanes of each pattern hit 16 different 8-byte banks.
 // All 255 twiddles of a block's eight stages sit in LDS, the one of local stage m and group i at 2^m - 1 + i.
 // In the product phase thread t owns the pairs (INNER_TILE tile + 2 INNER_THREADS i + 2 t, + 1), i < 4.
+// The 128 twiddles of a block's last stage, like all others, are contiguous in the block-major table (twd_blk), so a
+// tile's 8 KiB of twiddles are fetched straight into LDS.
 
 #ifndef INNER_THREADS
 #define INNER_THREADS 128
@@ -108,204 +132,380 @@ template <class Tv> __device__ __forceinline__ Tv ld_at(const void *base, unsign
     return *(const Tv *)((const char *)base + byte_off);
 }
 
-template <int LOGN> __global__ __launch_bounds__(INNER_THREADS, 4) void k_inner_blocks8(InnerArgs ia, DevTables T, HoistKeys hk)
+// Copies of 4 KiB (the two blocks that a wave owns) from global memory into LDS by loads that write to LDS directly:
+// lane i's 16 bytes land at dst + 16 i, and no registers are needed while they are in flight.  src: this lane's
+// address.  NT: cache policy 2, nontemporal.
+template <bool NT> __device__ __forceinline__ void wave_copy_4k(const char *src, char *dst)
 {
-    __shared__ u64 lds[INNER_BLOCKS * TILE_GROUP];
-    __shared__ double tws[INNER_BLOCKS * 256];
-    __shared__ u64 pre[INNER_BLOCKS * 256]; // the next raised digit of this tile, as it lies in memory
-    const int level = ia.level, M = ia.L + ia.K, Ma = level + ia.K;
+#pragma unroll
+    for (int c = 0; c < 4; c++)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + 1024 * c),
+                                         (__attribute__((address_space(3))) void *)(dst + 1024 * c), 16, 0, NT ? 2 : 0);
+}
+
+// This thread's place in the block pass and the LDS addresses of its three exchange patterns.
+struct BlockLane {
+    unsigned blk, t, g2;
+    u64 *l1, *l2, *l3;
+    const double *tw; // the block's 255 twiddles in LDS
+};
+__device__ __forceinline__ BlockLane block_lane(u64 *lds, const double *tws)
+{
+    BlockLane b;
+    b.blk = threadIdx.x >> 5, b.t = threadIdx.x & 31, b.g2 = b.t & 7;
+    b.l1 = lds + b.blk * TILE_GROUP + b.t + (b.t >> 4);
+    b.l2 = lds + b.blk * TILE_GROUP + 34 * b.g2 + (b.t >> 3);
+    b.l3 = lds + b.blk * TILE_GROUP + 4 * b.t + (b.t >> 2);
+    b.tw = tws + b.blk * 256;
+    return b;
+}
+// Block pass of the eight values dv of this thread (pattern of step 1); the result is left in LDS, element e of
+// block b at tile_at(b, e), for the caller to read behind a barrier.
+// Ranges (in units of q): the column pass leaves up to 3.7; reduced, step 1 ends below 2.7 and step 2 below 6.3;
+// reduced again, step 3 ends below 1.9, small enough for exact products.
+__device__ __forceinline__ void block_pass8(const ArithFp &ar, double (&dv)[8], const BlockLane &b)
+{
+    ar.fwd8_with(dv, true, [&](int sp, int gg) { return b.tw[(1 << sp) - 1 + gg]; });
+#pragma unroll
+    for (int k = 0; k < 8; k++) b.l1[34 * k] = ar.store_mid(dv[k]);
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(b.l2[4 * k + (k >> 2)]);
+    ar.fwd8_with(dv, false, [&](int sp, int gg) { return b.tw[(8 << sp) - 1 + (b.g2 << sp) + gg]; });
+#pragma unroll
+    for (int k = 0; k < 8; k++) b.l2[4 * k + (k >> 2)] = ar.store_mid(dv[k]);
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(b.l3[136 * (k >> 2) + (k & 3)]);
+    ar.fwd4x2_with(dv, true, [&](int h, int sp, int gg) { return b.tw[(64 << sp) - 1 + ((b.t + 32 * h) << sp) + gg]; });
+#pragma unroll
+    for (int k = 0; k < 8; k++) b.l3[136 * (k >> 2) + (k & 3)] = ar.store_mid(dv[k]);
+}
+
+// What one work-group works on.
+struct InnerTile {
+    unsigned op, tile, tile_in, g;
+    int a; // active limb
+    int level, beta; // of the operation
+    bool none;
+};
+template <int LOGN>
+__device__ __forceinline__ InnerTile inner_tile(const InnerArgs &ia, const OpArgs &oa, int limbs, int first)
+{
+    InnerTile w;
     const unsigned ntile = 1u << (LOGN - INNER_TLOG);
-    const unsigned slot = blockIdx.x / XCDS, op = slot % (unsigned)ia.count;
+    const unsigned slot = blockIdx.x / XCDS;
+    w.op = slot % (unsigned)ia.count;
     const unsigned tl = slot / (unsigned)ia.count * XCDS + blockIdx.x % XCDS;
-    if (tl >= ntile * (unsigned)Ma) return; // padding of the last group of eight (whole work-group)
-    const int a = Ma - 1 - (int)(tl / ntile); // special limbs (the slowest) first
-    const unsigned tile = tl % ntile;
-    const unsigned g = ia.hoisted ? hk.g[op] : ia.g;
-    // an operation below the layout's level has no limbs a in [its level, level) and fewer digits
-    const int op_level = ia.hoisted && hk.level[op] ? hk.level[op] : level;
-    if (a < level && a >= op_level) return;
-    const int beta = (op_level + ia.alpha - 1) / ia.alpha;
-    const int mi = active_mod(a, level, ia.L);
-    const int own = a < level ? a / ia.alpha : -1;
-    const ModConst m = T.mod[mi];
-    const unsigned blk = threadIdx.x >> 5, t = threadIdx.x & 31;
-    const unsigned tile_in = g == 1 ? tile : galois_index(tile << INNER_TLOG, g, LOGN) >> INNER_TLOG;
+    w.tile = tl % ntile;
+    w.a = first + limbs - 1 - (int)(tl / ntile); // special limbs (the slowest) first
+    w.g = ia.per_op ? oa.g[w.op] : ia.g;
+    w.tile_in = w.g == 1 ? w.tile : galois_index(w.tile << INNER_TLOG, w.g, LOGN) >> INNER_TLOG;
+    w.level = ia.per_op && oa.level[w.op] ? oa.level[w.op] : ia.level;
+    w.beta = (w.level + ia.alpha - 1) / ia.alpha;
+    // padding of the last group of eight; an operation below the layout's level has no limbs a in [its level, level)
+    w.none = tl >= ntile * (unsigned)limbs || (w.a < ia.level && w.a >= w.level);
+    return w;
+}
+
+// The products of one floating-point limb: acc0, acc1 = sums over the digits, within 3.5 q, for this thread's pairs.
+// If `then` is not null, the tile it points at (this lane's address of 4 KiB per wave) is on its way into `pre` when
+// the function returns.
+template <int LOGN>
+__device__ __forceinline__ void inner_products8(const InnerArgs &ia, const OpArgs &oa, const DevTables &T, const InnerTile &w,
+                                                unsigned mi, const ArithFp &ar, const BlockLane &b, u64 *lds, double *tws, u64 *pre,
+                                                const char *then, double (&acc0)[8], double (&acc1)[8])
+{
+    const int a = w.a, own = a < ia.level ? a / ia.alpha : -1, M = ia.L + ia.K, Ma = ia.level + ia.K;
+    const unsigned wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     // wave-uniform bases (bytes): raised digit 0 and key component 0 of digit 0 for this limb and tile; digit j is
     // raised_step / key_step further on, key component 1 comp_step after component 0
-    const char *raised0 = (const char *)(ia.raised + ((((size_t)op * ia.raised_stride + a) << LOGN) + ((size_t)tile_in << INNER_TLOG)));
-    const char *key0 = (const char *)((ia.hoisted ? hk.evk[op] : ia.evk) + (((size_t)mi << LOGN) + ((size_t)tile << INNER_TLOG)));
-    const char *d_limb = (const char *)((ia.hoisted && hk.d[op] ? hk.d[op] : ia.d + (((size_t)op * ia.d_stride) << LOGN)) + ((size_t)a << LOGN));
+    const char *raised0 = (const char *)(ia.raised + ((((size_t)w.op * ia.raised_stride + a) << LOGN) + ((size_t)w.tile_in << INNER_TLOG)));
+    const char *key0 = (const char *)((ia.per_op ? oa.evk[w.op] : ia.evk) + (((size_t)mi << LOGN) + ((size_t)w.tile << INNER_TLOG)));
     const size_t raised_step = ((size_t)Ma << LOGN) * 8, comp_step = ((size_t)M << LOGN) * 8, key_step = 2 * comp_step;
-    const unsigned lane16 = threadIdx.x * 16u;        // this thread's pair within a 512-pair row of the tile
-    const unsigned lane_mid = (blk * 256u + t) * 8u;  // element t of block blk
+    const unsigned lane16 = threadIdx.x * 16u; // this thread's pair within a row of INNER_THREADS pairs
+    // The raised digit after the one being worked on is already on its way into LDS.  A digit that only this operation
+    // reads is streamed past the key slices that the batch shares in L2.
+    auto prefetch = [&](int j) {
+        const char *src = raised0 + (size_t)j * raised_step + wave * 4096u + lane * 16u;
+        if (ia.raised_stride != 0)
+            wave_copy_4k<true>(src, (char *)(pre + wave * 512));
+        else
+            wave_copy_4k<false>(src, (char *)(pre + wave * 512));
+    };
+    wave_copy_4k<false>((const char *)(T.twd_blk + (((size_t)mi << LOGN) + ((size_t)w.tile_in << INNER_TLOG))) + wave * 4096u + lane * 16u,
+                        (char *)(tws + wave * 512));
+    const int j0 = own == 0 ? 1 : 0;
+    if (j0 < w.beta)
+        prefetch(j0);
+    else if (then)
+        wave_copy_4k<true>(then, (char *)(pre + wave * 512));
     // pair i of the product phase: LDS words of the sources of its even and odd element (an aligned pair, in
     // either order), and whether the pair arrives swapped
     unsigned lsx[4], lsy[4], swm = 0;
 #pragma unroll
     for (int i = 0; i < 4; i++) {
-        const unsigned pos = (tile << INNER_TLOG) + pair8_at(i);
-        const unsigned sr = g == 1 ? pos : galois_index(pos, g, LOGN);
+        const unsigned pos = (w.tile << INNER_TLOG) + pair8_at(i);
+        const unsigned sr = w.g == 1 ? pos : galois_index(pos, w.g, LOGN);
         const unsigned sl = sr & (INNER_TILE - 2u), sw = sr & 1u;
-        const unsigned w = (sl >> 8) * TILE_GROUP + (sl & 255u) + ((sl & 255u) >> 4);
-        lsx[i] = w + sw, lsy[i] = w + 1 - sw;
+        const unsigned wd = (sl >> 8) * TILE_GROUP + (sl & 255u) + ((sl & 255u) >> 4);
+        lsx[i] = wd + sw, lsy[i] = wd + 1 - sw;
         swm |= sw << i;
     }
-    u64 r0[8], r1[8];
-    if (m.qd != 0.0) {
-        const ArithFp ar = make_fp(T, mi, LOGN);
-        // The raised digit after the one being worked on is already on its way into LDS: each wave copies the two
-        // blocks its lanes own, 4 x 1 KiB, with loads that write to LDS directly (lane i's 16 bytes land at
-        // base + 16 i) and need no registers while they are in flight.
-        const unsigned wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-        auto prefetch = [&](int j) {
-            const char *src = raised0 + (size_t)j * raised_step + wave * 4096u + lane * 16u;
-            // a digit that only this operation reads is streamed past the key slices that the batch shares in L2
-            // (cache policy 2: nontemporal)
-            if (ia.raised_stride != 0) {
 #pragma unroll
-                for (int c = 0; c < 4; c++)
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + 1024 * c),
-                                                     (__attribute__((address_space(3))) void *)(pre + wave * 512 + c * 128), 16, 0, 2);
-            } else {
-#pragma unroll
-                for (int c = 0; c < 4; c++)
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + 1024 * c),
-                                                     (__attribute__((address_space(3))) void *)(pre + wave * 512 + c * 128), 16, 0, 0);
-            }
-        };
-        {
-            const int j0 = own == 0 ? 1 : 0;
-            if (j0 < beta) prefetch(j0);
-        }
-        double *tw = tws + blk * 256;
-        for (unsigned c = t; c < 255; c += 32) tw[c] = ar.twf[ArithFp::fwd16_twiddle(LOGN - 8, tile_in * INNER_BLOCKS + blk, c)];
-        __syncthreads();
-        const unsigned g2 = t & 7, r2 = t >> 3;
-        u64 *l1 = lds + blk * TILE_GROUP + t + (t >> 4);
-        u64 *l2 = lds + blk * TILE_GROUP + 34 * g2 + r2;
-        u64 *l3 = lds + blk * TILE_GROUP + 4 * t + (t >> 2);
-        double acc0[8], acc1[8];
-#pragma unroll
-        for (int k = 0; k < 8; k++) acc0[k] = acc1[k] = 0.0;
-        for (int j = 0; j < beta; j++) {
-            double dv[8];
-            f64x2 e0[4], e1[4]; // key words of a floating-point limb are balanced doubles
-            const char *kj = key0 + (size_t)j * key_step;
-            if (j == own) {
-#pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const unsigned pos = (tile << INNER_TLOG) + pair8_at(i);
-                    const unsigned sr = g == 1 ? pos : galois_index(pos, g, LOGN);
-                    const u64x2 v = ld_at<u64x2>(d_limb, (sr & ~1u) * 8u);
-                    const bool sw = (swm >> i) & 1u;
-                    dv[2 * i] = u2d(sw ? v.y : v.x), dv[2 * i + 1] = u2d(sw ? v.x : v.y);
-                }
-#pragma unroll
-                for (int i = 0; i < 4; i++)
-                    e0[i] = ld_at<f64x2>(kj + INNER_THREADS * 16 * i, lane16), e1[i] = ld_at<f64x2>(kj + comp_step + INNER_THREADS * 16 * i, lane16);
-            } else {
-                // this digit has arrived (nothing else of this wave is in flight here); once it is in registers the
-                // buffer is free for the next one
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                const u64 *pw = pre + blk * 256 + t;
-#pragma unroll
-                for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(pw[32 * k]);
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                {
-                    const int jn = j + 1 == own ? j + 2 : j + 1;
-                    if (jn < beta) prefetch(jn);
-                }
-                // the key loads are issued before the block pass and complete behind it
-#pragma unroll
-                for (int i = 0; i < 4; i++)
-                    e0[i] = ld_at<f64x2>(kj + INNER_THREADS * 16 * i, lane16), e1[i] = ld_at<f64x2>(kj + comp_step + INNER_THREADS * 16 * i, lane16);
-                // ranges (in units of q): the column pass leaves up to 3.7; reduced, step 1 ends below 2.7 and
-                // step 2 below 6.3; reduced again, step 3 ends below 1.9, small enough for exact products
-                ar.fwd8_with(dv, true, [&](int sp, int gg) { return tw[(1 << sp) - 1 + gg]; });
-#pragma unroll
-                for (int k = 0; k < 8; k++) l1[34 * k] = ar.store_mid(dv[k]);
-                block_sync();
-#pragma unroll
-                for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(l2[4 * k + (k >> 2)]);
-                ar.fwd8_with(dv, false, [&](int sp, int gg) { return tw[(8 << sp) - 1 + (g2 << sp) + gg]; });
-#pragma unroll
-                for (int k = 0; k < 8; k++) l2[4 * k + (k >> 2)] = ar.store_mid(dv[k]);
-                block_sync();
-#pragma unroll
-                for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(l3[136 * (k >> 2) + (k & 3)]);
-                ar.fwd4x2_with(dv, true, [&](int h, int sp, int gg) { return tw[(64 << sp) - 1 + ((t + 32 * h) << sp) + gg]; });
-#pragma unroll
-                for (int k = 0; k < 8; k++) l3[136 * (k >> 2) + (k & 3)] = ar.store_mid(dv[k]);
-                __syncthreads();
-#pragma unroll
-                for (int i = 0; i < 4; i++) dv[2 * i] = ar.load_mid(lds[lsx[i]]), dv[2 * i + 1] = ar.load_mid(lds[lsy[i]]);
-                __syncthreads();
-            }
+    for (int k = 0; k < 8; k++) acc0[k] = acc1[k] = 0.0;
+    for (int j = 0; j < w.beta; j++) {
+        double dv[8];
+        f64x2 e0[4], e1[4]; // key words of a floating-point limb are balanced doubles
+        const char *kj = key0 + (size_t)j * key_step;
+        if (j == own) {
+            const char *d_limb = (const char *)((ia.per_op && oa.d[w.op] ? oa.d[w.op] : ia.d + (((size_t)w.op * ia.d_stride) << LOGN)) + ((size_t)a << LOGN));
 #pragma unroll
             for (int i = 0; i < 4; i++) {
-                acc0[2 * i] += ar.mulmod(dv[2 * i], e0[i].x);
-                acc0[2 * i + 1] += ar.mulmod(dv[2 * i + 1], e0[i].y);
-                acc1[2 * i] += ar.mulmod(dv[2 * i], e1[i].x);
-                acc1[2 * i + 1] += ar.mulmod(dv[2 * i + 1], e1[i].y);
+                const unsigned pos = (w.tile << INNER_TLOG) + pair8_at(i);
+                const unsigned sr = w.g == 1 ? pos : galois_index(pos, w.g, LOGN);
+                const u64x2 v = ld_at<u64x2>(d_limb, (sr & ~1u) * 8u);
+                const bool sw = (swm >> i) & 1u;
+                dv[2 * i] = u2d(sw ? v.y : v.x), dv[2 * i + 1] = u2d(sw ? v.x : v.y);
             }
-            if ((j & 3) == 3) {
 #pragma unroll
-                for (int k = 0; k < 8; k++) acc0[k] = ar.reduce(acc0[k]), acc1[k] = ar.reduce(acc1[k]);
+            for (int i = 0; i < 4; i++)
+                e0[i] = ld_at<f64x2>(kj + INNER_THREADS * 16 * i, lane16), e1[i] = ld_at<f64x2>(kj + comp_step + INNER_THREADS * 16 * i, lane16);
+        } else {
+            // this digit has arrived (nothing else of this wave is in flight here); once it is in registers the
+            // buffer is free for the next one
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            const u64 *pw = pre + b.blk * 256 + b.t;
+#pragma unroll
+            for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(pw[32 * k]);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            {
+                const int jn = j + 1 == own ? j + 2 : j + 1;
+                if (jn < w.beta)
+                    prefetch(jn);
+                else if (then)
+                    wave_copy_4k<true>(then, (char *)(pre + wave * 512));
             }
+            // the key loads are issued before the block pass and complete behind it
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+                e0[i] = ld_at<f64x2>(kj + INNER_THREADS * 16 * i, lane16), e1[i] = ld_at<f64x2>(kj + comp_step + INNER_THREADS * 16 * i, lane16);
+            block_pass8(ar, dv, b);
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < 4; i++) dv[2 * i] = ar.load_mid(lds[lsx[i]]), dv[2 * i + 1] = ar.load_mid(lds[lsy[i]]);
+            __syncthreads();
         }
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            acc0[2 * i] += ar.mulmod(dv[2 * i], e0[i].x);
+            acc0[2 * i + 1] += ar.mulmod(dv[2 * i + 1], e0[i].y);
+            acc1[2 * i] += ar.mulmod(dv[2 * i], e1[i].x);
+            acc1[2 * i + 1] += ar.mulmod(dv[2 * i + 1], e1[i].y);
+        }
+        if ((j & 3) == 3) {
+#pragma unroll
+            for (int k = 0; k < 8; k++) acc0[k] = ar.reduce(acc0[k]), acc1[k] = ar.reduce(acc1[k]);
+        }
+    }
+}
+
+// Pair h of the product phase (h < 2: pairs 2 h and 2 h + 1) on the integer path: the raised digits arrive finished
+// (NTT domain) and are read through the index map.
+template <int LOGN>
+__device__ __forceinline__ void inner_products_int(const InnerArgs &ia, const OpArgs &oa, const InnerTile &w, unsigned mi,
+                                                   const ModConst &m, int h, u64 (&r0)[4], u64 (&r1)[4])
+{
+    const int a = w.a, own = a < ia.level ? a / ia.alpha : -1, M = ia.L + ia.K, Ma = ia.level + ia.K;
+    const char *key0 = (const char *)((ia.per_op ? oa.evk[w.op] : ia.evk) + (((size_t)mi << LOGN) + ((size_t)w.tile << INNER_TLOG)));
+    const char *d_limb = (const char *)((ia.per_op && oa.d[w.op] ? oa.d[w.op] : ia.d + (((size_t)w.op * ia.d_stride) << LOGN)) + ((size_t)a << LOGN));
+    const char *fin0 = (const char *)(ia.raised + (((size_t)w.op * ia.raised_stride + a) << LOGN));
+    const size_t raised_step = ((size_t)Ma << LOGN) * 8, comp_step = ((size_t)M << LOGN) * 8, key_step = 2 * comp_step;
+    const unsigned lane16 = threadIdx.x * 16u;
+    unsigned sr[2];
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        const unsigned pos = (w.tile << INNER_TLOG) + pair8_at(2 * h + i);
+        sr[i] = w.g == 1 ? pos : galois_index(pos, w.g, LOGN);
+    }
+    U128 acc0[4], acc1[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) acc0[k] = acc1[k] = U128{0, 0};
+    for (int j = 0; j < w.beta; j++) {
+        const char *dj = j == own ? d_limb : fin0 + (size_t)j * raised_step;
+        const char *kj = key0 + (size_t)j * key_step;
+#pragma unroll
+        for (int i = 0; i < 2; i++) {
+            const int ii = 2 * h + i;
+            const u64x2 v = ld_at<u64x2>(dj, (sr[i] & ~1u) * 8u);
+            const bool sw = sr[i] & 1u;
+            const u64 x = sw ? v.y : v.x, y = sw ? v.x : v.y;
+            const u64x2 ka = ld_at<u64x2>(kj + INNER_THREADS * 16 * ii, lane16), kb = ld_at<u64x2>(kj + comp_step + INNER_THREADS * 16 * ii, lane16);
+            mac128(acc0[2 * i], x, ka.x);
+            mac128(acc0[2 * i + 1], y, ka.y);
+            mac128(acc1[2 * i], x, kb.x);
+            mac128(acc1[2 * i + 1], y, kb.y);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; k++) r0[k] = reduce128(acc0[k], m), r1[k] = reduce128(acc1[k], m);
+}
+
+// First launch: active limbs ia.first .. level + K - 1 of every operation.
+template <int LOGN> __global__ __launch_bounds__(INNER_THREADS, 4) void k_inner_blocks8(InnerArgs ia, DevTables T, OpArgs oa)
+{
+    __shared__ u64 lds[INNER_BLOCKS * TILE_GROUP];
+    __shared__ __align__(16) double tws[INNER_BLOCKS * 256];
+    __shared__ __align__(16) u64 pre[INNER_BLOCKS * 256]; // the next raised digit of this tile, as it lies in memory
+    const int Ma = ia.level + ia.K;
+    const InnerTile w = inner_tile<LOGN>(ia, oa, Ma - ia.first, ia.first);
+    if (w.none) return;
+    const int mi = active_mod(w.a, ia.level, ia.L);
+    const ModConst m = T.mod[mi];
+    u64 r0[8], r1[8];
+    if (m.qd != 0.0) {
+        double acc0[8], acc1[8];
+        const BlockLane b = block_lane(lds, tws);
+        inner_products8<LOGN>(ia, oa, T, w, mi, make_fp(T, mi, LOGN), b, lds, tws, pre, nullptr, acc0, acc1);
 #pragma unroll
         for (int k = 0; k < 8; k++) r0[k] = fp_canon(acc0[k], m.qd, m.qinvd), r1[k] = fp_canon(acc1[k], m.qd, m.qinvd);
     } else {
-        // integer path: the raised digits arrive finished (NTT domain); read through the index map
-        unsigned so[4];
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const unsigned pos = (tile << INNER_TLOG) + pair8_at(i);
-            so[i] = ((g == 1 ? pos : galois_index(pos, g, LOGN)) & ~1u) * 8u;
-        }
-        const char *fin0 = (const char *)(ia.raised + (((size_t)op * ia.raised_stride + a) << LOGN));
 #pragma unroll
         for (int h = 0; h < 2; h++) { // two pairs at a time: the 128-bit accumulators of four would not fit
-            U128 acc0[4], acc1[4];
+            u64 x0[4], x1[4];
+            inner_products_int<LOGN>(ia, oa, w, mi, m, h, x0, x1);
 #pragma unroll
-            for (int k = 0; k < 4; k++) acc0[k] = acc1[k] = U128{0, 0};
-            for (int j = 0; j < beta; j++) {
-                const char *dj = j == own ? d_limb : fin0 + (size_t)j * raised_step;
-                const char *kj = key0 + (size_t)j * key_step;
-#pragma unroll
-                for (int i = 0; i < 2; i++) {
-                    const int ii = 2 * h + i;
-                    const u64x2 v = ld_at<u64x2>(dj, so[ii]);
-                    const bool sw = (swm >> ii) & 1u;
-                    const u64 x = sw ? v.y : v.x, y = sw ? v.x : v.y;
-                    const u64x2 ka = ld_at<u64x2>(kj + INNER_THREADS * 16 * ii, lane16), kb = ld_at<u64x2>(kj + comp_step + INNER_THREADS * 16 * ii, lane16);
-                    mac128(acc0[2 * i], x, ka.x);
-                    mac128(acc0[2 * i + 1], y, ka.y);
-                    mac128(acc1[2 * i], x, kb.x);
-                    mac128(acc1[2 * i + 1], y, kb.y);
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < 4; k++) r0[4 * h + k] = reduce128(acc0[k], m), r1[4 * h + k] = reduce128(acc1[k], m);
+            for (int k = 0; k < 4; k++) r0[4 * h + k] = x0[k], r1[4 * h + k] = x1[k];
         }
     }
-    u64 *u0 = ia.u + ((((size_t)op * ia.u_stride + a) << LOGN)), *u1 = u0 + ((size_t)Ma << LOGN);
-    if (ia.inv_special && a >= level) {
+    u64 *u0 = ia.u + ((((size_t)w.op * ia.u_stride + w.a) << LOGN)), *u1 = u0 + ((size_t)Ma << LOGN);
+    if (w.a >= ia.level) {
         if (m.qd != 0.0) {
             const ArithFp ar = make_fp(T, mi, LOGN);
-            inv_blocks_from_pairs8<LOGN>(r0, u0, ar, lds, tile);
-            inv_blocks_from_pairs8<LOGN>(r1, u1, ar, lds, tile);
+            inv_blocks_from_pairs8<LOGN>(r0, u0, ar, lds, w.tile);
+            inv_blocks_from_pairs8<LOGN>(r1, u1, ar, lds, w.tile);
         } else {
             const ArithInt ar = make_int(T, mi, LOGN);
-            inv_blocks_from_pairs8<LOGN>(r0, u0, ar, lds, tile);
-            inv_blocks_from_pairs8<LOGN>(r1, u1, ar, lds, tile);
+            inv_blocks_from_pairs8<LOGN>(r0, u0, ar, lds, w.tile);
+            inv_blocks_from_pairs8<LOGN>(r1, u1, ar, lds, w.tile);
         }
     } else {
-        char *o0 = (char *)(u0 + ((size_t)tile << INNER_TLOG)), *o1 = (char *)(u1 + ((size_t)tile << INNER_TLOG));
+        const unsigned lane16 = threadIdx.x * 16u;
+        char *o0 = (char *)(u0 + ((size_t)w.tile << INNER_TLOG)), *o1 = (char *)(u1 + ((size_t)w.tile << INNER_TLOG));
 #pragma unroll
         for (int i = 0; i < 4; i++) {
             __builtin_nontemporal_store(u64x2{r0[2 * i], r0[2 * i + 1]}, (u64x2 *)(o0 + INNER_THREADS * 16 * i + lane16));
             __builtin_nontemporal_store(u64x2{r1[2 * i], r1[2 * i + 1]}, (u64x2 *)(o1 + INNER_THREADS * 16 * i + lane16));
+        }
+    }
+}
+
+// Addend of pair i of component c, as canonical residues.
+template <int LOGN, int MODE>
+__device__ __forceinline__ u64x2 fin_addend(const FinishArgs &fa, const OpArgs &oa, const InnerArgs &ia, const InnerTile &w, int c,
+                                            int i, u64 q)
+{
+    const u64 *add = ia.per_op && oa.add[w.op] ? oa.add[w.op] : fa.add + (((size_t)w.op * fa.add_stride) << LOGN);
+    const unsigned pos = (w.tile << INNER_TLOG) + pair8_at(i);
+    u64x2 v = {0, 0};
+    if (MODE != FIN_ROT) v = ld_at<u64x2>(add + (((size_t)c * fa.add_cstride + w.a) << LOGN), pos * 8u);
+    if (MODE != FIN_ADD && c == 0) {
+        const unsigned sr = w.g == 1 ? pos : galois_index(pos, w.g, LOGN);
+        u64x2 s = ld_at<u64x2>(add + ((size_t)w.a << LOGN), (sr & ~1u) * 8u);
+        if (sr & 1u) s = u64x2{s.y, s.x};
+        v = MODE == FIN_ROT ? s : u64x2{csub(v.x + s.x, q), csub(v.y + s.y, q)};
+    }
+    return v;
+}
+
+// Second launch: the ciphertext limbs on the floating-point path (INT: those on the integer path, whose digits and
+// corrections arrive finished).
+// Bound by memory for batches with one key (the digits, r, the addend and the result once each); a call as a whole
+// takes less than the inner product over the same limbs and the finishing block pass took together: at N = 2^16, level 24,
+// 15 hoisted rotations 1200 -> 1061 us, 16 products 2120 -> 2017 us, 32 rotations of mixed levels 2515 -> 2362 us.
+template <int LOGN, int MODE, bool INT>
+__global__ __launch_bounds__(INNER_THREADS, INT ? 4 : 6) void k_inner_fin(InnerArgs ia, FinishArgs fa, DevTables T, OpArgs oa)
+{
+    const InnerTile w = inner_tile<LOGN>(ia, oa, fa.nl, 0);
+    const ModConst m = T.mod[w.a < 0 ? 0 : w.a];
+    if (w.none || (m.qd == 0.0) != INT) return;
+    const unsigned lane16 = threadIdx.x * 16u;
+    const u64 *r = fa.r + (((size_t)w.op * fa.r_stride + w.a) << LOGN);
+    const size_t r_step = ((size_t)ia.level << LOGN) * 8;
+    const char *r_tile = (const char *)(r + ((size_t)w.tile << INNER_TLOG));
+    const unsigned out_cstride = ia.per_op && oa.level[w.op] ? oa.level[w.op] : (unsigned)fa.out_cstride;
+    char *o = (char *)((ia.per_op ? oa.out[w.op] : fa.out + (((size_t)w.op * fa.out_stride) << LOGN)) + (((size_t)w.a << LOGN) + ((size_t)w.tile << INNER_TLOG)));
+    const size_t o_step = ((size_t)out_cstride << LOGN) * 8;
+    const bool scaled = MODE == FIN_ADD && fa.cst2 != nullptr;
+    if constexpr (INT) {
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            u64 x[2][4];
+            inner_products_int<LOGN>(ia, oa, w, w.a, m, h, x[0], x[1]);
+#pragma unroll
+            for (int c = 0; c < 2; c++)
+#pragma unroll
+                for (int i = 0; i < 2; i++) {
+                    const int ii = 2 * h + i;
+                    const u64x2 rv = ld_at<u64x2>(r_tile + c * r_step + INNER_THREADS * 16 * ii, lane16);
+                    const u64x2 av = fin_addend<LOGN, MODE>(fa, oa, ia, w, c, ii, m.q);
+                    u64x2 res;
+                    res.x = mul_shoup(x[c][2 * i] + m.q - rv.x, fa.cst[w.a], m.q);
+                    res.y = mul_shoup(x[c][2 * i + 1] + m.q - rv.y, fa.cst[w.a], m.q);
+                    res.x = csub(res.x + (scaled ? mul_shoup(av.x, fa.cst2[w.a], m.q) : av.x), m.q);
+                    res.y = csub(res.y + (scaled ? mul_shoup(av.y, fa.cst2[w.a], m.q) : av.y), m.q);
+                    *(u64x2 *)(o + c * o_step + INNER_THREADS * 16 * ii + lane16) = res;
+                }
+        }
+    } else {
+        __shared__ u64 lds[INNER_BLOCKS * TILE_GROUP];
+        __shared__ __align__(16) double tws[INNER_BLOCKS * 256];
+        __shared__ __align__(16) u64 pre[INNER_BLOCKS * 256];
+        const unsigned wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+        const ArithFp ar = make_fp(T, w.a, LOGN);
+        const BlockLane b = block_lane(lds, tws);
+        const char *r_lane = r_tile + wave * 4096u + lane * 16u;
+        double acc[2][8];
+        inner_products8<LOGN>(ia, oa, T, w, w.a, ar, b, lds, tws, pre, r_lane, acc[0], acc[1]);
+        // the corrections are transformed in the output's own blocks: other twiddles where a rotation maps the tile
+        // elsewhere (each wave replaces those of the two blocks it owns, its last reads of them are behind a barrier, and
+        // what it still has in flight was issued before the last key words and has arrived with them)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (w.tile_in != w.tile)
+            wave_copy_4k<false>((const char *)(T.twd_blk + (((size_t)w.a << LOGN) + ((size_t)w.tile << INNER_TLOG))) + wave * 4096u + lane * 16u,
+                                (char *)(tws + wave * 512));
+        const double k1 = fa.cst_d[w.a], k2 = scaled ? fa.cst2_d[w.a] : 0.0;
+#pragma unroll
+        for (int c = 0; c < 2; c++) {
+            double dv[8];
+            u64x2 av[4];
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            const u64 *pw = pre + b.blk * 256 + b.t;
+#pragma unroll
+            for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(pw[32 * k]);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (c == 0) wave_copy_4k<true>(r_lane + r_step, (char *)(pre + wave * 512));
+#pragma unroll
+            for (int i = 0; i < 4; i++) av[i] = fin_addend<LOGN, MODE>(fa, oa, ia, w, c, i, m.q);
+            block_pass8(ar, dv, b);
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const unsigned p = pair8_at(i), wd = tile_at(p >> 8, p & 255u);
+                dv[2 * i] = ar.load_mid(lds[wd]), dv[2 * i + 1] = ar.load_mid(lds[wd + 1]);
+            }
+            if (c == 0) __syncthreads();
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                u64x2 res;
+#pragma unroll
+                for (int e = 0; e < 2; e++) {
+                    const double ad = u2d(av[i][e]);
+                    const double v = ar.mulmod(acc[c][2 * i + e] - dv[2 * i + e], k1) + (scaled ? ar.mulmod(ad, k2) : ad);
+                    res[e] = fp_canon(v, m.qd, m.qinvd);
+                }
+                __builtin_nontemporal_store(res, (u64x2 *)(o + c * o_step + INNER_THREADS * 16 * i + lane16));
+            }
         }
     }
 }

@@ -72,20 +72,15 @@ __device__ __forceinline__ int conv_op_level(const ConvArgs &cv, unsigned slot)
     return l ? l : cv.level;
 }
 
-// A limb's slot within its operation decodes as component c = slot / nl, limb i = slot % nl.
+// Finishing epilogue of the block pass: out = (u - ntt) * cst + addend.  A limb's slot within its operation decodes
+// as component c = slot / nl, limb i = slot % nl.
 struct FinArgs {
     const u64 *u;   // minuend limbs, component stride u_cstride limbs
     u64 *out;       // component stride out_cstride limbs
-    const u64 *add; // mode 2: c0 limbs [nl][N], read through the automorphism index map; mode 3: component
-                    // stride add_cstride limbs
-    const u64 *self; // mode 4: [2][nl][N] per operation, self_stride limbs apart
-    const ShoupConst *cst, *cst2;
-    const double *cst_d, *cst2_d;
-    // mode 0: no addend; 1: add what `out` holds; 2: add sigma_g(c0) to component 0; 3: add the limb of `add`
-    // times cst2 (cst2 == nullptr: as it is); 4: as 2, plus the limb of `self` (rotate-and-add)
-    int u_cstride, out_cstride, add_cstride, self_stride, nl, mode;
-    unsigned g;
-    int hoisted; // operation o writes to out[o] and uses Galois element g[o] of the HoistOuts argument
+    const u64 *add; // addend limbs, component stride add_cstride limbs; null: no addend
+    const ShoupConst *cst;
+    const double *cst_d;
+    int u_cstride, out_cstride, add_cstride, nl;
     int dst_stride, u_stride, out_stride, add_stride; // limbs between two operations in each buffer
 };
 
@@ -321,67 +316,38 @@ __device__ __forceinline__ u64 conv_get(const ConvSetup<NSMAX> &S, const ArithIn
 
 // ---- epilogue: what the forward block pass does with a finished (canonical) NTT value ---------------------
 
-#define HOIST_OUT_MAX HE_OPS_MAX
-struct HoistOuts {
-    u64 *out[HOIST_OUT_MAX];
-    unsigned g[HOIST_OUT_MAX];
-    // mixed-level rotations: the operation's input c0 limbs (mode 2 addend) and the limbs per component of its
-    // output; null / 0: the launch-wide values of FinArgs
-    const u64 *add[HOIST_OUT_MAX];
-    uint8_t cstride[HOIST_OUT_MAX];
-};
-
 // Operands of the epilogue for one output: issued before the transform so that the loads overlap it.
 struct FinOperands {
     u64 uv, av;
 };
 template <int LOGN>
-__device__ __forceinline__ FinOperands fin_load(const FinArgs &fa, const HoistOuts &ho, const DevTables &T, unsigned slot,
-                                                unsigned pos)
+__device__ __forceinline__ FinOperands fin_load(const FinArgs &fa, unsigned slot, unsigned pos)
 {
     const unsigned op = slot / (unsigned)fa.dst_stride;
     slot -= op * (unsigned)fa.dst_stride;
     const unsigned c = slot / fa.nl, i = slot % fa.nl;
     FinOperands o;
     o.uv = __builtin_nontemporal_load(fa.u + ((((size_t)op * fa.u_stride + (size_t)c * fa.u_cstride + i) << LOGN) + pos));
-    o.av = 0;
-    if (fa.mode == 1)
-        o.av = fa.out[(((size_t)op * fa.out_stride + (size_t)c * fa.out_cstride + i) << LOGN) + pos];
-    else if (fa.mode == 2 && c == 0) {
-        const u64 *add = fa.hoisted && ho.add[op] ? ho.add[op] : fa.add + (((size_t)op * fa.add_stride) << LOGN);
-        o.av = add[((size_t)i << LOGN) + galois_index(pos, fa.hoisted ? ho.g[op] : fa.g, LOGN)];
-    }
-    else if (fa.mode == 3)
-        o.av = fa.add[(((size_t)op * fa.add_stride + (size_t)c * fa.add_cstride + i) << LOGN) + pos];
-    else if (fa.mode == 4) {
-        const u64 sv = fa.self[(((size_t)op * fa.self_stride + (size_t)c * fa.nl + i) << LOGN) + pos];
-        const u64 rv = c == 0 ? fa.add[(((size_t)op * fa.add_stride + i) << LOGN) + galois_index(pos, fa.g, LOGN)] : 0;
-        o.av = csub(sv + rv, T.mod[i].q);
-    }
+    o.av = fa.add ? fa.add[(((size_t)op * fa.add_stride + (size_t)c * fa.add_cstride + i) << LOGN) + pos] : 0;
     return o;
 }
 
 // FP: the limb's modulus is on the floating-point path (known from the transform's arithmetic at compile time)
 template <int LOGN, bool FP>
-__device__ __forceinline__ void fin_store(const FinArgs &fa, const HoistOuts &ho, const DevTables &T, unsigned slot,
-                                          unsigned pos, u64 rv, const FinOperands &fo)
+__device__ __forceinline__ void fin_store(const FinArgs &fa, const DevTables &T, unsigned slot, unsigned pos, u64 rv,
+                                          const FinOperands &fo)
 {
     const unsigned op = slot / (unsigned)fa.dst_stride;
     slot -= op * (unsigned)fa.dst_stride;
     const unsigned c = slot / fa.nl, i = slot % fa.nl;
     const ModConst m = T.mod[i];
-    const unsigned out_cstride = fa.hoisted && ho.cstride[op] ? ho.cstride[op] : (unsigned)fa.out_cstride;
-    const size_t o = (((size_t)op * fa.out_stride + (size_t)c * out_cstride + i) << LOGN) + pos;
-    const bool scaled = fa.mode == 3 && fa.cst2 != nullptr;
+    const size_t o = (((size_t)op * fa.out_stride + (size_t)c * fa.out_cstride + i) << LOGN) + pos;
     u64 res;
-    if (FP) {
-        const double av = scaled ? fp_mulmod(u2d(fo.av), fa.cst2_d[i], m.qd, m.qinvd) : u2d(fo.av);
-        res = fp_canon(fp_mulmod(u2d(fo.uv) - u2d(rv), fa.cst_d[i], m.qd, m.qinvd) + av, m.qd, m.qinvd);
-    } else {
-        const u64 av = scaled ? mul_shoup(fo.av, fa.cst2[i], m.q) : fo.av;
-        res = csub(mul_shoup(fo.uv + m.q - rv, fa.cst[i], m.q) + av, m.q);
-    }
-    __builtin_nontemporal_store(res, (fa.hoisted ? ho.out[op] : fa.out) + o); // a result: nothing in this launch reads it
+    if (FP)
+        res = fp_canon(fp_mulmod(u2d(fo.uv) - u2d(rv), fa.cst_d[i], m.qd, m.qinvd) + u2d(fo.av), m.qd, m.qinvd);
+    else
+        res = csub(mul_shoup(fo.uv + m.q - rv, fa.cst[i], m.q) + fo.av, m.q);
+    __builtin_nontemporal_store(res, fa.out + o); // a result: nothing in this launch reads it
 }
 
 // LDS tile of the block pass: 16 groups x 256 elements; one pad word per 16 elements and 16 pad words per
@@ -412,7 +378,7 @@ __device__ __forceinline__ unsigned col_at(unsigned r, unsigned c) { return (r >
 
 template <int LOGN, int EPI, class A>
 __device__ __forceinline__ void fwd_blocks_body(u64 *__restrict__ limb, const A &ar, u64 *lds, unsigned tile,
-                                                const FinArgs &fa, const HoistOuts &ho, const DevTables &T, unsigned slot)
+                                                const FinArgs &fa, const DevTables &T, unsigned slot)
 {
     const unsigned blk = threadIdx.x >> 4, il = threadIdx.x & 15;
     const unsigned bg = tile * BLK_PER_WG + blk; // block index within the limb
@@ -423,7 +389,7 @@ __device__ __forceinline__ void fwd_blocks_body(u64 *__restrict__ limb, const A 
         a[k] = ar.load_mid(__builtin_nontemporal_load(limb + bg * 256 + il + 16 * k)); // read once: the column pass wrote it
     if (EPI == EPI_FIN) {
 #pragma unroll
-        for (int k = 0; k < 16; k++) fo[k] = fin_load<LOGN>(fa, ho, T, slot, bg * 256 + il + 16 * k);
+        for (int k = 0; k < 16; k++) fo[k] = fin_load<LOGN>(fa, slot, bg * 256 + il + 16 * k);
     }
     ar.fwd16(a, LOGN - 8, bg, true);
 #pragma unroll
@@ -441,7 +407,7 @@ __device__ __forceinline__ void fwd_blocks_body(u64 *__restrict__ limb, const A 
         const unsigned pos = bg * 256 + il + 16 * k;
         const u64 v = lds[tile_at(blk, il + 16 * k)];
         if (EPI == EPI_FIN)
-            fin_store<LOGN, A::IS_FP>(fa, ho, T, slot, pos, v, fo[k]);
+            fin_store<LOGN, A::IS_FP>(fa, T, slot, pos, v, fo[k]);
         else
             __builtin_nontemporal_store(v, limb + pos);
     }
@@ -485,8 +451,7 @@ __device__ __forceinline__ void inv_blocks_body(const u64 *in, u64 *limb, const 
 
 // grid.x = (N/4096) * batch
 template <int LOGN, int EPI>
-__global__ __launch_bounds__(BLK_THREADS, EPI == EPI_FIN ? 4 : 1) void k_ntt_fwd_blocks(u64 *__restrict__ data, DevTables T, LimbBatch lb, FinArgs fa,
-                                                                HoistOuts ho)
+__global__ __launch_bounds__(BLK_THREADS, EPI == EPI_FIN ? 4 : 1) void k_ntt_fwd_blocks(u64 *__restrict__ data, DevTables T, LimbBatch lb, FinArgs fa)
 {
     __shared__ u64 lds[BLK_PER_WG * TILE_GROUP];
     constexpr unsigned TILES = (1u << LOGN) / (256 * BLK_PER_WG);
@@ -494,9 +459,9 @@ __global__ __launch_bounds__(BLK_THREADS, EPI == EPI_FIN ? 4 : 1) void k_ntt_fwd
     const unsigned mi = lb.mod[b], slot = lb.slot[b];
     u64 *limb = data + ((size_t)slot << LOGN);
     if (T.mod[mi].qd != 0.0)
-        fwd_blocks_body<LOGN, EPI>(limb, make_fp(T, mi, LOGN), lds, tile, fa, ho, T, slot);
+        fwd_blocks_body<LOGN, EPI>(limb, make_fp(T, mi, LOGN), lds, tile, fa, T, slot);
     else
-        fwd_blocks_body<LOGN, EPI>(limb, make_int(T, mi, LOGN), lds, tile, fa, ho, T, slot);
+        fwd_blocks_body<LOGN, EPI>(limb, make_int(T, mi, LOGN), lds, tile, fa, T, slot);
 }
 
 template <int LOGN>

@@ -13,7 +13,7 @@
 enum KernelId {
     KID_FWD_COLS, KID_FWD_COLS_MODUP, KID_FWD_COLS_MODDOWN, KID_FWD_COLS_RESCALE, KID_FWD_COLS_MODDOWN_RS, KID_FWD_BLOCKS,
     KID_FWD_BLOCKS_FIN,
-    KID_INV_BLOCKS, KID_INV_COLS, KID_LIMBWISE, KID_CMULT, KID_TENSOR, KID_INNER, KID_COUNT
+    KID_INV_BLOCKS, KID_INV_COLS, KID_LIMBWISE, KID_CMULT, KID_TENSOR, KID_INNER, KID_INNER_FIN, KID_COUNT
 };
 
 // Creates the event pair of one profiled launch and appends it to the context's record list.
@@ -42,13 +42,17 @@ struct DevLaunch {
     // the same with the corrected base conversions (entries of prologues without a conversion stay null)
     void (*fwd_cols_ex[5])(he_ctx *c, hipStream_t st, int kid, double bytes, bool wide, u64 *data, const LimbBatch &lb, int nb,
                            const ConvArgs &cv);
-    // forward block pass of the first nb limbs of lb; fin: with the ModDown / rescale epilogue
+    // forward block pass of the first nb limbs of lb; fin: with the finishing epilogue
     void (*fwd_blocks)(he_ctx *c, hipStream_t st, double bytes, bool fin, u64 *data, const LimbBatch &lb, int nb,
-                       const FinArgs &fa, const HoistOuts &ho);
+                       const FinArgs &fa);
     void (*inv_blocks)(he_ctx *c, hipStream_t st, double bytes, const u64 *src, u64 *dst, const LimbBatch &lb, int nb);
     void (*inv_cols)(he_ctx *c, hipStream_t st, double bytes, int scale, u64 *dst, const LimbBatch &lb, int nb,
                      const ConvArgs &cv);
-    void (*inner)(he_ctx *c, hipStream_t st, double bytes, unsigned grid, const InnerArgs &ia, const HoistKeys &hk);
+    // inner product on the limbs ia.first .. level + K - 1, and the finishing one on the first fa.nl limbs: those on the
+    // integer path or the others
+    void (*inner)(he_ctx *c, hipStream_t st, double bytes, unsigned grid, const InnerArgs &ia, const OpArgs &oa);
+    void (*inner_fin)(he_ctx *c, hipStream_t st, double bytes, unsigned grid, int mode, bool integer, const InnerArgs &ia,
+                      const FinishArgs &fa, const OpArgs &oa);
 };
 // Each translation unit fills its part of a ring size's table: dev_launch_cols<logN>_<p> the forward
 // column pass with prologue p (p = 5: the inverse column pass).
@@ -73,14 +77,14 @@ HE_DECL_COLS(17)
 
 template <int LOGN>
 static void launch_fwd_blocks(he_ctx *c, hipStream_t st, double bytes, bool fin, u64 *data, const LimbBatch &lb, int nb,
-                              const FinArgs &fa, const HoistOuts &ho)
+                              const FinArgs &fa)
 {
     if (fin)
         KLAUNCH_T(c, st, KID_FWD_BLOCKS_FIN, bytes, (k_ntt_fwd_blocks<LOGN, EPI_FIN>), BLK_TILES(c) * nb, BLK_THREADS, data,
-                  c->dev, lb, fa, ho);
+                  c->dev, lb, fa);
     else
         KLAUNCH_T(c, st, KID_FWD_BLOCKS, bytes, (k_ntt_fwd_blocks<LOGN, EPI_STORE>), BLK_TILES(c) * nb, BLK_THREADS, data,
-                  c->dev, lb, fa, ho);
+                  c->dev, lb, fa);
 }
 template <int LOGN>
 static void launch_inv_blocks(he_ctx *c, hipStream_t st, double bytes, const u64 *src, u64 *dst, const LimbBatch &lb, int nb)
@@ -88,7 +92,27 @@ static void launch_inv_blocks(he_ctx *c, hipStream_t st, double bytes, const u64
     KLAUNCH_T(c, st, KID_INV_BLOCKS, bytes, (k_ntt_inv_blocks<LOGN>), BLK_TILES(c) * nb, BLK_THREADS, src, dst, c->dev, lb);
 }
 template <int LOGN>
-static void launch_inner(he_ctx *c, hipStream_t st, double bytes, unsigned grid, const InnerArgs &ia, const HoistKeys &hk)
+static void launch_inner(he_ctx *c, hipStream_t st, double bytes, unsigned grid, const InnerArgs &ia, const OpArgs &oa)
 {
-    KLAUNCH_T(c, st, KID_INNER, bytes, (k_inner_blocks8<LOGN>), grid, INNER_THREADS, ia, c->dev, hk);
+    KLAUNCH_T(c, st, KID_INNER, bytes, (k_inner_blocks8<LOGN>), grid, INNER_THREADS, ia, c->dev, oa);
+}
+template <int LOGN, int MODE>
+static void launch_inner_fin_mode(he_ctx *c, hipStream_t st, double bytes, unsigned grid, bool integer, const InnerArgs &ia,
+                                  const FinishArgs &fa, const OpArgs &oa)
+{
+    if (integer)
+        KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_inner_fin<LOGN, MODE, true>), grid, INNER_THREADS, ia, fa, c->dev, oa);
+    else
+        KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_inner_fin<LOGN, MODE, false>), grid, INNER_THREADS, ia, fa, c->dev, oa);
+}
+template <int LOGN>
+static void launch_inner_fin(he_ctx *c, hipStream_t st, double bytes, unsigned grid, int mode, bool integer, const InnerArgs &ia,
+                             const FinishArgs &fa, const OpArgs &oa)
+{
+    if (mode == FIN_ADD)
+        launch_inner_fin_mode<LOGN, FIN_ADD>(c, st, bytes, grid, integer, ia, fa, oa);
+    else if (mode == FIN_ROT)
+        launch_inner_fin_mode<LOGN, FIN_ROT>(c, st, bytes, grid, integer, ia, fa, oa);
+    else
+        launch_inner_fin_mode<LOGN, FIN_ROTSUM>(c, st, bytes, grid, integer, ia, fa, oa);
 }
