@@ -70,57 +70,64 @@ __host__ __device__ inline unsigned inner_grid(unsigned tiles, unsigned limbs, u
     return (tiles * limbs + XCDS - 1) / XCDS * XCDS * count;
 }
 
-// Eight elements per thread and 128 threads per work-group: measured at 512, 256, 128 and 64 threads, work-groups of
-// 128 win by 3 to 8 % because the barriers between the phases of a digit then stall two waves instead of eight while
-// the other work-groups of the compute unit run.  25 KiB of LDS (exchange tile, twiddles, the next digit) allow six
-// work-groups per compute unit, three waves per SIMD, at up to 170 registers.  A 256-element
+// A wave works alone: it produces 512 consecutive outputs, eight per lane, and the sources of an aligned group of 512
+// are an aligned group of 512, so the wave transforms the very blocks that its outputs read and nothing is exchanged
+// between waves: no work-group barrier anywhere.  With the sources of a tile of 1024 shared between two waves, two barriers
+// per digit, the special limbs of 32 mixed rotations (N = 2^16, levels 8 .. 24) took 228 us instead of 186, a whole
+// rotation 113.9 us instead of 110.4 at N = 2^16, level 13, and 47.9 instead of 44.7 at N = 2^12.  Two waves per work-group
+// (one: the same within 0.7 %),
+// 25 KiB of LDS (exchange tile, twiddles, the next digit: 12.25 KiB per wave) allow three waves per SIMD, at up to
+// 170 registers.  A 256-element
 // block belongs to 32 lanes (half a wave) and its block pass runs as three register steps, stages 0-2, 3-5 and
 // 6-7 of the block, with two exchanges through LDS among those lanes:
 //   step 1: lane t holds e = t + 32 k;   step 2: lane (g = t & 7, r = t >> 3) holds e = 32 g + r + 4 k;
 //   step 3: lane t holds e = 4 t + k' and 128 + 4 t + k' (k' < 4).
 // With one pad word per 16 elements every 16 consecutive lanes of each pattern hit 16 different 8-byte banks.
 // All 255 twiddles of a block's eight stages sit in LDS, the one of local stage m and group i at 2^m - 1 + i.
-// In the product phase thread t owns the pairs (INNER_TILE tile + 2 INNER_THREADS i + 2 t, + 1), i < 4.
+// In the product phase lane t of wave v owns the pairs (INNER_TILE tile + 512 v + 128 i + 2 t, + 1), i < 4.
 // The 128 twiddles of a block's last stage, like all others, are contiguous in the block-major table (twd_blk), so a
-// tile's 8 KiB of twiddles are fetched straight into LDS.
+// wave's 4 KiB of twiddles are fetched straight into LDS.
 
-#ifndef INNER_THREADS
 #define INNER_THREADS 128
-#endif
 #define INNER_TILE (INNER_THREADS * 8)      // outputs per work-group
-#define INNER_BLOCKS (INNER_THREADS / 32)   // 256-element blocks per work-group
-#define INNER_TLOG (INNER_THREADS == 512 ? 12 : INNER_THREADS == 256 ? 11 : INNER_THREADS == 128 ? 10 : 9)
-static_assert(INNER_THREADS == 512 || INNER_THREADS == 256 || INNER_THREADS == 128 || INNER_THREADS == 64, "tile of 4096, 2048, 1024 or 512 outputs");
-__device__ __forceinline__ unsigned pair8_at(unsigned i) { return 2u * INNER_THREADS * i + 2u * threadIdx.x; }
+#define INNER_TLOG 10
+#define WAVE_OUT 512u                       // outputs per wave
+#define WAVE_LOG 9
+#define WAVE_BLOCKS 2                       // 256-element blocks per wave
+#define WAVE_LDS (WAVE_BLOCKS * (TILE_GROUP + 512)) // LDS words per wave: exchange tile, twiddles, the next digit
+__device__ __forceinline__ unsigned wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+__device__ __forceinline__ unsigned pair8_at(unsigned i) { return WAVE_OUT * wave_id() + 128u * i + 2u * (threadIdx.x & 63u); }
 
-// Inverse block pass of the special limbs from the pairs of the product phase: the results go through LDS to the
-// first half of the threads, which run the 16-element form; the other threads only take part in the barriers.
+// Inverse block pass of both components of a special limb from the pairs of the product phase: through the wave's LDS to
+// the 16-element form, one component per half of the wave (u: component 0, component 1 comp_limbs further on).
 template <int LOGN, class A>
-__device__ __forceinline__ void inv_blocks_from_pairs8(const u64 (&r)[8], u64 *limb, const A &ar, u64 *lds, unsigned tile)
+__device__ __forceinline__ void inv_blocks_from_pairs8(const u64 (&r0)[8], const u64 (&r1)[8], u64 *u, size_t comp_words, const A &ar,
+                                                       u64 *lds, unsigned grp)
 {
+    const unsigned lane = threadIdx.x & 63u;
+    static_assert(2 * WAVE_BLOCKS * TILE_GROUP <= WAVE_LDS, "both components in the wave's LDS");
+    block_sync(); // the product phase has read what is overwritten here
 #pragma unroll
     for (int i = 0; i < 4; i++) {
-        const unsigned p = pair8_at(i);
-        lds[tile_at(p >> 8, p & 255u)] = r[2 * i];
-        lds[tile_at(p >> 8, (p & 255u) + 1)] = r[2 * i + 1];
+        const unsigned p = 128u * i + 2u * lane, wd = tile_at(p >> 8, p & 255u);
+        lds[wd] = r0[2 * i], lds[wd + 1] = r0[2 * i + 1];
+        lds[WAVE_BLOCKS * TILE_GROUP + wd] = r1[2 * i], lds[WAVE_BLOCKS * TILE_GROUP + wd + 1] = r1[2 * i + 1];
     }
-    __syncthreads();
-    if (threadIdx.x < INNER_THREADS / 2) {
-        const unsigned blk = threadIdx.x >> 4, il = threadIdx.x & 15, bg = tile * INNER_BLOCKS + blk;
-        typename A::V a[16];
+    block_sync();
+    const unsigned blk = lane >> 4, il = lane & 15, bg = grp * WAVE_BLOCKS + (blk & 1u); // blk 2, 3: component 1
+    u64 *limb = u + (blk >> 1) * comp_words;
+    typename A::V a[16];
 #pragma unroll
-        for (int k = 0; k < 16; k++) a[k] = ar.load(lds[tile_at(blk, 16 * il + k)]);
-        ar.template inv16<false>(a, LOGN - 4, bg * 16 + il);
+    for (int k = 0; k < 16; k++) a[k] = ar.load(lds[tile_at(blk, 16 * il + k)]);
+    ar.template inv16<false>(a, LOGN - 4, bg * 16 + il);
 #pragma unroll
-        for (int k = 0; k < 16; k++) lds[tile_at(blk, 16 * il + k)] = ar.store_mid(a[k]);
-        block_sync();
+    for (int k = 0; k < 16; k++) lds[tile_at(blk, 16 * il + k)] = ar.store_mid(a[k]);
+    block_sync();
 #pragma unroll
-        for (int k = 0; k < 16; k++) a[k] = ar.load_mid(lds[tile_at(blk, il + 16 * k)]);
-        ar.template inv16<false>(a, LOGN - 8, bg);
+    for (int k = 0; k < 16; k++) a[k] = ar.load_mid(lds[tile_at(blk, il + 16 * k)]);
+    ar.template inv16<false>(a, LOGN - 8, bg);
 #pragma unroll
-        for (int k = 0; k < 16; k++) limb[bg * 256 + il + 16 * k] = ar.store_mid(a[k]);
-    }
-    __syncthreads();
+    for (int k = 0; k < 16; k++) limb[bg * 256 + il + 16 * k] = ar.store_mid(a[k]);
 }
 
 // Addresses are formed as a wave-uniform base plus a 32-bit lane offset so that they stay in scalar registers;
@@ -152,15 +159,15 @@ struct BlockLane {
 __device__ __forceinline__ BlockLane block_lane(u64 *lds, const double *tws)
 {
     BlockLane b;
-    b.blk = threadIdx.x >> 5, b.t = threadIdx.x & 31, b.g2 = b.t & 7;
+    b.blk = (threadIdx.x >> 5) & 1u, b.t = threadIdx.x & 31, b.g2 = b.t & 7;
     b.l1 = lds + b.blk * TILE_GROUP + b.t + (b.t >> 4);
     b.l2 = lds + b.blk * TILE_GROUP + 34 * b.g2 + (b.t >> 3);
     b.l3 = lds + b.blk * TILE_GROUP + 4 * b.t + (b.t >> 2);
     b.tw = tws + b.blk * 256;
     return b;
 }
-// Block pass of the eight values dv of this thread (pattern of step 1); the result is left in LDS, element e of
-// block b at tile_at(b, e), for the caller to read behind a barrier.
+// Block pass of the eight values dv of this thread (pattern of step 1); the result is left in the wave's LDS, element e
+// of block b at tile_at(b, e), for the caller to read after a block_sync.
 // Ranges (in units of q): the column pass leaves up to 3.7; reduced, step 1 ends below 2.7 and step 2 below 6.3;
 // reduced again, step 3 ends below 1.9, small enough for exact products.
 __device__ __forceinline__ void block_pass8(const ArithFp &ar, double (&dv)[8], const BlockLane &b)
@@ -184,7 +191,8 @@ __device__ __forceinline__ void block_pass8(const ArithFp &ar, double (&dv)[8], 
 
 // What one work-group works on.
 struct InnerTile {
-    unsigned op, tile, tile_in, g;
+    unsigned op, tile, g;
+    unsigned grp, grp_in; // this wave's group of 512 outputs within the limb, and the group its sources lie in
     int a; // active limb
     int level, beta; // of the operation
     bool none;
@@ -200,7 +208,8 @@ __device__ __forceinline__ InnerTile inner_tile(const InnerArgs &ia, const OpArg
     w.tile = tl % ntile;
     w.a = first + limbs - 1 - (int)(tl / ntile); // special limbs (the slowest) first
     w.g = ia.per_op ? oa.g[w.op] : ia.g;
-    w.tile_in = w.g == 1 ? w.tile : galois_index(w.tile << INNER_TLOG, w.g, LOGN) >> INNER_TLOG;
+    w.grp = w.tile * (INNER_TILE / WAVE_OUT) + wave_id();
+    w.grp_in = w.g == 1 ? w.grp : galois_index(w.grp << WAVE_LOG, w.g, LOGN) >> WAVE_LOG;
     w.level = ia.per_op && oa.level[w.op] ? oa.level[w.op] : ia.level;
     w.beta = (w.level + ia.alpha - 1) / ia.alpha;
     // padding of the last group of eight; an operation below the layout's level has no limbs a in [its level, level)
@@ -209,7 +218,7 @@ __device__ __forceinline__ InnerTile inner_tile(const InnerArgs &ia, const OpArg
 }
 
 // The products of one floating-point limb: acc0, acc1 = sums over the digits, within 3.5 q, for this thread's pairs.
-// If `then` is not null, the tile it points at (this lane's address of 4 KiB per wave) is on its way into `pre` when
+// If `then` is not null, the 4 KiB that it points at (this lane's address) are on their way into `pre` when
 // the function returns.
 template <int LOGN>
 __device__ __forceinline__ void inner_products8(const InnerArgs &ia, const OpArgs &oa, const DevTables &T, const InnerTile &w,
@@ -217,29 +226,27 @@ __device__ __forceinline__ void inner_products8(const InnerArgs &ia, const OpArg
                                                 const char *then, double (&acc0)[8], double (&acc1)[8])
 {
     const int a = w.a, own = a < ia.level ? a / ia.alpha : -1, M = ia.L + ia.K, Ma = ia.level + ia.K;
-    const unsigned wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    // wave-uniform bases (bytes): raised digit 0 and key component 0 of digit 0 for this limb and tile; digit j is
+    const unsigned lane16 = (threadIdx.x & 63) * 16u; // this lane's pair within a row of 64 pairs
+    // wave-uniform bases (bytes): raised digit 0 and key component 0 of digit 0 for this limb and group; digit j is
     // raised_step / key_step further on, key component 1 comp_step after component 0
-    const char *raised0 = (const char *)(ia.raised + ((((size_t)w.op * ia.raised_stride + a) << LOGN) + ((size_t)w.tile_in << INNER_TLOG)));
-    const char *key0 = (const char *)((ia.per_op ? oa.evk[w.op] : ia.evk) + (((size_t)mi << LOGN) + ((size_t)w.tile << INNER_TLOG)));
+    const char *raised0 = (const char *)(ia.raised + ((((size_t)w.op * ia.raised_stride + a) << LOGN) + ((size_t)w.grp_in << WAVE_LOG)));
+    const char *key0 = (const char *)((ia.per_op ? oa.evk[w.op] : ia.evk) + (((size_t)mi << LOGN) + ((size_t)w.grp << WAVE_LOG)));
     const size_t raised_step = ((size_t)Ma << LOGN) * 8, comp_step = ((size_t)M << LOGN) * 8, key_step = 2 * comp_step;
-    const unsigned lane16 = threadIdx.x * 16u; // this thread's pair within a row of INNER_THREADS pairs
     // The raised digit after the one being worked on is already on its way into LDS.  A digit that only this operation
     // reads is streamed past the key slices that the batch shares in L2.
     auto prefetch = [&](int j) {
-        const char *src = raised0 + (size_t)j * raised_step + wave * 4096u + lane * 16u;
+        const char *src = raised0 + (size_t)j * raised_step + lane16;
         if (ia.raised_stride != 0)
-            wave_copy_4k<true>(src, (char *)(pre + wave * 512));
+            wave_copy_4k<true>(src, (char *)pre);
         else
-            wave_copy_4k<false>(src, (char *)(pre + wave * 512));
+            wave_copy_4k<false>(src, (char *)pre);
     };
-    wave_copy_4k<false>((const char *)(T.twd_blk + (((size_t)mi << LOGN) + ((size_t)w.tile_in << INNER_TLOG))) + wave * 4096u + lane * 16u,
-                        (char *)(tws + wave * 512));
+    wave_copy_4k<false>((const char *)(T.twd_blk + (((size_t)mi << LOGN) + ((size_t)w.grp_in << WAVE_LOG))) + lane16, (char *)tws);
     const int j0 = own == 0 ? 1 : 0;
     if (j0 < w.beta)
         prefetch(j0);
     else if (then)
-        wave_copy_4k<true>(then, (char *)(pre + wave * 512));
+        wave_copy_4k<true>(then, (char *)pre);
     // pair i of the product phase: LDS words of the sources of its even and odd element (an aligned pair, in
     // either order), and whether the pair arrives swapped
     unsigned lsx[4], lsy[4], swm = 0;
@@ -247,7 +254,7 @@ __device__ __forceinline__ void inner_products8(const InnerArgs &ia, const OpArg
     for (int i = 0; i < 4; i++) {
         const unsigned pos = (w.tile << INNER_TLOG) + pair8_at(i);
         const unsigned sr = w.g == 1 ? pos : galois_index(pos, w.g, LOGN);
-        const unsigned sl = sr & (INNER_TILE - 2u), sw = sr & 1u;
+        const unsigned sl = sr & (WAVE_OUT - 2u), sw = sr & 1u;
         const unsigned wd = (sl >> 8) * TILE_GROUP + (sl & 255u) + ((sl & 255u) >> 4);
         lsx[i] = wd + sw, lsy[i] = wd + 1 - sw;
         swm |= sw << i;
@@ -270,7 +277,7 @@ __device__ __forceinline__ void inner_products8(const InnerArgs &ia, const OpArg
             }
 #pragma unroll
             for (int i = 0; i < 4; i++)
-                e0[i] = ld_at<f64x2>(kj + INNER_THREADS * 16 * i, lane16), e1[i] = ld_at<f64x2>(kj + comp_step + INNER_THREADS * 16 * i, lane16);
+                e0[i] = ld_at<f64x2>(kj + 1024 * i, lane16), e1[i] = ld_at<f64x2>(kj + comp_step + 1024 * i, lane16);
         } else {
             // this digit has arrived (nothing else of this wave is in flight here); once it is in registers the
             // buffer is free for the next one
@@ -284,17 +291,17 @@ __device__ __forceinline__ void inner_products8(const InnerArgs &ia, const OpArg
                 if (jn < w.beta)
                     prefetch(jn);
                 else if (then)
-                    wave_copy_4k<true>(then, (char *)(pre + wave * 512));
+                    wave_copy_4k<true>(then, (char *)pre);
             }
             // the key loads are issued before the block pass and complete behind it
 #pragma unroll
             for (int i = 0; i < 4; i++)
-                e0[i] = ld_at<f64x2>(kj + INNER_THREADS * 16 * i, lane16), e1[i] = ld_at<f64x2>(kj + comp_step + INNER_THREADS * 16 * i, lane16);
+                e0[i] = ld_at<f64x2>(kj + 1024 * i, lane16), e1[i] = ld_at<f64x2>(kj + comp_step + 1024 * i, lane16);
             block_pass8(ar, dv, b);
-            __syncthreads();
+            block_sync();
 #pragma unroll
             for (int i = 0; i < 4; i++) dv[2 * i] = ar.load_mid(lds[lsx[i]]), dv[2 * i + 1] = ar.load_mid(lds[lsy[i]]);
-            __syncthreads();
+            block_sync();
         }
 #pragma unroll
         for (int i = 0; i < 4; i++) {
@@ -317,11 +324,11 @@ __device__ __forceinline__ void inner_products_int(const InnerArgs &ia, const Op
                                                    const ModConst &m, int h, u64 (&r0)[4], u64 (&r1)[4])
 {
     const int a = w.a, own = a < ia.level ? a / ia.alpha : -1, M = ia.L + ia.K, Ma = ia.level + ia.K;
-    const char *key0 = (const char *)((ia.per_op ? oa.evk[w.op] : ia.evk) + (((size_t)mi << LOGN) + ((size_t)w.tile << INNER_TLOG)));
+    const char *key0 = (const char *)((ia.per_op ? oa.evk[w.op] : ia.evk) + (((size_t)mi << LOGN) + ((size_t)w.grp << WAVE_LOG)));
     const char *d_limb = (const char *)((ia.per_op && oa.d[w.op] ? oa.d[w.op] : ia.d + (((size_t)w.op * ia.d_stride) << LOGN)) + ((size_t)a << LOGN));
     const char *fin0 = (const char *)(ia.raised + (((size_t)w.op * ia.raised_stride + a) << LOGN));
     const size_t raised_step = ((size_t)Ma << LOGN) * 8, comp_step = ((size_t)M << LOGN) * 8, key_step = 2 * comp_step;
-    const unsigned lane16 = threadIdx.x * 16u;
+    const unsigned lane16 = (threadIdx.x & 63) * 16u;
     unsigned sr[2];
 #pragma unroll
     for (int i = 0; i < 2; i++) {
@@ -340,7 +347,7 @@ __device__ __forceinline__ void inner_products_int(const InnerArgs &ia, const Op
             const u64x2 v = ld_at<u64x2>(dj, (sr[i] & ~1u) * 8u);
             const bool sw = sr[i] & 1u;
             const u64 x = sw ? v.y : v.x, y = sw ? v.x : v.y;
-            const u64x2 ka = ld_at<u64x2>(kj + INNER_THREADS * 16 * ii, lane16), kb = ld_at<u64x2>(kj + comp_step + INNER_THREADS * 16 * ii, lane16);
+            const u64x2 ka = ld_at<u64x2>(kj + 1024 * ii, lane16), kb = ld_at<u64x2>(kj + comp_step + 1024 * ii, lane16);
             mac128(acc0[2 * i], x, ka.x);
             mac128(acc0[2 * i + 1], y, ka.y);
             mac128(acc1[2 * i], x, kb.x);
@@ -354,9 +361,10 @@ __device__ __forceinline__ void inner_products_int(const InnerArgs &ia, const Op
 // First launch: active limbs ia.first .. level + K - 1 of every operation.
 template <int LOGN> __global__ __launch_bounds__(INNER_THREADS, 4) void k_inner_blocks8(InnerArgs ia, DevTables T, OpArgs oa)
 {
-    __shared__ u64 lds[INNER_BLOCKS * TILE_GROUP];
-    __shared__ __align__(16) double tws[INNER_BLOCKS * 256];
-    __shared__ __align__(16) u64 pre[INNER_BLOCKS * 256]; // the next raised digit of this tile, as it lies in memory
+    __shared__ __align__(16) u64 wave_lds[INNER_THREADS / 64][WAVE_LDS];
+    u64 *lds = wave_lds[wave_id()]; // pre: the next raised digit of this group, as it lies in memory
+    double *tws = (double *)(lds + WAVE_BLOCKS * TILE_GROUP);
+    u64 *pre = lds + WAVE_BLOCKS * (TILE_GROUP + 256);
     const int Ma = ia.level + ia.K;
     const InnerTile w = inner_tile<LOGN>(ia, oa, Ma - ia.first, ia.first);
     if (w.none) return;
@@ -380,22 +388,17 @@ template <int LOGN> __global__ __launch_bounds__(INNER_THREADS, 4) void k_inner_
     }
     u64 *u0 = ia.u + ((((size_t)w.op * ia.u_stride + w.a) << LOGN)), *u1 = u0 + ((size_t)Ma << LOGN);
     if (w.a >= ia.level) {
-        if (m.qd != 0.0) {
-            const ArithFp ar = make_fp(T, mi, LOGN);
-            inv_blocks_from_pairs8<LOGN>(r0, u0, ar, lds, w.tile);
-            inv_blocks_from_pairs8<LOGN>(r1, u1, ar, lds, w.tile);
-        } else {
-            const ArithInt ar = make_int(T, mi, LOGN);
-            inv_blocks_from_pairs8<LOGN>(r0, u0, ar, lds, w.tile);
-            inv_blocks_from_pairs8<LOGN>(r1, u1, ar, lds, w.tile);
-        }
+        if (m.qd != 0.0)
+            inv_blocks_from_pairs8<LOGN>(r0, r1, u0, (size_t)Ma << LOGN, make_fp(T, mi, LOGN), lds, w.grp);
+        else
+            inv_blocks_from_pairs8<LOGN>(r0, r1, u0, (size_t)Ma << LOGN, make_int(T, mi, LOGN), lds, w.grp);
     } else {
-        const unsigned lane16 = threadIdx.x * 16u;
-        char *o0 = (char *)(u0 + ((size_t)w.tile << INNER_TLOG)), *o1 = (char *)(u1 + ((size_t)w.tile << INNER_TLOG));
+        const unsigned lane16 = (threadIdx.x & 63) * 16u;
+        char *o0 = (char *)(u0 + ((size_t)w.grp << WAVE_LOG)), *o1 = (char *)(u1 + ((size_t)w.grp << WAVE_LOG));
 #pragma unroll
         for (int i = 0; i < 4; i++) {
-            __builtin_nontemporal_store(u64x2{r0[2 * i], r0[2 * i + 1]}, (u64x2 *)(o0 + INNER_THREADS * 16 * i + lane16));
-            __builtin_nontemporal_store(u64x2{r1[2 * i], r1[2 * i + 1]}, (u64x2 *)(o1 + INNER_THREADS * 16 * i + lane16));
+            __builtin_nontemporal_store(u64x2{r0[2 * i], r0[2 * i + 1]}, (u64x2 *)(o0 + 1024 * i + lane16));
+            __builtin_nontemporal_store(u64x2{r1[2 * i], r1[2 * i + 1]}, (u64x2 *)(o1 + 1024 * i + lane16));
         }
     }
 }
@@ -429,12 +432,12 @@ __global__ __launch_bounds__(INNER_THREADS, INT ? 4 : 6) void k_inner_fin(InnerA
     const InnerTile w = inner_tile<LOGN>(ia, oa, fa.nl, 0);
     const ModConst m = T.mod[w.a < 0 ? 0 : w.a];
     if (w.none || (m.qd == 0.0) != INT) return;
-    const unsigned lane16 = threadIdx.x * 16u;
+    const unsigned lane16 = (threadIdx.x & 63) * 16u;
     const u64 *r = fa.r + (((size_t)w.op * fa.r_stride + w.a) << LOGN);
     const size_t r_step = ((size_t)ia.level << LOGN) * 8;
-    const char *r_tile = (const char *)(r + ((size_t)w.tile << INNER_TLOG));
+    const char *r_grp = (const char *)(r + ((size_t)w.grp << WAVE_LOG));
     const unsigned out_cstride = ia.per_op && oa.level[w.op] ? oa.level[w.op] : (unsigned)fa.out_cstride;
-    char *o = (char *)((ia.per_op ? oa.out[w.op] : fa.out + (((size_t)w.op * fa.out_stride) << LOGN)) + (((size_t)w.a << LOGN) + ((size_t)w.tile << INNER_TLOG)));
+    char *o = (char *)((ia.per_op ? oa.out[w.op] : fa.out + (((size_t)w.op * fa.out_stride) << LOGN)) + (((size_t)w.a << LOGN) + ((size_t)w.grp << WAVE_LOG)));
     const size_t o_step = ((size_t)out_cstride << LOGN) * 8;
     const bool scaled = MODE == FIN_ADD && fa.cst2 != nullptr;
     if constexpr (INT) {
@@ -447,33 +450,32 @@ __global__ __launch_bounds__(INNER_THREADS, INT ? 4 : 6) void k_inner_fin(InnerA
 #pragma unroll
                 for (int i = 0; i < 2; i++) {
                     const int ii = 2 * h + i;
-                    const u64x2 rv = ld_at<u64x2>(r_tile + c * r_step + INNER_THREADS * 16 * ii, lane16);
+                    const u64x2 rv = ld_at<u64x2>(r_grp + c * r_step + 1024 * ii, lane16);
                     const u64x2 av = fin_addend<LOGN, MODE>(fa, oa, ia, w, c, ii, m.q);
                     u64x2 res;
                     res.x = mul_shoup(x[c][2 * i] + m.q - rv.x, fa.cst[w.a], m.q);
                     res.y = mul_shoup(x[c][2 * i + 1] + m.q - rv.y, fa.cst[w.a], m.q);
                     res.x = csub(res.x + (scaled ? mul_shoup(av.x, fa.cst2[w.a], m.q) : av.x), m.q);
                     res.y = csub(res.y + (scaled ? mul_shoup(av.y, fa.cst2[w.a], m.q) : av.y), m.q);
-                    *(u64x2 *)(o + c * o_step + INNER_THREADS * 16 * ii + lane16) = res;
+                    *(u64x2 *)(o + c * o_step + 1024 * ii + lane16) = res;
                 }
         }
     } else {
-        __shared__ u64 lds[INNER_BLOCKS * TILE_GROUP];
-        __shared__ __align__(16) double tws[INNER_BLOCKS * 256];
-        __shared__ __align__(16) u64 pre[INNER_BLOCKS * 256];
-        const unsigned wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+        __shared__ __align__(16) u64 wave_lds[INNER_THREADS / 64][WAVE_LDS];
+        u64 *lds = wave_lds[wave_id()];
+        double *tws = (double *)(lds + WAVE_BLOCKS * TILE_GROUP);
+        u64 *pre = lds + WAVE_BLOCKS * (TILE_GROUP + 256);
         const ArithFp ar = make_fp(T, w.a, LOGN);
         const BlockLane b = block_lane(lds, tws);
-        const char *r_lane = r_tile + wave * 4096u + lane * 16u;
+        const char *r_lane = r_grp + lane16;
         double acc[2][8];
         inner_products8<LOGN>(ia, oa, T, w, w.a, ar, b, lds, tws, pre, r_lane, acc[0], acc[1]);
-        // the corrections are transformed in the output's own blocks: other twiddles where a rotation maps the tile
-        // elsewhere (each wave replaces those of the two blocks it owns, its last reads of them are behind a barrier, and
-        // what it still has in flight was issued before the last key words and has arrived with them)
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (w.tile_in != w.tile)
-            wave_copy_4k<false>((const char *)(T.twd_blk + (((size_t)w.a << LOGN) + ((size_t)w.tile << INNER_TLOG))) + wave * 4096u + lane * 16u,
-                                (char *)(tws + wave * 512));
+        // the corrections are transformed in the output's own blocks: other twiddles where a rotation maps the group
+        // elsewhere (the wave's own reads of the old ones have returned, and what it still has in flight was issued
+        // before the last key words and has arrived with them)
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        if (w.grp_in != w.grp)
+            wave_copy_4k<false>((const char *)(T.twd_blk + (((size_t)w.a << LOGN) + ((size_t)w.grp << WAVE_LOG))) + lane16, (char *)tws);
         const double k1 = fa.cst_d[w.a], k2 = scaled ? fa.cst2_d[w.a] : 0.0;
 #pragma unroll
         for (int c = 0; c < 2; c++) {
@@ -484,17 +486,17 @@ __global__ __launch_bounds__(INNER_THREADS, INT ? 4 : 6) void k_inner_fin(InnerA
 #pragma unroll
             for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(pw[32 * k]);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            if (c == 0) wave_copy_4k<true>(r_lane + r_step, (char *)(pre + wave * 512));
+            if (c == 0) wave_copy_4k<true>(r_lane + r_step, (char *)pre);
 #pragma unroll
             for (int i = 0; i < 4; i++) av[i] = fin_addend<LOGN, MODE>(fa, oa, ia, w, c, i, m.q);
             block_pass8(ar, dv, b);
-            __syncthreads();
+            block_sync();
 #pragma unroll
             for (int i = 0; i < 4; i++) {
-                const unsigned p = pair8_at(i), wd = tile_at(p >> 8, p & 255u);
+                const unsigned p = 128u * i + 2u * (threadIdx.x & 63), wd = tile_at(p >> 8, p & 255u);
                 dv[2 * i] = ar.load_mid(lds[wd]), dv[2 * i + 1] = ar.load_mid(lds[wd + 1]);
             }
-            if (c == 0) __syncthreads();
+            block_sync();
 #pragma unroll
             for (int i = 0; i < 4; i++) {
                 u64x2 res;
@@ -504,7 +506,7 @@ __global__ __launch_bounds__(INNER_THREADS, INT ? 4 : 6) void k_inner_fin(InnerA
                     const double v = ar.mulmod(acc[c][2 * i + e] - dv[2 * i + e], k1) + (scaled ? ar.mulmod(ad, k2) : ad);
                     res[e] = fp_canon(v, m.qd, m.qinvd);
                 }
-                __builtin_nontemporal_store(res, (u64x2 *)(o + c * o_step + INNER_THREADS * 16 * i + lane16));
+                __builtin_nontemporal_store(res, (u64x2 *)(o + c * o_step + 1024 * i + lane16));
             }
         }
     }
