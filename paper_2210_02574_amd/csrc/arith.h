@@ -96,8 +96,16 @@ __device__ __forceinline__ u64 fp_canon(double v, double q, double qinv)
 // after reduce_first (|v| <= q/2) ends below 4.7q; an inverse phase reduces the sum path at its
 // second and fourth stage and never exceeds 7.4q.  Everything stays below 8q < 2^53.
 
+// index of twiddle c (stage sp's at c = 2^sp - 1 .. 2^(sp+1) - 2) of the 16-element step that starts at stage s_base in group G
+__device__ __forceinline__ unsigned step16_twiddle(unsigned s_base, unsigned G, unsigned c)
+{
+    const unsigned sp = 31u - (unsigned)__clz((int)(c + 1));
+    return (1u << (s_base + sp)) + (G << sp) + (c + 1 - (1u << sp));
+}
+
 struct ArithFp {
     typedef double V;
+    typedef double W; // a twiddle
     static constexpr bool IS_FP = true;
     double q, qinv, n0, n1;
     const double *twf, *twi;
@@ -181,26 +189,23 @@ struct ArithFp {
             }
         }
     }
-    // index in twf of twiddle c (as above) of the step that starts at stage s_base in group G
-    static __device__ __forceinline__ unsigned fwd16_twiddle(unsigned s_base, unsigned G, unsigned c)
-    {
-        const unsigned sp = 31u - (unsigned)__clz((int)(c + 1));
-        return (1u << (s_base + sp)) + (G << sp) + (c + 1 - (1u << sp));
-    }
     __device__ __forceinline__ void fwd16(V (&a)[16], unsigned s_base, unsigned G, bool reduce_first) const
     {
-        fwd16_with(a, reduce_first, [&](int c) { return twf[fwd16_twiddle(s_base, G, (unsigned)c)]; });
+        fwd16_with(a, reduce_first, [&](int c) { return twf[step16_twiddle(s_base, G, (unsigned)c)]; });
     }
     template <bool LAST> __device__ __forceinline__ void inv16(V (&a)[16], unsigned s_base, unsigned G) const
+    {
+        inv16_with<LAST>(a, [&](int c) { return twi[step16_twiddle(s_base, G, (unsigned)c)]; });
+    }
+    template <bool LAST, class F> __device__ __forceinline__ void inv16_with(V (&a)[16], F tw) const
     {
 #pragma unroll
         for (int sp = 3; sp >= 0; sp--) {
             const int dist = 8 >> sp;
-            const unsigned idx0 = (1u << (s_base + sp)) + (G << sp);
 #pragma unroll
             for (int g = 0; g < (1 << sp); g++) {
                 const bool fin = LAST && sp == 0;
-                const double w = fin ? n1 : twi[idx0 + g];
+                const double w = fin ? n1 : tw((1 << sp) - 1 + g);
 #pragma unroll
                 for (int e = 0; e < dist; e++) {
                     const int k0 = g * 2 * dist + e, k1 = k0 + dist;
@@ -247,6 +252,7 @@ struct ArithFp {
 // inverse stages; every product with a table constant uses the cheaper quotient and lands in [0, 4q).
 struct ArithInt {
     typedef u64 V;
+    typedef ShoupConst W;
     static constexpr bool IS_FP = false;
     u64 q, q2, q4;
     ShoupConst n0, n1, post; // post: optional extra constant applied by store_final (post.w == 0: none)
@@ -266,15 +272,18 @@ struct ArithInt {
         lo = u + v;
         hi = u - v + q4;
     }
-    __device__ __forceinline__ void fwd16(V (&a)[16], unsigned s_base, unsigned G, bool) const
+    __device__ __forceinline__ void fwd16(V (&a)[16], unsigned s_base, unsigned G, bool reduce_first) const
+    {
+        fwd16_with(a, reduce_first, [&](int c) { return twf[step16_twiddle(s_base, G, (unsigned)c)]; });
+    }
+    template <class F> __device__ __forceinline__ void fwd16_with(V (&a)[16], bool, F tw) const
     {
 #pragma unroll
         for (int sp = 0; sp < 4; sp++) {
             const int dist = 8 >> sp;
-            const unsigned idx0 = (1u << (s_base + sp)) + (G << sp);
 #pragma unroll
             for (int g = 0; g < (1 << sp); g++) {
-                const ShoupConst w = twf[idx0 + g];
+                const ShoupConst w = tw((1 << sp) - 1 + g);
 #pragma unroll
                 for (int e = 0; e < dist; e++) fwd_bfly(a[g * 2 * dist + e], a[g * 2 * dist + e + dist], w);
             }
@@ -282,14 +291,17 @@ struct ArithInt {
     }
     template <bool LAST> __device__ __forceinline__ void inv16(V (&a)[16], unsigned s_base, unsigned G) const
     {
+        inv16_with<LAST>(a, [&](int c) { return twi[step16_twiddle(s_base, G, (unsigned)c)]; });
+    }
+    template <bool LAST, class F> __device__ __forceinline__ void inv16_with(V (&a)[16], F tw) const
+    {
 #pragma unroll
         for (int sp = 3; sp >= 0; sp--) {
             const int dist = 8 >> sp;
-            const unsigned idx0 = (1u << (s_base + sp)) + (G << sp);
 #pragma unroll
             for (int g = 0; g < (1 << sp); g++) {
                 const bool fin = LAST && sp == 0;
-                const ShoupConst w = fin ? n1 : twi[idx0 + g];
+                const ShoupConst w = fin ? n1 : tw((1 << sp) - 1 + g);
 #pragma unroll
                 for (int e = 0; e < dist; e++) {
                     const int k0 = g * 2 * dist + e, k1 = k0 + dist;

@@ -1,37 +1,76 @@
 // Kernels of the ring size N = 2^12 and their launchers.
 #include "launch.h"
+#include "kernels_n12.h"
 
-template <int PRO, bool EX>
-static void fwd_cols12(he_ctx *c, hipStream_t st, int kid, double bytes, bool wide, u64 *data, const LimbBatch &lb, int nb,
-                       const ConvArgs &cv)
+template <int PRO, int NSMAX, bool EX>
+static void launch_fwd12(he_ctx *c, hipStream_t st, int kid, double bytes, u64 *data, const LimbBatch &lb, int nb, const ConvArgs &cv,
+                         const FinArgs *fin)
 {
-    if (wide && PRO != PRO_LOAD && PRO != PRO_RESCALE)
-        KLAUNCH(c, st, kid, bytes, (k_ntt_fwd_cols12<PRO, 8, EX>), nb, data, c->dev, lb, cv);
-    else
-        KLAUNCH(c, st, kid, bytes, (k_ntt_fwd_cols12<PRO, 4, EX>), nb, data, c->dev, lb, cv);
-}
-static void inv_cols12(he_ctx *c, hipStream_t st, double bytes, int scale, u64 *dst, const LimbBatch &lb, int nb,
-                       const ConvArgs &cv)
-{
-    switch (scale) {
-    case SCALE_NONE: KLAUNCH(c, st, KID_INV_COLS, bytes, (k_ntt_inv_cols12<SCALE_NONE>), nb, dst, c->dev, lb, cv); break;
-    case SCALE_MODUP: KLAUNCH(c, st, KID_INV_COLS, bytes, (k_ntt_inv_cols12<SCALE_MODUP>), nb, dst, c->dev, lb, cv); break;
-    default: KLAUNCH(c, st, KID_INV_COLS, bytes, (k_ntt_inv_cols12<SCALE_MODDOWN>), nb, dst, c->dev, lb, cv); break;
+    if constexpr (PRO == PRO_RESCALE) { // the one prologue that the finishing epilogue follows here
+        if (fin) {
+            KLAUNCH(c, st, kid, bytes, (k_ntt_fwd12<PRO, NSMAX, EX, EPI_FIN>), nb, data, c->dev, lb, cv, *fin);
+            return;
+        }
     }
+    KLAUNCH(c, st, kid, bytes, (k_ntt_fwd12<PRO, NSMAX, EX, EPI_STORE>), nb, data, c->dev, lb, cv, FinArgs{});
+}
+template <int PRO>
+static void fwd12(he_ctx *c, hipStream_t st, int kid, double bytes, bool wide, u64 *data, const LimbBatch &lb, int nb,
+                  const ConvArgs &cv, const FinArgs *fin)
+{
+    if constexpr (PRO == PRO_MODUP) {
+        if (cv.exact)
+            (wide ? launch_fwd12<PRO, 8, true> : launch_fwd12<PRO, 4, true>)(c, st, kid, bytes, data, lb, nb, cv, fin);
+        else
+            (wide ? launch_fwd12<PRO, 8, false> : launch_fwd12<PRO, 4, false>)(c, st, kid, bytes, data, lb, nb, cv, fin);
+    } else
+        launch_fwd12<PRO, 4, false>(c, st, kid, bytes, data, lb, nb, cv, fin);
+}
+static void inv12(he_ctx *c, hipStream_t st, double bytes, int scale, const u64 *src, u64 *dst, const LimbBatch &lb, int nb,
+                  const ConvArgs &cv)
+{
+    switch (scale) { // special limbs are scaled where they are produced
+    case SCALE_NONE: KLAUNCH(c, st, KID_INV_COLS, bytes, (k_ntt_inv12<SCALE_NONE>), nb, src, dst, c->dev, lb, cv); break;
+    default: KLAUNCH(c, st, KID_INV_COLS, bytes, (k_ntt_inv12<SCALE_MODUP>), nb, src, dst, c->dev, lb, cv); break;
+    }
+}
+static void inner12(he_ctx *c, hipStream_t st, double bytes, const InnerArgs &ia, const OpArgs &oa)
+{
+    KLAUNCH(c, st, KID_INNER, bytes, (k_inner12), dim3(ia.level + ia.K, 2, ia.count), ia, c->dev, oa);
+}
+template <int PRO, bool DROP>
+static void launch_fin12(he_ctx *c, hipStream_t st, double bytes, bool wide, int mode, const InnerArgs &ia, const FinishArgs &fa,
+                         const OpArgs &oa, const ConvArgs &cv)
+{
+    const dim3 grid(DROP ? 1 : fa.nl, 2, ia.count);
+    if (cv.exact) {
+        if (wide)
+            KLAUNCH(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 8, true, DROP>), grid, ia, fa, c->dev, oa, cv, mode);
+        else
+            KLAUNCH(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 4, true, DROP>), grid, ia, fa, c->dev, oa, cv, mode);
+    } else {
+        if (wide)
+            KLAUNCH(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 8, false, DROP>), grid, ia, fa, c->dev, oa, cv, mode);
+        else
+            KLAUNCH(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 4, false, DROP>), grid, ia, fa, c->dev, oa, cv, mode);
+    }
+}
+static void fin12(he_ctx *c, hipStream_t st, double bytes, bool wide, int pro, bool drop, int mode, const InnerArgs &ia,
+                  const FinishArgs &fa, const OpArgs &oa, const ConvArgs &cv)
+{
+    if (drop)
+        launch_fin12<PRO_MODDOWN, true>(c, st, bytes, wide, mode, ia, fa, oa, cv);
+    else if (pro == PRO_MODDOWN_RS)
+        launch_fin12<PRO_MODDOWN_RS, false>(c, st, bytes, wide, mode, ia, fa, oa, cv);
+    else
+        launch_fin12<PRO_MODDOWN, false>(c, st, bytes, wide, mode, ia, fa, oa, cv);
 }
 void dev_launch_n12(DevLaunch &t)
 {
-    t.fwd_cols[PRO_LOAD] = fwd_cols12<PRO_LOAD, false>;
-    t.fwd_cols[PRO_MODUP] = fwd_cols12<PRO_MODUP, false>;
-    t.fwd_cols[PRO_MODDOWN] = fwd_cols12<PRO_MODDOWN, false>;
-    t.fwd_cols[PRO_RESCALE] = fwd_cols12<PRO_RESCALE, false>;
-    t.fwd_cols[PRO_MODDOWN_RS] = fwd_cols12<PRO_MODDOWN_RS, false>;
-    t.fwd_cols_ex[PRO_MODUP] = fwd_cols12<PRO_MODUP, true>;
-    t.fwd_cols_ex[PRO_MODDOWN] = fwd_cols12<PRO_MODDOWN, true>;
-    t.fwd_cols_ex[PRO_MODDOWN_RS] = fwd_cols12<PRO_MODDOWN_RS, true>;
-    t.inv_cols = inv_cols12;
-    t.fwd_blocks = launch_fwd_blocks<12>;
-    t.inv_blocks = launch_inv_blocks<12>;
-    t.inner = launch_inner<12>;
-    t.inner_fin = launch_inner_fin<12>;
+    t.fwd_limb[PRO_LOAD] = fwd12<PRO_LOAD>;
+    t.fwd_limb[PRO_MODUP] = fwd12<PRO_MODUP>;
+    t.fwd_limb[PRO_RESCALE] = fwd12<PRO_RESCALE>;
+    t.inv_limb = inv12;
+    t.inner_limb = inner12;
+    t.fin_limb = fin12;
 }

@@ -349,6 +349,11 @@ static int32_t ntt_forward(he_ctx *c, hipStream_t st, u64 *data, const LimbList 
                              : pro == PRO_MODDOWN ? KID_FWD_COLS_MODDOWN
                              : pro == PRO_MODDOWN_RS ? KID_FWD_COLS_MODDOWN_RS
                                                   : KID_FWD_COLS_RESCALE;
+        if (dl.fwd_limb[pro]) { // the whole transform in one launch, on every limb
+            const double extra = fin ? (double)nb * N8 * (fin->add ? 2.0 : 1.0) : 0.0;
+            dl.fwd_limb[pro](c, st, kid_cols, cols_bytes + extra, wide, data, lb, nb, cv, fin);
+            return;
+        }
         (cv.exact && dl.fwd_cols_ex[pro] ? dl.fwd_cols_ex[pro] : dl.fwd_cols[pro])(c, st, kid_cols, cols_bytes, wide, data, lb, nb, cv);
         if (fin) {
             // reads the transform's input, the minuend and the addend, writes the result
@@ -356,7 +361,7 @@ static int32_t ntt_forward(he_ctx *c, hipStream_t st, u64 *data, const LimbList 
         } else if (!int_blocks_only)
             dl.fwd_blocks(c, st, 2.0 * nb * N8, false, data, lb, nb, kNoFin);
     });
-    if (rc != HE_OK || !int_blocks_only) return rc;
+    if (rc != HE_OK || !int_blocks_only || dl.fwd_limb[pro]) return rc;
     // block pass of the integer-path limbs alone, after all column passes: few launches, each as large as possible
     LimbList li;
     for (int b = 0; b < l.size(); b++)
@@ -376,6 +381,10 @@ static int32_t ntt_inverse(he_ctx *c, hipStream_t st, const u64 *src, u64 *dst, 
     const DevLaunch &dl = dev_launch(c);
     return for_batches(c, l, [&](const LimbBatch &lb, int nb) {
         const double bytes = 2.0 * nb * N8;
+        if (dl.inv_limb) {
+            dl.inv_limb(c, st, bytes, scale, src, dst, lb, nb, cv);
+            return;
+        }
         if (!blocks_done) dl.inv_blocks(c, st, bytes, src, dst, lb, nb);
         dl.inv_cols(c, st, bytes, scale, dst, lb, nb, cv);
     });
@@ -672,6 +681,10 @@ static int32_t ks_special(he_ctx *c, const InnerArgs &ia, const OpArgs *oa, cons
     const size_t N = c->N;
     const int K = c->K, Ma = ia.level + K, W = (int)w.total;
     if (misaligned16(ia.raised) || misaligned16(ia.d) || misaligned16(ia.evk)) return HE_EINVAL; // entry points check first
+    if (dev_launch(c).inner_limb) { // u on every limb
+        dev_launch(c).inner_limb(c, st, (inner_words(c, ia, oa, 0, Ma) + 2.0 * ia.count * Ma) * N * 8.0, ia, oa ? *oa : kNoOps);
+        return launch_ok(c);
+    }
     const double bytes = (inner_words(c, ia, oa, ia.first, Ma) + 2.0 * ia.count * (Ma - ia.first)) * N * 8.0;
     dev_launch(c).inner(c, st, bytes, inner_grid((unsigned)(N / INNER_TILE), (unsigned)(Ma - ia.first), (unsigned)ia.count), ia,
                         oa ? *oa : kNoOps);
@@ -701,9 +714,14 @@ static int32_t ks_finish(he_ctx *c, const InnerArgs &ia, const OpArgs *oa, const
             for (int i = 0; i < limbs; i++) l.add(o * W + cc * ia.level + i, i);
         words += limbs * (4.0 + (mode == FIN_ADD ? 2.0 : mode == FIN_ROT ? 1.0 : 3.0)); // r, results, addends
     }
+    fa.r = r, fa.r_stride = W;
+    if (dev_launch(c).fin_limb) { // reads u and the special limbs in place of digits, keys and r
+        words += 2.0 * c->K * ia.count + extra - l.size() - inner_words(c, ia, oa, 0, fa.nl);
+        dev_launch(c).fin_limb(c, st, words * N * 8.0, std::max(c->alpha, c->K) > 4, pro, false, mode, ia, fa, oa ? *oa : kNoOps, cv);
+        return launch_ok(c);
+    }
     int32_t rc = ntt_forward(c, st, r, l, pro, cv, nullptr, 2 * c->K * ia.count + extra, true);
     if (rc != HE_OK) return rc;
-    fa.r = r, fa.r_stride = W;
     const unsigned grid = inner_grid((unsigned)(N / INNER_TILE), (unsigned)fa.nl, (unsigned)ia.count);
     int n_int = 0;
     for (int i = 0; i < fa.nl; i++) n_int += c->modc[i].qd == 0.0 ? 1 : 0;
@@ -809,15 +827,22 @@ extern "C" int32_t he_hmult_relin_rescale_batch(he_ctx *ctx, const he_evk *relin
     ConvArgs cv = conv_args(ctx, ws + w.u * N, level, W, W);
     cv.src2 = rbuf;
     cv.src2_stride = W;
-    // ModDown of the last limb of both components, in place in the correction buffer
-    LimbList last;
-    for (int o = 0; o < count; o++)
-        for (int cc = 0; cc < 2; cc++) last.add(o * W + cc * level + level - 1, level - 1);
-    const FinArgs fl = {ws + w.u * N, rbuf, d01, ctx->dev.dn_pinv, ctx->dev.dn_pinv_d, Ma, level, level, level, W, W, W, W};
-    if ((rc = ntt_forward(ctx, st, rbuf, last, PRO_MODDOWN, cv, &fl, 2 * K * count)) != HE_OK) return rc;
-    if ((rc = ntt_inverse(ctx, st, rbuf, rbuf, last, SCALE_NONE, cv)) != HE_OK) return rc;
-    // every other limb: ModDown and rescale corrections in one transform
+    // ModDown of the last limb of both components, in place in the correction buffer, and its inverse transform
     FinishArgs fa = finish_args(ctx, d_out, 2 * (level - 1), d01, W, level, level);
+    fa.r = rbuf, fa.r_stride = W;
+    if (dev_launch(ctx).fin_limb) {
+        const double bytes = (2.0 * K + 6.0) * count * N * 8.0;
+        dev_launch(ctx).fin_limb(ctx, st, bytes, std::max(ctx->alpha, K) > 4, PRO_MODDOWN, true, FIN_ADD, ia, fa, kNoOps, cv);
+        if ((rc = launch_ok(ctx)) != HE_OK) return rc;
+    } else {
+        LimbList last;
+        for (int o = 0; o < count; o++)
+            for (int cc = 0; cc < 2; cc++) last.add(o * W + cc * level + level - 1, level - 1);
+        const FinArgs fl = {ws + w.u * N, rbuf, d01, ctx->dev.dn_pinv, ctx->dev.dn_pinv_d, Ma, level, level, level, W, W, W, W};
+        if ((rc = ntt_forward(ctx, st, rbuf, last, PRO_MODDOWN, cv, &fl, 2 * K * count)) != HE_OK) return rc;
+        if ((rc = ntt_inverse(ctx, st, rbuf, rbuf, last, SCALE_NONE, cv)) != HE_OK) return rc;
+    }
+    // every other limb: ModDown and rescale corrections in one transform
     fa.nl = fa.out_cstride = level - 1;
     fa.cst = ctx->dev.rsp_inv + (size_t)(level - 1) * L, fa.cst_d = ctx->dev.rsp_inv_d + (size_t)(level - 1) * L;
     fa.cst2 = ctx->dev.rs_inv + (size_t)(level - 1) * L, fa.cst2_d = ctx->dev.rs_inv_d + (size_t)(level - 1) * L;

@@ -1,0 +1,318 @@
+// Kernels of the ring size N = 2^12: a limb is 32 KiB and fits the LDS of one compute unit, so one work-group of 256
+// threads, 16 elements each, runs a whole transform (stages 0-3 with one thread per column of 16 elements, then 4-7 and
+// 8-11 on the blocks of 256), and a key switch is four launches:
+//   1. inverse transform of the input limbs, scaled                                  (k_ntt_inv12<SCALE_MODUP>)
+//   2. ModUp and forward transform of every raised limb                                 (k_ntt_fwd12<PRO_MODUP>)
+//   3. per active limb and component: inner product u, for special limbs its inverse transform, scaled (k_inner12)
+//   4. per ciphertext limb and component: ModDown correction, its forward transform, (u - r) * const + addend (k_fin12)
+// and one more for Mult with rescale, which finishes the dropped limb between 3 and 4 (k_fin12 with DROP).
+//
+// At this size nothing is bound by memory or by instructions: a launch is a chain of dependent steps on few
+// work-groups, so what counts is the number of launches and the length of the chain in each.  With two launches per
+// transform (column pass, block pass) and the digits finished inside the inner product, one rotation (three primes, one
+// special prime) took seven launches of 4 to 10 us, 46 us in all; it takes 40 now (6, 9, 9 and 15), and eight transforms
+// 7.4 us instead of 11.7.  The chain is kept short by fetching a step's twiddles before the step ahead of it is worked
+// on, and by giving every component a work-group of its own.
+#pragma once
+#include "kernels_ks.h"
+
+#define N12_THREADS 256
+#define N12_LDS (16 * TILE_GROUP)
+
+// twiddles of the 16-element step that starts at stage s_base in group G
+template <class A> struct Step16 {
+    typename A::W w[15];
+    __device__ __forceinline__ Step16(const typename A::W *tw, unsigned s_base, unsigned G)
+    {
+#pragma unroll
+        for (int c = 0; c < 15; c++) w[c] = tw[step16_twiddle(s_base, G, (unsigned)c)];
+    }
+};
+
+// Forward transform: a[k] = element 256 k + thread (of the range that fwd16 takes); the canonical result is left in
+// LDS, element e of block b at tile_at(b, e), where the 16 lanes of block b find it after a block_sync.
+template <class A> __device__ __forceinline__ void fwd12(typename A::V (&a)[16], const A &ar, u64 *lds, bool reduce_first)
+{
+    const unsigned t = threadIdx.x, blk = t >> 4, il = t & 15;
+    const Step16<A> w2(ar.twf, 4, blk);
+    ar.fwd16(a, 0, 0, reduce_first);
+#pragma unroll
+    for (int k = 0; k < 16; k++) lds[tile_at(k, t)] = ar.store_mid(a[k]);
+    const Step16<A> w3(ar.twf, 8, t);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 16; k++) a[k] = ar.load_mid(lds[tile_at(blk, il + 16 * k)]);
+    ar.fwd16_with(a, true, [&](int c) { return w2.w[c]; });
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 16; k++) lds[tile_at(blk, il + 16 * k)] = ar.store_mid(a[k]);
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 16; k++) a[k] = ar.load_mid(lds[tile_at(blk, 16 * il + k)]);
+    ar.fwd16_with(a, true, [&](int c) { return w3.w[c]; });
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 16; k++) lds[tile_at(blk, 16 * il + k)] = ar.store_final(a[k]);
+}
+
+// Inverse transform of canonical values v[k] = element 16 k + il of block blk; stores the finished limb.
+template <class A> __device__ __forceinline__ void inv12(const u64 (&v)[16], u64 *limb, const A &ar, u64 *lds)
+{
+    const unsigned t = threadIdx.x, blk = t >> 4, il = t & 15;
+    const Step16<A> w3(ar.twi, 8, t), w2(ar.twi, 4, blk);
+    typename A::V a[16];
+#pragma unroll
+    for (int k = 0; k < 16; k++) lds[tile_at(blk, il + 16 * k)] = v[k];
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 16; k++) a[k] = ar.load(lds[tile_at(blk, 16 * il + k)]);
+    ar.template inv16_with<false>(a, [&](int c) { return w3.w[c]; });
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 16; k++) lds[tile_at(blk, 16 * il + k)] = ar.store_mid(a[k]);
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 16; k++) a[k] = ar.load_mid(lds[tile_at(blk, il + 16 * k)]);
+    ar.template inv16_with<false>(a, [&](int c) { return w2.w[c]; });
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 16; k++) lds[tile_at(blk, il + 16 * k)] = ar.store_mid(a[k]);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 16; k++) a[k] = ar.load_mid(lds[tile_at(k, t)]);
+    ar.template inv16<true>(a, 0, 0);
+#pragma unroll
+    for (int k = 0; k < 16; k++) limb[k * 256 + t] = ar.store_final(a[k]);
+}
+
+// Calls f(arithmetic, split, tint) with the variant of the prologue that modulus and tables ask for (split, tint: types
+// whose `value` is the template argument of conv_get).
+template <int PRO, int NSMAX, bool EX, class F>
+__device__ __forceinline__ void conv_variant12(const DevTables &T, unsigned mi, const ModConst &m, double qld, F f)
+{
+    constexpr bool MD = pro_is_moddown(PRO), FOLD = MD && !EX && NSMAX <= 4;
+    const bool split = PRO == PRO_MODUP ? T.up_split != 0 : MD ? T.dn_split != 0 : false;
+    if (m.qd == 0.0)
+        f(make_int(T, mi, 12), std::integral_constant<int, 0>{}, std::false_type{});
+    else if (PRO == PRO_MODDOWN_RS && qld == 0.0) { // dropped limb on the integer path
+        if (split)
+            f(make_fp(T, mi, 12), std::integral_constant<int, 1>{}, std::integral_constant<bool, PRO == PRO_MODDOWN_RS>{});
+        else
+            f(make_fp(T, mi, 12), std::integral_constant<int, 0>{}, std::integral_constant<bool, PRO == PRO_MODDOWN_RS>{});
+    } else if (FOLD && T.dn_fold != 0)
+        f(make_fp(T, mi, 12), std::integral_constant<int, FOLD ? 2 : 0>{}, std::false_type{});
+    else if (split)
+        f(make_fp(T, mi, 12), std::integral_constant<int, 1>{}, std::false_type{});
+    else
+        f(make_fp(T, mi, 12), std::integral_constant<int, 0>{}, std::false_type{});
+}
+
+// Column inputs of the forward transform of the limb at `limb` / of the conversion S.
+template <int PRO, int SPLIT, bool TINT, bool EX, int NSMAX, class A>
+__device__ __forceinline__ void inputs12(typename A::V (&a)[16], const u64 *limb, const A &ar, const ConvSetup<NSMAX> &S,
+                                         const ModConst &m)
+{
+#pragma unroll
+    for (int k = 0; k < 16; k++) {
+        const unsigned pos = k * 256 + threadIdx.x;
+        a[k] = PRO == PRO_LOAD ? ar.load(limb[pos]) : conv_get<PRO, SPLIT, TINT, EX>(S, ar, m, pos);
+    }
+}
+
+// grid.x = limbs
+template <int PRO, int NSMAX, bool EX, int EPI>
+__global__ __launch_bounds__(N12_THREADS) void k_ntt_fwd12(u64 *data, DevTables T, LimbBatch lb, ConvArgs cv, FinArgs fa)
+{
+    __shared__ u64 lds[N12_LDS];
+    const unsigned mi = lb.mod[blockIdx.x], slot = lb.slot[blockIdx.x], blk = threadIdx.x >> 4, il = threadIdx.x & 15;
+    u64 *limb = data + ((size_t)slot << 12);
+    const ModConst m = T.mod[mi];
+    const ConvSetup<NSMAX> S = conv_setup<PRO, NSMAX, 12>(cv, T, slot, mi);
+    FinOperands fo[EPI == EPI_FIN ? 16 : 1];
+    if (EPI == EPI_FIN) {
+#pragma unroll
+        for (int k = 0; k < 16; k++) fo[k] = fin_load<12>(fa, slot, blk * 256 + il + 16 * k);
+    }
+    conv_variant12<PRO, NSMAX, EX>(T, mi, m, S.qld, [&](auto ar, auto split, auto tint) {
+        typedef decltype(ar) A;
+        typename A::V a[16];
+        inputs12<PRO, decltype(split)::value, decltype(tint)::value, EX>(a, limb, ar, S, m);
+        fwd12(a, ar, lds, PRO != PRO_LOAD);
+        block_sync();
+#pragma unroll
+        for (int k = 0; k < 16; k++) {
+            const unsigned pos = blk * 256 + il + 16 * k;
+            const u64 v = lds[tile_at(blk, il + 16 * k)];
+            if (EPI == EPI_FIN)
+                fin_store<12, A::IS_FP>(fa, T, slot, pos, v, fo[k]);
+            else
+                limb[pos] = v;
+        }
+    });
+}
+
+// grid.x = limbs; in place where src and dst are the same buffer and slots (a work-group has read its limb before it stores)
+template <int SCALE>
+__global__ __launch_bounds__(N12_THREADS) void k_ntt_inv12(const u64 *src, u64 *dst, DevTables T, LimbBatch lb, ConvArgs cv)
+{
+    __shared__ u64 lds[N12_LDS];
+    const unsigned mi = lb.mod[blockIdx.x], slot = lb.slot[blockIdx.x], blk = threadIdx.x >> 4, il = threadIdx.x & 15;
+    const u64 *in = src + ((size_t)lb.src[blockIdx.x] << 12);
+    u64 *limb = dst + ((size_t)slot << 12);
+    u64 v[16];
+#pragma unroll
+    for (int k = 0; k < 16; k++) v[k] = in[blk * 256 + il + 16 * k];
+    ShoupConst ci;
+    double cd;
+    scale_consts(SCALE, cv, T, mi, slot, ci, cd);
+    if (T.mod[mi].qd != 0.0)
+        inv12(v, limb, make_fp(T, mi, 12, cd), lds);
+    else
+        inv12(v, limb, make_int(T, mi, 12, ci), lds);
+}
+
+// What a work-group of the inner product works on: component c of active limb a of operation op.
+struct Inner12 {
+    unsigned op, g;
+    int a, c, level, beta;
+    bool none;
+};
+__device__ __forceinline__ Inner12 inner12_of(const InnerArgs &ia, const OpArgs &oa, int a)
+{
+    Inner12 w;
+    w.op = blockIdx.z, w.c = (int)blockIdx.y, w.a = a;
+    w.g = ia.per_op ? oa.g[w.op] : ia.g;
+    w.level = ia.per_op && oa.level[w.op] ? oa.level[w.op] : ia.level;
+    w.beta = (w.level + ia.alpha - 1) / ia.alpha;
+    w.none = w.a < ia.level && w.a >= w.level; // an operation below the layout's level
+    return w;
+}
+// u at elements 16 k + il of block blk, k < 16: on the floating-point path within 3.5 q of zero (not canonical), as a
+// double; canonical residues on the integer path.
+template <class A>
+__device__ __forceinline__ void inner12(typename A::V (&r)[16], const InnerArgs &ia, const OpArgs &oa, const Inner12 &w, unsigned mi,
+                                        const A &ar, const ModConst &m)
+{
+    const unsigned blk = threadIdx.x >> 4, il = threadIdx.x & 15, n0 = blk * 256 + il;
+    const int own = w.a < ia.level ? w.a / ia.alpha : -1, M = ia.L + ia.K, Ma = ia.level + ia.K;
+    const u64 *key0 = (ia.per_op ? oa.evk[w.op] : ia.evk) + (((size_t)w.c * M + mi) << 12);
+    const u64 *dig0 = ia.raised + (((size_t)w.op * ia.raised_stride + w.a) << 12);
+    const u64 *d_limb = (ia.per_op && oa.d[w.op] ? oa.d[w.op] : ia.d + (((size_t)w.op * ia.d_stride) << 12)) + ((size_t)w.a << 12);
+    unsigned sr[16];
+#pragma unroll
+    for (int k = 0; k < 16; k++) sr[k] = w.g == 1 ? n0 + 16 * k : galois_index(n0 + 16 * k, w.g, 12);
+    if constexpr (A::IS_FP) {
+#pragma unroll
+        for (int k = 0; k < 16; k++) r[k] = 0.0;
+        for (int j = 0; j < w.beta; j++) {
+            const u64 *dj = j == own ? d_limb : dig0 + (((size_t)j * Ma) << 12), *kj = key0 + (((size_t)j * 2 * M) << 12);
+            u64 x[16], e[16];
+#pragma unroll
+            for (int k = 0; k < 16; k++) x[k] = dj[sr[k]], e[k] = kj[n0 + 16 * k];
+#pragma unroll
+            for (int k = 0; k < 16; k++) r[k] += ar.mulmod(u2d(x[k]), ar.load_mid(e[k])); // key words are balanced doubles
+            if ((j & 3) == 3) {
+#pragma unroll
+                for (int k = 0; k < 16; k++) r[k] = ar.reduce(r[k]);
+            }
+        }
+    } else {
+        U128 acc[16];
+#pragma unroll
+        for (int k = 0; k < 16; k++) acc[k] = U128{0, 0};
+        for (int j = 0; j < w.beta; j++) {
+            const u64 *dj = j == own ? d_limb : dig0 + (((size_t)j * Ma) << 12), *kj = key0 + (((size_t)j * 2 * M) << 12);
+#pragma unroll
+            for (int k = 0; k < 16; k++) mac128(acc[k], dj[sr[k]], kj[n0 + 16 * k]);
+        }
+#pragma unroll
+        for (int k = 0; k < 16; k++) r[k] = reduce128(acc[k], m);
+    }
+}
+
+// grid (active limbs, components, operations).  u of the ciphertext limbs, and of the special ones (the longest work, first)
+// the inverse transform, scaled by (P/p_k)^-1.  All limbs in one launch: formed in k_fin12, u added its chain of loads, a
+// round per digit, to the longest kernel (one rotation 40.2 us instead of 39.6 with three digits).
+__global__ __launch_bounds__(N12_THREADS) void k_inner12(InnerArgs ia, DevTables T, OpArgs oa)
+{
+    __shared__ u64 lds[N12_LDS];
+    const unsigned n0 = (threadIdx.x >> 4) * 256 + (threadIdx.x & 15);
+    const Inner12 w = inner12_of(ia, oa, (int)blockIdx.x < ia.K ? ia.level + (int)blockIdx.x : (int)blockIdx.x - ia.K);
+    if (w.none) return;
+    const bool special = w.a >= ia.level;
+    const unsigned mi = active_mod(w.a, ia.level, ia.L), k_sp = special ? w.a - ia.level : 0;
+    const ModConst m = T.mod[mi];
+    u64 *limb = ia.u + (((size_t)w.op * ia.u_stride + (size_t)w.c * (ia.level + ia.K) + w.a) << 12);
+    u64 v[16];
+    if (m.qd != 0.0) {
+        const ArithFp ar = make_fp(T, mi, 12, special ? T.dn_inv_d[k_sp] : 0.0);
+        double r[16];
+        inner12(r, ia, oa, w, mi, ar, m);
+#pragma unroll
+        for (int k = 0; k < 16; k++) v[k] = fp_canon(r[k], m.qd, m.qinvd);
+        if (special) inv12(v, limb, ar, lds);
+    } else {
+        const ArithInt ar = make_int(T, mi, 12, special ? T.dn_inv[k_sp] : ShoupConst{0, 0});
+        inner12(v, ia, oa, w, mi, ar, m);
+        if (special) inv12(v, limb, ar, lds);
+    }
+    if (!special) {
+#pragma unroll
+        for (int k = 0; k < 16; k++) limb[n0 + 16 * k] = v[k];
+    }
+}
+
+// grid (ciphertext limbs, components, operations).  DROP: the limb that a rescale drops (limb level - 1 alone); its
+// finished value goes through the inverse transform and is left, in the coefficient domain, in its slot of the
+// correction buffer.
+template <int PRO, int NSMAX, bool EX, bool DROP>
+__global__ __launch_bounds__(N12_THREADS) void k_fin12(InnerArgs ia, FinishArgs fa, DevTables T, OpArgs oa, ConvArgs cv, int mode)
+{
+    __shared__ u64 lds[N12_LDS];
+    const unsigned blk = threadIdx.x >> 4, il = threadIdx.x & 15, n0 = blk * 256 + il;
+    const Inner12 w = inner12_of(ia, oa, DROP ? ia.level - 1 : (int)blockIdx.x);
+    if (w.none) return;
+    const ModConst m = T.mod[w.a];
+    const unsigned slot = w.op * (unsigned)cv.dst_stride + (unsigned)(w.c * ia.level + w.a);
+    const ConvSetup<NSMAX> S = conv_setup<PRO, NSMAX, 12>(cv, T, slot, w.a);
+    // u and the addends (canonical residues) are on their way while the corrections are transformed
+    const u64 *u = ia.u + (((size_t)w.op * ia.u_stride + (size_t)w.c * (ia.level + ia.K) + w.a) << 12);
+    const u64 *add = ia.per_op && oa.add[w.op] ? oa.add[w.op] : fa.add + (((size_t)w.op * fa.add_stride) << 12);
+    const u64 *add_same = add + (((size_t)w.c * fa.add_cstride + w.a) << 12), *add_rot = add + ((size_t)w.a << 12);
+    u64 uv[16], v[16];
+#pragma unroll
+    for (int k = 0; k < 16; k++) {
+        const unsigned n = n0 + 16 * k;
+        uv[k] = u[n];
+        v[k] = mode != FIN_ROT ? add_same[n] : 0;
+        if (mode != FIN_ADD && w.c == 0) v[k] = csub(v[k] + add_rot[w.g == 1 ? n : galois_index(n, w.g, 12)], m.q);
+    }
+    const bool scaled = mode == FIN_ADD && fa.cst2 != nullptr;
+    conv_variant12<PRO, NSMAX, EX>(T, w.a, m, S.qld, [&](auto ar, auto split, auto tint) {
+        typedef decltype(ar) A;
+        typename A::V a[16];
+        inputs12<PRO, decltype(split)::value, decltype(tint)::value, EX>(a, nullptr, ar, S, m);
+        fwd12(a, ar, lds, true);
+        block_sync();
+#pragma unroll
+        for (int k = 0; k < 16; k++) {
+            const u64 rv = lds[tile_at(blk, il + 16 * k)];
+            if constexpr (A::IS_FP) {
+                const double ad = u2d(v[k]), k2 = scaled ? fa.cst2_d[w.a] : 0.0;
+                const double x = ar.mulmod(u2d(uv[k]) - u2d(rv), fa.cst_d[w.a]) + (scaled ? ar.mulmod(ad, k2) : ad);
+                v[k] = fp_canon(x, m.qd, m.qinvd);
+            } else {
+                const u64 x = mul_shoup(uv[k] + m.q - rv, fa.cst[w.a], m.q);
+                v[k] = csub(x + (scaled ? mul_shoup(v[k], fa.cst2[w.a], m.q) : v[k]), m.q);
+            }
+        }
+        if constexpr (DROP)
+            inv12(v, const_cast<u64 *>(fa.r) + ((size_t)slot << 12), ar, lds);
+        else {
+            const unsigned out_cstride = ia.per_op && oa.level[w.op] ? oa.level[w.op] : (unsigned)fa.out_cstride;
+            u64 *o = (ia.per_op ? oa.out[w.op] : fa.out + (((size_t)w.op * fa.out_stride) << 12)) + (((size_t)w.c * out_cstride + w.a) << 12);
+#pragma unroll
+            for (int k = 0; k < 16; k++) o[n0 + 16 * k] = v[k];
+        }
+    });
+}

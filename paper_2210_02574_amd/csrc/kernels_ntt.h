@@ -7,7 +7,7 @@
 // two kernels: the column pass (stages 0-7 on 16 columns x 256 rows, row stride 256 elements,
 // 128-byte global segments) and the block pass (stages 8-15 on 16 contiguous blocks of 256).
 // N = 2^17 keeps the two kernels: its column pass runs nine stages on 512 rows (32 elements per thread).
-// N = 2^12 uses a four-stage column pass (one thread per column) and the same block pass.
+// N = 2^12 has kernels of its own (kernels_n12.h).
 // The inverse runs the block pass first and the column pass last.
 //
 // Fusions, all bit-identical to the unfused steps:
@@ -746,68 +746,4 @@ template <int SCALE>
 __global__ __launch_bounds__(256, 3) void k_ntt_inv_cols17(u64 *__restrict__ data, DevTables T, LimbBatch lb, ConvArgs cv)
 {
     inv_cols_kernel<17, SCALE>(data, T, lb, cv);
-}
-
-// ---- column pass, N = 2^12: 16 rows x 256 columns, one thread per column --------------------------------------
-
-template <int PRO, int SPLIT, bool TINT, bool EX, int NSMAX, class A>
-__device__ __forceinline__ void fwd_cols12_body(u64 *__restrict__ limb, const A &ar, const ConvSetup<NSMAX> &S,
-                                                const ModConst &m)
-{
-    const unsigned c = threadIdx.x;
-    typename A::V a[16];
-#pragma unroll
-    for (int k = 0; k < 16; k++) a[k] = PRO == PRO_LOAD ? ar.load(limb[k * 256 + c]) : conv_get<PRO, SPLIT, TINT, EX>(S, ar, m, k * 256 + c);
-    ar.fwd16(a, 0, 0, PRO != PRO_LOAD);
-#pragma unroll
-    for (int k = 0; k < 16; k++) limb[k * 256 + c] = ar.store_mid(a[k]);
-}
-template <class A> __device__ __forceinline__ void inv_cols12_body(u64 *__restrict__ limb, const A &ar)
-{
-    const unsigned c = threadIdx.x;
-    typename A::V a[16];
-#pragma unroll
-    for (int k = 0; k < 16; k++) a[k] = ar.load_mid(limb[k * 256 + c]);
-    ar.template inv16<true>(a, 0, 0);
-#pragma unroll
-    for (int k = 0; k < 16; k++) limb[k * 256 + c] = ar.store_final(a[k]);
-}
-
-template <int PRO, int NSMAX, bool EX>
-__global__ __launch_bounds__(256) void k_ntt_fwd_cols12(u64 *__restrict__ data, DevTables T, LimbBatch lb, ConvArgs cv)
-{
-    const unsigned mi = lb.mod[blockIdx.x], slot = lb.slot[blockIdx.x];
-    u64 *limb = data + ((size_t)slot << 12);
-    const ModConst m = T.mod[mi];
-    const ConvSetup<NSMAX> S = conv_setup<PRO, NSMAX, 12>(cv, T, slot, mi);
-    const bool split = PRO == PRO_MODUP ? T.up_split != 0 : pro_is_moddown(PRO) ? T.dn_split != 0 : false;
-    const bool tint = PRO == PRO_MODDOWN_RS && S.qld == 0.0; // dropped limb on the integer path
-    const bool fold = pro_is_moddown(PRO) && !EX && NSMAX <= 4 && T.dn_fold != 0; // the common case only: each variant costs code
-    if (m.qd == 0.0)
-        fwd_cols12_body<PRO, 0, false, EX>(limb, make_int(T, mi, 12), S, m);
-    else if (PRO == PRO_MODDOWN_RS && tint) {
-        if (split)
-            fwd_cols12_body<PRO, 1, PRO == PRO_MODDOWN_RS, EX>(limb, make_fp(T, mi, 12), S, m);
-        else
-            fwd_cols12_body<PRO, 0, PRO == PRO_MODDOWN_RS, EX>(limb, make_fp(T, mi, 12), S, m);
-    } else if (fold)
-        fwd_cols12_body<PRO, pro_is_moddown(PRO) && !EX && NSMAX <= 4 ? 2 : 0, false, EX>(limb, make_fp(T, mi, 12), S, m);
-    else if (split)
-        fwd_cols12_body<PRO, 1, false, EX>(limb, make_fp(T, mi, 12), S, m);
-    else
-        fwd_cols12_body<PRO, 0, false, EX>(limb, make_fp(T, mi, 12), S, m);
-}
-
-template <int SCALE>
-__global__ __launch_bounds__(256) void k_ntt_inv_cols12(u64 *__restrict__ data, DevTables T, LimbBatch lb, ConvArgs cv)
-{
-    const unsigned mi = lb.mod[blockIdx.x];
-    u64 *limb = data + ((size_t)lb.slot[blockIdx.x] << 12);
-    ShoupConst ci;
-    double cd;
-    scale_consts(SCALE, cv, T, mi, lb.slot[blockIdx.x], ci, cd);
-    if (T.mod[mi].qd != 0.0)
-        inv_cols12_body(limb, make_fp(T, mi, 12, cd));
-    else
-        inv_cols12_body(limb, make_int(T, mi, 12, ci));
 }

@@ -1,7 +1,7 @@
 // Kernel launch plumbing shared by the translation units of the device library.
 //
 // The kernels are templates over the ring size; each ring size is instantiated in a translation unit of
-// its own (dev_n12.hip, dev_n16_blocks.hip, dev_n17_blocks.hip, and dev_cols.hip once per ring size and
+// its own (dev_n12.hip, dev_n16_blocks.hip, dev_n17_blocks.hip, and dev_cols.hip once per larger ring size and
 // prologue) so that the library builds in parallel, and device.hip reaches them through one table of launchers per ring size.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -36,6 +36,17 @@ bool prof_events(he_ctx *c, int kid, double bytes, ProfRecord &r);
 
 // Launchers of one ring size.  `wide`: a base conversion has more than four source limbs.
 struct DevLaunch {
+    // Ring sizes whose limbs fit one work-group (N = 2^12; null otherwise) have whole transforms and key-switch halves in
+    // place of the passes below: fwd_limb, with the finishing epilogue if fin is not null; inv_limb; the inner product, with
+    // the special limbs' inverse transform; the finishing of the first fa.nl limbs (rescale: with the dropped limb's
+    // share in the corrections; drop: of the dropped limb alone, into fa.r).
+    void (*fwd_limb[5])(he_ctx *c, hipStream_t st, int kid, double bytes, bool wide, u64 *data, const LimbBatch &lb, int nb,
+                        const ConvArgs &cv, const FinArgs *fin);
+    void (*inv_limb)(he_ctx *c, hipStream_t st, double bytes, int scale, const u64 *src, u64 *dst, const LimbBatch &lb, int nb,
+                     const ConvArgs &cv);
+    void (*inner_limb)(he_ctx *c, hipStream_t st, double bytes, const InnerArgs &ia, const OpArgs &oa);
+    void (*fin_limb)(he_ctx *c, hipStream_t st, double bytes, bool wide, int pro, bool drop, int mode, const InnerArgs &ia,
+                     const FinishArgs &fa, const OpArgs &oa, const ConvArgs &cv);
     // forward column pass of the nb limbs of lb, one launcher per prologue (PRO_*)
     void (*fwd_cols[5])(he_ctx *c, hipStream_t st, int kid, double bytes, bool wide, u64 *data, const LimbBatch &lb, int nb,
                         const ConvArgs &cv);
