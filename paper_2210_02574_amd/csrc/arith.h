@@ -15,20 +15,40 @@
 
 __device__ __forceinline__ u64 mulhi64(u64 a, u64 b) { return __umul64hi(a, b); }
 __device__ __forceinline__ u64 csub(u64 x, u64 q) { return x >= q ? x - q : x; }
+// -q, q the same in every lane, in scalar registers and as a value the compiler does not know to be a negation: adding it is
+// one 64-bit addition (v_lshl_add_u64) or the addend of a multiply-add, where subtracting q would be two instructions
+// chained by the borrow.
+__device__ __forceinline__ u64 negated(u64 q)
+{
+    const u64 nq = 0 - q;
+    return (u64)(unsigned)__builtin_amdgcn_readfirstlane((int)(nq >> 32)) << 32 | (unsigned)__builtin_amdgcn_readfirstlane((int)nq);
+}
+// x - q, or x where that is negative, for x < 2^63 + q, given nq = -q: the sign of the difference decides
+__device__ __forceinline__ u64 csub_neg(u64 x, u64 nq)
+{
+    const u64 d = x + nq;
+    return (int)(d >> 32) < 0 ? x : d;
+}
 // w*x mod q up to one extra q, for any 64-bit x; w < q with wp = floor(w 2^64 / q)
 __device__ __forceinline__ u64 mul_shoup_lazy(u64 x, ShoupConst w, u64 q) { return x * w.w - mulhi64(x, w.wp) * q; }
 __device__ __forceinline__ u64 mul_shoup(u64 x, ShoupConst w, u64 q) { return csub(mul_shoup_lazy(x, w, q), q); }
 // The same product with a cheaper quotient: of the four 32-bit partial products of x * wp only the high one and
 // the high halves of the two middle ones are kept, so the estimate is at most three below floor(x wp / 2^64)
-// and the result lies in [0, 4q) for any 64-bit x (exact arithmetic modulo 2^64, since 4q < 2^64).
-__device__ __forceinline__ u64 mul_shoup_sloppy(u64 x, ShoupConst w, u64 q)
+// and the result lies in [0, 4q) for any 64-bit x (exact arithmetic modulo 2^64, since 4q < 2^64).  nq = negated(q).
+__device__ __forceinline__ u64 mul_shoup_sloppy(u64 x, ShoupConst w, u64 nq)
 {
     const unsigned xl = (unsigned)x, xh = (unsigned)(x >> 32);
     const unsigned pl = (unsigned)w.wp, ph = (unsigned)(w.wp >> 32);
     u64 quo = (u64)xh * ph;
     quo += __umulhi(xh, pl);
     quo += __umulhi(xl, ph);
-    return x * w.w - quo * q;
+    // x w - quo q modulo 2^64 as x w + quo (-q): two multiply-adds for the low words, four products for the high one and
+    // no subtraction with borrow
+    const unsigned ql = (unsigned)quo, qh = (unsigned)(quo >> 32), wl = (unsigned)w.w, wh = (unsigned)(w.w >> 32);
+    const unsigned nl = (unsigned)nq, nh = (unsigned)(nq >> 32);
+    const u64 lo = (u64)ql * nl + (u64)xl * wl;
+    const unsigned hi = (unsigned)(lo >> 32) + xl * wh + xh * wl + ql * nh + qh * nl;
+    return (u64)hi << 32 | (unsigned)lo;
 }
 
 struct U128 {
@@ -255,6 +275,7 @@ struct ArithInt {
     typedef ShoupConst W;
     static constexpr bool IS_FP = false;
     u64 q, q2, q4;
+    u64 nq, nq4; // -q, -4q (negated)
     ShoupConst n0, n1, post; // post: optional extra constant applied by store_final (post.w == 0: none)
     const ShoupConst *twf, *twi;
     __device__ __forceinline__ V load(u64 m) const { return m; }
@@ -267,8 +288,8 @@ struct ArithInt {
     }
     __device__ __forceinline__ void fwd_bfly(V &lo, V &hi, ShoupConst w) const
     {
-        const u64 u = csub(lo, q4);
-        const u64 v = mul_shoup_sloppy(hi, w, q);
+        const u64 u = csub_neg(lo, nq4);
+        const u64 v = mul_shoup_sloppy(hi, w, nq);
         lo = u + v;
         hi = u - v + q4;
     }
@@ -306,8 +327,8 @@ struct ArithInt {
                 for (int e = 0; e < dist; e++) {
                     const int k0 = g * 2 * dist + e, k1 = k0 + dist;
                     const u64 u = a[k0], v = a[k1];
-                    a[k0] = fin ? mul_shoup_sloppy(u + v, n0, q) : csub(u + v, q4);
-                    a[k1] = mul_shoup_sloppy(u - v + q4, w, q);
+                    a[k0] = fin ? mul_shoup_sloppy(u + v, n0, nq) : csub_neg(u + v, nq4);
+                    a[k1] = mul_shoup_sloppy(u - v + q4, w, nq);
                 }
             }
         }
@@ -323,8 +344,8 @@ struct ArithInt {
 #pragma unroll
         for (int k = 0; k < 16; k++) {
             const u64 u = lo[k], v = hi[k];
-            lo[k] = mul_shoup_sloppy(u + v, n0, q);
-            hi[k] = mul_shoup_sloppy(u - v + q4, n1, q);
+            lo[k] = mul_shoup_sloppy(u + v, n0, nq);
+            hi[k] = mul_shoup_sloppy(u - v + q4, n1, nq);
         }
     }
 };
@@ -351,6 +372,8 @@ __device__ __forceinline__ ArithInt make_int(const DevTables &T, unsigned mi, in
     A.q = T.mod[mi].q;
     A.q2 = 2 * A.q;
     A.q4 = 4 * A.q;
+    A.nq = negated(A.q);
+    A.nq4 = negated(A.q4);
     A.twf = T.tw_fwd + ((size_t)mi << logN);
     A.twi = T.tw_inv + ((size_t)mi << logN);
     A.n0 = T.ninv[2 * mi];

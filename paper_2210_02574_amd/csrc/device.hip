@@ -334,10 +334,10 @@ static const OpArgs kNoOps = {};
 // limb's own content, or a base conversion of cv.src); with fin != nullptr the block pass writes
 // (u - ntt) * const + addend to fin->out instead of the transform itself.
 // src_limbs = number of source limbs the prologue reads in total (for the byte count).
-// int_blocks_only: the block pass runs only for limbs on the integer path (the others are finished by the
-// kernel that consumes them).
+// int_blocks_only: the block pass runs only for ciphertext limbs on the integer path (the others are finished by
+// the kernel that consumes them); special_too: and for the special limbs on that path.
 static int32_t ntt_forward(he_ctx *c, hipStream_t st, u64 *data, const LimbList &l, int pro, const ConvArgs &cv,
-                           const FinArgs *fin, int src_limbs, bool int_blocks_only = false)
+                           const FinArgs *fin, int src_limbs, bool int_blocks_only = false, bool special_too = false)
 {
     const bool wide = std::max(c->alpha, c->K) > 4;
     const double N8 = (double)c->N * 8.0;
@@ -362,10 +362,11 @@ static int32_t ntt_forward(he_ctx *c, hipStream_t st, u64 *data, const LimbList 
             dl.fwd_blocks(c, st, 2.0 * nb * N8, false, data, lb, nb, kNoFin);
     });
     if (rc != HE_OK || !int_blocks_only || dl.fwd_limb[pro]) return rc;
-    // block pass of the integer-path limbs alone, after all column passes: few launches, each as large as possible
+    // block pass of the integer-path limbs alone, after all column passes: few launches, each as large as possible;
+    // k_inner_special finishes the special limbs
     LimbList li;
     for (int b = 0; b < l.size(); b++)
-        if (c->modc[l.mod[b]].qd == 0.0) li.add(l.slot[b], l.src[b], l.mod[b]);
+        if (c->modc[l.mod[b]].qd == 0.0 && (special_too || l.mod[b] < c->L)) li.add(l.slot[b], l.src[b], l.mod[b]);
     return for_batches(c, li, [&](const LimbBatch &lb, int nb) {
         dl.fwd_blocks(c, st, 2.0 * nb * N8, false, data, lb, nb, kNoFin);
     });
@@ -615,9 +616,10 @@ static bool batch_fits(const WsLayout &w, int count) { return count >= 1 && w.to
 
 // Steps 1-2 of the key switch for `count` polynomials: operation o reads its NTT-domain input at
 // d_ntt + o*d_stride limbs and works in ws + o*w.total limbs.  Raised limbs on the floating-point path
-// are left as the column pass wrote them (the inner-product kernel finishes them).
+// and special ones are left as the column pass wrote them (the inner-product kernels finish them), unless
+// `finish_special`: then the block pass is applied to the special limbs on the integer path.
 static int32_t ks_raise(he_ctx *c, const u64 *d_ntt, int d_stride, u64 *ws, const WsLayout &w, int level, int count,
-                        hipStream_t st)
+                        hipStream_t st, bool finish_special = false)
 {
     const size_t N = c->N;
     const int K = c->K, Ma = level + K, beta = (level + c->alpha - 1) / c->alpha, W = (int)w.total;
@@ -636,7 +638,7 @@ static int32_t ks_raise(he_ctx *c, const u64 *d_ntt, int d_stride, u64 *ws, cons
                 r.add(o * W + j * Ma + a, a < level ? a : c->L + (a - level));
             }
         }
-    return ntt_forward(c, st, ws + w.raised * N, r, PRO_MODUP, cv, nullptr, level * count, true);
+    return ntt_forward(c, st, ws + w.raised * N, r, PRO_MODUP, cv, nullptr, level * count, true, finish_special);
 }
 
 static InnerArgs inner_args(const he_ctx *c, const he_evk *evk, const u64 *d_ntt, int d_stride, u64 *ws, const WsLayout &w,
@@ -647,7 +649,7 @@ static InnerArgs inner_args(const he_ctx *c, const he_evk *evk, const u64 *d_ntt
     ia.level = level, ia.L = c->L, ia.K = c->K, ia.alpha = c->alpha, ia.first = level;
     ia.g = (unsigned)evk->galois;
     ia.raised_stride = shared_raised ? 0 : (int)w.total, ia.u_stride = (int)w.total, ia.d_stride = d_stride;
-    ia.per_op = oa ? 1 : 0, ia.count = count;
+    ia.per_op = oa ? 1 : 0, ia.count = count, ia.finished = shared_raised ? 1 : 0;
     return ia;
 }
 // Words per index that the inner product has to move on the active limbs [lo, hi), by the definition of the step and
@@ -870,7 +872,8 @@ extern "C" int32_t he_hrot_many(he_ctx *ctx, const he_evk *const *rots, int32_t 
     u64 *ws = (u64 *)d_ws;
     const WsLayout w = ws_layout(ctx, level);
     const u64 *c1 = d_ct + (size_t)level * ctx->N;
-    if ((rc = ks_raise(ctx, c1, 0, ws, w, level, 1, st)) != HE_OK) return rc;
+    // every rotation reads the same digits: their special limbs are finished once
+    if ((rc = ks_raise(ctx, c1, 0, ws, w, level, 1, st, true)) != HE_OK) return rc;
     // With workspace for several operations the rotations share every launch: operation o keeps its inner
     // products and ModDown corrections in workspace o, all read the raised digits of workspace 0.
     int fit = (int)std::min<size_t>(ws_bytes / (w.total * ctx->N * sizeof(u64)), HE_OPS_MAX);

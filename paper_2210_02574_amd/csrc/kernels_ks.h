@@ -11,10 +11,10 @@
 // (2 brv(k) + 1) g depend only on the low bits of brv(k), i.e. on the high bits of k), so the sources of
 // these outputs are the indices of one input tile of that size.  For a limb on the floating-point path the raised
 // digits arrive as the column pass left them; each is finished here (stages logN-8 .. logN-1) into LDS
-// and read back through the index map, so the transformed digits never travel to memory.  Limbs on
-// the integer path read digits that the block-pass kernel has finished.
+// and read back through the index map, so the transformed digits never travel to memory.  Ciphertext limbs on
+// the integer path read digits that the block-pass kernel has finished (the special ones finish theirs here too).
 //
-// Two launches make a key switch's inner product.  The first (k_inner_blocks8) takes the special limbs, whose
+// Two launches make a key switch's inner product.  The first (k_inner_special) takes the special limbs, whose
 // results leave it with the block pass of their inverse transform already applied.  The second (k_inner_fin) runs
 // after the ModDown corrections r have been through their column pass: it forms u on the ciphertext limbs, finishes
 // the transform of r the way it finishes a digit, and writes (u - r) * const + addend, so that u never travels to
@@ -28,10 +28,11 @@ struct InnerArgs {
     const u64 *raised, *d, *evk;
     u64 *u;
     int level, L, K, alpha;
-    int first; // k_inner_blocks8: the lowest active limb it works on (level: the special limbs alone)
+    int first; // k_inner_special: the lowest active limb it works on (level: the special limbs alone)
     unsigned g;
     int raised_stride, u_stride, d_stride; // limbs between two operations of a batch in each buffer
     int per_op; // operation z uses entry z of the OpArgs argument
+    int finished; // the raised special limbs on the integer path have been through their block pass
     int count;  // operations in this launch
 };
 // What differs between the operations of one launch, when anything but their place in the buffers does.
@@ -97,38 +98,6 @@ __host__ __device__ inline unsigned inner_grid(unsigned tiles, unsigned limbs, u
 #define WAVE_LDS (WAVE_BLOCKS * (TILE_GROUP + 512)) // LDS words per wave: exchange tile, twiddles, the next digit
 __device__ __forceinline__ unsigned wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 __device__ __forceinline__ unsigned pair8_at(unsigned i) { return WAVE_OUT * wave_id() + 128u * i + 2u * (threadIdx.x & 63u); }
-
-// Inverse block pass of both components of a special limb from the pairs of the product phase: through the wave's LDS to
-// the 16-element form, one component per half of the wave (u: component 0, component 1 comp_limbs further on).
-template <int LOGN, class A>
-__device__ __forceinline__ void inv_blocks_from_pairs8(const u64 (&r0)[8], const u64 (&r1)[8], u64 *u, size_t comp_words, const A &ar,
-                                                       u64 *lds, unsigned grp)
-{
-    const unsigned lane = threadIdx.x & 63u;
-    static_assert(2 * WAVE_BLOCKS * TILE_GROUP <= WAVE_LDS, "both components in the wave's LDS");
-    block_sync(); // the product phase has read what is overwritten here
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        const unsigned p = 128u * i + 2u * lane, wd = tile_at(p >> 8, p & 255u);
-        lds[wd] = r0[2 * i], lds[wd + 1] = r0[2 * i + 1];
-        lds[WAVE_BLOCKS * TILE_GROUP + wd] = r1[2 * i], lds[WAVE_BLOCKS * TILE_GROUP + wd + 1] = r1[2 * i + 1];
-    }
-    block_sync();
-    const unsigned blk = lane >> 4, il = lane & 15, bg = grp * WAVE_BLOCKS + (blk & 1u); // blk 2, 3: component 1
-    u64 *limb = u + (blk >> 1) * comp_words;
-    typename A::V a[16];
-#pragma unroll
-    for (int k = 0; k < 16; k++) a[k] = ar.load(lds[tile_at(blk, 16 * il + k)]);
-    ar.template inv16<false>(a, LOGN - 4, bg * 16 + il);
-#pragma unroll
-    for (int k = 0; k < 16; k++) lds[tile_at(blk, 16 * il + k)] = ar.store_mid(a[k]);
-    block_sync();
-#pragma unroll
-    for (int k = 0; k < 16; k++) a[k] = ar.load_mid(lds[tile_at(blk, il + 16 * k)]);
-    ar.template inv16<false>(a, LOGN - 8, bg);
-#pragma unroll
-    for (int k = 0; k < 16; k++) limb[bg * 256 + il + 16 * k] = ar.store_mid(a[k]);
-}
 
 // Addresses are formed as a wave-uniform base plus a 32-bit lane offset so that they stay in scalar registers;
 // the three LDS patterns of the block pass are one base each plus compile-time offsets (with the pad word per
@@ -358,50 +327,199 @@ __device__ __forceinline__ void inner_products_int(const InnerArgs &ia, const Op
     for (int k = 0; k < 4; k++) r0[k] = reduce128(acc0[k], m), r1[k] = reduce128(acc1[k], m);
 }
 
-// First launch: active limbs ia.first .. level + K - 1 of every operation.
-template <int LOGN> __global__ __launch_bounds__(INNER_THREADS, 4) void k_inner_blocks8(InnerArgs ia, DevTables T, OpArgs oa)
+// ---- first launch: the special limbs ------------------------------------------------------------------------------------
+//
+// Few limbs (K per operation) with the most work per word: the special primes are on the integer path, whose block pass
+// takes about three times the instructions of the floating-point one, so what a wave of k_inner_fin does alone is shared
+// out here: a work-group of four waves makes SPECIAL_TILE outputs of both components, and in each round every wave finishes
+// the transform of another digit (16 lanes a block of 256, 16 elements per lane, the steps of k_ntt_fwd_blocks) into LDS;
+// then all threads multiply the digits of the round, read through the index map, with the key.  One operation
+// alone then has four digits in work at a time, and the finished digits never travel to memory (but where several
+// operations share their digits, k_ntt_fwd_blocks finishes them once for all: `finished`).  The result leaves with the
+// block pass of its inverse transform applied.
+// Bound by the chain of a round (load, two steps with their twiddles, exchange, products) in small launches: at N = 2^16 it
+// takes 19 us for one operation, where the block pass as a launch of its own and the products after it took 10 + 17;
+// one rotation at level 13 110.8 -> 105.4 us, one product at level 6 132.8 -> 129.9.  Large launches gain nothing (32 mixed
+// rotations: 390 us, in two launches 172 + 182; the calls as a whole take the same within 0.3 %).
+#define SPECIAL_THREADS 256
+#define SPECIAL_WAVES (SPECIAL_THREADS / 64)
+#define SPECIAL_TLOG 10
+#define SPECIAL_TILE (1 << SPECIAL_TLOG)                    // outputs per work-group: four blocks, 16 elements per lane of a wave
+#define SPECIAL_DIGIT (SPECIAL_TILE / 256 * TILE_GROUP)     // LDS words of one digit
+
+// Element p of the tile in LDS.
+__device__ __forceinline__ unsigned special_at(unsigned p) { return tile_at(p >> 8, p & 255u); }
+
+// limb a of one operation; the results of the thread's pairs (512 i + 2 thread, + 1), i < 2, of both components
+template <int LOGN, class A>
+__device__ __forceinline__ void special_products(const InnerArgs &ia, const OpArgs &oa, const DevTables &T, unsigned op, unsigned tile,
+                                                 int a, unsigned g, int beta, unsigned mi, const ModConst &m, const A &ar, u64 *lds,
+                                                 u64 (&r0)[4], u64 (&r1)[4])
 {
-    __shared__ __align__(16) u64 wave_lds[INNER_THREADS / 64][WAVE_LDS];
-    u64 *lds = wave_lds[wave_id()]; // pre: the next raised digit of this group, as it lies in memory
-    double *tws = (double *)(lds + WAVE_BLOCKS * TILE_GROUP);
-    u64 *pre = lds + WAVE_BLOCKS * (TILE_GROUP + 256);
+    const int own = a < ia.level ? a / ia.alpha : -1, M = ia.L + ia.K, Ma = ia.level + ia.K;
+    const unsigned tile_in = g == 1 ? tile : galois_index(tile << SPECIAL_TLOG, g, LOGN) >> SPECIAL_TLOG;
+    const char *key0 = (const char *)((ia.per_op ? oa.evk[op] : ia.evk) + (((size_t)mi << LOGN) + ((size_t)tile << SPECIAL_TLOG)));
+    const u64 *d_limb = (ia.per_op && oa.d[op] ? oa.d[op] : ia.d + (((size_t)op * ia.d_stride) << LOGN)) + ((size_t)a << LOGN);
+    const u64 *raised0 = ia.raised + ((((size_t)op * ia.raised_stride + a) << LOGN) + ((size_t)tile_in << SPECIAL_TLOG));
+    const size_t raised_step = (size_t)Ma << LOGN, comp_step = ((size_t)M << LOGN) * 8, key_step = 2 * comp_step;
+    const unsigned wave = wave_id(), lane = threadIdx.x & 63u, blk = lane >> 4, il = lane & 15u, bg = tile_in * 4 + blk;
+    // an integer-path ciphertext limb (the one a rescale drops) has been finished with the other ciphertext limbs
+    const bool finished = !A::IS_FP && (a < ia.level || ia.finished);
+    const bool shared = ia.raised_stride == 0; // digits that every operation reads stay in L2
+    unsigned sr[2], lx[2], ly[2]; // sources of the pairs: index in the limb, LDS words of the even and the odd element
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        const unsigned pos = (tile << SPECIAL_TLOG) + 512u * i + 2u * threadIdx.x;
+        sr[i] = g == 1 ? pos : galois_index(pos, g, LOGN);
+        const unsigned sl = sr[i] & (SPECIAL_TILE - 2u), sw = sr[i] & 1u;
+        lx[i] = special_at(sl) + sw, ly[i] = special_at(sl) + 1 - sw;
+    }
+    double f0[4], f1[4];
+    U128 s0[4], s1[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) f0[k] = f1[k] = 0.0, s0[k] = s1[k] = U128{0, 0};
+    // the key words of the digit after the one at hand are on their way, those of a round's first through the transforms
+    u64x2 ka[2], kb[2];
+    const auto load_key = [&](int j) {
+        const char *kj = key0 + (size_t)j * key_step;
+#pragma unroll
+        for (int i = 0; i < 2; i++)
+            ka[i] = ld_at<u64x2>(kj + 4096 * i, threadIdx.x * 16u), kb[i] = ld_at<u64x2>(kj + comp_step + 4096 * i, threadIdx.x * 16u);
+    };
+    load_key(0);
+    for (int j0 = 0; j0 < beta; j0 += SPECIAL_WAVES) {
+        const int jw = j0 + (int)wave;
+        if (jw < beta && jw != own) {
+            const u64 *in = raised0 + (size_t)jw * raised_step + blk * 256 + il;
+            u64 *dig = lds + wave * SPECIAL_DIGIT;
+            u64 x[16];
+#pragma unroll
+            for (int k = 0; k < 16; k++) x[k] = shared ? in[16 * k] : __builtin_nontemporal_load(in + 16 * k);
+            if (finished) {
+#pragma unroll
+                for (int k = 0; k < 16; k++) dig[tile_at(blk, il + 16 * k)] = x[k];
+            } else {
+                typename A::V v[16];
+#pragma unroll
+                for (int k = 0; k < 16; k++) v[k] = ar.load_mid(x[k]);
+                ar.fwd16(v, LOGN - 8, bg, true);
+#pragma unroll
+                for (int k = 0; k < 16; k++) dig[tile_at(blk, il + 16 * k)] = ar.store_mid(v[k]);
+                block_sync();
+#pragma unroll
+                for (int k = 0; k < 16; k++) v[k] = ar.load_mid(dig[tile_at(blk, 16 * il + k)]);
+                ar.fwd16(v, LOGN - 4, bg * 16 + il, true);
+                block_sync();
+#pragma unroll
+                for (int k = 0; k < 16; k++) dig[tile_at(blk, 16 * il + k)] = ar.store_final(v[k]);
+            }
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int jj = 0; jj < SPECIAL_WAVES && j0 + jj < beta; jj++) {
+            const int j = j0 + jj;
+            const u64 *dig = lds + jj * SPECIAL_DIGIT;
+            const u64x2 ca[2] = {ka[0], ka[1]}, cb[2] = {kb[0], kb[1]};
+            if (j + 1 < beta) load_key(j + 1);
+#pragma unroll
+            for (int i = 0; i < 2; i++) {
+                u64 x, y;
+                if (j == own) {
+                    const u64x2 v = ld_at<u64x2>(d_limb, (sr[i] & ~1u) * 8u);
+                    x = sr[i] & 1u ? v.y : v.x, y = sr[i] & 1u ? v.x : v.y;
+                } else
+                    x = dig[lx[i]], y = dig[ly[i]];
+                if constexpr (A::IS_FP) { // key words are balanced doubles
+                    const double xd = u2d(x), yd = u2d(y);
+                    f0[2 * i] += ar.mulmod(xd, ar.load_mid(ca[i].x)), f0[2 * i + 1] += ar.mulmod(yd, ar.load_mid(ca[i].y));
+                    f1[2 * i] += ar.mulmod(xd, ar.load_mid(cb[i].x)), f1[2 * i + 1] += ar.mulmod(yd, ar.load_mid(cb[i].y));
+                } else {
+                    mac128(s0[2 * i], x, ca[i].x);
+                    mac128(s0[2 * i + 1], y, ca[i].y);
+                    mac128(s1[2 * i], x, cb[i].x);
+                    mac128(s1[2 * i + 1], y, cb[i].y);
+                }
+            }
+        }
+        if constexpr (A::IS_FP) { // after at most four products
+#pragma unroll
+            for (int k = 0; k < 4; k++) f0[k] = ar.reduce(f0[k]), f1[k] = ar.reduce(f1[k]);
+        }
+        __syncthreads(); // the digits have been read
+    }
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        if constexpr (A::IS_FP)
+            r0[k] = ar.store_final(f0[k]), r1[k] = ar.store_final(f1[k]);
+        else
+            r0[k] = reduce128(s0[k], m), r1[k] = reduce128(s1[k], m);
+    }
+}
+
+// Inverse block pass of both components from the pairs of special_products, through LDS (which nothing reads any more) to
+// one component per wave; u: component 0, component 1 comp_words further on.
+template <int LOGN, class A>
+__device__ __forceinline__ void special_inverse(const u64 (&r0)[4], const u64 (&r1)[4], u64 *u, size_t comp_words, const A &ar, u64 *lds,
+                                                unsigned tile)
+{
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        const unsigned wd = special_at(512u * i + 2u * threadIdx.x);
+        lds[wd] = r0[2 * i], lds[wd + 1] = r0[2 * i + 1];
+        lds[SPECIAL_DIGIT + wd] = r1[2 * i], lds[SPECIAL_DIGIT + wd + 1] = r1[2 * i + 1];
+    }
+    __syncthreads();
+    const unsigned comp = wave_id(), lane = threadIdx.x & 63u, blk = lane >> 4, il = lane & 15u, bg = tile * 4 + blk;
+    if (comp > 1) return;
+    u64 *limb = u + comp * comp_words, *w = lds + comp * SPECIAL_DIGIT;
+    typename A::V v[16];
+#pragma unroll
+    for (int k = 0; k < 16; k++) v[k] = ar.load(w[tile_at(blk, 16 * il + k)]);
+    ar.template inv16<false>(v, LOGN - 4, bg * 16 + il);
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 16; k++) w[tile_at(blk, 16 * il + k)] = ar.store_mid(v[k]);
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 16; k++) v[k] = ar.load_mid(w[tile_at(blk, il + 16 * k)]);
+    ar.template inv16<false>(v, LOGN - 8, bg);
+#pragma unroll
+    for (int k = 0; k < 16; k++) limb[bg * 256 + il + 16 * k] = ar.store_mid(v[k]);
+}
+
+// Active limbs ia.first .. level + K - 1 of every operation.  The same order of work-groups as k_inner_fin.
+template <int LOGN> __global__ __launch_bounds__(SPECIAL_THREADS, 3) void k_inner_special(InnerArgs ia, DevTables T, OpArgs oa)
+{
+    __shared__ u64 lds[SPECIAL_WAVES * SPECIAL_DIGIT];
+    static_assert(SPECIAL_TILE == INNER_TILE, "inner_grid and inner_tile serve both kernels");
     const int Ma = ia.level + ia.K;
     const InnerTile w = inner_tile<LOGN>(ia, oa, Ma - ia.first, ia.first);
     if (w.none) return;
     const int mi = active_mod(w.a, ia.level, ia.L);
     const ModConst m = T.mod[mi];
-    u64 r0[8], r1[8];
+    u64 *u0 = ia.u + (((size_t)w.op * ia.u_stride + w.a) << LOGN);
+    const size_t comp_words = (size_t)Ma << LOGN;
+    u64 r0[4], r1[4];
     if (m.qd != 0.0) {
-        double acc0[8], acc1[8];
-        const BlockLane b = block_lane(lds, tws);
-        inner_products8<LOGN>(ia, oa, T, w, mi, make_fp(T, mi, LOGN), b, lds, tws, pre, nullptr, acc0, acc1);
-#pragma unroll
-        for (int k = 0; k < 8; k++) r0[k] = fp_canon(acc0[k], m.qd, m.qinvd), r1[k] = fp_canon(acc1[k], m.qd, m.qinvd);
+        const ArithFp ar = make_fp(T, mi, LOGN);
+        special_products<LOGN>(ia, oa, T, w.op, w.tile, w.a, w.g, w.beta, mi, m, ar, lds, r0, r1);
+        if (w.a >= ia.level) special_inverse<LOGN>(r0, r1, u0, comp_words, ar, lds, w.tile);
     } else {
-#pragma unroll
-        for (int h = 0; h < 2; h++) { // two pairs at a time: the 128-bit accumulators of four would not fit
-            u64 x0[4], x1[4];
-            inner_products_int<LOGN>(ia, oa, w, mi, m, h, x0, x1);
-#pragma unroll
-            for (int k = 0; k < 4; k++) r0[4 * h + k] = x0[k], r1[4 * h + k] = x1[k];
-        }
+        const ArithInt ar = make_int(T, mi, LOGN);
+        special_products<LOGN>(ia, oa, T, w.op, w.tile, w.a, w.g, w.beta, mi, m, ar, lds, r0, r1);
+        if (w.a >= ia.level) special_inverse<LOGN>(r0, r1, u0, comp_words, ar, lds, w.tile);
     }
-    u64 *u0 = ia.u + ((((size_t)w.op * ia.u_stride + w.a) << LOGN)), *u1 = u0 + ((size_t)Ma << LOGN);
-    if (w.a >= ia.level) {
-        if (m.qd != 0.0)
-            inv_blocks_from_pairs8<LOGN>(r0, r1, u0, (size_t)Ma << LOGN, make_fp(T, mi, LOGN), lds, w.grp);
-        else
-            inv_blocks_from_pairs8<LOGN>(r0, r1, u0, (size_t)Ma << LOGN, make_int(T, mi, LOGN), lds, w.grp);
-    } else {
-        const unsigned lane16 = (threadIdx.x & 63) * 16u;
-        char *o0 = (char *)(u0 + ((size_t)w.grp << WAVE_LOG)), *o1 = (char *)(u1 + ((size_t)w.grp << WAVE_LOG));
+    if (w.a < ia.level) {
 #pragma unroll
-        for (int i = 0; i < 4; i++) {
-            __builtin_nontemporal_store(u64x2{r0[2 * i], r0[2 * i + 1]}, (u64x2 *)(o0 + 1024 * i + lane16));
-            __builtin_nontemporal_store(u64x2{r1[2 * i], r1[2 * i + 1]}, (u64x2 *)(o1 + 1024 * i + lane16));
+        for (int i = 0; i < 2; i++) {
+            char *o = (char *)(u0 + ((size_t)w.tile << SPECIAL_TLOG)) + 4096 * i + threadIdx.x * 16u;
+            __builtin_nontemporal_store(u64x2{r0[2 * i], r0[2 * i + 1]}, (u64x2 *)o);
+            __builtin_nontemporal_store(u64x2{r1[2 * i], r1[2 * i + 1]}, (u64x2 *)(o + comp_words * 8));
         }
     }
 }
+
+// ---- second launch: the ciphertext limbs ------------------------------------------------------------------------------------
 
 // Addend of pair i of component c, as canonical residues.
 template <int LOGN, int MODE>

@@ -253,7 +253,7 @@ __device__ __forceinline__ double conv_get(const ConvSetup<NSMAX> &S, const Arit
 }
 
 template <int PRO, int SPLIT, bool TINT, bool EX, int NSMAX>
-__device__ __forceinline__ u64 conv_get(const ConvSetup<NSMAX> &S, const ArithInt &, const ModConst &m, unsigned pos)
+__device__ __forceinline__ u64 conv_get(const ConvSetup<NSMAX> &S, const ArithInt &ar, const ModConst &m, unsigned pos)
 {
     if (PRO == PRO_RESCALE) {
         const u64 tv = S.sp[0][pos];
@@ -268,7 +268,7 @@ __device__ __forceinline__ u64 conv_get(const ConvSetup<NSMAX> &S, const ArithIn
 #pragma unroll
         for (int s = 0; s < NSMAX; s++) {
             const u64 y = S.sp[s][pos];
-            lazy += mul_shoup_sloppy(y, ShoupConst{S.ci[s], S.cp[s]}, m.q);
+            lazy += mul_shoup_sloppy(y, ShoupConst{S.ci[s], S.cp[s]}, ar.nq);
             if (EX) sv = sv + (double)y * S.rq[s];
         }
         lazy = csub(lazy, 8 * m.q); // the range the transform takes

@@ -105,7 +105,7 @@ static void launch_inv_blocks(he_ctx *c, hipStream_t st, double bytes, const u64
 template <int LOGN>
 static void launch_inner(he_ctx *c, hipStream_t st, double bytes, unsigned grid, const InnerArgs &ia, const OpArgs &oa)
 {
-    KLAUNCH_T(c, st, KID_INNER, bytes, (k_inner_blocks8<LOGN>), grid, INNER_THREADS, ia, c->dev, oa);
+    KLAUNCH_T(c, st, KID_INNER, bytes, (k_inner_special<LOGN>), grid, SPECIAL_THREADS, ia, c->dev, oa);
 }
 template <int LOGN, int MODE>
 static void launch_inner_fin_mode(he_ctx *c, hipStream_t st, double bytes, unsigned grid, bool integer, const InnerArgs &ia,
