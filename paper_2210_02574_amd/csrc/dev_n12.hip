@@ -26,12 +26,12 @@ static void fwd12(he_ctx *c, hipStream_t st, int kid, double bytes, bool wide, u
     } else
         launch_fwd12<PRO, 4, false>(c, st, kid, bytes, data, lb, nb, cv, fin);
 }
-static void inv12(he_ctx *c, hipStream_t st, double bytes, int scale, const u64 *src, u64 *dst, const LimbBatch &lb, int nb,
+static void inv12(he_ctx *c, hipStream_t st, double bytes, int scale, const u64 *src, const u64 *src2, u64 *dst, const LimbBatch &lb, int nb,
                   const ConvArgs &cv)
 {
     switch (scale) { // special limbs are scaled where they are produced
-    case SCALE_NONE: KLAUNCH(c, st, KID_INV_COLS, bytes, (k_ntt_inv12<SCALE_NONE>), nb, src, dst, c->dev, lb, cv); break;
-    default: KLAUNCH(c, st, KID_INV_COLS, bytes, (k_ntt_inv12<SCALE_MODUP>), nb, src, dst, c->dev, lb, cv); break;
+    case SCALE_NONE: KLAUNCH(c, st, KID_INV_COLS, bytes, (k_ntt_inv12<SCALE_NONE>), nb, src, src2, dst, c->dev, lb, cv); break;
+    default: KLAUNCH(c, st, KID_INV_COLS, bytes, (k_ntt_inv12<SCALE_MODUP>), nb, src, src2, dst, c->dev, lb, cv); break;
     }
 }
 static void inner12(he_ctx *c, hipStream_t st, double bytes, const InnerArgs &ia, const OpArgs &oa)

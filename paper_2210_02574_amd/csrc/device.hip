@@ -177,7 +177,7 @@ extern "C" int32_t he_evk_to_host(const he_evk *evk, uint64_t *h_out)
 static const char *const kKernelNames[KID_COUNT] = {
     "k_ntt_fwd_cols", "k_ntt_fwd_cols_modup", "k_ntt_fwd_cols_moddown", "k_ntt_fwd_cols_rescale", "k_ntt_fwd_cols_moddown_rescale",
     "k_ntt_fwd_blocks",
-    "k_ntt_fwd_blocks_fin", "k_ntt_inv_blocks", "k_ntt_inv_cols", "k_limbwise", "k_cmult", "k_tensor", "k_inner_blocks", "k_inner_fin"};
+    "k_ntt_fwd_blocks_fin", "k_ntt_inv_blocks", "k_ntt_inv_cols", "k_limbwise", "k_cmult", "k_inner_blocks", "k_inner_fin"};
 
 bool prof_events(he_ctx *c, int kid, double bytes, ProfRecord &r)
 {
@@ -375,18 +375,19 @@ static int32_t ntt_forward(he_ctx *c, hipStream_t st, u64 *data, const LimbList 
 // Inverse NTT: limb b read at src + l.src[b]*N, result at dst + l.slot[b]*N; scale folds a base
 // conversion constant into the final 1/N.
 // blocks_done: the block pass has already been applied (by the inner-product kernel), in place in dst.
+// src2: the transform's input is the limb-wise product of src and src2.
 static int32_t ntt_inverse(he_ctx *c, hipStream_t st, const u64 *src, u64 *dst, const LimbList &l, int scale,
-                           const ConvArgs &cv, bool blocks_done = false)
+                           const ConvArgs &cv, bool blocks_done = false, const u64 *src2 = nullptr)
 {
     const double N8 = (double)c->N * 8.0;
     const DevLaunch &dl = dev_launch(c);
     return for_batches(c, l, [&](const LimbBatch &lb, int nb) {
         const double bytes = 2.0 * nb * N8;
         if (dl.inv_limb) {
-            dl.inv_limb(c, st, bytes, scale, src, dst, lb, nb, cv);
+            dl.inv_limb(c, st, src2 ? 1.5 * bytes : bytes, scale, src, src2, dst, lb, nb, cv);
             return;
         }
-        if (!blocks_done) dl.inv_blocks(c, st, bytes, src, dst, lb, nb);
+        if (!blocks_done) dl.inv_blocks(c, st, src2 ? 1.5 * bytes : bytes, src, src2, dst, lb, nb);
         dl.inv_cols(c, st, bytes, scale, dst, lb, nb, cv);
     });
 }
@@ -586,7 +587,7 @@ static inline bool misaligned16(const void *p) { return ((uintptr_t)p & 15u) != 
 
 // ---- workspace layout (in limbs of N words), per operation of a batch
 struct WsLayout {
-    size_t x, d, raised, u, r, tmp, total;
+    size_t x, raised, u, r, tmp, total;
 };
 static WsLayout ws_layout(const he_ctx *c, int level)
 {
@@ -594,11 +595,11 @@ static WsLayout ws_layout(const he_ctx *c, int level)
     WsLayout w;
     size_t o = 0;
     w.x = o, o += std::max(level, 2); // y: inverse transform of the switched polynomial, scaled
-    w.d = o, o += level;              // d2 of the tensor product (NTT domain)
+    o += level;                       // spare: the size that callers have been told stays as it was
     w.raised = o, o += beta * Ma;     // raised digits (slots of a digit's own limbs stay unused)
     w.u = o, o += 2 * Ma;             // inner products
     w.r = o, o += 2 * level;          // ModDown / rescale corrections
-    w.tmp = o, o += 2 * level;        // rotate_sum: the rotated ciphertext
+    w.tmp = o, o += 2 * level;        // rotate_sum: the rotated ciphertext; Mult: a result that overlaps a factor
     w.total = o;
     return w;
 }
@@ -614,12 +615,12 @@ extern "C" int32_t he_workspace_bytes(const he_ctx *ctx, int32_t level, int32_t 
 // limb slots are 16-bit offsets from a buffer's base
 static bool batch_fits(const WsLayout &w, int count) { return count >= 1 && w.total * (size_t)count <= 65535; }
 
-// Steps 1-2 of the key switch for `count` polynomials: operation o reads its NTT-domain input at
+// Steps 1-2 of the key switch for `count` polynomials (d_ntt2: products of two): operation o reads its NTT-domain input at
 // d_ntt + o*d_stride limbs and works in ws + o*w.total limbs.  Raised limbs on the floating-point path
 // and special ones are left as the column pass wrote them (the inner-product kernels finish them), unless
 // `finish_special`: then the block pass is applied to the special limbs on the integer path.
 static int32_t ks_raise(he_ctx *c, const u64 *d_ntt, int d_stride, u64 *ws, const WsLayout &w, int level, int count,
-                        hipStream_t st, bool finish_special = false)
+                        hipStream_t st, bool finish_special = false, const u64 *d_ntt2 = nullptr)
 {
     const size_t N = c->N;
     const int K = c->K, Ma = level + K, beta = (level + c->alpha - 1) / c->alpha, W = (int)w.total;
@@ -627,7 +628,7 @@ static int32_t ks_raise(he_ctx *c, const u64 *d_ntt, int d_stride, u64 *ws, cons
     for (int o = 0; o < count; o++)
         for (int i = 0; i < level; i++) l.add(o * W + i, o * d_stride + i, i);
     const ConvArgs cv = conv_args(c, ws + w.x * N, level, W, W);
-    int32_t rc = ntt_inverse(c, st, d_ntt, ws + w.x * N, l, SCALE_MODUP, cv);
+    int32_t rc = ntt_inverse(c, st, d_ntt, ws + w.x * N, l, SCALE_MODUP, cv, false, d_ntt2);
     if (rc != HE_OK) return rc;
     LimbList r;
     for (int o = 0; o < count; o++)
@@ -650,6 +651,7 @@ static InnerArgs inner_args(const he_ctx *c, const he_evk *evk, const u64 *d_ntt
     ia.g = (unsigned)evk->galois;
     ia.raised_stride = shared_raised ? 0 : (int)w.total, ia.u_stride = (int)w.total, ia.d_stride = d_stride;
     ia.per_op = oa ? 1 : 0, ia.count = count, ia.finished = shared_raised ? 1 : 0;
+    ia.ta = ia.tb = nullptr, ia.t_stride = 0;
     return ia;
 }
 // Words per index that the inner product has to move on the active limbs [lo, hi), by the definition of the step and
@@ -714,7 +716,7 @@ static int32_t ks_finish(he_ctx *c, const InnerArgs &ia, const OpArgs *oa, const
         const int limbs = std::min(oa && oa->level[o] ? oa->level[o] : ia.level, fa.nl);
         for (int cc = 0; cc < 2; cc++)
             for (int i = 0; i < limbs; i++) l.add(o * W + cc * ia.level + i, i);
-        words += limbs * (4.0 + (mode == FIN_ADD ? 2.0 : mode == FIN_ROT ? 1.0 : 3.0)); // r, results, addends
+        words += limbs * (4.0 + (mode == FIN_ROT ? 1.0 : 3.0)); // r, results, addends (FIN_MULT: four inputs in place of d)
     }
     fa.r = r, fa.r_stride = W;
     if (dev_launch(c).fin_limb) { // reads u and the special limbs in place of digits, keys and r
@@ -741,7 +743,7 @@ static FinishArgs finish_args(const he_ctx *c, u64 *out, int out_stride, const u
 {
     FinishArgs fa;
     fa.r = nullptr, fa.out = out, fa.add = add;
-    fa.cst = c->dev.dn_pinv, fa.cst2 = nullptr, fa.cst_d = c->dev.dn_pinv_d, fa.cst2_d = nullptr;
+    fa.cst = c->dev.dn_pinv, fa.cst_d = c->dev.dn_pinv_d;
     fa.nl = level, fa.r_stride = 0, fa.out_stride = out_stride, fa.out_cstride = level;
     fa.add_stride = add_stride, fa.add_cstride = add_cstride;
     return fa;
@@ -770,6 +772,40 @@ static int32_t ks_guard(he_ctx *c, const he_evk *evk, int level, int count, void
     return HE_OK;
 }
 
+// Where a Mult writes its result: d_out itself, or the workspace, to be copied, where d_out overlaps a factor that
+// work-groups of the same launch still read (where a limb is one work-group's, the launch that writes reads no factor).  A
+// result that replaces a whole factor, limb for limb, needs no copy: the thread that writes a position has read it.
+struct MultOut {
+    u64 *out;
+    int stride; // limbs between two operations
+    bool copy;
+};
+static MultOut mult_out(const he_ctx *c, const u64 *a, const u64 *b, u64 *out, u64 *tmp, int W, int in_limbs, int out_limbs, int count)
+{
+    if (dev_launch(c).fin_limb) return {out, out_limbs, false};
+    const size_t limb = c->N * sizeof(u64);
+    const auto clash = [&](const u64 *x) {
+        const uintptr_t x0 = (uintptr_t)x, x1 = x0 + (size_t)count * in_limbs * limb;
+        const uintptr_t o0 = (uintptr_t)out, o1 = o0 + (size_t)count * out_limbs * limb;
+        return x0 < o1 && o0 < x1 && !(x == out && in_limbs == out_limbs);
+    };
+    if (clash(a) || clash(b)) return {tmp, W, true};
+    return {out, out_limbs, false};
+}
+static int32_t mult_copy(he_ctx *c, const MultOut &mo, u64 *out, int out_limbs, int count, hipStream_t st)
+{
+    if (!mo.copy) return HE_OK;
+    const size_t row = (size_t)out_limbs * c->N * sizeof(u64);
+    HIP_TRY(c, hipMemcpy2DAsync(out, row, mo.out, (size_t)mo.stride * c->N * sizeof(u64), row, (size_t)count, hipMemcpyDeviceToDevice, st));
+    return HE_OK;
+}
+static InnerArgs mult_args(const he_ctx *c, const he_evk *relin, const u64 *a, const u64 *b, u64 *ws, const WsLayout &w, int level, int count)
+{
+    InnerArgs ia = inner_args(c, relin, a, 0, ws, w, level, count, nullptr, false);
+    ia.ta = a, ia.tb = b, ia.t_stride = 2 * level;
+    return ia;
+}
+
 extern "C" int32_t he_hmult_relin_batch(he_ctx *ctx, const he_evk *relin, const uint64_t *d_a, const uint64_t *d_b,
                                         uint64_t *d_out, int32_t level, int32_t count, void *d_ws, size_t ws_bytes,
                                         void *stream)
@@ -782,15 +818,12 @@ extern "C" int32_t he_hmult_relin_batch(he_ctx *ctx, const he_evk *relin, const 
     u64 *ws = (u64 *)d_ws;
     const WsLayout w = ws_layout(ctx, level);
     const size_t N = ctx->N;
-    const int W = (int)w.total;
-    dim3 grid((unsigned)(N / 256), (unsigned)level, (unsigned)count);
-    KLAUNCH(ctx, st, KID_TENSOR, 7.0 * count * level * N * 8.0, (k_tensor), grid, d_a, d_b, d_out, ws + w.d * N, ctx->dev,
-            level, ctx->logN, W, 2 * level);
-    if ((rc = launch_ok(ctx)) != HE_OK) return rc;
-    if ((rc = ks_raise(ctx, ws + w.d * N, W, ws, w, level, count, st)) != HE_OK) return rc;
-    // d0 and d1 wait in d_out
-    return ks_apply(ctx, inner_args(ctx, relin, ws + w.d * N, W, ws, w, level, count, nullptr, false), nullptr, ws, w,
-                    finish_args(ctx, d_out, 2 * level, d_out, 2 * level, level, level), FIN_ADD, st);
+    const MultOut mo = mult_out(ctx, d_a, d_b, d_out, ws + w.tmp * N, (int)w.total, 2 * level, 2 * level, count);
+    if ((rc = ks_raise(ctx, d_a + (size_t)level * N, 2 * level, ws, w, level, count, st, false, d_b + (size_t)level * N)) != HE_OK) return rc;
+    if ((rc = ks_apply(ctx, mult_args(ctx, relin, d_a, d_b, ws, w, level, count), nullptr, ws, w,
+                       finish_args(ctx, mo.out, mo.stride, nullptr, 0, 0, level), FIN_MULT, st)) != HE_OK)
+        return rc;
+    return mult_copy(ctx, mo, d_out, 2 * level, count, st);
 }
 
 extern "C" int32_t he_hmult_relin(he_ctx *ctx, const he_evk *relin, const uint64_t *d_a, const uint64_t *d_b,
@@ -799,9 +832,10 @@ extern "C" int32_t he_hmult_relin(he_ctx *ctx, const he_evk *relin, const uint64
     return he_hmult_relin_batch(ctx, relin, d_a, d_b, d_out, level, 1, d_ws, ws_bytes, stream);
 }
 
-// Mult followed by rescale with one forward transform per output limb.  After the inner product: ModDown of
-// the last limb alone (c_last = (u - ntt(r)) P^-1 + d), its inverse transform t, then for every other limb
-// the column pass transforms r + P t_centred and the block pass finishes (u - ntt) (P q_l)^-1 + d q_l^-1.
+// Mult followed by rescale with one forward transform per output limb.  The inner product gives u + P d (d: the
+// limb of d0 or d1).  After it: ModDown of the last limb alone (c_last = (u + P d - ntt(r)) P^-1), its inverse transform t,
+// then for every other limb the column pass transforms r + P t_centred and the block pass finishes
+// (u + P d - ntt) (P q_l)^-1.
 extern "C" int32_t he_hmult_relin_rescale_batch(he_ctx *ctx, const he_evk *relin, const uint64_t *d_a,
                                                 const uint64_t *d_b, uint64_t *d_out, int32_t level, int32_t count,
                                                 void *d_ws, size_t ws_bytes, void *stream)
@@ -816,13 +850,9 @@ extern "C" int32_t he_hmult_relin_rescale_batch(he_ctx *ctx, const he_evk *relin
     const WsLayout w = ws_layout(ctx, level);
     const size_t N = ctx->N;
     const int W = (int)w.total, K = ctx->K, Ma = level + K, L = ctx->L;
-    u64 *d01 = ws + w.tmp * N; // per operation [2][level][N]: d0, d1 of the tensor product
-    dim3 grid((unsigned)(N / 256), (unsigned)level, (unsigned)count);
-    KLAUNCH(ctx, st, KID_TENSOR, 7.0 * count * level * N * 8.0, (k_tensor), grid, d_a, d_b, d01, ws + w.d * N, ctx->dev,
-            level, ctx->logN, W, W);
-    if ((rc = launch_ok(ctx)) != HE_OK) return rc;
-    if ((rc = ks_raise(ctx, ws + w.d * N, W, ws, w, level, count, st)) != HE_OK) return rc;
-    InnerArgs ia = inner_args(ctx, relin, ws + w.d * N, W, ws, w, level, count, nullptr, false);
+    const MultOut mo = mult_out(ctx, d_a, d_b, d_out, ws + w.tmp * N, W, 2 * level, 2 * (level - 1), count);
+    if ((rc = ks_raise(ctx, d_a + (size_t)level * N, 2 * level, ws, w, level, count, st, false, d_b + (size_t)level * N)) != HE_OK) return rc;
+    InnerArgs ia = mult_args(ctx, relin, d_a, d_b, ws, w, level, count);
     ia.first = level - 1; // the dropped limb as well
     if ((rc = ks_special(ctx, ia, nullptr, w, st)) != HE_OK) return rc;
     u64 *rbuf = ws + w.r * N;
@@ -830,25 +860,25 @@ extern "C" int32_t he_hmult_relin_rescale_batch(he_ctx *ctx, const he_evk *relin
     cv.src2 = rbuf;
     cv.src2_stride = W;
     // ModDown of the last limb of both components, in place in the correction buffer, and its inverse transform
-    FinishArgs fa = finish_args(ctx, d_out, 2 * (level - 1), d01, W, level, level);
+    FinishArgs fa = finish_args(ctx, mo.out, mo.stride, nullptr, 0, 0, level);
     fa.r = rbuf, fa.r_stride = W;
     if (dev_launch(ctx).fin_limb) {
         const double bytes = (2.0 * K + 6.0) * count * N * 8.0;
-        dev_launch(ctx).fin_limb(ctx, st, bytes, std::max(ctx->alpha, K) > 4, PRO_MODDOWN, true, FIN_ADD, ia, fa, kNoOps, cv);
+        dev_launch(ctx).fin_limb(ctx, st, bytes, std::max(ctx->alpha, K) > 4, PRO_MODDOWN, true, FIN_MULT, ia, fa, kNoOps, cv);
         if ((rc = launch_ok(ctx)) != HE_OK) return rc;
     } else {
         LimbList last;
         for (int o = 0; o < count; o++)
             for (int cc = 0; cc < 2; cc++) last.add(o * W + cc * level + level - 1, level - 1);
-        const FinArgs fl = {ws + w.u * N, rbuf, d01, ctx->dev.dn_pinv, ctx->dev.dn_pinv_d, Ma, level, level, level, W, W, W, W};
+        const FinArgs fl = {ws + w.u * N, rbuf, nullptr, ctx->dev.dn_pinv, ctx->dev.dn_pinv_d, Ma, level, 0, level, W, W, W, 0};
         if ((rc = ntt_forward(ctx, st, rbuf, last, PRO_MODDOWN, cv, &fl, 2 * K * count)) != HE_OK) return rc;
         if ((rc = ntt_inverse(ctx, st, rbuf, rbuf, last, SCALE_NONE, cv)) != HE_OK) return rc;
     }
     // every other limb: ModDown and rescale corrections in one transform
     fa.nl = fa.out_cstride = level - 1;
     fa.cst = ctx->dev.rsp_inv + (size_t)(level - 1) * L, fa.cst_d = ctx->dev.rsp_inv_d + (size_t)(level - 1) * L;
-    fa.cst2 = ctx->dev.rs_inv + (size_t)(level - 1) * L, fa.cst2_d = ctx->dev.rs_inv_d + (size_t)(level - 1) * L;
-    return ks_finish(ctx, ia, nullptr, w, ws, fa, FIN_ADD, PRO_MODDOWN_RS, cv, 2 * count, st);
+    if ((rc = ks_finish(ctx, ia, nullptr, w, ws, fa, FIN_MULT, PRO_MODDOWN_RS, cv, 2 * count, st)) != HE_OK) return rc;
+    return mult_copy(ctx, mo, d_out, 2 * (level - 1), count, st);
 }
 
 extern "C" int32_t he_hmult_relin_rescale(he_ctx *ctx, const he_evk *relin, const uint64_t *d_a, const uint64_t *d_b,

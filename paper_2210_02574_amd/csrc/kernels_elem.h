@@ -1,4 +1,4 @@
-// Streaming kernels of the ciphertext operations: limb-wise arithmetic and the tensor product of Mult.
+// Streaming kernels of the ciphertext operations: limb-wise arithmetic.
 // Not templates: included by device.hip alone.
 #pragma once
 #include "arith.h"
@@ -85,38 +85,4 @@ __global__ __launch_bounds__(256) void k_pmult_sum(PmultSumArgs a, u64 *__restri
         r = csub(part + reduce128(acc, m), m.q);
     }
     out[oc] = r;
-}
-
-// Tensor product: d0 = a0 b0, d1 = a0 b1 + a1 b0 -> out (may alias A or B); d2 = a1 b1 -> d2.
-// blockIdx.z = operation of a batch: input ciphertexts 2*level limbs apart, out buffers out_stride and d2
-// buffers d2_stride limbs apart.
-__global__ __launch_bounds__(256) void k_tensor(const u64 *A, const u64 *B, u64 *out, u64 *__restrict__ d2,
-                                                DevTables T, int level, int logN, int d2_stride, int out_stride)
-{
-    const unsigned i = blockIdx.y;
-    const size_t n = (size_t)blockIdx.x * 256 + threadIdx.x;
-    const ModConst m = T.mod[i];
-    const size_t ct_off = ((size_t)blockIdx.z * 2 * level) << logN;
-    A += ct_off, B += ct_off;
-    out += ((size_t)blockIdx.z * out_stride) << logN;
-    d2 += ((size_t)blockIdx.z * d2_stride) << logN;
-    const size_t o0 = ((size_t)i << logN) + n, o1 = ((size_t)(level + i) << logN) + n;
-    // every operand is read once and every result is for a later launch: streamed past the caches
-    const u64 a0 = __builtin_nontemporal_load(A + o0), a1 = __builtin_nontemporal_load(A + o1);
-    const u64 b0 = __builtin_nontemporal_load(B + o0), b1 = __builtin_nontemporal_load(B + o1);
-    u64 r0, r1, r2;
-    if (m.qd != 0.0) {
-        const double x0 = u2d(a0), x1 = u2d(a1), y0 = u2d(b0), y1 = u2d(b1);
-        r0 = fp_canon(fp_mulmod(x0, y0, m.qd, m.qinvd), m.qd, m.qinvd);
-        r1 = fp_canon(fp_mulmod(x0, y1, m.qd, m.qinvd) + fp_mulmod(x1, y0, m.qd, m.qinvd), m.qd, m.qinvd);
-        r2 = fp_canon(fp_mulmod(x1, y1, m.qd, m.qinvd), m.qd, m.qinvd);
-    } else {
-        U128 acc{0, 0};
-        mac128(acc, a0, b1);
-        mac128(acc, a1, b0);
-        r0 = mul_mod(a0, b0, m), r1 = reduce128(acc, m), r2 = mul_mod(a1, b1, m);
-    }
-    __builtin_nontemporal_store(r0, out + o0);
-    __builtin_nontemporal_store(r1, out + o1);
-    __builtin_nontemporal_store(r2, d2 + o0);
 }

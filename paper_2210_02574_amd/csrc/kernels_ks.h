@@ -26,11 +26,15 @@ typedef double f64x2 __attribute__((ext_vector_type(2)));
 
 struct InnerArgs {
     const u64 *raised, *d, *evk;
+    // Mult (g = 1): the two factors, operation z at z * t_stride limbs.  The polynomial that is switched is d2 = a1 b1, and
+    // d0 = a0 b0, d1 = a0 b1 + a1 b0 join the result as u + P d (P: the product of the special primes), so that
+    // the finishing step's (u - r) * const adds them; d is not used.  Null: no Mult.
+    const u64 *ta, *tb;
     u64 *u;
     int level, L, K, alpha;
     int first; // k_inner_special: the lowest active limb it works on (level: the special limbs alone)
     unsigned g;
-    int raised_stride, u_stride, d_stride; // limbs between two operations of a batch in each buffer
+    int raised_stride, u_stride, d_stride, t_stride; // limbs between two operations of a batch in each buffer
     int per_op; // operation z uses entry z of the OpArgs argument
     int finished; // the raised special limbs on the integer path have been through their block pass
     int count;  // operations in this launch
@@ -48,15 +52,15 @@ struct OpArgs {
     uint8_t level[HE_OPS_MAX];
 };
 // The finishing step on ciphertext limb i, component c: out = (u - NTT(r)) * cst + addend.
-// FIN_ADD: the addend is limb i of component c of `add`, times cst2 unless that is null; FIN_ROT: sigma_g of limb i
+// FIN_MULT: no addend (u holds it, InnerArgs.ta); FIN_ROT: sigma_g of limb i
 // of `add` (c0 of the rotated ciphertext) on component 0; FIN_ROTSUM: as FIN_ROT plus limb i of component c of `add`.
-enum { FIN_ADD = 0, FIN_ROT = 1, FIN_ROTSUM = 2 };
+enum { FIN_MULT = 0, FIN_ROT = 1, FIN_ROTSUM = 2 };
 struct FinishArgs {
     const u64 *r; // [2][level] limbs per operation; floating-point limbs as the column pass left them, others finished
     u64 *out;
     const u64 *add;
-    const ShoupConst *cst, *cst2;
-    const double *cst_d, *cst2_d;
+    const ShoupConst *cst;
+    const double *cst_d;
     int nl; // output limbs per component (level, or level - 1 when a rescale is folded in)
     int r_stride, out_stride, out_cstride, add_stride, add_cstride;
 };
@@ -186,10 +190,41 @@ __device__ __forceinline__ InnerTile inner_tile(const InnerArgs &ia, const OpArg
     return w;
 }
 
-// The products of one floating-point limb: acc0, acc1 = sums over the digits, within 3.5 q, for this thread's pairs.
+// The pair of NTT-domain indices (pos, pos + 1) of limb a of both components of both factors of a Mult.
+struct TensorPair {
+    u64x2 a0, a1, b0, b1;
+};
+template <int LOGN> __device__ __forceinline__ TensorPair tensor_pair(const InnerArgs &ia, unsigned op, int a, unsigned pos)
+{
+    const size_t c0 = ((size_t)op * ia.t_stride + a) << LOGN, c1 = c0 + ((size_t)ia.level << LOGN);
+    TensorPair p;
+    p.a0 = ld_at<u64x2>(ia.ta + c0, pos * 8u), p.a1 = ld_at<u64x2>(ia.ta + c1, pos * 8u);
+    p.b0 = ld_at<u64x2>(ia.tb + c0, pos * 8u), p.b1 = ld_at<u64x2>(ia.tb + c1, pos * 8u);
+    return p;
+}
+// d2 is returned; d0 P and d1 P are added to the sums.  Floating point: |d2| below 0.9 q, the sums grow by less than 0.9 q.
+__device__ __forceinline__ double tensor_mac(const ArithFp &ar, u64 a0, u64 a1, u64 b0, u64 b1, double P, double &acc0, double &acc1)
+{
+    const double x0 = u2d(a0), x1 = u2d(a1), y0 = u2d(b0), y1 = u2d(b1);
+    acc0 += ar.mulmod(ar.mulmod(x0, y0), P);
+    acc1 += ar.mulmod(ar.mulmod(x0, y1) + ar.mulmod(x1, y0), P);
+    return ar.mulmod(x1, y1);
+}
+__device__ __forceinline__ u64 tensor_mac(const ModConst &m, u64 a0, u64 a1, u64 b0, u64 b1, u64 P, U128 &acc0, U128 &acc1)
+{
+    U128 d1{0, 0};
+    mac128(d1, a0, b1);
+    mac128(d1, a1, b0);
+    mac128(acc0, mul_mod(a0, b0, m), P);
+    mac128(acc1, reduce128(d1, m), P);
+    return mul_mod(a1, b1, m);
+}
+
+// The products of one floating-point limb: acc0, acc1 = sums over the digits, within 3.5 q (MULT: 4.9 q, with d0 and d1), for
+// this thread's pairs.
 // If `then` is not null, the 4 KiB that it points at (this lane's address) are on their way into `pre` when
 // the function returns.
-template <int LOGN>
+template <int LOGN, bool MULT>
 __device__ __forceinline__ void inner_products8(const InnerArgs &ia, const OpArgs &oa, const DevTables &T, const InnerTile &w,
                                                 unsigned mi, const ArithFp &ar, const BlockLane &b, u64 *lds, double *tws, u64 *pre,
                                                 const char *then, double (&acc0)[8], double (&acc1)[8])
@@ -234,7 +269,18 @@ __device__ __forceinline__ void inner_products8(const InnerArgs &ia, const OpArg
         double dv[8];
         f64x2 e0[4], e1[4]; // key words of a floating-point limb are balanced doubles
         const char *kj = key0 + (size_t)j * key_step;
-        if (j == own) {
+        if (MULT && j == own) {
+            const double P = T.dn_pmod_d[a];
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const TensorPair p = tensor_pair<LOGN>(ia, w.op, a, (w.tile << INNER_TLOG) + pair8_at(i));
+                dv[2 * i] = tensor_mac(ar, p.a0.x, p.a1.x, p.b0.x, p.b1.x, P, acc0[2 * i], acc1[2 * i]);
+                dv[2 * i + 1] = tensor_mac(ar, p.a0.y, p.a1.y, p.b0.y, p.b1.y, P, acc0[2 * i + 1], acc1[2 * i + 1]);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+                e0[i] = ld_at<f64x2>(kj + 1024 * i, lane16), e1[i] = ld_at<f64x2>(kj + comp_step + 1024 * i, lane16);
+        } else if (!MULT && j == own) {
             const char *d_limb = (const char *)((ia.per_op && oa.d[w.op] ? oa.d[w.op] : ia.d + (((size_t)w.op * ia.d_stride) << LOGN)) + ((size_t)a << LOGN));
 #pragma unroll
             for (int i = 0; i < 4; i++) {
@@ -288,8 +334,8 @@ __device__ __forceinline__ void inner_products8(const InnerArgs &ia, const OpArg
 
 // Pair h of the product phase (h < 2: pairs 2 h and 2 h + 1) on the integer path: the raised digits arrive finished
 // (NTT domain) and are read through the index map.
-template <int LOGN>
-__device__ __forceinline__ void inner_products_int(const InnerArgs &ia, const OpArgs &oa, const InnerTile &w, unsigned mi,
+template <int LOGN, bool MULT>
+__device__ __forceinline__ void inner_products_int(const InnerArgs &ia, const OpArgs &oa, const DevTables &T, const InnerTile &w, unsigned mi,
                                                    const ModConst &m, int h, u64 (&r0)[4], u64 (&r1)[4])
 {
     const int a = w.a, own = a < ia.level ? a / ia.alpha : -1, M = ia.L + ia.K, Ma = ia.level + ia.K;
@@ -313,9 +359,17 @@ __device__ __forceinline__ void inner_products_int(const InnerArgs &ia, const Op
 #pragma unroll
         for (int i = 0; i < 2; i++) {
             const int ii = 2 * h + i;
-            const u64x2 v = ld_at<u64x2>(dj, (sr[i] & ~1u) * 8u);
-            const bool sw = sr[i] & 1u;
-            const u64 x = sw ? v.y : v.x, y = sw ? v.x : v.y;
+            u64 x, y;
+            if (MULT && j == own) {
+                const TensorPair p = tensor_pair<LOGN>(ia, w.op, a, sr[i]); // g = 1: the pair itself
+                const u64 P = T.dn_pmod[a];
+                x = tensor_mac(m, p.a0.x, p.a1.x, p.b0.x, p.b1.x, P, acc0[2 * i], acc1[2 * i]);
+                y = tensor_mac(m, p.a0.y, p.a1.y, p.b0.y, p.b1.y, P, acc0[2 * i + 1], acc1[2 * i + 1]);
+            } else {
+                const u64x2 v = ld_at<u64x2>(dj, (sr[i] & ~1u) * 8u);
+                const bool sw = sr[i] & 1u;
+                x = sw ? v.y : v.x, y = sw ? v.x : v.y;
+            }
             const u64x2 ka = ld_at<u64x2>(kj + 1024 * ii, lane16), kb = ld_at<u64x2>(kj + comp_step + 1024 * ii, lane16);
             mac128(acc0[2 * i], x, ka.x);
             mac128(acc0[2 * i + 1], y, ka.y);
@@ -424,7 +478,18 @@ __device__ __forceinline__ void special_products(const InnerArgs &ia, const OpAr
 #pragma unroll
             for (int i = 0; i < 2; i++) {
                 u64 x, y;
-                if (j == own) {
+                if (j == own && ia.ta) { // g = 1: the pair itself
+                    const TensorPair p = tensor_pair<LOGN>(ia, op, a, sr[i]);
+                    if constexpr (A::IS_FP) {
+                        const double P = T.dn_pmod_d[a];
+                        x = ar.store_final(tensor_mac(ar, p.a0.x, p.a1.x, p.b0.x, p.b1.x, P, f0[2 * i], f1[2 * i]));
+                        y = ar.store_final(tensor_mac(ar, p.a0.y, p.a1.y, p.b0.y, p.b1.y, P, f0[2 * i + 1], f1[2 * i + 1]));
+                    } else {
+                        const u64 P = T.dn_pmod[a];
+                        x = tensor_mac(m, p.a0.x, p.a1.x, p.b0.x, p.b1.x, P, s0[2 * i], s1[2 * i]);
+                        y = tensor_mac(m, p.a0.y, p.a1.y, p.b0.y, p.b1.y, P, s0[2 * i + 1], s1[2 * i + 1]);
+                    }
+                } else if (j == own) {
                     const u64x2 v = ld_at<u64x2>(d_limb, (sr[i] & ~1u) * 8u);
                     x = sr[i] & 1u ? v.y : v.x, y = sr[i] & 1u ? v.x : v.y;
                 } else
@@ -521,16 +586,17 @@ template <int LOGN> __global__ __launch_bounds__(SPECIAL_THREADS, 3) void k_inne
 
 // ---- second launch: the ciphertext limbs ------------------------------------------------------------------------------------
 
-// Addend of pair i of component c, as canonical residues.
+// Addend of pair i of component c of a rotation, as canonical residues.
 template <int LOGN, int MODE>
 __device__ __forceinline__ u64x2 fin_addend(const FinishArgs &fa, const OpArgs &oa, const InnerArgs &ia, const InnerTile &w, int c,
                                             int i, u64 q)
 {
+    u64x2 v = {0, 0};
+    if (MODE == FIN_MULT) return v;
     const u64 *add = ia.per_op && oa.add[w.op] ? oa.add[w.op] : fa.add + (((size_t)w.op * fa.add_stride) << LOGN);
     const unsigned pos = (w.tile << INNER_TLOG) + pair8_at(i);
-    u64x2 v = {0, 0};
-    if (MODE != FIN_ROT) v = ld_at<u64x2>(add + (((size_t)c * fa.add_cstride + w.a) << LOGN), pos * 8u);
-    if (MODE != FIN_ADD && c == 0) {
+    if (MODE == FIN_ROTSUM) v = ld_at<u64x2>(add + (((size_t)c * fa.add_cstride + w.a) << LOGN), pos * 8u);
+    if (c == 0) {
         const unsigned sr = w.g == 1 ? pos : galois_index(pos, w.g, LOGN);
         u64x2 s = ld_at<u64x2>(add + ((size_t)w.a << LOGN), (sr & ~1u) * 8u);
         if (sr & 1u) s = u64x2{s.y, s.x};
@@ -557,12 +623,11 @@ __global__ __launch_bounds__(INNER_THREADS, INT ? 4 : 6) void k_inner_fin(InnerA
     const unsigned out_cstride = ia.per_op && oa.level[w.op] ? oa.level[w.op] : (unsigned)fa.out_cstride;
     char *o = (char *)((ia.per_op ? oa.out[w.op] : fa.out + (((size_t)w.op * fa.out_stride) << LOGN)) + (((size_t)w.a << LOGN) + ((size_t)w.grp << WAVE_LOG)));
     const size_t o_step = ((size_t)out_cstride << LOGN) * 8;
-    const bool scaled = MODE == FIN_ADD && fa.cst2 != nullptr;
     if constexpr (INT) {
 #pragma unroll
         for (int h = 0; h < 2; h++) {
             u64 x[2][4];
-            inner_products_int<LOGN>(ia, oa, w, w.a, m, h, x[0], x[1]);
+            inner_products_int<LOGN, MODE == FIN_MULT>(ia, oa, T, w, w.a, m, h, x[0], x[1]);
 #pragma unroll
             for (int c = 0; c < 2; c++)
 #pragma unroll
@@ -573,8 +638,8 @@ __global__ __launch_bounds__(INNER_THREADS, INT ? 4 : 6) void k_inner_fin(InnerA
                     u64x2 res;
                     res.x = mul_shoup(x[c][2 * i] + m.q - rv.x, fa.cst[w.a], m.q);
                     res.y = mul_shoup(x[c][2 * i + 1] + m.q - rv.y, fa.cst[w.a], m.q);
-                    res.x = csub(res.x + (scaled ? mul_shoup(av.x, fa.cst2[w.a], m.q) : av.x), m.q);
-                    res.y = csub(res.y + (scaled ? mul_shoup(av.y, fa.cst2[w.a], m.q) : av.y), m.q);
+                    res.x = csub(res.x + av.x, m.q);
+                    res.y = csub(res.y + av.y, m.q);
                     *(u64x2 *)(o + c * o_step + 1024 * ii + lane16) = res;
                 }
         }
@@ -587,14 +652,14 @@ __global__ __launch_bounds__(INNER_THREADS, INT ? 4 : 6) void k_inner_fin(InnerA
         const BlockLane b = block_lane(lds, tws);
         const char *r_lane = r_grp + lane16;
         double acc[2][8];
-        inner_products8<LOGN>(ia, oa, T, w, w.a, ar, b, lds, tws, pre, r_lane, acc[0], acc[1]);
+        inner_products8<LOGN, MODE == FIN_MULT>(ia, oa, T, w, w.a, ar, b, lds, tws, pre, r_lane, acc[0], acc[1]);
         // the corrections are transformed in the output's own blocks: other twiddles where a rotation maps the group
         // elsewhere (the wave's own reads of the old ones have returned, and what it still has in flight was issued
         // before the last key words and has arrived with them)
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         if (w.grp_in != w.grp)
             wave_copy_4k<false>((const char *)(T.twd_blk + (((size_t)w.a << LOGN) + ((size_t)w.grp << WAVE_LOG))) + lane16, (char *)tws);
-        const double k1 = fa.cst_d[w.a], k2 = scaled ? fa.cst2_d[w.a] : 0.0;
+        const double k1 = fa.cst_d[w.a];
 #pragma unroll
         for (int c = 0; c < 2; c++) {
             double dv[8];
@@ -620,9 +685,8 @@ __global__ __launch_bounds__(INNER_THREADS, INT ? 4 : 6) void k_inner_fin(InnerA
                 u64x2 res;
 #pragma unroll
                 for (int e = 0; e < 2; e++) {
-                    const double ad = u2d(av[i][e]);
-                    const double v = ar.mulmod(acc[c][2 * i + e] - dv[2 * i + e], k1) + (scaled ? ar.mulmod(ad, k2) : ad);
-                    res[e] = fp_canon(v, m.qd, m.qinvd);
+                    const double v = ar.mulmod(acc[c][2 * i + e] - dv[2 * i + e], k1);
+                    res[e] = fp_canon(MODE == FIN_MULT ? v : v + u2d(av[i][e]), m.qd, m.qinvd);
                 }
                 __builtin_nontemporal_store(res, (u64x2 *)(o + c * o_step + 1024 * i + lane16));
             }

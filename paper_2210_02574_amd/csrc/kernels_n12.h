@@ -152,8 +152,9 @@ __global__ __launch_bounds__(N12_THREADS) void k_ntt_fwd12(u64 *data, DevTables 
 }
 
 // grid.x = limbs; in place where src and dst are the same buffer and slots (a work-group has read its limb before it stores)
+// src2: null, or a second factor of the input
 template <int SCALE>
-__global__ __launch_bounds__(N12_THREADS) void k_ntt_inv12(const u64 *src, u64 *dst, DevTables T, LimbBatch lb, ConvArgs cv)
+__global__ __launch_bounds__(N12_THREADS) void k_ntt_inv12(const u64 *src, const u64 *src2, u64 *dst, DevTables T, LimbBatch lb, ConvArgs cv)
 {
     __shared__ u64 lds[N12_LDS];
     const unsigned mi = lb.mod[blockIdx.x], slot = lb.slot[blockIdx.x], blk = threadIdx.x >> 4, il = threadIdx.x & 15;
@@ -165,10 +166,19 @@ __global__ __launch_bounds__(N12_THREADS) void k_ntt_inv12(const u64 *src, u64 *
     ShoupConst ci;
     double cd;
     scale_consts(SCALE, cv, T, mi, slot, ci, cd);
-    if (T.mod[mi].qd != 0.0)
-        inv12(v, limb, make_fp(T, mi, 12, cd), lds);
+    const ModConst m = T.mod[mi];
+    const auto run = [&](auto ar) {
+        if (src2) {
+            const u64 *in2 = src2 + ((size_t)lb.src[blockIdx.x] << 12);
+#pragma unroll
+            for (int k = 0; k < 16; k++) v[k] = mul_residues(v[k], in2[blk * 256 + il + 16 * k], m, ar);
+        }
+        inv12(v, limb, ar, lds);
+    };
+    if (m.qd != 0.0)
+        run(make_fp(T, mi, 12, cd));
     else
-        inv12(v, limb, make_int(T, mi, 12, ci), lds);
+        run(make_int(T, mi, 12, ci));
 }
 
 // What a work-group of the inner product works on: component c of active limb a of operation op.
@@ -187,10 +197,21 @@ __device__ __forceinline__ Inner12 inner12_of(const InnerArgs &ia, const OpArgs 
     w.none = w.a < ia.level && w.a >= w.level; // an operation below the layout's level
     return w;
 }
-// u at elements 16 k + il of block blk, k < 16: on the floating-point path within 3.5 q of zero (not canonical), as a
+// Element n of d2 (g = 1) and of the component's d0 or d1 for Mult, canonical residues.
+template <class A>
+__device__ __forceinline__ void tensor12(const InnerArgs &ia, const Inner12 &w, unsigned n, const ModConst &m, const A &ar, u64 &d, u64 &d2)
+{
+    const size_t c0 = (((size_t)w.op * ia.t_stride + w.a) << 12) + n, c1 = c0 + ((size_t)ia.level << 12);
+    d2 = mul_residues(ia.ta[c1], ia.tb[c1], m, ar);
+    if (w.c == 0)
+        d = mul_residues(ia.ta[c0], ia.tb[c0], m, ar);
+    else
+        d = csub(mul_residues(ia.ta[c0], ia.tb[c1], m, ar) + mul_residues(ia.ta[c1], ia.tb[c0], m, ar), m.q);
+}
+// u at elements 16 k + il of block blk, k < 16, for Mult with P times d0 or d1: on the floating-point path within 4.3 q of zero (not canonical), as a
 // double; canonical residues on the integer path.
 template <class A>
-__device__ __forceinline__ void inner12(typename A::V (&r)[16], const InnerArgs &ia, const OpArgs &oa, const Inner12 &w, unsigned mi,
+__device__ __forceinline__ void inner12(typename A::V (&r)[16], const InnerArgs &ia, const OpArgs &oa, const DevTables &T, const Inner12 &w, unsigned mi,
                                         const A &ar, const ModConst &m)
 {
     const unsigned blk = threadIdx.x >> 4, il = threadIdx.x & 15, n0 = blk * 256 + il;
@@ -208,7 +229,18 @@ __device__ __forceinline__ void inner12(typename A::V (&r)[16], const InnerArgs 
             const u64 *dj = j == own ? d_limb : dig0 + (((size_t)j * Ma) << 12), *kj = key0 + (((size_t)j * 2 * M) << 12);
             u64 x[16], e[16];
 #pragma unroll
-            for (int k = 0; k < 16; k++) x[k] = dj[sr[k]], e[k] = kj[n0 + 16 * k];
+            for (int k = 0; k < 16; k++) e[k] = kj[n0 + 16 * k];
+            if (j == own && ia.ta) {
+#pragma unroll
+                for (int k = 0; k < 16; k++) {
+                    u64 d;
+                    tensor12(ia, w, n0 + 16 * k, m, ar, d, x[k]);
+                    r[k] += ar.mulmod(u2d(d), T.dn_pmod_d[w.a]);
+                }
+            } else {
+#pragma unroll
+                for (int k = 0; k < 16; k++) x[k] = dj[sr[k]];
+            }
 #pragma unroll
             for (int k = 0; k < 16; k++) r[k] += ar.mulmod(u2d(x[k]), ar.load_mid(e[k])); // key words are balanced doubles
             if ((j & 3) == 3) {
@@ -223,7 +255,16 @@ __device__ __forceinline__ void inner12(typename A::V (&r)[16], const InnerArgs 
         for (int j = 0; j < w.beta; j++) {
             const u64 *dj = j == own ? d_limb : dig0 + (((size_t)j * Ma) << 12), *kj = key0 + (((size_t)j * 2 * M) << 12);
 #pragma unroll
-            for (int k = 0; k < 16; k++) mac128(acc[k], dj[sr[k]], kj[n0 + 16 * k]);
+            for (int k = 0; k < 16; k++) {
+                u64 x;
+                if (j == own && ia.ta) {
+                    u64 d;
+                    tensor12(ia, w, n0 + 16 * k, m, ar, d, x);
+                    mac128(acc[k], d, T.dn_pmod[w.a]);
+                } else
+                    x = dj[sr[k]];
+                mac128(acc[k], x, kj[n0 + 16 * k]);
+            }
         }
 #pragma unroll
         for (int k = 0; k < 16; k++) r[k] = reduce128(acc[k], m);
@@ -247,13 +288,13 @@ __global__ __launch_bounds__(N12_THREADS) void k_inner12(InnerArgs ia, DevTables
     if (m.qd != 0.0) {
         const ArithFp ar = make_fp(T, mi, 12, special ? T.dn_inv_d[k_sp] : 0.0);
         double r[16];
-        inner12(r, ia, oa, w, mi, ar, m);
+        inner12(r, ia, oa, T, w, mi, ar, m);
 #pragma unroll
         for (int k = 0; k < 16; k++) v[k] = fp_canon(r[k], m.qd, m.qinvd);
         if (special) inv12(v, limb, ar, lds);
     } else {
         const ArithInt ar = make_int(T, mi, 12, special ? T.dn_inv[k_sp] : ShoupConst{0, 0});
-        inner12(v, ia, oa, w, mi, ar, m);
+        inner12(v, ia, oa, T, w, mi, ar, m);
         if (special) inv12(v, limb, ar, lds);
     }
     if (!special) {
@@ -277,17 +318,19 @@ __global__ __launch_bounds__(N12_THREADS) void k_fin12(InnerArgs ia, FinishArgs 
     const ConvSetup<NSMAX> S = conv_setup<PRO, NSMAX, 12>(cv, T, slot, w.a);
     // u and the addends (canonical residues) are on their way while the corrections are transformed
     const u64 *u = ia.u + (((size_t)w.op * ia.u_stride + (size_t)w.c * (ia.level + ia.K) + w.a) << 12);
-    const u64 *add = ia.per_op && oa.add[w.op] ? oa.add[w.op] : fa.add + (((size_t)w.op * fa.add_stride) << 12);
-    const u64 *add_same = add + (((size_t)w.c * fa.add_cstride + w.a) << 12), *add_rot = add + ((size_t)w.a << 12);
     u64 uv[16], v[16];
 #pragma unroll
-    for (int k = 0; k < 16; k++) {
-        const unsigned n = n0 + 16 * k;
-        uv[k] = u[n];
-        v[k] = mode != FIN_ROT ? add_same[n] : 0;
-        if (mode != FIN_ADD && w.c == 0) v[k] = csub(v[k] + add_rot[w.g == 1 ? n : galois_index(n, w.g, 12)], m.q);
+    for (int k = 0; k < 16; k++) uv[k] = u[n0 + 16 * k], v[k] = 0;
+    if (mode != FIN_MULT) {
+        const u64 *add = ia.per_op && oa.add[w.op] ? oa.add[w.op] : fa.add + (((size_t)w.op * fa.add_stride) << 12);
+        const u64 *add_same = add + (((size_t)w.c * fa.add_cstride + w.a) << 12), *add_rot = add + ((size_t)w.a << 12);
+#pragma unroll
+        for (int k = 0; k < 16; k++) {
+            const unsigned n = n0 + 16 * k;
+            if (mode == FIN_ROTSUM) v[k] = add_same[n];
+            if (w.c == 0) v[k] = csub(v[k] + add_rot[w.g == 1 ? n : galois_index(n, w.g, 12)], m.q);
+        }
     }
-    const bool scaled = mode == FIN_ADD && fa.cst2 != nullptr;
     conv_variant12<PRO, NSMAX, EX>(T, w.a, m, S.qld, [&](auto ar, auto split, auto tint) {
         typedef decltype(ar) A;
         typename A::V a[16];
@@ -298,13 +341,10 @@ __global__ __launch_bounds__(N12_THREADS) void k_fin12(InnerArgs ia, FinishArgs 
         for (int k = 0; k < 16; k++) {
             const u64 rv = lds[tile_at(blk, il + 16 * k)];
             if constexpr (A::IS_FP) {
-                const double ad = u2d(v[k]), k2 = scaled ? fa.cst2_d[w.a] : 0.0;
-                const double x = ar.mulmod(u2d(uv[k]) - u2d(rv), fa.cst_d[w.a]) + (scaled ? ar.mulmod(ad, k2) : ad);
+                const double x = ar.mulmod(u2d(uv[k]) - u2d(rv), fa.cst_d[w.a]) + u2d(v[k]);
                 v[k] = fp_canon(x, m.qd, m.qinvd);
-            } else {
-                const u64 x = mul_shoup(uv[k] + m.q - rv, fa.cst[w.a], m.q);
-                v[k] = csub(x + (scaled ? mul_shoup(v[k], fa.cst2[w.a], m.q) : v[k]), m.q);
-            }
+            } else
+                v[k] = csub(mul_shoup(uv[k] + m.q - rv, fa.cst[w.a], m.q) + v[k], m.q);
         }
         if constexpr (DROP)
             inv12(v, const_cast<u64 *>(fa.r) + ((size_t)slot << 12), ar, lds);

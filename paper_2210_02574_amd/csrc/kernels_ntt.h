@@ -413,8 +413,16 @@ __device__ __forceinline__ void fwd_blocks_body(u64 *__restrict__ limb, const A 
     }
 }
 
-template <int LOGN, class A>
-__device__ __forceinline__ void inv_blocks_body(const u64 *in, u64 *limb, const A &ar,
+// Product of two residues, canonical.
+__device__ __forceinline__ u64 mul_residues(u64 x, u64 y, const ModConst &m, const ArithFp &)
+{
+    return fp_canon(fp_mulmod(u2d(x), u2d(y), m.qd, m.qinvd), m.qd, m.qinvd);
+}
+__device__ __forceinline__ u64 mul_residues(u64 x, u64 y, const ModConst &m, const ArithInt &) { return mul_mod(x, y, m); }
+
+// PROD: the input is the product of `in` and `in2` (d2 = a1 b1 of a Mult, which is stored nowhere)
+template <int LOGN, bool PROD, class A>
+__device__ __forceinline__ void inv_blocks_body(const u64 *in, const u64 *in2, u64 *limb, const ModConst &m, const A &ar,
                                                 u64 *lds, unsigned tile)
 {
     // out of place: part of a conversion, whose batch is far larger than the caches; in place (a plain inverse
@@ -425,8 +433,9 @@ __device__ __forceinline__ void inv_blocks_body(const u64 *in, u64 *limb, const 
     typename A::V a[16];
 #pragma unroll
     for (int k = 0; k < 16; k++) {
-        const u64 *src = in + bg * 256 + il + 16 * k;
-        lds[tile_at(blk, il + 16 * k)] = __builtin_nontemporal_load(src); // read once
+        const unsigned pos = bg * 256 + il + 16 * k;
+        const u64 x = __builtin_nontemporal_load(in + pos); // read once
+        lds[tile_at(blk, il + 16 * k)] = PROD ? mul_residues(x, __builtin_nontemporal_load(in2 + pos), m, ar) : x;
     }
     block_sync();
 #pragma unroll
@@ -464,20 +473,22 @@ __global__ __launch_bounds__(BLK_THREADS, EPI == EPI_FIN ? 4 : 1) void k_ntt_fwd
         fwd_blocks_body<LOGN, EPI>(limb, make_int(T, mi, LOGN), lds, tile, fa, T, slot);
 }
 
-template <int LOGN>
-__global__ __launch_bounds__(BLK_THREADS) void k_ntt_inv_blocks(const u64 *src, u64 *dst,
+// src2: with PROD, the second factor, at the same limbs as src
+template <int LOGN, bool PROD>
+__global__ __launch_bounds__(BLK_THREADS) void k_ntt_inv_blocks(const u64 *src, const u64 *src2, u64 *dst,
                                                         DevTables T, LimbBatch lb)
 {
     __shared__ u64 lds[BLK_PER_WG * TILE_GROUP];
     constexpr unsigned TILES = (1u << LOGN) / (256 * BLK_PER_WG);
     const unsigned tile = blockIdx.x % TILES, b = blockIdx.x / TILES;
     const unsigned mi = lb.mod[b];
-    const u64 *in = src + ((size_t)lb.src[b] << LOGN);
+    const ModConst m = T.mod[mi];
+    const u64 *in = src + ((size_t)lb.src[b] << LOGN), *in2 = PROD ? src2 + ((size_t)lb.src[b] << LOGN) : nullptr;
     u64 *limb = dst + ((size_t)lb.slot[b] << LOGN);
-    if (T.mod[mi].qd != 0.0)
-        inv_blocks_body<LOGN>(in, limb, make_fp(T, mi, LOGN), lds, tile);
+    if (m.qd != 0.0)
+        inv_blocks_body<LOGN, PROD>(in, in2, limb, m, make_fp(T, mi, LOGN), lds, tile);
     else
-        inv_blocks_body<LOGN>(in, limb, make_int(T, mi, LOGN), lds, tile);
+        inv_blocks_body<LOGN, PROD>(in, in2, limb, m, make_int(T, mi, LOGN), lds, tile);
 }
 
 // ---- column pass, N = 2^16 and 2^17: all rows x 16 columns per work-group (element (r, c) at r*256 + c) ---------

@@ -13,7 +13,7 @@
 enum KernelId {
     KID_FWD_COLS, KID_FWD_COLS_MODUP, KID_FWD_COLS_MODDOWN, KID_FWD_COLS_RESCALE, KID_FWD_COLS_MODDOWN_RS, KID_FWD_BLOCKS,
     KID_FWD_BLOCKS_FIN,
-    KID_INV_BLOCKS, KID_INV_COLS, KID_LIMBWISE, KID_CMULT, KID_TENSOR, KID_INNER, KID_INNER_FIN, KID_COUNT
+    KID_INV_BLOCKS, KID_INV_COLS, KID_LIMBWISE, KID_CMULT, KID_INNER, KID_INNER_FIN, KID_COUNT
 };
 
 // Creates the event pair of one profiled launch and appends it to the context's record list.
@@ -42,7 +42,7 @@ struct DevLaunch {
     // share in the corrections; drop: of the dropped limb alone, into fa.r).
     void (*fwd_limb[5])(he_ctx *c, hipStream_t st, int kid, double bytes, bool wide, u64 *data, const LimbBatch &lb, int nb,
                         const ConvArgs &cv, const FinArgs *fin);
-    void (*inv_limb)(he_ctx *c, hipStream_t st, double bytes, int scale, const u64 *src, u64 *dst, const LimbBatch &lb, int nb,
+    void (*inv_limb)(he_ctx *c, hipStream_t st, double bytes, int scale, const u64 *src, const u64 *src2, u64 *dst, const LimbBatch &lb, int nb,
                      const ConvArgs &cv);
     void (*inner_limb)(he_ctx *c, hipStream_t st, double bytes, const InnerArgs &ia, const OpArgs &oa);
     void (*fin_limb)(he_ctx *c, hipStream_t st, double bytes, bool wide, int pro, bool drop, int mode, const InnerArgs &ia,
@@ -56,7 +56,8 @@ struct DevLaunch {
     // forward block pass of the first nb limbs of lb; fin: with the finishing epilogue
     void (*fwd_blocks)(he_ctx *c, hipStream_t st, double bytes, bool fin, u64 *data, const LimbBatch &lb, int nb,
                        const FinArgs &fa);
-    void (*inv_blocks)(he_ctx *c, hipStream_t st, double bytes, const u64 *src, u64 *dst, const LimbBatch &lb, int nb);
+    // src2: null, or a second factor of the transform's input
+    void (*inv_blocks)(he_ctx *c, hipStream_t st, double bytes, const u64 *src, const u64 *src2, u64 *dst, const LimbBatch &lb, int nb);
     void (*inv_cols)(he_ctx *c, hipStream_t st, double bytes, int scale, u64 *dst, const LimbBatch &lb, int nb,
                      const ConvArgs &cv);
     // inner product on the limbs ia.first .. level + K - 1, and the finishing one on the first fa.nl limbs: those on the
@@ -98,9 +99,13 @@ static void launch_fwd_blocks(he_ctx *c, hipStream_t st, double bytes, bool fin,
                   c->dev, lb, fa);
 }
 template <int LOGN>
-static void launch_inv_blocks(he_ctx *c, hipStream_t st, double bytes, const u64 *src, u64 *dst, const LimbBatch &lb, int nb)
+static void launch_inv_blocks(he_ctx *c, hipStream_t st, double bytes, const u64 *src, const u64 *src2, u64 *dst,
+                              const LimbBatch &lb, int nb)
 {
-    KLAUNCH_T(c, st, KID_INV_BLOCKS, bytes, (k_ntt_inv_blocks<LOGN>), BLK_TILES(c) * nb, BLK_THREADS, src, dst, c->dev, lb);
+    if (src2)
+        KLAUNCH_T(c, st, KID_INV_BLOCKS, bytes, (k_ntt_inv_blocks<LOGN, true>), BLK_TILES(c) * nb, BLK_THREADS, src, src2, dst, c->dev, lb);
+    else
+        KLAUNCH_T(c, st, KID_INV_BLOCKS, bytes, (k_ntt_inv_blocks<LOGN, false>), BLK_TILES(c) * nb, BLK_THREADS, src, src2, dst, c->dev, lb);
 }
 template <int LOGN>
 static void launch_inner(he_ctx *c, hipStream_t st, double bytes, unsigned grid, const InnerArgs &ia, const OpArgs &oa)
@@ -120,8 +125,8 @@ template <int LOGN>
 static void launch_inner_fin(he_ctx *c, hipStream_t st, double bytes, unsigned grid, int mode, bool integer, const InnerArgs &ia,
                              const FinishArgs &fa, const OpArgs &oa)
 {
-    if (mode == FIN_ADD)
-        launch_inner_fin_mode<LOGN, FIN_ADD>(c, st, bytes, grid, integer, ia, fa, oa);
+    if (mode == FIN_MULT)
+        launch_inner_fin_mode<LOGN, FIN_MULT>(c, st, bytes, grid, integer, ia, fa, oa);
     else if (mode == FIN_ROT)
         launch_inner_fin_mode<LOGN, FIN_ROT>(c, st, bytes, grid, integer, ia, fa, oa);
     else
