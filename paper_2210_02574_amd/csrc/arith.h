@@ -241,6 +241,27 @@ struct ArithFp {
             }
         }
     }
+    // Three inverse stages on 8 elements (pairs 1, 2, 4 apart), tw as for fwd8_with; sums are reduced at the second and
+    // third stage.  From |v| <= 1.6q it stays below 6.4q and ends below 1.6q.
+    template <bool LAST, class F> __device__ __forceinline__ void inv8_with(V (&a)[8], F tw) const
+    {
+#pragma unroll
+        for (int sp = 2; sp >= 0; sp--) {
+            const int dist = 4 >> sp;
+#pragma unroll
+            for (int g = 0; g < (1 << sp); g++) {
+                const bool fin = LAST && sp == 0;
+                const double w = fin ? n1 : tw(sp, g);
+#pragma unroll
+                for (int e = 0; e < dist; e++) {
+                    const int k0 = g * 2 * dist + e, k1 = k0 + dist;
+                    const double u = a[k0], v = a[k1], t = u + v;
+                    a[k0] = fin ? mulmod(t, n0) : sp < 2 ? reduce(t) : t;
+                    a[k1] = mulmod(u - v, w);
+                }
+            }
+        }
+    }
     // Stage 0 of a 32-element column step (N = 2^17): pairs (lo[k], hi[k]) are N/2 apart, twiddle index 1.
     // Forward: inputs within 1q of zero (reduced or canonical).  Inverse: last stage, with the 1/N factors.
     __device__ __forceinline__ void fwd_stage0(V (&lo)[16], V (&hi)[16], bool reduce_first) const
@@ -296,6 +317,39 @@ struct ArithInt {
     __device__ __forceinline__ void fwd16(V (&a)[16], unsigned s_base, unsigned G, bool reduce_first) const
     {
         fwd16_with(a, reduce_first, [&](int c) { return twf[step16_twiddle(s_base, G, (unsigned)c)]; });
+    }
+    // the steps of 8 elements, as in ArithFp
+    template <class F> __device__ __forceinline__ void fwd8_with(V (&a)[8], bool, F tw) const
+    {
+#pragma unroll
+        for (int sp = 0; sp < 3; sp++) {
+            const int dist = 4 >> sp;
+#pragma unroll
+            for (int g = 0; g < (1 << sp); g++) {
+                const ShoupConst w = tw(sp, g);
+#pragma unroll
+                for (int e = 0; e < dist; e++) fwd_bfly(a[g * 2 * dist + e], a[g * 2 * dist + e + dist], w);
+            }
+        }
+    }
+    template <bool LAST, class F> __device__ __forceinline__ void inv8_with(V (&a)[8], F tw) const
+    {
+#pragma unroll
+        for (int sp = 2; sp >= 0; sp--) {
+            const int dist = 4 >> sp;
+#pragma unroll
+            for (int g = 0; g < (1 << sp); g++) {
+                const bool fin = LAST && sp == 0;
+                const ShoupConst w = fin ? n1 : tw(sp, g);
+#pragma unroll
+                for (int e = 0; e < dist; e++) {
+                    const int k0 = g * 2 * dist + e, k1 = k0 + dist;
+                    const u64 u = a[k0], v = a[k1];
+                    a[k0] = fin ? mul_shoup_sloppy(u + v, n0, nq) : csub_neg(u + v, nq4);
+                    a[k1] = mul_shoup_sloppy(u - v + q4, w, nq);
+                }
+            }
+        }
     }
     template <class F> __device__ __forceinline__ void fwd16_with(V (&a)[16], bool, F tw) const
     {

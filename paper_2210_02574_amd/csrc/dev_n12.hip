@@ -8,11 +8,11 @@ static void launch_fwd12(he_ctx *c, hipStream_t st, int kid, double bytes, u64 *
 {
     if constexpr (PRO == PRO_RESCALE) { // the one prologue that the finishing epilogue follows here
         if (fin) {
-            KLAUNCH(c, st, kid, bytes, (k_ntt_fwd12<PRO, NSMAX, EX, EPI_FIN>), nb, data, c->dev, lb, cv, *fin);
+            KLAUNCH_T(c, st, kid, bytes, (k_ntt_fwd12<PRO, NSMAX, EX, EPI_FIN>), nb, N12_THREADS, data, c->dev, lb, cv, *fin);
             return;
         }
     }
-    KLAUNCH(c, st, kid, bytes, (k_ntt_fwd12<PRO, NSMAX, EX, EPI_STORE>), nb, data, c->dev, lb, cv, FinArgs{});
+    KLAUNCH_T(c, st, kid, bytes, (k_ntt_fwd12<PRO, NSMAX, EX, EPI_STORE>), nb, N12_THREADS, data, c->dev, lb, cv, FinArgs{});
 }
 template <int PRO>
 static void fwd12(he_ctx *c, hipStream_t st, int kid, double bytes, bool wide, u64 *data, const LimbBatch &lb, int nb,
@@ -30,13 +30,13 @@ static void inv12(he_ctx *c, hipStream_t st, double bytes, int scale, const u64 
                   const ConvArgs &cv)
 {
     switch (scale) { // special limbs are scaled where they are produced
-    case SCALE_NONE: KLAUNCH(c, st, KID_INV_COLS, bytes, (k_ntt_inv12<SCALE_NONE>), nb, src, src2, dst, c->dev, lb, cv); break;
-    default: KLAUNCH(c, st, KID_INV_COLS, bytes, (k_ntt_inv12<SCALE_MODUP>), nb, src, src2, dst, c->dev, lb, cv); break;
+    case SCALE_NONE: KLAUNCH_T(c, st, KID_INV_COLS, bytes, (k_ntt_inv12<SCALE_NONE>), nb, N12_THREADS, src, src2, dst, c->dev, lb, cv); break;
+    default: KLAUNCH_T(c, st, KID_INV_COLS, bytes, (k_ntt_inv12<SCALE_MODUP>), nb, N12_THREADS, src, src2, dst, c->dev, lb, cv); break;
     }
 }
 static void inner12(he_ctx *c, hipStream_t st, double bytes, const InnerArgs &ia, const OpArgs &oa)
 {
-    KLAUNCH(c, st, KID_INNER, bytes, (k_inner12), dim3(ia.level + ia.K, 2, ia.count), ia, c->dev, oa);
+    KLAUNCH_T(c, st, KID_INNER, bytes, (k_inner12), dim3(ia.level + ia.K, 2, ia.count), N12_THREADS, ia, c->dev, oa);
 }
 template <int PRO, bool DROP>
 static void launch_fin12(he_ctx *c, hipStream_t st, double bytes, bool wide, int mode, const InnerArgs &ia, const FinishArgs &fa,
@@ -45,14 +45,14 @@ static void launch_fin12(he_ctx *c, hipStream_t st, double bytes, bool wide, int
     const dim3 grid(DROP ? 1 : fa.nl, 2, ia.count);
     if (cv.exact) {
         if (wide)
-            KLAUNCH(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 8, true, DROP>), grid, ia, fa, c->dev, oa, cv, mode);
+            KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 8, true, DROP>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
         else
-            KLAUNCH(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 4, true, DROP>), grid, ia, fa, c->dev, oa, cv, mode);
+            KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 4, true, DROP>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
     } else {
         if (wide)
-            KLAUNCH(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 8, false, DROP>), grid, ia, fa, c->dev, oa, cv, mode);
+            KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 8, false, DROP>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
         else
-            KLAUNCH(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 4, false, DROP>), grid, ia, fa, c->dev, oa, cv, mode);
+            KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 4, false, DROP>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
     }
 }
 static void fin12(he_ctx *c, hipStream_t st, double bytes, bool wide, int pro, bool drop, int mode, const InnerArgs &ia,

@@ -1,6 +1,5 @@
-// Kernels of the ring size N = 2^12: a limb is 32 KiB and fits the LDS of one compute unit, so one work-group of 256
-// threads, 16 elements each, runs a whole transform (stages 0-3 with one thread per column of 16 elements, then 4-7 and
-// 8-11 on the blocks of 256), and a key switch is four launches:
+// Kernels of the ring size N = 2^12: a limb is 32 KiB and fits the LDS of one compute unit, so one work-group of 512
+// threads, 8 elements each, runs a whole transform (four steps of three stages), and a key switch is four launches:
 //   1. inverse transform of the input limbs, scaled                                  (k_ntt_inv12<SCALE_MODUP>)
 //   2. ModUp and forward transform of every raised limb                                 (k_ntt_fwd12<PRO_MODUP>)
 //   3. per active limb and component: inner product u, for special limbs its inverse transform, scaled (k_inner12)
@@ -16,73 +15,113 @@
 #pragma once
 #include "kernels_ks.h"
 
-#define N12_THREADS 256
-#define N12_LDS (16 * TILE_GROUP)
+#define N12_THREADS 512
+#define N12_LDS (4096 + 256)
+// Word of element e in LDS: one pad word per 16 keeps the patterns below free of most bank conflicts.
+__device__ __forceinline__ unsigned at12(unsigned e) { return e + (e >> 4); }
+// A thread's elements in step i (stages 3 i .. 3 i + 2): base + k * 2^SH, k < 8, with SH = 9 - 3 i.  From step 1 on the 64
+// lanes of a wave own an aligned group of 512 elements, so that only the exchange behind step 0 crosses waves.
+template <int SH> __device__ __forceinline__ unsigned base12()
+{
+    return (threadIdx.x >> SH) << (SH + 3) | (threadIdx.x & ((1u << SH) - 1u));
+}
+// offset of element k from the base, in LDS words: linear in k but for SH = 3, where every second k passes a pad word
+template <int SH> __device__ __forceinline__ constexpr unsigned step12(int k)
+{
+    return SH >= 4 ? (unsigned)k * ((1u << SH) + (1u << SH >> 4)) : SH == 3 ? 8u * k + (k >> 1) : (unsigned)k;
+}
+// A thread's elements where limbs are read and written in the NTT domain: step 1's.
+#define N12_BASE base12<6>()
 
-// twiddles of the 16-element step that starts at stage s_base in group G
-template <class A> struct Step16 {
-    typename A::W w[15];
-    __device__ __forceinline__ Step16(const typename A::W *tw, unsigned s_base, unsigned G)
+// twiddles of the 8-element step that starts at stage s_base in group G
+template <class A> struct Step8 {
+    typename A::W w[7];
+    __device__ __forceinline__ Step8(const typename A::W *tw, unsigned s_base, unsigned G)
     {
 #pragma unroll
-        for (int c = 0; c < 15; c++) w[c] = tw[step16_twiddle(s_base, G, (unsigned)c)];
+        for (int c = 0; c < 7; c++) w[c] = tw[step16_twiddle(s_base, G, (unsigned)c)];
     }
+    __device__ __forceinline__ typename A::W operator()(int sp, int g) const { return w[(1 << sp) - 1 + g]; }
 };
-
-// Forward transform: a[k] = element 256 k + thread (of the range that fwd16 takes); the canonical result is left in
-// LDS, element e of block b at tile_at(b, e), where the 16 lanes of block b find it after a block_sync.
-template <class A> __device__ __forceinline__ void fwd12(typename A::V (&a)[16], const A &ar, u64 *lds, bool reduce_first)
+template <int SH, class A> __device__ __forceinline__ void put12(const typename A::V (&a)[8], const A &ar, u64 *lds)
 {
-    const unsigned t = threadIdx.x, blk = t >> 4, il = t & 15;
-    const Step16<A> w2(ar.twf, 4, blk);
-    ar.fwd16(a, 0, 0, reduce_first);
+    u64 *p = lds + at12(base12<SH>());
 #pragma unroll
-    for (int k = 0; k < 16; k++) lds[tile_at(k, t)] = ar.store_mid(a[k]);
-    const Step16<A> w3(ar.twf, 8, t);
-    __syncthreads();
+    for (int k = 0; k < 8; k++) p[step12<SH>(k)] = ar.store_mid(a[k]);
+}
+template <int SH, class A> __device__ __forceinline__ void get12(typename A::V (&a)[8], const A &ar, const u64 *lds)
+{
+    const u64 *p = lds + at12(base12<SH>());
 #pragma unroll
-    for (int k = 0; k < 16; k++) a[k] = ar.load_mid(lds[tile_at(blk, il + 16 * k)]);
-    ar.fwd16_with(a, true, [&](int c) { return w2.w[c]; });
-    block_sync();
-#pragma unroll
-    for (int k = 0; k < 16; k++) lds[tile_at(blk, il + 16 * k)] = ar.store_mid(a[k]);
-    block_sync();
-#pragma unroll
-    for (int k = 0; k < 16; k++) a[k] = ar.load_mid(lds[tile_at(blk, 16 * il + k)]);
-    ar.fwd16_with(a, true, [&](int c) { return w3.w[c]; });
-    block_sync();
-#pragma unroll
-    for (int k = 0; k < 16; k++) lds[tile_at(blk, 16 * il + k)] = ar.store_final(a[k]);
+    for (int k = 0; k < 8; k++) a[k] = ar.load_mid(p[step12<SH>(k)]);
 }
 
-// Inverse transform of canonical values v[k] = element 16 k + il of block blk; stores the finished limb.
-template <class A> __device__ __forceinline__ void inv12(const u64 (&v)[16], u64 *limb, const A &ar, u64 *lds)
+// Forward transform: a[k] = element 512 k + thread (of the range that fwd8_with takes); v: the canonical result at
+// elements N12_BASE + 64 k.
+template <class A> __device__ __forceinline__ void fwd12(typename A::V (&a)[8], u64 (&v)[8], const A &ar, u64 *lds, bool reduce_first)
 {
-    const unsigned t = threadIdx.x, blk = t >> 4, il = t & 15;
-    const Step16<A> w3(ar.twi, 8, t), w2(ar.twi, 4, blk);
-    typename A::V a[16];
-#pragma unroll
-    for (int k = 0; k < 16; k++) lds[tile_at(blk, il + 16 * k)] = v[k];
-    block_sync();
-#pragma unroll
-    for (int k = 0; k < 16; k++) a[k] = ar.load(lds[tile_at(blk, 16 * il + k)]);
-    ar.template inv16_with<false>(a, [&](int c) { return w3.w[c]; });
-    block_sync();
-#pragma unroll
-    for (int k = 0; k < 16; k++) lds[tile_at(blk, 16 * il + k)] = ar.store_mid(a[k]);
-    block_sync();
-#pragma unroll
-    for (int k = 0; k < 16; k++) a[k] = ar.load_mid(lds[tile_at(blk, il + 16 * k)]);
-    ar.template inv16_with<false>(a, [&](int c) { return w2.w[c]; });
-    block_sync();
-#pragma unroll
-    for (int k = 0; k < 16; k++) lds[tile_at(blk, il + 16 * k)] = ar.store_mid(a[k]);
+    const unsigned t = threadIdx.x;
+    const Step8<A> w0(ar.twf, 0, 0), w1(ar.twf, 3, t >> 6);
+    ar.fwd8_with(a, reduce_first, w0);
+    put12<9>(a, ar, lds);
+    const Step8<A> w2(ar.twf, 6, t >> 3);
     __syncthreads();
+    get12<6>(a, ar, lds);
+    ar.fwd8_with(a, true, w1);
+    const Step8<A> w3(ar.twf, 9, t);
+    block_sync();
+    put12<6>(a, ar, lds);
+    block_sync();
+    get12<3>(a, ar, lds);
+    ar.fwd8_with(a, true, w2);
+    block_sync();
+    put12<3>(a, ar, lds);
+    block_sync();
+    get12<0>(a, ar, lds);
+    ar.fwd8_with(a, true, w3);
+    block_sync();
+    u64 *p = lds + at12(base12<0>());
 #pragma unroll
-    for (int k = 0; k < 16; k++) a[k] = ar.load_mid(lds[tile_at(k, t)]);
-    ar.template inv16<true>(a, 0, 0);
+    for (int k = 0; k < 8; k++) p[k] = ar.store_final(a[k]);
+    block_sync();
+    const u64 *r = lds + at12(N12_BASE);
 #pragma unroll
-    for (int k = 0; k < 16; k++) limb[k * 256 + t] = ar.store_final(a[k]);
+    for (int k = 0; k < 8; k++) v[k] = r[step12<6>(k)];
+}
+
+// Inverse transform of canonical values v[k] = element N12_BASE + 64 k; stores the finished limb.
+template <class A> __device__ __forceinline__ void inv12(const u64 (&v)[8], u64 *limb, const A &ar, u64 *lds)
+{
+    const unsigned t = threadIdx.x;
+    const Step8<A> w3(ar.twi, 9, t), w2(ar.twi, 6, t >> 3);
+    typename A::V a[8];
+    block_sync(); // the wave has read what it overwrites
+    u64 *p = lds + at12(N12_BASE);
+#pragma unroll
+    for (int k = 0; k < 8; k++) p[step12<6>(k)] = v[k];
+    block_sync();
+    const u64 *r = lds + at12(base12<0>());
+#pragma unroll
+    for (int k = 0; k < 8; k++) a[k] = ar.load(r[k]);
+    ar.template inv8_with<false>(a, w3);
+    const Step8<A> w1(ar.twi, 3, t >> 6), w0(ar.twi, 0, 0);
+    block_sync();
+    put12<0>(a, ar, lds);
+    block_sync();
+    get12<3>(a, ar, lds);
+    ar.template inv8_with<false>(a, w2);
+    block_sync();
+    put12<3>(a, ar, lds);
+    block_sync();
+    get12<6>(a, ar, lds);
+    ar.template inv8_with<false>(a, w1);
+    block_sync();
+    put12<6>(a, ar, lds);
+    __syncthreads();
+    get12<9>(a, ar, lds);
+    ar.template inv8_with<true>(a, w0);
+#pragma unroll
+    for (int k = 0; k < 8; k++) limb[k * 512 + t] = ar.store_final(a[k]);
 }
 
 // Calls f(arithmetic, split, tint) with the variant of the prologue that modulus and tables ask for (split, tint: types
@@ -109,12 +148,12 @@ __device__ __forceinline__ void conv_variant12(const DevTables &T, unsigned mi, 
 
 // Column inputs of the forward transform of the limb at `limb` / of the conversion S.
 template <int PRO, int SPLIT, bool TINT, bool EX, int NSMAX, class A>
-__device__ __forceinline__ void inputs12(typename A::V (&a)[16], const u64 *limb, const A &ar, const ConvSetup<NSMAX> &S,
+__device__ __forceinline__ void inputs12(typename A::V (&a)[8], const u64 *limb, const A &ar, const ConvSetup<NSMAX> &S,
                                          const ModConst &m)
 {
 #pragma unroll
-    for (int k = 0; k < 16; k++) {
-        const unsigned pos = k * 256 + threadIdx.x;
+    for (int k = 0; k < 8; k++) {
+        const unsigned pos = k * 512 + threadIdx.x;
         a[k] = PRO == PRO_LOAD ? ar.load(limb[pos]) : conv_get<PRO, SPLIT, TINT, EX>(S, ar, m, pos);
     }
 }
@@ -124,29 +163,28 @@ template <int PRO, int NSMAX, bool EX, int EPI>
 __global__ __launch_bounds__(N12_THREADS) void k_ntt_fwd12(u64 *data, DevTables T, LimbBatch lb, ConvArgs cv, FinArgs fa)
 {
     __shared__ u64 lds[N12_LDS];
-    const unsigned mi = lb.mod[blockIdx.x], slot = lb.slot[blockIdx.x], blk = threadIdx.x >> 4, il = threadIdx.x & 15;
+    const unsigned mi = lb.mod[blockIdx.x], slot = lb.slot[blockIdx.x], nb = N12_BASE;
     u64 *limb = data + ((size_t)slot << 12);
     const ModConst m = T.mod[mi];
     const ConvSetup<NSMAX> S = conv_setup<PRO, NSMAX, 12>(cv, T, slot, mi);
-    FinOperands fo[EPI == EPI_FIN ? 16 : 1];
+    FinOperands fo[EPI == EPI_FIN ? 8 : 1];
     if (EPI == EPI_FIN) {
 #pragma unroll
-        for (int k = 0; k < 16; k++) fo[k] = fin_load<12>(fa, slot, blk * 256 + il + 16 * k);
+        for (int k = 0; k < 8; k++) fo[k] = fin_load<12>(fa, slot, nb + 64 * k);
     }
     conv_variant12<PRO, NSMAX, EX>(T, mi, m, S.qld, [&](auto ar, auto split, auto tint) {
         typedef decltype(ar) A;
-        typename A::V a[16];
+        typename A::V a[8];
         inputs12<PRO, decltype(split)::value, decltype(tint)::value, EX>(a, limb, ar, S, m);
-        fwd12(a, ar, lds, PRO != PRO_LOAD);
-        block_sync();
+        u64 v[8];
+        fwd12(a, v, ar, lds, PRO != PRO_LOAD);
 #pragma unroll
-        for (int k = 0; k < 16; k++) {
-            const unsigned pos = blk * 256 + il + 16 * k;
-            const u64 v = lds[tile_at(blk, il + 16 * k)];
+        for (int k = 0; k < 8; k++) {
+            const unsigned pos = nb + 64 * k;
             if (EPI == EPI_FIN)
-                fin_store<12, A::IS_FP>(fa, T, slot, pos, v, fo[k]);
+                fin_store<12, A::IS_FP>(fa, T, slot, pos, v[k], fo[k]);
             else
-                limb[pos] = v;
+                limb[pos] = v[k];
         }
     });
 }
@@ -157,12 +195,12 @@ template <int SCALE>
 __global__ __launch_bounds__(N12_THREADS) void k_ntt_inv12(const u64 *src, const u64 *src2, u64 *dst, DevTables T, LimbBatch lb, ConvArgs cv)
 {
     __shared__ u64 lds[N12_LDS];
-    const unsigned mi = lb.mod[blockIdx.x], slot = lb.slot[blockIdx.x], blk = threadIdx.x >> 4, il = threadIdx.x & 15;
+    const unsigned mi = lb.mod[blockIdx.x], slot = lb.slot[blockIdx.x], nb = N12_BASE;
     const u64 *in = src + ((size_t)lb.src[blockIdx.x] << 12);
     u64 *limb = dst + ((size_t)slot << 12);
-    u64 v[16];
+    u64 v[8];
 #pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = in[blk * 256 + il + 16 * k];
+    for (int k = 0; k < 8; k++) v[k] = in[nb + 64 * k];
     ShoupConst ci;
     double cd;
     scale_consts(SCALE, cv, T, mi, slot, ci, cd);
@@ -171,7 +209,7 @@ __global__ __launch_bounds__(N12_THREADS) void k_ntt_inv12(const u64 *src, const
         if (src2) {
             const u64 *in2 = src2 + ((size_t)lb.src[blockIdx.x] << 12);
 #pragma unroll
-            for (int k = 0; k < 16; k++) v[k] = mul_residues(v[k], in2[blk * 256 + il + 16 * k], m, ar);
+            for (int k = 0; k < 8; k++) v[k] = mul_residues(v[k], in2[nb + 64 * k], m, ar);
         }
         inv12(v, limb, ar, lds);
     };
@@ -208,66 +246,66 @@ __device__ __forceinline__ void tensor12(const InnerArgs &ia, const Inner12 &w, 
     else
         d = csub(mul_residues(ia.ta[c0], ia.tb[c1], m, ar) + mul_residues(ia.ta[c1], ia.tb[c0], m, ar), m.q);
 }
-// u at elements 16 k + il of block blk, k < 16, for Mult with P times d0 or d1: on the floating-point path within 4.3 q of zero (not canonical), as a
+// u at elements N12_BASE + 64 k, for Mult with P times d0 or d1: on the floating-point path within 4.3 q of zero (not canonical), as a
 // double; canonical residues on the integer path.
 template <class A>
-__device__ __forceinline__ void inner12(typename A::V (&r)[16], const InnerArgs &ia, const OpArgs &oa, const DevTables &T, const Inner12 &w, unsigned mi,
+__device__ __forceinline__ void inner12(typename A::V (&r)[8], const InnerArgs &ia, const OpArgs &oa, const DevTables &T, const Inner12 &w, unsigned mi,
                                         const A &ar, const ModConst &m)
 {
-    const unsigned blk = threadIdx.x >> 4, il = threadIdx.x & 15, n0 = blk * 256 + il;
+    const unsigned nb = N12_BASE;
     const int own = w.a < ia.level ? w.a / ia.alpha : -1, M = ia.L + ia.K, Ma = ia.level + ia.K;
     const u64 *key0 = (ia.per_op ? oa.evk[w.op] : ia.evk) + (((size_t)w.c * M + mi) << 12);
     const u64 *dig0 = ia.raised + (((size_t)w.op * ia.raised_stride + w.a) << 12);
     const u64 *d_limb = (ia.per_op && oa.d[w.op] ? oa.d[w.op] : ia.d + (((size_t)w.op * ia.d_stride) << 12)) + ((size_t)w.a << 12);
-    unsigned sr[16];
+    unsigned sr[8];
 #pragma unroll
-    for (int k = 0; k < 16; k++) sr[k] = w.g == 1 ? n0 + 16 * k : galois_index(n0 + 16 * k, w.g, 12);
+    for (int k = 0; k < 8; k++) sr[k] = w.g == 1 ? nb + 64 * k : galois_index(nb + 64 * k, w.g, 12);
     if constexpr (A::IS_FP) {
 #pragma unroll
-        for (int k = 0; k < 16; k++) r[k] = 0.0;
+        for (int k = 0; k < 8; k++) r[k] = 0.0;
         for (int j = 0; j < w.beta; j++) {
             const u64 *dj = j == own ? d_limb : dig0 + (((size_t)j * Ma) << 12), *kj = key0 + (((size_t)j * 2 * M) << 12);
-            u64 x[16], e[16];
+            u64 x[8], e[8];
 #pragma unroll
-            for (int k = 0; k < 16; k++) e[k] = kj[n0 + 16 * k];
+            for (int k = 0; k < 8; k++) e[k] = kj[nb + 64 * k];
             if (j == own && ia.ta) {
 #pragma unroll
-                for (int k = 0; k < 16; k++) {
+                for (int k = 0; k < 8; k++) {
                     u64 d;
-                    tensor12(ia, w, n0 + 16 * k, m, ar, d, x[k]);
+                    tensor12(ia, w, nb + 64 * k, m, ar, d, x[k]);
                     r[k] += ar.mulmod(u2d(d), T.dn_pmod_d[w.a]);
                 }
             } else {
 #pragma unroll
-                for (int k = 0; k < 16; k++) x[k] = dj[sr[k]];
+                for (int k = 0; k < 8; k++) x[k] = dj[sr[k]];
             }
 #pragma unroll
-            for (int k = 0; k < 16; k++) r[k] += ar.mulmod(u2d(x[k]), ar.load_mid(e[k])); // key words are balanced doubles
+            for (int k = 0; k < 8; k++) r[k] += ar.mulmod(u2d(x[k]), ar.load_mid(e[k])); // key words are balanced doubles
             if ((j & 3) == 3) {
 #pragma unroll
-                for (int k = 0; k < 16; k++) r[k] = ar.reduce(r[k]);
+                for (int k = 0; k < 8; k++) r[k] = ar.reduce(r[k]);
             }
         }
     } else {
-        U128 acc[16];
+        U128 acc[8];
 #pragma unroll
-        for (int k = 0; k < 16; k++) acc[k] = U128{0, 0};
+        for (int k = 0; k < 8; k++) acc[k] = U128{0, 0};
         for (int j = 0; j < w.beta; j++) {
             const u64 *dj = j == own ? d_limb : dig0 + (((size_t)j * Ma) << 12), *kj = key0 + (((size_t)j * 2 * M) << 12);
 #pragma unroll
-            for (int k = 0; k < 16; k++) {
+            for (int k = 0; k < 8; k++) {
                 u64 x;
                 if (j == own && ia.ta) {
                     u64 d;
-                    tensor12(ia, w, n0 + 16 * k, m, ar, d, x);
+                    tensor12(ia, w, nb + 64 * k, m, ar, d, x);
                     mac128(acc[k], d, T.dn_pmod[w.a]);
                 } else
                     x = dj[sr[k]];
-                mac128(acc[k], x, kj[n0 + 16 * k]);
+                mac128(acc[k], x, kj[nb + 64 * k]);
             }
         }
 #pragma unroll
-        for (int k = 0; k < 16; k++) r[k] = reduce128(acc[k], m);
+        for (int k = 0; k < 8; k++) r[k] = reduce128(acc[k], m);
     }
 }
 
@@ -277,20 +315,20 @@ __device__ __forceinline__ void inner12(typename A::V (&r)[16], const InnerArgs 
 __global__ __launch_bounds__(N12_THREADS) void k_inner12(InnerArgs ia, DevTables T, OpArgs oa)
 {
     __shared__ u64 lds[N12_LDS];
-    const unsigned n0 = (threadIdx.x >> 4) * 256 + (threadIdx.x & 15);
+    const unsigned nb = N12_BASE;
     const Inner12 w = inner12_of(ia, oa, (int)blockIdx.x < ia.K ? ia.level + (int)blockIdx.x : (int)blockIdx.x - ia.K);
     if (w.none) return;
     const bool special = w.a >= ia.level;
     const unsigned mi = active_mod(w.a, ia.level, ia.L), k_sp = special ? w.a - ia.level : 0;
     const ModConst m = T.mod[mi];
     u64 *limb = ia.u + (((size_t)w.op * ia.u_stride + (size_t)w.c * (ia.level + ia.K) + w.a) << 12);
-    u64 v[16];
+    u64 v[8];
     if (m.qd != 0.0) {
         const ArithFp ar = make_fp(T, mi, 12, special ? T.dn_inv_d[k_sp] : 0.0);
-        double r[16];
+        double r[8];
         inner12(r, ia, oa, T, w, mi, ar, m);
 #pragma unroll
-        for (int k = 0; k < 16; k++) v[k] = fp_canon(r[k], m.qd, m.qinvd);
+        for (int k = 0; k < 8; k++) v[k] = fp_canon(r[k], m.qd, m.qinvd);
         if (special) inv12(v, limb, ar, lds);
     } else {
         const ArithInt ar = make_int(T, mi, 12, special ? T.dn_inv[k_sp] : ShoupConst{0, 0});
@@ -299,7 +337,7 @@ __global__ __launch_bounds__(N12_THREADS) void k_inner12(InnerArgs ia, DevTables
     }
     if (!special) {
 #pragma unroll
-        for (int k = 0; k < 16; k++) limb[n0 + 16 * k] = v[k];
+        for (int k = 0; k < 8; k++) limb[nb + 64 * k] = v[k];
     }
 }
 
@@ -310,7 +348,7 @@ template <int PRO, int NSMAX, bool EX, bool DROP>
 __global__ __launch_bounds__(N12_THREADS) void k_fin12(InnerArgs ia, FinishArgs fa, DevTables T, OpArgs oa, ConvArgs cv, int mode)
 {
     __shared__ u64 lds[N12_LDS];
-    const unsigned blk = threadIdx.x >> 4, il = threadIdx.x & 15, n0 = blk * 256 + il;
+    const unsigned nb = N12_BASE;
     const Inner12 w = inner12_of(ia, oa, DROP ? ia.level - 1 : (int)blockIdx.x);
     if (w.none) return;
     const ModConst m = T.mod[w.a];
@@ -318,33 +356,32 @@ __global__ __launch_bounds__(N12_THREADS) void k_fin12(InnerArgs ia, FinishArgs 
     const ConvSetup<NSMAX> S = conv_setup<PRO, NSMAX, 12>(cv, T, slot, w.a);
     // u and the addends (canonical residues) are on their way while the corrections are transformed
     const u64 *u = ia.u + (((size_t)w.op * ia.u_stride + (size_t)w.c * (ia.level + ia.K) + w.a) << 12);
-    u64 uv[16], v[16];
+    u64 uv[8], v[8];
 #pragma unroll
-    for (int k = 0; k < 16; k++) uv[k] = u[n0 + 16 * k], v[k] = 0;
+    for (int k = 0; k < 8; k++) uv[k] = u[nb + 64 * k], v[k] = 0;
     if (mode != FIN_MULT) {
         const u64 *add = ia.per_op && oa.add[w.op] ? oa.add[w.op] : fa.add + (((size_t)w.op * fa.add_stride) << 12);
         const u64 *add_same = add + (((size_t)w.c * fa.add_cstride + w.a) << 12), *add_rot = add + ((size_t)w.a << 12);
 #pragma unroll
-        for (int k = 0; k < 16; k++) {
-            const unsigned n = n0 + 16 * k;
+        for (int k = 0; k < 8; k++) {
+            const unsigned n = nb + 64 * k;
             if (mode == FIN_ROTSUM) v[k] = add_same[n];
             if (w.c == 0) v[k] = csub(v[k] + add_rot[w.g == 1 ? n : galois_index(n, w.g, 12)], m.q);
         }
     }
     conv_variant12<PRO, NSMAX, EX>(T, w.a, m, S.qld, [&](auto ar, auto split, auto tint) {
         typedef decltype(ar) A;
-        typename A::V a[16];
+        typename A::V a[8];
         inputs12<PRO, decltype(split)::value, decltype(tint)::value, EX>(a, nullptr, ar, S, m);
-        fwd12(a, ar, lds, true);
-        block_sync();
+        u64 rv[8];
+        fwd12(a, rv, ar, lds, true);
 #pragma unroll
-        for (int k = 0; k < 16; k++) {
-            const u64 rv = lds[tile_at(blk, il + 16 * k)];
+        for (int k = 0; k < 8; k++) {
             if constexpr (A::IS_FP) {
-                const double x = ar.mulmod(u2d(uv[k]) - u2d(rv), fa.cst_d[w.a]) + u2d(v[k]);
+                const double x = ar.mulmod(u2d(uv[k]) - u2d(rv[k]), fa.cst_d[w.a]) + u2d(v[k]);
                 v[k] = fp_canon(x, m.qd, m.qinvd);
             } else
-                v[k] = csub(mul_shoup(uv[k] + m.q - rv, fa.cst[w.a], m.q) + v[k], m.q);
+                v[k] = csub(mul_shoup(uv[k] + m.q - rv[k], fa.cst[w.a], m.q) + v[k], m.q);
         }
         if constexpr (DROP)
             inv12(v, const_cast<u64 *>(fa.r) + ((size_t)slot << 12), ar, lds);
@@ -352,7 +389,7 @@ __global__ __launch_bounds__(N12_THREADS) void k_fin12(InnerArgs ia, FinishArgs 
             const unsigned out_cstride = ia.per_op && oa.level[w.op] ? oa.level[w.op] : (unsigned)fa.out_cstride;
             u64 *o = (ia.per_op ? oa.out[w.op] : fa.out + (((size_t)w.op * fa.out_stride) << 12)) + (((size_t)w.c * out_cstride + w.a) << 12);
 #pragma unroll
-            for (int k = 0; k < 16; k++) o[n0 + 16 * k] = v[k];
+            for (int k = 0; k < 8; k++) o[nb + 64 * k] = v[k];
         }
     });
 }
