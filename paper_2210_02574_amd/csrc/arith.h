@@ -215,17 +215,14 @@ struct ArithFp {
     }
     template <bool LAST> __device__ __forceinline__ void inv16(V (&a)[16], unsigned s_base, unsigned G) const
     {
-        inv16_with<LAST>(a, [&](int c) { return twi[step16_twiddle(s_base, G, (unsigned)c)]; });
-    }
-    template <bool LAST, class F> __device__ __forceinline__ void inv16_with(V (&a)[16], F tw) const
-    {
 #pragma unroll
         for (int sp = 3; sp >= 0; sp--) {
             const int dist = 8 >> sp;
+            const unsigned idx0 = (1u << (s_base + sp)) + (G << sp);
 #pragma unroll
             for (int g = 0; g < (1 << sp); g++) {
                 const bool fin = LAST && sp == 0;
-                const double w = fin ? n1 : tw((1 << sp) - 1 + g);
+                const double w = fin ? n1 : twi[idx0 + g];
 #pragma unroll
                 for (int e = 0; e < dist; e++) {
                     const int k0 = g * 2 * dist + e, k1 = k0 + dist;
@@ -314,10 +311,6 @@ struct ArithInt {
         lo = u + v;
         hi = u - v + q4;
     }
-    __device__ __forceinline__ void fwd16(V (&a)[16], unsigned s_base, unsigned G, bool reduce_first) const
-    {
-        fwd16_with(a, reduce_first, [&](int c) { return twf[step16_twiddle(s_base, G, (unsigned)c)]; });
-    }
     // the steps of 8 elements, as in ArithFp
     template <class F> __device__ __forceinline__ void fwd8_with(V (&a)[8], bool, F tw) const
     {
@@ -351,14 +344,15 @@ struct ArithInt {
             }
         }
     }
-    template <class F> __device__ __forceinline__ void fwd16_with(V (&a)[16], bool, F tw) const
+    __device__ __forceinline__ void fwd16(V (&a)[16], unsigned s_base, unsigned G, bool) const
     {
 #pragma unroll
         for (int sp = 0; sp < 4; sp++) {
             const int dist = 8 >> sp;
+            const unsigned idx0 = (1u << (s_base + sp)) + (G << sp);
 #pragma unroll
             for (int g = 0; g < (1 << sp); g++) {
-                const ShoupConst w = tw((1 << sp) - 1 + g);
+                const ShoupConst w = twf[idx0 + g];
 #pragma unroll
                 for (int e = 0; e < dist; e++) fwd_bfly(a[g * 2 * dist + e], a[g * 2 * dist + e + dist], w);
             }
@@ -366,17 +360,14 @@ struct ArithInt {
     }
     template <bool LAST> __device__ __forceinline__ void inv16(V (&a)[16], unsigned s_base, unsigned G) const
     {
-        inv16_with<LAST>(a, [&](int c) { return twi[step16_twiddle(s_base, G, (unsigned)c)]; });
-    }
-    template <bool LAST, class F> __device__ __forceinline__ void inv16_with(V (&a)[16], F tw) const
-    {
 #pragma unroll
         for (int sp = 3; sp >= 0; sp--) {
             const int dist = 8 >> sp;
+            const unsigned idx0 = (1u << (s_base + sp)) + (G << sp);
 #pragma unroll
             for (int g = 0; g < (1 << sp); g++) {
                 const bool fin = LAST && sp == 0;
-                const ShoupConst w = fin ? n1 : tw((1 << sp) - 1 + g);
+                const ShoupConst w = fin ? n1 : twi[idx0 + g];
 #pragma unroll
                 for (int e = 0; e < dist; e++) {
                     const int k0 = g * 2 * dist + e, k1 = k0 + dist;
