@@ -405,7 +405,7 @@ __device__ __forceinline__ void inner_products_int(const InnerArgs &ia, const Op
 __device__ __forceinline__ unsigned special_at(unsigned p) { return tile_at(p >> 8, p & 255u); }
 
 // limb a of one operation; the results of the thread's pairs (512 i + 2 thread, + 1), i < 2, of both components
-template <int LOGN, class A>
+template <int LOGN, bool MULT, class A>
 __device__ __forceinline__ void special_products(const InnerArgs &ia, const OpArgs &oa, const DevTables &T, unsigned op, unsigned tile,
                                                  int a, unsigned g, int beta, unsigned mi, const ModConst &m, const A &ar, u64 *lds,
                                                  u64 (&r0)[4], u64 (&r1)[4])
@@ -478,7 +478,7 @@ __device__ __forceinline__ void special_products(const InnerArgs &ia, const OpAr
 #pragma unroll
             for (int i = 0; i < 2; i++) {
                 u64 x, y;
-                if (j == own && ia.ta) { // g = 1: the pair itself
+                if (MULT && j == own) { // g = 1: the pair itself
                     const TensorPair p = tensor_pair<LOGN>(ia, op, a, sr[i]);
                     if constexpr (A::IS_FP) {
                         const double P = T.dn_pmod_d[a];
@@ -553,7 +553,9 @@ __device__ __forceinline__ void special_inverse(const u64 (&r0)[4], const u64 (&
 }
 
 // Active limbs ia.first .. level + K - 1 of every operation.  The same order of work-groups as k_inner_fin.
-template <int LOGN> __global__ __launch_bounds__(SPECIAL_THREADS, 3) void k_inner_special(InnerArgs ia, DevTables T, OpArgs oa)
+// MULT: of a Mult with rescale, whose dropped limb takes d0, d1 and d2 (a kernel of its own: with their code in every launch
+// 32 mixed rotations at N = 2^16 took 2388 us instead of 2342)
+template <int LOGN, bool MULT> __global__ __launch_bounds__(SPECIAL_THREADS, 3) void k_inner_special(InnerArgs ia, DevTables T, OpArgs oa)
 {
     __shared__ u64 lds[SPECIAL_WAVES * SPECIAL_DIGIT];
     static_assert(SPECIAL_TILE == INNER_TILE, "inner_grid and inner_tile serve both kernels");
@@ -567,11 +569,11 @@ template <int LOGN> __global__ __launch_bounds__(SPECIAL_THREADS, 3) void k_inne
     u64 r0[4], r1[4];
     if (m.qd != 0.0) {
         const ArithFp ar = make_fp(T, mi, LOGN);
-        special_products<LOGN>(ia, oa, T, w.op, w.tile, w.a, w.g, w.beta, mi, m, ar, lds, r0, r1);
+        special_products<LOGN, MULT>(ia, oa, T, w.op, w.tile, w.a, w.g, w.beta, mi, m, ar, lds, r0, r1);
         if (w.a >= ia.level) special_inverse<LOGN>(r0, r1, u0, comp_words, ar, lds, w.tile);
     } else {
         const ArithInt ar = make_int(T, mi, LOGN);
-        special_products<LOGN>(ia, oa, T, w.op, w.tile, w.a, w.g, w.beta, mi, m, ar, lds, r0, r1);
+        special_products<LOGN, MULT>(ia, oa, T, w.op, w.tile, w.a, w.g, w.beta, mi, m, ar, lds, r0, r1);
         if (w.a >= ia.level) special_inverse<LOGN>(r0, r1, u0, comp_words, ar, lds, w.tile);
     }
     if (w.a < ia.level) {

@@ -110,7 +110,10 @@ static void launch_inv_blocks(he_ctx *c, hipStream_t st, double bytes, const u64
 template <int LOGN>
 static void launch_inner(he_ctx *c, hipStream_t st, double bytes, unsigned grid, const InnerArgs &ia, const OpArgs &oa)
 {
-    KLAUNCH_T(c, st, KID_INNER, bytes, (k_inner_special<LOGN>), grid, SPECIAL_THREADS, ia, c->dev, oa);
+    if (ia.ta && ia.first < ia.level)
+        KLAUNCH_T(c, st, KID_INNER, bytes, (k_inner_special<LOGN, true>), grid, SPECIAL_THREADS, ia, c->dev, oa);
+    else
+        KLAUNCH_T(c, st, KID_INNER, bytes, (k_inner_special<LOGN, false>), grid, SPECIAL_THREADS, ia, c->dev, oa);
 }
 template <int LOGN, int MODE>
 static void launch_inner_fin_mode(he_ctx *c, hipStream_t st, double bytes, unsigned grid, bool integer, const InnerArgs &ia,
