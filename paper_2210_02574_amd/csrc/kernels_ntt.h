@@ -582,13 +582,15 @@ __device__ __forceinline__ void inv_cols_body(u64 *__restrict__ limb, unsigned c
     // LDS, then stages 3 .. 0 (N = 2^16) or 4 .. 1 (N = 2^17: stage 0 pairs the halves afterwards).  Written as two calls:
     // as a loop it is too large for the compiler to unroll, and the values, indexed by the half, go to scratch memory
     // (34 limbs at N = 2^17: 46.6 us, against 41.5 while it was small enough)
+#pragma unroll
+    for (int h = 0; h < H; h++)
+#pragma unroll
+        for (int k = 0; k < 16; k++) { // both halves are on their way before the first is worked on
+            const u64 *src = limb + (16 * (rl + 16 * h) + k) * 256 + col0 + c;
+            a[h][k] = ar.load_mid(STREAM ? __builtin_nontemporal_load(src) : *src);
+        }
     const auto half = [&](V (&v)[16], int h) __attribute__((always_inline)) {
         const unsigned g = rl + 16 * h;
-#pragma unroll
-        for (int k = 0; k < 16; k++) {
-            const u64 *src = limb + (16 * g + k) * 256 + col0 + c;
-            v[k] = ar.load_mid(STREAM ? __builtin_nontemporal_load(src) : *src);
-        }
         ar.template inv16<false>(v, H + 3, g);
         if (h > 0) __syncthreads(); // the previous half has been read back by every thread
 #pragma unroll
