@@ -36,34 +36,39 @@ static void inv12(he_ctx *c, hipStream_t st, double bytes, int scale, const u64 
 }
 static void inner12(he_ctx *c, hipStream_t st, double bytes, const InnerArgs &ia, const OpArgs &oa)
 {
-    KLAUNCH_T(c, st, KID_INNER, bytes, (k_inner12), dim3(ia.level + ia.K, 2, ia.count), N12_THREADS, ia, c->dev, oa);
+    if (ia.ta)
+        KLAUNCH_T(c, st, KID_INNER, bytes, (k_inner12<true>), dim3(ia.level + ia.K, 2, ia.count), N12_THREADS, ia, c->dev, oa);
+    else
+        KLAUNCH_T(c, st, KID_INNER, bytes, (k_inner12<false>), dim3(ia.level + 2 * ia.K, 1, ia.count), N12_THREADS, ia, c->dev, oa);
 }
-template <int PRO, bool DROP>
+template <int PRO, bool DROP, bool INTS>
 static void launch_fin12(he_ctx *c, hipStream_t st, double bytes, bool wide, int mode, const InnerArgs &ia, const FinishArgs &fa,
                          const OpArgs &oa, const ConvArgs &cv)
 {
     const dim3 grid(DROP ? 1 : fa.nl, 2, ia.count);
     if (cv.exact) {
         if (wide)
-            KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 8, true, DROP>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
+            KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 8, true, DROP, INTS>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
         else
-            KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 4, true, DROP>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
+            KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 4, true, DROP, INTS>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
     } else {
         if (wide)
-            KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 8, false, DROP>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
+            KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 8, false, DROP, INTS>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
         else
-            KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 4, false, DROP>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
+            KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 4, false, DROP, INTS>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
     }
 }
 static void fin12(he_ctx *c, hipStream_t st, double bytes, bool wide, int pro, bool drop, int mode, const InnerArgs &ia,
                   const FinishArgs &fa, const OpArgs &oa, const ConvArgs &cv)
 {
+    bool ints = false;
+    for (int i = 0; i < ia.level; i++) ints |= c->modc[i].qd == 0.0;
     if (drop)
-        launch_fin12<PRO_MODDOWN, true>(c, st, bytes, wide, mode, ia, fa, oa, cv);
+        (ints ? launch_fin12<PRO_MODDOWN, true, true> : launch_fin12<PRO_MODDOWN, true, false>)(c, st, bytes, wide, mode, ia, fa, oa, cv);
     else if (pro == PRO_MODDOWN_RS)
-        launch_fin12<PRO_MODDOWN_RS, false>(c, st, bytes, wide, mode, ia, fa, oa, cv);
+        (ints ? launch_fin12<PRO_MODDOWN_RS, false, true> : launch_fin12<PRO_MODDOWN_RS, false, false>)(c, st, bytes, wide, mode, ia, fa, oa, cv);
     else
-        launch_fin12<PRO_MODDOWN, false>(c, st, bytes, wide, mode, ia, fa, oa, cv);
+        (ints ? launch_fin12<PRO_MODDOWN, false, true> : launch_fin12<PRO_MODDOWN, false, false>)(c, st, bytes, wide, mode, ia, fa, oa, cv);
 }
 void dev_launch_n12(DevLaunch &t)
 {

@@ -13,7 +13,9 @@
 // transforms 7.4 to 8.4 us, the host's time for one call, instead of 11.5.  The chain is kept short by fetching a step's
 // twiddles before the step ahead of it is worked on, by giving every component a work-group of its own, and by short
 // code: a launch runs it once, and with 256 threads of 16 elements, twice the instructions, it took 37 us (the
-// finishing kernel 14.9).
+// finishing kernel 14.9).  Batches are bound by memory and by how many work-groups are resident: at most 128 registers keep two
+// per compute unit (64 rotations of 24 primes, with k_fin12 at 137 and the digits read once per component, took 572 us against
+// 510 in two passes per transform; 511 now.  1024 of three primes: 778, 685 and 659).
 #pragma once
 #include "kernels_ks.h"
 
@@ -127,19 +129,19 @@ template <class A> __device__ __forceinline__ void inv12(const u64 (&v)[8], u64 
 }
 
 // Calls f(arithmetic, split, tint) with the variant of the prologue that modulus and tables ask for (split, tint: types
-// whose `value` is the template argument of conv_get).
-template <int PRO, int NSMAX, bool EX, class F>
+// whose `value` is the template argument of conv_get).  INTS false: no limb of the launch, nor one that is dropped, is on the integer path.
+template <int PRO, int NSMAX, bool EX, bool INTS, class F>
 __device__ __forceinline__ void conv_variant12(const DevTables &T, unsigned mi, const ModConst &m, double qld, F f)
 {
     constexpr bool MD = pro_is_moddown(PRO), FOLD = MD && !EX && NSMAX <= 4;
     const bool split = PRO == PRO_MODUP ? T.up_split != 0 : MD ? T.dn_split != 0 : false;
-    if (m.qd == 0.0)
-        f(make_int(T, mi, 12), std::integral_constant<int, 0>{}, std::false_type{});
-    else if (PRO == PRO_MODDOWN_RS && qld == 0.0) { // dropped limb on the integer path
+    if (INTS && m.qd == 0.0) {
+        if constexpr (INTS) f(make_int(T, mi, 12), std::integral_constant<int, 0>{}, std::false_type{});
+    } else if (INTS && PRO == PRO_MODDOWN_RS && qld == 0.0) { // dropped limb on the integer path
         if (split)
-            f(make_fp(T, mi, 12), std::integral_constant<int, 1>{}, std::integral_constant<bool, PRO == PRO_MODDOWN_RS>{});
+            f(make_fp(T, mi, 12), std::integral_constant<int, 1>{}, std::integral_constant<bool, INTS && PRO == PRO_MODDOWN_RS>{});
         else
-            f(make_fp(T, mi, 12), std::integral_constant<int, 0>{}, std::integral_constant<bool, PRO == PRO_MODDOWN_RS>{});
+            f(make_fp(T, mi, 12), std::integral_constant<int, 0>{}, std::integral_constant<bool, INTS && PRO == PRO_MODDOWN_RS>{});
     } else if (FOLD && T.dn_fold != 0)
         f(make_fp(T, mi, 12), std::integral_constant<int, FOLD ? 2 : 0>{}, std::false_type{});
     else if (split)
@@ -162,7 +164,7 @@ __device__ __forceinline__ void inputs12(typename A::V (&a)[8], const u64 *limb,
 
 // grid.x = limbs
 template <int PRO, int NSMAX, bool EX, int EPI>
-__global__ __launch_bounds__(N12_THREADS) void k_ntt_fwd12(u64 *data, DevTables T, LimbBatch lb, ConvArgs cv, FinArgs fa)
+__global__ __launch_bounds__(N12_THREADS, EPI == EPI_FIN ? 4 : 1) void k_ntt_fwd12(u64 *data, DevTables T, LimbBatch lb, ConvArgs cv, FinArgs fa)
 {
     __shared__ u64 lds[N12_LDS];
     const unsigned mi = lb.mod[blockIdx.x], slot = lb.slot[blockIdx.x], nb = N12_BASE;
@@ -174,7 +176,7 @@ __global__ __launch_bounds__(N12_THREADS) void k_ntt_fwd12(u64 *data, DevTables 
 #pragma unroll
         for (int k = 0; k < 8; k++) fo[k] = fin_load<12>(fa, slot, nb + 64 * k);
     }
-    conv_variant12<PRO, NSMAX, EX>(T, mi, m, S.qld, [&](auto ar, auto split, auto tint) {
+    conv_variant12<PRO, NSMAX, EX, true>(T, mi, m, S.qld, [&](auto ar, auto split, auto tint) {
         typedef decltype(ar) A;
         typename A::V a[8];
         inputs12<PRO, decltype(split)::value, decltype(tint)::value, EX>(a, limb, ar, S, m);
@@ -221,74 +223,95 @@ __global__ __launch_bounds__(N12_THREADS) void k_ntt_inv12(const u64 *src, const
         run(make_int(T, mi, 12, ci));
 }
 
-// What a work-group of the inner product works on: component c of active limb a of operation op.
+// What a work-group of the inner product works on: active limb a of operation op, from component c on.
 struct Inner12 {
     unsigned op, g;
     int a, c, level, beta;
     bool none;
 };
-__device__ __forceinline__ Inner12 inner12_of(const InnerArgs &ia, const OpArgs &oa, int a)
+__device__ __forceinline__ Inner12 inner12_of(const InnerArgs &ia, const OpArgs &oa, unsigned op, int a, int c)
 {
     Inner12 w;
-    w.op = blockIdx.z, w.c = (int)blockIdx.y, w.a = a;
+    w.op = op, w.c = c, w.a = a;
     w.g = ia.per_op ? oa.g[w.op] : ia.g;
     w.level = ia.per_op && oa.level[w.op] ? oa.level[w.op] : ia.level;
     w.beta = (w.level + ia.alpha - 1) / ia.alpha;
     w.none = w.a < ia.level && w.a >= w.level; // an operation below the layout's level
     return w;
 }
-// Element n of d2 (g = 1) and of the component's d0 or d1 for Mult, canonical residues.
-template <class A>
-__device__ __forceinline__ void tensor12(const InnerArgs &ia, const Inner12 &w, unsigned n, const ModConst &m, const A &ar, u64 &d, u64 &d2)
+// Element n of d2 (g = 1) and of d0, d1 for Mult, of the C components from w.c on, canonical residues.
+template <int C, class A>
+__device__ __forceinline__ void tensor12(const InnerArgs &ia, const Inner12 &w, unsigned n, const ModConst &m, const A &ar, u64 (&d)[C], u64 &d2)
 {
     const size_t c0 = (((size_t)w.op * ia.t_stride + w.a) << 12) + n, c1 = c0 + ((size_t)ia.level << 12);
     d2 = mul_residues(ia.ta[c1], ia.tb[c1], m, ar);
-    if (w.c == 0)
-        d = mul_residues(ia.ta[c0], ia.tb[c0], m, ar);
-    else
-        d = csub(mul_residues(ia.ta[c0], ia.tb[c1], m, ar) + mul_residues(ia.ta[c1], ia.tb[c0], m, ar), m.q);
+#pragma unroll
+    for (int c = 0; c < C; c++) {
+        if (w.c + c == 0)
+            d[c] = mul_residues(ia.ta[c0], ia.tb[c0], m, ar);
+        else
+            d[c] = csub(mul_residues(ia.ta[c0], ia.tb[c1], m, ar) + mul_residues(ia.ta[c1], ia.tb[c0], m, ar), m.q);
+    }
 }
-// u at elements N12_BASE + 64 k, for Mult with P times d0 or d1: on the floating-point path within 4.3 q of zero (not canonical), as a
-// double; canonical residues on the integer path.
-template <class A>
-__device__ __forceinline__ void inner12(typename A::V (&r)[8], const InnerArgs &ia, const OpArgs &oa, const DevTables &T, const Inner12 &w, unsigned mi,
+// u of the C components from w.c on at elements N12_BASE + 64 k, for Mult with P times d0 or d1: on the floating-point path within 4.3 q of
+// zero (not canonical), as a double; canonical residues on the integer path.
+template <int C, bool MULT, class A>
+__device__ __forceinline__ void inner12(typename A::V (&r)[C][8], const InnerArgs &ia, const OpArgs &oa, const DevTables &T, const Inner12 &w, unsigned mi,
                                         const A &ar, const ModConst &m)
 {
     const unsigned nb = N12_BASE;
+    constexpr int PART = 8 / C; // elements at a time: as many loads in flight and 128-bit sums with two components as with one
     const int own = w.a < ia.level ? w.a / ia.alpha : -1, M = ia.L + ia.K, Ma = ia.level + ia.K;
     const u64 *key0 = (ia.per_op ? oa.evk[w.op] : ia.evk) + (((size_t)w.c * M + mi) << 12);
+    const size_t comp_words = (size_t)M << 12;
     const u64 *dig0 = ia.raised + (((size_t)w.op * ia.raised_stride + w.a) << 12);
     const u64 *d_limb = (ia.per_op && oa.d[w.op] ? oa.d[w.op] : ia.d + (((size_t)w.op * ia.d_stride) << 12)) + ((size_t)w.a << 12);
     unsigned sr[8];
 #pragma unroll
-    for (int k = 0; k < 8; k++) sr[k] = w.g == 1 ? nb + 64 * k : galois_index(nb + 64 * k, w.g, 12);
+    for (int k = 0; k < 8; k++) sr[k] = MULT || w.g == 1 ? nb + 64 * k : galois_index(nb + 64 * k, w.g, 12); // a Mult's g is 1
     if constexpr (A::IS_FP) {
 #pragma unroll
-        for (int k = 0; k < 8; k++) r[k] = 0.0;
+        for (int c = 0; c < C; c++)
+#pragma unroll
+            for (int k = 0; k < 8; k++) r[c][k] = 0.0;
+        if (MULT && own >= 0) { // the digit's own limb: few elements in flight, each takes four factors
+            const u64 *kj = key0 + (((size_t)own * 2 * M) << 12);
+#pragma unroll
+            for (int k = 0; k < 8; k++) {
+                u64 d[C], x;
+                tensor12<C>(ia, w, nb + 64 * k, m, ar, d, x);
+#pragma unroll
+                for (int c = 0; c < C; c++)
+                    r[c][k] = ar.mulmod(u2d(d[c]), T.dn_pmod_d[w.a]) + ar.mulmod(u2d(x), ar.load_mid(kj[c * comp_words + nb + 64 * k]));
+            }
+        }
         for (int j = 0; j < w.beta; j++) {
             const u64 *dj = j == own ? d_limb : dig0 + (((size_t)j * Ma) << 12), *kj = key0 + (((size_t)j * 2 * M) << 12);
-            u64 x[8], e[8];
+            if (!(MULT && j == own)) {
 #pragma unroll
-            for (int k = 0; k < 8; k++) e[k] = kj[nb + 64 * k];
-            if (j == own && ia.ta) {
+                for (int p = 0; p < 8; p += PART) {
+                    u64 x[PART], e[C][PART];
 #pragma unroll
-                for (int k = 0; k < 8; k++) {
-                    u64 d;
-                    tensor12(ia, w, nb + 64 * k, m, ar, d, x[k]);
-                    r[k] += ar.mulmod(u2d(d), T.dn_pmod_d[w.a]);
+                    for (int c = 0; c < C; c++)
+#pragma unroll
+                        for (int k = 0; k < PART; k++) e[c][k] = kj[c * comp_words + nb + 64 * (p + k)];
+#pragma unroll
+                    for (int k = 0; k < PART; k++) x[k] = dj[sr[p + k]];
+#pragma unroll
+                    for (int c = 0; c < C; c++)
+#pragma unroll
+                        for (int k = 0; k < PART; k++) r[c][p + k] += ar.mulmod(u2d(x[k]), ar.load_mid(e[c][k])); // key words are balanced doubles
                 }
-            } else {
-#pragma unroll
-                for (int k = 0; k < 8; k++) x[k] = dj[sr[k]];
             }
-#pragma unroll
-            for (int k = 0; k < 8; k++) r[k] += ar.mulmod(u2d(x[k]), ar.load_mid(e[k])); // key words are balanced doubles
             if ((j & 3) == 3) {
 #pragma unroll
-                for (int k = 0; k < 8; k++) r[k] = ar.reduce(r[k]);
+                for (int c = 0; c < C; c++)
+#pragma unroll
+                    for (int k = 0; k < 8; k++) r[c][k] = ar.reduce(r[c][k]);
             }
         }
     } else {
+        static_assert(C == 1, "128-bit sums: one component at a time");
         U128 acc[8];
 #pragma unroll
         for (int k = 0; k < 8; k++) acc[k] = U128{0, 0};
@@ -297,61 +320,96 @@ __device__ __forceinline__ void inner12(typename A::V (&r)[8], const InnerArgs &
 #pragma unroll
             for (int k = 0; k < 8; k++) {
                 u64 x;
-                if (j == own && ia.ta) {
-                    u64 d;
-                    tensor12(ia, w, nb + 64 * k, m, ar, d, x);
-                    mac128(acc[k], d, T.dn_pmod[w.a]);
+                if (MULT && j == own) {
+                    u64 d[1];
+                    tensor12<1>(ia, w, nb + 64 * k, m, ar, d, x);
+                    mac128(acc[k], d[0], T.dn_pmod[w.a]);
                 } else
                     x = dj[sr[k]];
                 mac128(acc[k], x, kj[nb + 64 * k]);
             }
         }
 #pragma unroll
-        for (int k = 0; k < 8; k++) r[k] = reduce128(acc[k], m);
+        for (int k = 0; k < 8; k++) r[0][k] = reduce128(acc[k], m);
     }
 }
 
-// grid (active limbs, components, operations).  u of the ciphertext limbs, and of the special ones (the longest work, first)
-// the inverse transform, scaled by (P/p_k)^-1.  All limbs in one launch: formed in k_fin12, u added its chain of loads, a
-// round per digit, to the longest kernel (one rotation 40.2 us instead of 39.6 with three digits).
-__global__ __launch_bounds__(N12_THREADS) void k_inner12(InnerArgs ia, DevTables T, OpArgs oa)
+// u of the ciphertext limbs, and of the special ones (the longest work, first) the inverse transform, scaled by (P/p_k)^-1.  All
+// limbs in one launch: formed in k_fin12, u would add its chain of loads, a round per digit, to the longest kernel.
+// Rotations: grid (level + 2 K, 1, operations); a work-group makes both components of a ciphertext limb, so that its digits are read
+// once, or one of a special limb.  With one component per work-group everywhere, 1024 rotations of three primes took 715 us instead of 667,
+// 128 of 24 primes 1025 instead of 997, a single one of 24 primes 50.3 instead of 47.8 (three primes: the same within 0.5 us).
+// MULT (the switched polynomial is a product, InnerArgs.ta): grid (level + K, 2, operations), one component per work-group: with the factors
+// of both components the registers of two work-groups per compute unit do not suffice (16 products of three primes 41.3 -> 45.5 us).
+template <bool MULT> __global__ __launch_bounds__(N12_THREADS, 4) void k_inner12(InnerArgs ia, DevTables T, OpArgs oa)
 {
+    constexpr bool BOTH = !MULT;
     __shared__ u64 lds[N12_LDS];
     const unsigned nb = N12_BASE;
-    const Inner12 w = inner12_of(ia, oa, (int)blockIdx.x < ia.K ? ia.level + (int)blockIdx.x : (int)blockIdx.x - ia.K);
+    unsigned unit = blockIdx.x, c0 = blockIdx.y;
+    if constexpr (BOTH) {
+        c0 = unit < 2u * ia.K ? unit & 1u : 0;
+        unit = unit < 2u * ia.K ? unit >> 1 : unit - ia.K;
+    }
+    Inner12 w = inner12_of(ia, oa, blockIdx.z, (int)unit < ia.K ? ia.level + (int)unit : (int)unit - ia.K, (int)c0);
     if (w.none) return;
     const bool special = w.a >= ia.level;
     const unsigned mi = active_mod(w.a, ia.level, ia.L), k_sp = special ? w.a - ia.level : 0;
     const ModConst m = T.mod[mi];
-    u64 *limb = ia.u + (((size_t)w.op * ia.u_stride + (size_t)w.c * (ia.level + ia.K) + w.a) << 12);
-    u64 v[8];
-    if (m.qd != 0.0) {
-        const ArithFp ar = make_fp(T, mi, 12, special ? T.dn_inv_d[k_sp] : 0.0);
-        double r[8];
-        inner12(r, ia, oa, T, w, mi, ar, m);
+    const size_t comp_words = (size_t)(ia.level + ia.K) << 12;
+    u64 *limb = ia.u + (((size_t)w.op * ia.u_stride + w.a) << 12) + w.c * comp_words;
+    const auto store = [&](const u64 (&v)[8], u64 *out) {
 #pragma unroll
-        for (int k = 0; k < 8; k++) v[k] = fp_canon(r[k], m.qd, m.qinvd);
-        if (special) inv12(v, limb, ar, lds);
+        for (int k = 0; k < 8; k++) out[nb + 64 * k] = v[k];
+    };
+    if (BOTH && !special) {
+        if (m.qd != 0.0) {
+            double r[2][8];
+            inner12<2, MULT>(r, ia, oa, T, w, mi, make_fp(T, mi, 12), m);
+#pragma unroll
+            for (int c = 0; c < 2; c++)
+#pragma unroll
+                for (int k = 0; k < 8; k++) limb[c * comp_words + nb + 64 * k] = fp_canon(r[c][k], m.qd, m.qinvd);
+        } else {
+#pragma unroll 1
+            for (w.c = 0; w.c < 2; w.c++) {
+                u64 v[1][8];
+                inner12<1, MULT>(v, ia, oa, T, w, mi, make_int(T, mi, 12), m);
+                store(v[0], limb + w.c * comp_words);
+            }
+        }
+    } else if (m.qd != 0.0) {
+        const ArithFp ar = make_fp(T, mi, 12, special ? T.dn_inv_d[k_sp] : 0.0);
+        double r[1][8];
+        inner12<1, MULT>(r, ia, oa, T, w, mi, ar, m);
+        u64 v[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++) v[k] = fp_canon(r[0][k], m.qd, m.qinvd);
+        if (special)
+            inv12(v, limb, ar, lds);
+        else
+            store(v, limb);
     } else {
         const ArithInt ar = make_int(T, mi, 12, special ? T.dn_inv[k_sp] : ShoupConst{0, 0});
-        inner12(v, ia, oa, T, w, mi, ar, m);
-        if (special) inv12(v, limb, ar, lds);
-    }
-    if (!special) {
-#pragma unroll
-        for (int k = 0; k < 8; k++) limb[nb + 64 * k] = v[k];
+        u64 v[1][8];
+        inner12<1, MULT>(v, ia, oa, T, w, mi, ar, m);
+        if (special)
+            inv12(v[0], limb, ar, lds);
+        else
+            store(v[0], limb);
     }
 }
 
 // grid (ciphertext limbs, components, operations).  DROP: the limb that a rescale drops (limb level - 1 alone); its
 // finished value goes through the inverse transform and is left, in the coefficient domain, in its slot of the
-// correction buffer.
-template <int PRO, int NSMAX, bool EX, bool DROP>
-__global__ __launch_bounds__(N12_THREADS) void k_fin12(InnerArgs ia, FinishArgs fa, DevTables T, OpArgs oa, ConvArgs cv, int mode)
+// correction buffer.  INTS: some ciphertext limb is on the integer path, whose conversion takes up to 256 registers; without it every form
+// stays within 128 and two work-groups fit a compute unit (128 products with rescale, digits of six primes: 649 -> 476 us).
+template <int PRO, int NSMAX, bool EX, bool DROP, bool INTS>
+__global__ __launch_bounds__(N12_THREADS, INTS && (EX || DROP) ? 1 : 4) void k_fin12(InnerArgs ia, FinishArgs fa, DevTables T, OpArgs oa, ConvArgs cv, int mode)
 {
     __shared__ u64 lds[N12_LDS];
     const unsigned nb = N12_BASE;
-    const Inner12 w = inner12_of(ia, oa, DROP ? ia.level - 1 : (int)blockIdx.x);
+    const Inner12 w = inner12_of(ia, oa, blockIdx.z, DROP ? ia.level - 1 : (int)blockIdx.x, (int)blockIdx.y);
     if (w.none) return;
     const ModConst m = T.mod[w.a];
     const unsigned slot = w.op * (unsigned)cv.dst_stride + (unsigned)(w.c * ia.level + w.a);
@@ -371,7 +429,7 @@ __global__ __launch_bounds__(N12_THREADS) void k_fin12(InnerArgs ia, FinishArgs 
             if (w.c == 0) v[k] = csub(v[k] + add_rot[w.g == 1 ? n : galois_index(n, w.g, 12)], m.q);
         }
     }
-    conv_variant12<PRO, NSMAX, EX>(T, w.a, m, S.qld, [&](auto ar, auto split, auto tint) {
+    conv_variant12<PRO, NSMAX, EX, INTS>(T, w.a, m, S.qld, [&](auto ar, auto split, auto tint) {
         typedef decltype(ar) A;
         typename A::V a[8];
         inputs12<PRO, decltype(split)::value, decltype(tint)::value, EX>(a, nullptr, ar, S, m);
