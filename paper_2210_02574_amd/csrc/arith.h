@@ -325,6 +325,22 @@ struct ArithInt {
             }
         }
     }
+    template <class F> __device__ __forceinline__ void fwd4x2_with(V (&a)[8], bool, F tw) const
+    {
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+#pragma unroll
+            for (int sp = 0; sp < 2; sp++) {
+                const int dist = 2 >> sp;
+#pragma unroll
+                for (int g = 0; g < (1 << sp); g++) {
+                    const ShoupConst w = tw(h, sp, g);
+#pragma unroll
+                    for (int e = 0; e < dist; e++) fwd_bfly(a[4 * h + g * 2 * dist + e], a[4 * h + g * 2 * dist + e + dist], w);
+                }
+            }
+        }
+    }
     template <bool LAST, class F> __device__ __forceinline__ void inv8_with(V (&a)[8], F tw) const
     {
 #pragma unroll

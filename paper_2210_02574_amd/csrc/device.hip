@@ -334,10 +334,11 @@ static const OpArgs kNoOps = {};
 // limb's own content, or a base conversion of cv.src); with fin != nullptr the block pass writes
 // (u - ntt) * const + addend to fin->out instead of the transform itself.
 // src_limbs = number of source limbs the prologue reads in total (for the byte count).
-// int_blocks_only: the block pass runs only for ciphertext limbs on the integer path (the others are finished by
-// the kernel that consumes them); special_too: and for the special limbs on that path.
+// blocks: the limbs whose block pass runs here (the others are finished by the kernel that consumes them): all, the
+// ciphertext limbs on the integer path, these and the special limbs on that path, or none.
+enum { BLOCKS_ALL, BLOCKS_INT, BLOCKS_INT_SPECIAL, BLOCKS_NONE };
 static int32_t ntt_forward(he_ctx *c, hipStream_t st, u64 *data, const LimbList &l, int pro, const ConvArgs &cv,
-                           const FinArgs *fin, int src_limbs, bool int_blocks_only = false, bool special_too = false)
+                           const FinArgs *fin, int src_limbs, int blocks = BLOCKS_ALL)
 {
     const bool wide = std::max(c->alpha, c->K) > 4;
     const double N8 = (double)c->N * 8.0;
@@ -358,15 +359,15 @@ static int32_t ntt_forward(he_ctx *c, hipStream_t st, u64 *data, const LimbList 
         if (fin) {
             // reads the transform's input, the minuend and the addend, writes the result
             dl.fwd_blocks(c, st, (double)nb * N8 * (fin->add ? 4.0 : 3.0), true, data, lb, nb, *fin);
-        } else if (!int_blocks_only)
+        } else if (blocks == BLOCKS_ALL)
             dl.fwd_blocks(c, st, 2.0 * nb * N8, false, data, lb, nb, kNoFin);
     });
-    if (rc != HE_OK || !int_blocks_only || dl.fwd_limb[pro]) return rc;
+    if (rc != HE_OK || blocks == BLOCKS_ALL || blocks == BLOCKS_NONE || dl.fwd_limb[pro]) return rc;
     // block pass of the integer-path limbs alone, after all column passes: few launches, each as large as possible;
     // k_inner_special finishes the special limbs
     LimbList li;
     for (int b = 0; b < l.size(); b++)
-        if (c->modc[l.mod[b]].qd == 0.0 && (special_too || l.mod[b] < c->L)) li.add(l.slot[b], l.src[b], l.mod[b]);
+        if (c->modc[l.mod[b]].qd == 0.0 && (blocks == BLOCKS_INT_SPECIAL || l.mod[b] < c->L)) li.add(l.slot[b], l.src[b], l.mod[b]);
     return for_batches(c, li, [&](const LimbBatch &lb, int nb) {
         dl.fwd_blocks(c, st, 2.0 * nb * N8, false, data, lb, nb, kNoFin);
     });
@@ -639,7 +640,7 @@ static int32_t ks_raise(he_ctx *c, const u64 *d_ntt, int d_stride, u64 *ws, cons
                 r.add(o * W + j * Ma + a, a < level ? a : c->L + (a - level));
             }
         }
-    return ntt_forward(c, st, ws + w.raised * N, r, PRO_MODUP, cv, nullptr, level * count, true, finish_special);
+    return ntt_forward(c, st, ws + w.raised * N, r, PRO_MODUP, cv, nullptr, level * count, finish_special ? BLOCKS_INT_SPECIAL : BLOCKS_INT);
 }
 
 static InnerArgs inner_args(const he_ctx *c, const he_evk *evk, const u64 *d_ntt, int d_stride, u64 *ws, const WsLayout &w,
@@ -724,19 +725,13 @@ static int32_t ks_finish(he_ctx *c, const InnerArgs &ia, const OpArgs *oa, const
         dev_launch(c).fin_limb(c, st, words * N * 8.0, std::max(c->alpha, c->K) > 4, pro, false, mode, ia, fa, oa ? *oa : kNoOps, cv);
         return launch_ok(c);
     }
-    int32_t rc = ntt_forward(c, st, r, l, pro, cv, nullptr, 2 * c->K * ia.count + extra, true);
+    int32_t rc = ntt_forward(c, st, r, l, pro, cv, nullptr, 2 * c->K * ia.count + extra, BLOCKS_NONE);
     if (rc != HE_OK) return rc;
     const unsigned grid = inner_grid((unsigned)(N / INNER_TILE), (unsigned)fa.nl, (unsigned)ia.count);
     int n_int = 0;
     for (int i = 0; i < fa.nl; i++) n_int += c->modc[i].qd == 0.0 ? 1 : 0;
-    const OpArgs &ops = oa ? *oa : kNoOps;
-    for (int integer = 1; integer >= 0; integer--) {
-        const int limbs = integer ? n_int : fa.nl - n_int;
-        if (!limbs) continue;
-        dev_launch(c).inner_fin(c, st, words * N * 8.0 * limbs / fa.nl, grid, mode, integer != 0, ia, fa, ops);
-        if ((rc = launch_ok(c)) != HE_OK) return rc;
-    }
-    return HE_OK;
+    dev_launch(c).inner_fin(c, st, words * N * 8.0, grid, mode, n_int == 0 ? FIN_FP : n_int == fa.nl ? FIN_INT : FIN_BOTH, ia, fa, oa ? *oa : kNoOps);
+    return launch_ok(c);
 }
 
 static FinishArgs finish_args(const he_ctx *c, u64 *out, int out_stride, const u64 *add, int add_stride, int add_cstride, int level)
@@ -1067,7 +1062,7 @@ extern "C" int32_t he_hrot_batch_levels(he_ctx *ctx, const he_evk *const *rots, 
                 }
             }
         }
-        if ((rc = ntt_forward(ctx, st, ws + w.raised * N, rl, PRO_MODUP, cv, nullptr, src_limbs, true)) != HE_OK) return rc;
+        if ((rc = ntt_forward(ctx, st, ws + w.raised * N, rl, PRO_MODUP, cv, nullptr, src_limbs, BLOCKS_INT)) != HE_OK) return rc;
         // 3 - 6
         if (misaligned16(ws)) return HE_EINVAL;
         if ((rc = ks_apply(ctx, inner_args(ctx, rots[r], in0, 0, ws, w, lmax, nb, &oa, false), &oa, ws, w,

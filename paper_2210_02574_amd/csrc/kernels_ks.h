@@ -56,7 +56,7 @@ struct OpArgs {
 // of `add` (c0 of the rotated ciphertext) on component 0; FIN_ROTSUM: as FIN_ROT plus limb i of component c of `add`.
 enum { FIN_MULT = 0, FIN_ROT = 1, FIN_ROTSUM = 2 };
 struct FinishArgs {
-    const u64 *r; // [2][level] limbs per operation; floating-point limbs as the column pass left them, others finished
+    const u64 *r; // [2][level] limbs per operation, as the column pass left them
     u64 *out;
     const u64 *add;
     const ShoupConst *cst;
@@ -140,26 +140,31 @@ __device__ __forceinline__ BlockLane block_lane(u64 *lds, const double *tws)
     return b;
 }
 // Block pass of the eight values dv of this thread (pattern of step 1); the result is left in the wave's LDS, element e
-// of block b at tile_at(b, e), for the caller to read after a block_sync.
-// Ranges (in units of q): the column pass leaves up to 3.7; reduced, step 1 ends below 2.7 and step 2 below 6.3;
-// reduced again, step 3 ends below 1.9, small enough for exact products.
-__device__ __forceinline__ void block_pass8(const ArithFp &ar, double (&dv)[8], const BlockLane &b)
+// of block b at tile_at(b, e), for the caller to read after a block_sync.  tw(m, i): twiddle of local stage m, group i of the block.
+// Ranges (in units of q): floating point: the column pass leaves up to 3.7; reduced, step 1 ends below 2.7 and step 2 below 6.3;
+// reduced again, step 3 ends below 1.9, small enough for exact products.  Integer: in [0, 8) throughout.
+template <class A, class F> __device__ __forceinline__ void block_pass8(const A &ar, typename A::V (&dv)[8], const BlockLane &b, F tw)
 {
-    ar.fwd8_with(dv, true, [&](int sp, int gg) { return b.tw[(1 << sp) - 1 + gg]; });
+    ar.fwd8_with(dv, true, [&](int sp, int gg) { return tw(sp, (unsigned)gg); });
 #pragma unroll
     for (int k = 0; k < 8; k++) b.l1[34 * k] = ar.store_mid(dv[k]);
     block_sync();
 #pragma unroll
     for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(b.l2[4 * k + (k >> 2)]);
-    ar.fwd8_with(dv, false, [&](int sp, int gg) { return b.tw[(8 << sp) - 1 + (b.g2 << sp) + gg]; });
+    ar.fwd8_with(dv, false, [&](int sp, int gg) { return tw(3 + sp, (b.g2 << sp) + gg); });
 #pragma unroll
     for (int k = 0; k < 8; k++) b.l2[4 * k + (k >> 2)] = ar.store_mid(dv[k]);
     block_sync();
 #pragma unroll
     for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(b.l3[136 * (k >> 2) + (k & 3)]);
-    ar.fwd4x2_with(dv, true, [&](int h, int sp, int gg) { return b.tw[(64 << sp) - 1 + ((b.t + 32 * h) << sp) + gg]; });
+    ar.fwd4x2_with(dv, true, [&](int h, int sp, int gg) { return tw(6 + sp, ((b.t + 32 * h) << sp) + gg); });
 #pragma unroll
     for (int k = 0; k < 8; k++) b.l3[136 * (k >> 2) + (k & 3)] = ar.store_mid(dv[k]);
+}
+// the same with the twiddles in LDS
+__device__ __forceinline__ void block_pass8(const ArithFp &ar, double (&dv)[8], const BlockLane &b)
+{
+    block_pass8(ar, dv, b, [&](int m, unsigned i) { return b.tw[(1u << m) - 1 + i]; });
 }
 
 // What one work-group works on.
@@ -607,91 +612,125 @@ __device__ __forceinline__ u64x2 fin_addend(const FinishArgs &fa, const OpArgs &
     return v;
 }
 
-// Second launch: the ciphertext limbs on the floating-point path (INT: those on the integer path, whose digits and
-// corrections arrive finished).
+// Second launch: the ciphertext limbs.  PATH: the arithmetic of the limbs of this launch; FIN_BOTH where a chain mixes them, one launch for
+// all rather than one per path: half a grid's work-groups would return at once, and the second launch waited for the first (primes
+// of 55 and 50 bits in turn at N = 2^16, one rotation at level 12: 170 -> 148 us, 150 as one inner product and a finishing pass; eight
+// 55-bit primes, eight rotations: 382 -> 343, 370).
 // Bound by memory for batches with one key (the digits, r, the addend and the result once each); a call as a whole
 // takes less than the inner product over the same limbs and the finishing block pass took together: at N = 2^16, level 24,
 // 15 hoisted rotations 1200 -> 1061 us, 16 products 2120 -> 2017 us, 32 rotations of mixed levels 2515 -> 2362 us.
-template <int LOGN, int MODE, bool INT>
-__global__ __launch_bounds__(INNER_THREADS, INT ? 4 : 6) void k_inner_fin(InnerArgs ia, FinishArgs fa, DevTables T, OpArgs oa)
+enum { FIN_FP = 0, FIN_INT = 1, FIN_BOTH = 2 };
+
+// One integer-path limb: both corrections through their block pass first, the twiddles from the table (the wave keeps both, in
+// [0, 8q), in its LDS), then pair by pair the products and the finishing step.
+template <int LOGN, int MODE>
+__device__ __forceinline__ void inner_fin_int(const InnerArgs &ia, const FinishArgs &fa, const DevTables &T, const OpArgs &oa, const InnerTile &w,
+                                              const ModConst &m, const u64 *r_grp, char *o, size_t o_step, u64 *lds)
 {
-    const InnerTile w = inner_tile<LOGN>(ia, oa, fa.nl, 0);
-    const ModConst m = T.mod[w.a < 0 ? 0 : w.a];
-    if (w.none || (m.qd == 0.0) != INT) return;
     const unsigned lane16 = (threadIdx.x & 63) * 16u;
-    const u64 *r = fa.r + (((size_t)w.op * fa.r_stride + w.a) << LOGN);
+    const ArithInt ar = make_int(T, w.a, LOGN);
+#pragma unroll 1
+    for (int c = 0; c < 2; c++) {
+        const BlockLane b = block_lane(lds + c * WAVE_BLOCKS * TILE_GROUP, nullptr);
+        const u64 *in = r_grp + c * ((size_t)ia.level << LOGN) + b.blk * 256 + b.t;
+        u64 v[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++) v[k] = __builtin_nontemporal_load(in + 32 * k);
+        const unsigned G = w.grp * WAVE_BLOCKS + b.blk;
+        block_pass8(ar, v, b, [&](int st, unsigned i) { return ar.twf[(1u << (LOGN - 8 + st)) + (G << st) + i]; });
+    }
+    block_sync();
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        u64 x[2][4];
+        inner_products_int<LOGN, MODE == FIN_MULT>(ia, oa, T, w, w.a, m, h, x[0], x[1]);
+#pragma unroll
+        for (int c = 0; c < 2; c++)
+#pragma unroll
+            for (int i = 0; i < 2; i++) {
+                const int ii = 2 * h + i;
+                const unsigned p = 128u * ii + 2u * (threadIdx.x & 63);
+                const u64 *rv = lds + c * WAVE_BLOCKS * TILE_GROUP + tile_at(p >> 8, p & 255u);
+                const u64x2 av = fin_addend<LOGN, MODE>(fa, oa, ia, w, c, ii, m.q);
+                u64x2 res; // u - r + 8q stays below 9q < 2^64
+                res.x = mul_shoup(x[c][2 * i] + 8 * m.q - rv[0], fa.cst[w.a], m.q);
+                res.y = mul_shoup(x[c][2 * i + 1] + 8 * m.q - rv[1], fa.cst[w.a], m.q);
+                res.x = csub(res.x + av.x, m.q);
+                res.y = csub(res.y + av.y, m.q);
+                __builtin_nontemporal_store(res, (u64x2 *)(o + c * o_step + 1024 * ii + lane16));
+            }
+    }
+}
+
+// One floating-point limb.
+template <int LOGN, int MODE>
+__device__ __forceinline__ void inner_fin_fp(const InnerArgs &ia, const FinishArgs &fa, const DevTables &T, const OpArgs &oa, const InnerTile &w,
+                                             const ModConst &m, const u64 *r_grp, char *o, size_t o_step, u64 *lds)
+{
+    const unsigned lane16 = (threadIdx.x & 63) * 16u;
     const size_t r_step = ((size_t)ia.level << LOGN) * 8;
-    const char *r_grp = (const char *)(r + ((size_t)w.grp << WAVE_LOG));
+    double *tws = (double *)(lds + WAVE_BLOCKS * TILE_GROUP);
+    u64 *pre = lds + WAVE_BLOCKS * (TILE_GROUP + 256);
+    const ArithFp ar = make_fp(T, w.a, LOGN);
+    const BlockLane b = block_lane(lds, tws);
+    const char *r_lane = (const char *)r_grp + lane16;
+    double acc[2][8];
+    inner_products8<LOGN, MODE == FIN_MULT>(ia, oa, T, w, w.a, ar, b, lds, tws, pre, r_lane, acc[0], acc[1]);
+    // the corrections are transformed in the output's own blocks: other twiddles where a rotation maps the group
+    // elsewhere (the wave's own reads of the old ones have returned, and what it still has in flight was issued
+    // before the last key words and has arrived with them)
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    if (w.grp_in != w.grp)
+        wave_copy_4k<false>((const char *)(T.twd_blk + (((size_t)w.a << LOGN) + ((size_t)w.grp << WAVE_LOG))) + lane16, (char *)tws);
+    const double k1 = fa.cst_d[w.a];
+#pragma unroll
+    for (int c = 0; c < 2; c++) {
+        double dv[8];
+        u64x2 av[4];
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const u64 *pw = pre + b.blk * 256 + b.t;
+#pragma unroll
+        for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(pw[32 * k]);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (c == 0) wave_copy_4k<true>(r_lane + r_step, (char *)pre);
+#pragma unroll
+        for (int i = 0; i < 4; i++) av[i] = fin_addend<LOGN, MODE>(fa, oa, ia, w, c, i, m.q);
+        block_pass8(ar, dv, b);
+        block_sync();
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const unsigned p = 128u * i + 2u * (threadIdx.x & 63), wd = tile_at(p >> 8, p & 255u);
+            dv[2 * i] = ar.load_mid(lds[wd]), dv[2 * i + 1] = ar.load_mid(lds[wd + 1]);
+        }
+        block_sync();
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            u64x2 res;
+#pragma unroll
+            for (int e = 0; e < 2; e++) {
+                const double v = ar.mulmod(acc[c][2 * i + e] - dv[2 * i + e], k1);
+                res[e] = fp_canon(MODE == FIN_MULT ? v : v + u2d(av[i][e]), m.qd, m.qinvd);
+            }
+            __builtin_nontemporal_store(res, (u64x2 *)(o + c * o_step + 1024 * i + lane16));
+        }
+    }
+}
+
+template <int LOGN, int MODE, int PATH>
+__global__ __launch_bounds__(INNER_THREADS, PATH != FIN_INT ? 6 : MODE == FIN_MULT ? 3 : 4) void k_inner_fin(InnerArgs ia, FinishArgs fa, DevTables T, OpArgs oa)
+{
+    __shared__ __align__(16) u64 wave_lds[INNER_THREADS / 64][PATH == FIN_INT ? 2 * WAVE_BLOCKS * TILE_GROUP : WAVE_LDS];
+    const InnerTile w = inner_tile<LOGN>(ia, oa, fa.nl, 0);
+    if (w.none) return;
+    const ModConst m = T.mod[w.a];
+    const u64 *r_grp = fa.r + (((size_t)w.op * fa.r_stride + w.a) << LOGN) + ((size_t)w.grp << WAVE_LOG);
     const unsigned out_cstride = ia.per_op && oa.level[w.op] ? oa.level[w.op] : (unsigned)fa.out_cstride;
     char *o = (char *)((ia.per_op ? oa.out[w.op] : fa.out + (((size_t)w.op * fa.out_stride) << LOGN)) + (((size_t)w.a << LOGN) + ((size_t)w.grp << WAVE_LOG)));
     const size_t o_step = ((size_t)out_cstride << LOGN) * 8;
-    if constexpr (INT) {
-#pragma unroll
-        for (int h = 0; h < 2; h++) {
-            u64 x[2][4];
-            inner_products_int<LOGN, MODE == FIN_MULT>(ia, oa, T, w, w.a, m, h, x[0], x[1]);
-#pragma unroll
-            for (int c = 0; c < 2; c++)
-#pragma unroll
-                for (int i = 0; i < 2; i++) {
-                    const int ii = 2 * h + i;
-                    const u64x2 rv = ld_at<u64x2>(r_grp + c * r_step + 1024 * ii, lane16);
-                    const u64x2 av = fin_addend<LOGN, MODE>(fa, oa, ia, w, c, ii, m.q);
-                    u64x2 res;
-                    res.x = mul_shoup(x[c][2 * i] + m.q - rv.x, fa.cst[w.a], m.q);
-                    res.y = mul_shoup(x[c][2 * i + 1] + m.q - rv.y, fa.cst[w.a], m.q);
-                    res.x = csub(res.x + av.x, m.q);
-                    res.y = csub(res.y + av.y, m.q);
-                    *(u64x2 *)(o + c * o_step + 1024 * ii + lane16) = res;
-                }
-        }
+    u64 *lds = wave_lds[wave_id()];
+    if (PATH == FIN_INT || (PATH == FIN_BOTH && m.qd == 0.0)) {
+        if constexpr (PATH != FIN_FP) inner_fin_int<LOGN, MODE>(ia, fa, T, oa, w, m, r_grp, o, o_step, lds);
     } else {
-        __shared__ __align__(16) u64 wave_lds[INNER_THREADS / 64][WAVE_LDS];
-        u64 *lds = wave_lds[wave_id()];
-        double *tws = (double *)(lds + WAVE_BLOCKS * TILE_GROUP);
-        u64 *pre = lds + WAVE_BLOCKS * (TILE_GROUP + 256);
-        const ArithFp ar = make_fp(T, w.a, LOGN);
-        const BlockLane b = block_lane(lds, tws);
-        const char *r_lane = r_grp + lane16;
-        double acc[2][8];
-        inner_products8<LOGN, MODE == FIN_MULT>(ia, oa, T, w, w.a, ar, b, lds, tws, pre, r_lane, acc[0], acc[1]);
-        // the corrections are transformed in the output's own blocks: other twiddles where a rotation maps the group
-        // elsewhere (the wave's own reads of the old ones have returned, and what it still has in flight was issued
-        // before the last key words and has arrived with them)
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-        if (w.grp_in != w.grp)
-            wave_copy_4k<false>((const char *)(T.twd_blk + (((size_t)w.a << LOGN) + ((size_t)w.grp << WAVE_LOG))) + lane16, (char *)tws);
-        const double k1 = fa.cst_d[w.a];
-#pragma unroll
-        for (int c = 0; c < 2; c++) {
-            double dv[8];
-            u64x2 av[4];
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            const u64 *pw = pre + b.blk * 256 + b.t;
-#pragma unroll
-            for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(pw[32 * k]);
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            if (c == 0) wave_copy_4k<true>(r_lane + r_step, (char *)pre);
-#pragma unroll
-            for (int i = 0; i < 4; i++) av[i] = fin_addend<LOGN, MODE>(fa, oa, ia, w, c, i, m.q);
-            block_pass8(ar, dv, b);
-            block_sync();
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const unsigned p = 128u * i + 2u * (threadIdx.x & 63), wd = tile_at(p >> 8, p & 255u);
-                dv[2 * i] = ar.load_mid(lds[wd]), dv[2 * i + 1] = ar.load_mid(lds[wd + 1]);
-            }
-            block_sync();
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                u64x2 res;
-#pragma unroll
-                for (int e = 0; e < 2; e++) {
-                    const double v = ar.mulmod(acc[c][2 * i + e] - dv[2 * i + e], k1);
-                    res[e] = fp_canon(MODE == FIN_MULT ? v : v + u2d(av[i][e]), m.qd, m.qinvd);
-                }
-                __builtin_nontemporal_store(res, (u64x2 *)(o + c * o_step + 1024 * i + lane16));
-            }
-        }
+        if constexpr (PATH != FIN_INT) inner_fin_fp<LOGN, MODE>(ia, fa, T, oa, w, m, r_grp, o, o_step, lds);
     }
 }

@@ -60,11 +60,10 @@ struct DevLaunch {
     void (*inv_blocks)(he_ctx *c, hipStream_t st, double bytes, const u64 *src, const u64 *src2, u64 *dst, const LimbBatch &lb, int nb);
     void (*inv_cols)(he_ctx *c, hipStream_t st, double bytes, int scale, u64 *dst, const LimbBatch &lb, int nb,
                      const ConvArgs &cv);
-    // inner product on the limbs ia.first .. level + K - 1, and the finishing one on the first fa.nl limbs: those on the
-    // integer path or the others
+    // inner product on the limbs ia.first .. level + K - 1, and the finishing one on the first fa.nl limbs (path: FIN_FP, ..)
     void (*inner)(he_ctx *c, hipStream_t st, double bytes, unsigned grid, const InnerArgs &ia, const OpArgs &oa);
-    void (*inner_fin)(he_ctx *c, hipStream_t st, double bytes, unsigned grid, int mode, bool integer, const InnerArgs &ia,
-                      const FinishArgs &fa, const OpArgs &oa);
+    void (*inner_fin)(he_ctx *c, hipStream_t st, double bytes, unsigned grid, int mode, int path, const InnerArgs &ia, const FinishArgs &fa,
+                      const OpArgs &oa);
 };
 // Each translation unit fills its part of a ring size's table: dev_launch_cols<logN>_<p> the forward
 // column pass with prologue p (p = 5: the inverse column pass).
@@ -116,22 +115,24 @@ static void launch_inner(he_ctx *c, hipStream_t st, double bytes, unsigned grid,
         KLAUNCH_T(c, st, KID_INNER, bytes, (k_inner_special<LOGN, false>), grid, SPECIAL_THREADS, ia, c->dev, oa);
 }
 template <int LOGN, int MODE>
-static void launch_inner_fin_mode(he_ctx *c, hipStream_t st, double bytes, unsigned grid, bool integer, const InnerArgs &ia,
-                                  const FinishArgs &fa, const OpArgs &oa)
+static void launch_inner_fin_mode(he_ctx *c, hipStream_t st, double bytes, unsigned grid, int path, const InnerArgs &ia, const FinishArgs &fa,
+                                  const OpArgs &oa)
 {
-    if (integer)
-        KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_inner_fin<LOGN, MODE, true>), grid, INNER_THREADS, ia, fa, c->dev, oa);
+    if (path == FIN_FP)
+        KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_inner_fin<LOGN, MODE, FIN_FP>), grid, INNER_THREADS, ia, fa, c->dev, oa);
+    else if (path == FIN_INT)
+        KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_inner_fin<LOGN, MODE, FIN_INT>), grid, INNER_THREADS, ia, fa, c->dev, oa);
     else
-        KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_inner_fin<LOGN, MODE, false>), grid, INNER_THREADS, ia, fa, c->dev, oa);
+        KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_inner_fin<LOGN, MODE, FIN_BOTH>), grid, INNER_THREADS, ia, fa, c->dev, oa);
 }
 template <int LOGN>
-static void launch_inner_fin(he_ctx *c, hipStream_t st, double bytes, unsigned grid, int mode, bool integer, const InnerArgs &ia,
-                             const FinishArgs &fa, const OpArgs &oa)
+static void launch_inner_fin(he_ctx *c, hipStream_t st, double bytes, unsigned grid, int mode, int path, const InnerArgs &ia, const FinishArgs &fa,
+                             const OpArgs &oa)
 {
     if (mode == FIN_MULT)
-        launch_inner_fin_mode<LOGN, FIN_MULT>(c, st, bytes, grid, integer, ia, fa, oa);
+        launch_inner_fin_mode<LOGN, FIN_MULT>(c, st, bytes, grid, path, ia, fa, oa);
     else if (mode == FIN_ROT)
-        launch_inner_fin_mode<LOGN, FIN_ROT>(c, st, bytes, grid, integer, ia, fa, oa);
+        launch_inner_fin_mode<LOGN, FIN_ROT>(c, st, bytes, grid, path, ia, fa, oa);
     else
-        launch_inner_fin_mode<LOGN, FIN_ROTSUM>(c, st, bytes, grid, integer, ia, fa, oa);
+        launch_inner_fin_mode<LOGN, FIN_ROTSUM>(c, st, bytes, grid, path, ia, fa, oa);
 }
