@@ -177,7 +177,7 @@ extern "C" int32_t he_evk_to_host(const he_evk *evk, uint64_t *h_out)
 static const char *const kKernelNames[KID_COUNT] = {
     "k_ntt_fwd_cols", "k_ntt_fwd_cols_modup", "k_ntt_fwd_cols_moddown", "k_ntt_fwd_cols_rescale", "k_ntt_fwd_cols_moddown_rescale",
     "k_ntt_fwd_blocks",
-    "k_ntt_fwd_blocks_fin", "k_ntt_inv_blocks", "k_ntt_inv_cols", "k_limbwise", "k_cmult", "k_inner_blocks", "k_inner_fin"};
+    "k_ntt_fwd_blocks_fin", "k_ntt_inv_blocks", "k_ntt_inv_cols", "k_limbwise", "k_cmult", "k_inner_blocks", "k_inner_finished", "k_inner_fin"};
 
 bool prof_events(he_ctx *c, int kid, double bytes, ProfRecord &r)
 {
@@ -334,11 +334,11 @@ static const OpArgs kNoOps = {};
 // limb's own content, or a base conversion of cv.src); with fin != nullptr the block pass writes
 // (u - ntt) * const + addend to fin->out instead of the transform itself.
 // src_limbs = number of source limbs the prologue reads in total (for the byte count).
-// blocks: the limbs whose block pass runs here (the others are finished by the kernel that consumes them): all, the
-// ciphertext limbs on the integer path, these and the special limbs on that path, or none.
-enum { BLOCKS_ALL, BLOCKS_INT, BLOCKS_INT_SPECIAL, BLOCKS_NONE };
+// blocks: the limbs whose block pass runs here (the others are finished by the kernel that consumes them): all, none, or
+// the ciphertext limbs on the integer path and every limb with a modulus index from finish_from on.
+enum { BLOCKS_ALL, BLOCKS_SOME, BLOCKS_NONE };
 static int32_t ntt_forward(he_ctx *c, hipStream_t st, u64 *data, const LimbList &l, int pro, const ConvArgs &cv,
-                           const FinArgs *fin, int src_limbs, int blocks = BLOCKS_ALL)
+                           const FinArgs *fin, int src_limbs, int blocks = BLOCKS_ALL, int finish_from = 0)
 {
     const bool wide = std::max(c->alpha, c->K) > 4;
     const double N8 = (double)c->N * 8.0;
@@ -362,12 +362,11 @@ static int32_t ntt_forward(he_ctx *c, hipStream_t st, u64 *data, const LimbList 
         } else if (blocks == BLOCKS_ALL)
             dl.fwd_blocks(c, st, 2.0 * nb * N8, false, data, lb, nb, kNoFin);
     });
-    if (rc != HE_OK || blocks == BLOCKS_ALL || blocks == BLOCKS_NONE || dl.fwd_limb[pro]) return rc;
-    // block pass of the integer-path limbs alone, after all column passes: few launches, each as large as possible;
-    // k_inner_special finishes the special limbs
+    if (rc != HE_OK || blocks != BLOCKS_SOME || dl.fwd_limb[pro]) return rc;
+    // after all column passes: few launches, each as large as possible
     LimbList li;
     for (int b = 0; b < l.size(); b++)
-        if (c->modc[l.mod[b]].qd == 0.0 && (blocks == BLOCKS_INT_SPECIAL || l.mod[b] < c->L)) li.add(l.slot[b], l.src[b], l.mod[b]);
+        if (l.mod[b] >= finish_from || (c->modc[l.mod[b]].qd == 0.0 && l.mod[b] < c->L)) li.add(l.slot[b], l.src[b], l.mod[b]);
     return for_batches(c, li, [&](const LimbBatch &lb, int nb) {
         dl.fwd_blocks(c, st, 2.0 * nb * N8, false, data, lb, nb, kNoFin);
     });
@@ -616,12 +615,33 @@ extern "C" int32_t he_workspace_bytes(const he_ctx *ctx, int32_t level, int32_t 
 // limb slots are 16-bit offsets from a buffer's base
 static bool batch_fits(const WsLayout &w, int count) { return count >= 1 && w.total * (size_t)count <= 65535; }
 
+// Whether the block pass of the raised limbs from active limb `first` on runs ahead of the first inner-product launch
+// (k_inner_finished), rather than inside it (k_inner_special).  Digits that three or more rotations share: yes (N = 2^16, 15 rotations at
+// level 24 1106 -> 1029 us, 4 at level 6 129 -> 126, 2 99 -> 102).  Otherwise k_inner_special is the faster one as long as its launch leaves
+// the chip part empty or its four waves have a digit each in every round: at level 13 (four digits) 8 rotations take 445 us, not
+// 460, at level 24 (six) 852, not 859.  It loses in launches of four and more work-groups per compute unit where half of the waves
+// have none (one or two digits: 8 rotations at level 4 170 -> 162 us, at level 8 259 -> 255, 4 at level 4 of N = 2^17 172 -> 165), and in a Mult
+// with rescale, whose dropped limb takes its registers for the tensor product, where a quarter has none (16 at level 24 1861 -> 1840).
+// Special limbs on the floating-point path (none of 2^50 or above) are cheap to finish: k_inner_special (8 rotations 267 us, not 282).
+static bool special_finished(const he_ctx *c, int level, int first, int count, bool shared)
+{
+    if (dev_launch(c).inner_limb) return false; // N = 2^12: every raised limb is finished
+    if (shared) return count > 2;
+    bool ints = false;
+    for (int k = 0; k < c->K; k++) ints |= c->modc[c->L + k].qd == 0.0;
+    const size_t groups = (size_t)(level + c->K - first) * count * (c->N / SPECIAL_TILE);
+    const int beta = (level + c->alpha - 1) / c->alpha, rounds = (beta + SPECIAL_WAVES - 1) / SPECIAL_WAVES, idle = rounds * SPECIAL_WAVES - beta;
+    return ints && groups >= 1024 && idle * (first < level ? 4 : 2) >= rounds * SPECIAL_WAVES;
+}
+// the modulus index from which on ks_raise finishes raised limbs
+static int finish_from(const he_ctx *c, int level, int first, bool finished) { return !finished ? c->M : first < level ? first : c->L; }
+
 // Steps 1-2 of the key switch for `count` polynomials (d_ntt2: products of two): operation o reads its NTT-domain input at
-// d_ntt + o*d_stride limbs and works in ws + o*w.total limbs.  Raised limbs on the floating-point path
-// and special ones are left as the column pass wrote them (the inner-product kernels finish them), unless
-// `finish_special`: then the block pass is applied to the special limbs on the integer path.
+// d_ntt + o*d_stride limbs and works in ws + o*w.total limbs.  Raised ciphertext limbs on the floating-point path
+// and special ones are left as the column pass wrote them (the inner-product kernels finish them), but for those of
+// modulus index finish_at and above.
 static int32_t ks_raise(he_ctx *c, const u64 *d_ntt, int d_stride, u64 *ws, const WsLayout &w, int level, int count,
-                        hipStream_t st, bool finish_special = false, const u64 *d_ntt2 = nullptr)
+                        hipStream_t st, int finish_at, const u64 *d_ntt2 = nullptr)
 {
     const size_t N = c->N;
     const int K = c->K, Ma = level + K, beta = (level + c->alpha - 1) / c->alpha, W = (int)w.total;
@@ -640,18 +660,18 @@ static int32_t ks_raise(he_ctx *c, const u64 *d_ntt, int d_stride, u64 *ws, cons
                 r.add(o * W + j * Ma + a, a < level ? a : c->L + (a - level));
             }
         }
-    return ntt_forward(c, st, ws + w.raised * N, r, PRO_MODUP, cv, nullptr, level * count, finish_special ? BLOCKS_INT_SPECIAL : BLOCKS_INT);
+    return ntt_forward(c, st, ws + w.raised * N, r, PRO_MODUP, cv, nullptr, level * count, BLOCKS_SOME, finish_at);
 }
 
 static InnerArgs inner_args(const he_ctx *c, const he_evk *evk, const u64 *d_ntt, int d_stride, u64 *ws, const WsLayout &w,
-                            int level, int count, const OpArgs *oa, bool shared_raised)
+                            int level, int count, const OpArgs *oa, bool shared_raised, bool finished)
 {
     InnerArgs ia;
     ia.raised = ws + w.raised * c->N, ia.d = d_ntt, ia.evk = evk->dev, ia.u = ws + w.u * c->N;
     ia.level = level, ia.L = c->L, ia.K = c->K, ia.alpha = c->alpha, ia.first = level;
     ia.g = (unsigned)evk->galois;
     ia.raised_stride = shared_raised ? 0 : (int)w.total, ia.u_stride = (int)w.total, ia.d_stride = d_stride;
-    ia.per_op = oa ? 1 : 0, ia.count = count, ia.finished = shared_raised ? 1 : 0;
+    ia.per_op = oa ? 1 : 0, ia.count = count, ia.finished = finished ? 1 : 0;
     ia.ta = ia.tb = nullptr, ia.t_stride = 0;
     return ia;
 }
@@ -794,9 +814,10 @@ static int32_t mult_copy(he_ctx *c, const MultOut &mo, u64 *out, int out_limbs, 
     HIP_TRY(c, hipMemcpy2DAsync(out, row, mo.out, (size_t)mo.stride * c->N * sizeof(u64), row, (size_t)count, hipMemcpyDeviceToDevice, st));
     return HE_OK;
 }
-static InnerArgs mult_args(const he_ctx *c, const he_evk *relin, const u64 *a, const u64 *b, u64 *ws, const WsLayout &w, int level, int count)
+static InnerArgs mult_args(const he_ctx *c, const he_evk *relin, const u64 *a, const u64 *b, u64 *ws, const WsLayout &w, int level, int count,
+                           bool finished)
 {
-    InnerArgs ia = inner_args(c, relin, a, 0, ws, w, level, count, nullptr, false);
+    InnerArgs ia = inner_args(c, relin, a, 0, ws, w, level, count, nullptr, false, finished);
     ia.ta = a, ia.tb = b, ia.t_stride = 2 * level;
     return ia;
 }
@@ -814,8 +835,11 @@ extern "C" int32_t he_hmult_relin_batch(he_ctx *ctx, const he_evk *relin, const 
     const WsLayout w = ws_layout(ctx, level);
     const size_t N = ctx->N;
     const MultOut mo = mult_out(ctx, d_a, d_b, d_out, ws + w.tmp * N, (int)w.total, 2 * level, 2 * level, count);
-    if ((rc = ks_raise(ctx, d_a + (size_t)level * N, 2 * level, ws, w, level, count, st, false, d_b + (size_t)level * N)) != HE_OK) return rc;
-    if ((rc = ks_apply(ctx, mult_args(ctx, relin, d_a, d_b, ws, w, level, count), nullptr, ws, w,
+    const bool finished = special_finished(ctx, level, level, count, false);
+    if ((rc = ks_raise(ctx, d_a + (size_t)level * N, 2 * level, ws, w, level, count, st, finish_from(ctx, level, level, finished),
+                       d_b + (size_t)level * N)) != HE_OK)
+        return rc;
+    if ((rc = ks_apply(ctx, mult_args(ctx, relin, d_a, d_b, ws, w, level, count, finished), nullptr, ws, w,
                        finish_args(ctx, mo.out, mo.stride, nullptr, 0, 0, level), FIN_MULT, st)) != HE_OK)
         return rc;
     return mult_copy(ctx, mo, d_out, 2 * level, count, st);
@@ -846,9 +870,13 @@ extern "C" int32_t he_hmult_relin_rescale_batch(he_ctx *ctx, const he_evk *relin
     const size_t N = ctx->N;
     const int W = (int)w.total, K = ctx->K, Ma = level + K, L = ctx->L;
     const MultOut mo = mult_out(ctx, d_a, d_b, d_out, ws + w.tmp * N, W, 2 * level, 2 * (level - 1), count);
-    if ((rc = ks_raise(ctx, d_a + (size_t)level * N, 2 * level, ws, w, level, count, st, false, d_b + (size_t)level * N)) != HE_OK) return rc;
-    InnerArgs ia = mult_args(ctx, relin, d_a, d_b, ws, w, level, count);
-    ia.first = level - 1; // the dropped limb as well
+    const int first = level - 1; // the dropped limb goes with the special ones
+    const bool finished = special_finished(ctx, level, first, count, false);
+    if ((rc = ks_raise(ctx, d_a + (size_t)level * N, 2 * level, ws, w, level, count, st, finish_from(ctx, level, first, finished),
+                       d_b + (size_t)level * N)) != HE_OK)
+        return rc;
+    InnerArgs ia = mult_args(ctx, relin, d_a, d_b, ws, w, level, count, finished);
+    ia.first = first;
     if ((rc = ks_special(ctx, ia, nullptr, w, st)) != HE_OK) return rc;
     u64 *rbuf = ws + w.r * N;
     ConvArgs cv = conv_args(ctx, ws + w.u * N, level, W, W);
@@ -897,8 +925,8 @@ extern "C" int32_t he_hrot_many(he_ctx *ctx, const he_evk *const *rots, int32_t 
     u64 *ws = (u64 *)d_ws;
     const WsLayout w = ws_layout(ctx, level);
     const u64 *c1 = d_ct + (size_t)level * ctx->N;
-    // every rotation reads the same digits: their special limbs are finished once
-    if ((rc = ks_raise(ctx, c1, 0, ws, w, level, 1, st, true)) != HE_OK) return rc;
+    const bool finished = special_finished(ctx, level, level, count, true);
+    if ((rc = ks_raise(ctx, c1, 0, ws, w, level, 1, st, finish_from(ctx, level, level, finished))) != HE_OK) return rc;
     // With workspace for several operations the rotations share every launch: operation o keeps its inner
     // products and ModDown corrections in workspace o, all read the raised digits of workspace 0.
     int fit = (int)std::min<size_t>(ws_bytes / (w.total * ctx->N * sizeof(u64)), HE_OPS_MAX);
@@ -910,7 +938,7 @@ extern "C" int32_t he_hrot_many(he_ctx *ctx, const he_evk *const *rots, int32_t 
             oa.evk[o] = rots[r + o]->dev, oa.g[o] = (unsigned)rots[r + o]->galois;
             oa.d[o] = c1, oa.add[o] = d_ct, oa.out[o] = h_d_outs[r + o];
         }
-        if ((rc = ks_apply(ctx, inner_args(ctx, rots[r], c1, 0, ws, w, level, nb, &oa, true), &oa, ws, w,
+        if ((rc = ks_apply(ctx, inner_args(ctx, rots[r], c1, 0, ws, w, level, nb, &oa, true, finished), &oa, ws, w,
                            finish_args(ctx, nullptr, 0, d_ct, 0, level, level), FIN_ROT, st)) != HE_OK)
             return rc;
         r += nb;
@@ -930,8 +958,9 @@ static int32_t hrot_batch_to(he_ctx *ctx, const he_evk *rot, const u64 *d_ct, in
     u64 *ws = (u64 *)d_ws;
     const WsLayout w = ws_layout(ctx, level);
     const u64 *c1 = d_ct + (size_t)level * ctx->N;
-    if ((rc = ks_raise(ctx, c1, in_stride, ws, w, level, count, st)) != HE_OK) return rc;
-    return ks_apply(ctx, inner_args(ctx, rot, c1, in_stride, ws, w, level, count, nullptr, false), nullptr, ws, w,
+    const bool finished = special_finished(ctx, level, level, count, false);
+    if ((rc = ks_raise(ctx, c1, in_stride, ws, w, level, count, st, finish_from(ctx, level, level, finished))) != HE_OK) return rc;
+    return ks_apply(ctx, inner_args(ctx, rot, c1, in_stride, ws, w, level, count, nullptr, false, finished), nullptr, ws, w,
                     finish_args(ctx, d_out, out_stride, d_ct, in_stride, level, level), plus_input ? FIN_ROTSUM : FIN_ROT, st);
 }
 
@@ -979,13 +1008,14 @@ extern "C" int32_t he_hrot_batch_keys(he_ctx *ctx, const he_evk *const *rots, co
     for (int r = 0; r < count;) {
         const int nb = std::min(fit, count - r);
         const u64 *in = d_ct + (size_t)r * ct_limbs * N, *c1 = in + (size_t)level * N;
-        if ((rc = ks_raise(ctx, c1, ct_limbs, ws, w, level, nb, st)) != HE_OK) return rc;
+        const bool finished = special_finished(ctx, level, level, nb, false);
+        if ((rc = ks_raise(ctx, c1, ct_limbs, ws, w, level, nb, st, finish_from(ctx, level, level, finished))) != HE_OK) return rc;
         OpArgs oa = {};
         for (int o = 0; o < nb; o++) {
             oa.evk[o] = rots[r + o]->dev, oa.g[o] = (unsigned)rots[r + o]->galois;
             oa.out[o] = d_out + (size_t)(r + o) * ct_limbs * N;
         }
-        if ((rc = ks_apply(ctx, inner_args(ctx, rots[r], c1, ct_limbs, ws, w, level, nb, &oa, false), &oa, ws, w,
+        if ((rc = ks_apply(ctx, inner_args(ctx, rots[r], c1, ct_limbs, ws, w, level, nb, &oa, false, finished), &oa, ws, w,
                            finish_args(ctx, nullptr, 0, in, ct_limbs, level, level), FIN_ROT, st)) != HE_OK)
             return rc;
         r += nb;
@@ -1049,6 +1079,7 @@ extern "C" int32_t he_hrot_batch_levels(he_ctx *ctx, const he_evk *const *rots, 
             for (int i = 0; i < h_levels[r + o]; i++) l.add(o * W + i, (int)(off[o] + h_levels[r + o] + i), i);
         if ((rc = ntt_inverse(ctx, st, in0, ws + w.x * N, l, SCALE_MODUP, cv)) != HE_OK) return rc;
         // 2. raised digits
+        const bool finished = special_finished(ctx, lmax, lmax, nb, false);
         LimbList rl;
         int src_limbs = 0;
         for (int o = 0; o < nb; o++) {
@@ -1062,10 +1093,11 @@ extern "C" int32_t he_hrot_batch_levels(he_ctx *ctx, const he_evk *const *rots, 
                 }
             }
         }
-        if ((rc = ntt_forward(ctx, st, ws + w.raised * N, rl, PRO_MODUP, cv, nullptr, src_limbs, BLOCKS_INT)) != HE_OK) return rc;
+        if ((rc = ntt_forward(ctx, st, ws + w.raised * N, rl, PRO_MODUP, cv, nullptr, src_limbs, BLOCKS_SOME, finish_from(ctx, lmax, lmax, finished))) != HE_OK)
+            return rc;
         // 3 - 6
         if (misaligned16(ws)) return HE_EINVAL;
-        if ((rc = ks_apply(ctx, inner_args(ctx, rots[r], in0, 0, ws, w, lmax, nb, &oa, false), &oa, ws, w,
+        if ((rc = ks_apply(ctx, inner_args(ctx, rots[r], in0, 0, ws, w, lmax, nb, &oa, false, finished), &oa, ws, w,
                            finish_args(ctx, nullptr, 0, in0, 0, lmax, lmax), FIN_ROT, st)) != HE_OK)
             return rc;
         done_limbs += off[nb];

@@ -12,9 +12,9 @@
 // these outputs are the indices of one input tile of that size.  For a limb on the floating-point path the raised
 // digits arrive as the column pass left them; each is finished here (stages logN-8 .. logN-1) into LDS
 // and read back through the index map, so the transformed digits never travel to memory.  Ciphertext limbs on
-// the integer path read digits that the block-pass kernel has finished (the special ones finish theirs here too).
+// the integer path read digits that the block-pass kernel has finished.
 //
-// Two launches make a key switch's inner product.  The first (k_inner_special) takes the special limbs, whose
+// Two launches make a key switch's inner product.  The first (k_inner_special, k_inner_finished) takes the special limbs, whose
 // results leave it with the block pass of their inverse transform already applied.  The second (k_inner_fin) runs
 // after the ModDown corrections r have been through their column pass: it forms u on the ciphertext limbs, finishes
 // the transform of r the way it finishes a digit, and writes (u - r) * const + addend, so that u never travels to
@@ -32,11 +32,11 @@ struct InnerArgs {
     const u64 *ta, *tb;
     u64 *u;
     int level, L, K, alpha;
-    int first; // k_inner_special: the lowest active limb it works on (level: the special limbs alone)
+    int first; // the lowest active limb of the first launch (level: the special limbs alone)
     unsigned g;
     int raised_stride, u_stride, d_stride, t_stride; // limbs between two operations of a batch in each buffer
     int per_op; // operation z uses entry z of the OpArgs argument
-    int finished; // the raised special limbs on the integer path have been through their block pass
+    int finished; // the raised limbs from `first` on have been through their block pass: k_inner_finished in place of k_inner_special
     int count;  // operations in this launch
 };
 // What differs between the operations of one launch, when anything but their place in the buffers does.
@@ -389,17 +389,23 @@ __device__ __forceinline__ void inner_products_int(const InnerArgs &ia, const Op
 // ---- first launch: the special limbs ------------------------------------------------------------------------------------
 //
 // Few limbs (K per operation) with the most work per word: the special primes are on the integer path, whose block pass
-// takes about three times the instructions of the floating-point one, so what a wave of k_inner_fin does alone is shared
-// out here: a work-group of four waves makes SPECIAL_TILE outputs of both components, and in each round every wave finishes
+// takes about three times the instructions of the floating-point one.  Two forms, chosen by special_finished() in device.hip:
+//
+// k_inner_special, for launches that leave the chip part empty: what a wave of k_inner_fin does alone is shared
+// out: a work-group of four waves makes SPECIAL_TILE outputs of both components, and in each round every wave finishes
 // the transform of another digit (16 lanes a block of 256, 16 elements per lane, the steps of k_ntt_fwd_blocks) into LDS;
 // then all threads multiply the digits of the round, read through the index map, with the key.  One operation
-// alone then has four digits in work at a time, and the finished digits never travel to memory (but where several
-// operations share their digits, k_ntt_fwd_blocks finishes them once for all: `finished`).  The result leaves with the
-// block pass of its inverse transform applied.
-// Bound by the chain of a round (load, two steps with their twiddles, exchange, products) in small launches: at N = 2^16 it
-// takes 19 us for one operation, where the block pass as a launch of its own and the products after it took 10 + 17;
-// one rotation at level 13 110.8 -> 105.4 us, one product at level 6 132.8 -> 129.9.  Large launches gain nothing (32 mixed
-// rotations: 390 us, in two launches 172 + 182; the calls as a whole take the same within 0.3 %).
+// alone then has four digits in work at a time, and the finished digits never travel to memory.
+// Bound by the chain of a round (load, two steps with their twiddles, exchange, products): at N = 2^16 it
+// takes 19 us for one operation, where the block pass as a launch of its own and the products after it took 10 + 17.
+//
+// k_inner_finished, for launches that fill it and for digits that several operations share: k_ntt_fwd_blocks finishes the
+// digits, each thread reads them through the index map straight into its sums, without LDS and without a barrier.
+// Of 16 products at level 24 (the dropped limb among them) the two launches take 143 + 142 us; with k_inner_special 293.  32 rotations of mixed
+// levels take 359 us in k_inner_special, as much as in two launches of this form (170 + 183); with 168 registers and some of them in
+// scratch memory it was 407.
+//
+// The result leaves either with the block pass of its inverse transform applied.
 #define SPECIAL_THREADS 256
 #define SPECIAL_WAVES (SPECIAL_THREADS / 64)
 #define SPECIAL_TLOG 10
@@ -415,16 +421,14 @@ __device__ __forceinline__ void special_products(const InnerArgs &ia, const OpAr
                                                  int a, unsigned g, int beta, unsigned mi, const ModConst &m, const A &ar, u64 *lds,
                                                  u64 (&r0)[4], u64 (&r1)[4])
 {
-    const int own = a < ia.level ? a / ia.alpha : -1, M = ia.L + ia.K, Ma = ia.level + ia.K;
+    const int own = MULT && a < ia.level ? a / ia.alpha : -1, M = ia.L + ia.K, Ma = ia.level + ia.K; // the dropped limb of a Mult
     const unsigned tile_in = g == 1 ? tile : galois_index(tile << SPECIAL_TLOG, g, LOGN) >> SPECIAL_TLOG;
     const char *key0 = (const char *)((ia.per_op ? oa.evk[op] : ia.evk) + (((size_t)mi << LOGN) + ((size_t)tile << SPECIAL_TLOG)));
-    const u64 *d_limb = (ia.per_op && oa.d[op] ? oa.d[op] : ia.d + (((size_t)op * ia.d_stride) << LOGN)) + ((size_t)a << LOGN);
     const u64 *raised0 = ia.raised + ((((size_t)op * ia.raised_stride + a) << LOGN) + ((size_t)tile_in << SPECIAL_TLOG));
     const size_t raised_step = (size_t)Ma << LOGN, comp_step = ((size_t)M << LOGN) * 8, key_step = 2 * comp_step;
     const unsigned wave = wave_id(), lane = threadIdx.x & 63u, blk = lane >> 4, il = lane & 15u, bg = tile_in * 4 + blk;
     // an integer-path ciphertext limb (the one a rescale drops) has been finished with the other ciphertext limbs
-    const bool finished = !A::IS_FP && (a < ia.level || ia.finished);
-    const bool shared = ia.raised_stride == 0; // digits that every operation reads stay in L2
+    const bool finished = MULT && !A::IS_FP && a < ia.level;
     unsigned sr[2], lx[2], ly[2]; // sources of the pairs: index in the limb, LDS words of the even and the odd element
 #pragma unroll
     for (int i = 0; i < 2; i++) {
@@ -453,7 +457,7 @@ __device__ __forceinline__ void special_products(const InnerArgs &ia, const OpAr
             u64 *dig = lds + wave * SPECIAL_DIGIT;
             u64 x[16];
 #pragma unroll
-            for (int k = 0; k < 16; k++) x[k] = shared ? in[16 * k] : __builtin_nontemporal_load(in + 16 * k);
+            for (int k = 0; k < 16; k++) x[k] = __builtin_nontemporal_load(in + 16 * k);
             if (finished) {
 #pragma unroll
                 for (int k = 0; k < 16; k++) dig[tile_at(blk, il + 16 * k)] = x[k];
@@ -494,9 +498,6 @@ __device__ __forceinline__ void special_products(const InnerArgs &ia, const OpAr
                         x = tensor_mac(m, p.a0.x, p.a1.x, p.b0.x, p.b1.x, P, s0[2 * i], s1[2 * i]);
                         y = tensor_mac(m, p.a0.y, p.a1.y, p.b0.y, p.b1.y, P, s0[2 * i + 1], s1[2 * i + 1]);
                     }
-                } else if (j == own) {
-                    const u64x2 v = ld_at<u64x2>(d_limb, (sr[i] & ~1u) * 8u);
-                    x = sr[i] & 1u ? v.y : v.x, y = sr[i] & 1u ? v.x : v.y;
                 } else
                     x = dig[lx[i]], y = dig[ly[i]];
                 if constexpr (A::IS_FP) { // key words are balanced doubles
@@ -557,37 +558,130 @@ __device__ __forceinline__ void special_inverse(const u64 (&r0)[4], const u64 (&
     for (int k = 0; k < 16; k++) limb[bg * 256 + il + 16 * k] = ar.store_mid(v[k]);
 }
 
+// What both forms do with their sums: u on a ciphertext limb, the inverse block pass on a special one.
+template <int LOGN, class A>
+__device__ __forceinline__ void special_result(const InnerArgs &ia, const InnerTile &w, const u64 (&r0)[4], const u64 (&r1)[4], const A &ar, u64 *lds)
+{
+    u64 *u0 = ia.u + (((size_t)w.op * ia.u_stride + w.a) << LOGN);
+    const size_t comp_words = (size_t)(ia.level + ia.K) << LOGN;
+    if (w.a >= ia.level) {
+        special_inverse<LOGN>(r0, r1, u0, comp_words, ar, lds, w.tile);
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        char *o = (char *)(u0 + ((size_t)w.tile << SPECIAL_TLOG)) + 4096 * i + threadIdx.x * 16u;
+        __builtin_nontemporal_store(u64x2{r0[2 * i], r0[2 * i + 1]}, (u64x2 *)o);
+        __builtin_nontemporal_store(u64x2{r1[2 * i], r1[2 * i + 1]}, (u64x2 *)(o + comp_words * 8));
+    }
+}
+
 // Active limbs ia.first .. level + K - 1 of every operation.  The same order of work-groups as k_inner_fin.
 // MULT: of a Mult with rescale, whose dropped limb takes d0, d1 and d2 (a kernel of its own: with their code in every launch
 // 32 mixed rotations at N = 2^16 took 2388 us instead of 2342)
-template <int LOGN, bool MULT> __global__ __launch_bounds__(SPECIAL_THREADS, 3) void k_inner_special(InnerArgs ia, DevTables T, OpArgs oa)
+template <int LOGN, bool MULT> __global__ __launch_bounds__(SPECIAL_THREADS, 2) void k_inner_special(InnerArgs ia, DevTables T, OpArgs oa)
 {
     __shared__ u64 lds[SPECIAL_WAVES * SPECIAL_DIGIT];
     static_assert(SPECIAL_TILE == INNER_TILE, "inner_grid and inner_tile serve both kernels");
-    const int Ma = ia.level + ia.K;
-    const InnerTile w = inner_tile<LOGN>(ia, oa, Ma - ia.first, ia.first);
+    const InnerTile w = inner_tile<LOGN>(ia, oa, ia.level + ia.K - ia.first, ia.first);
     if (w.none) return;
     const int mi = active_mod(w.a, ia.level, ia.L);
     const ModConst m = T.mod[mi];
-    u64 *u0 = ia.u + (((size_t)w.op * ia.u_stride + w.a) << LOGN);
-    const size_t comp_words = (size_t)Ma << LOGN;
     u64 r0[4], r1[4];
     if (m.qd != 0.0) {
         const ArithFp ar = make_fp(T, mi, LOGN);
         special_products<LOGN, MULT>(ia, oa, T, w.op, w.tile, w.a, w.g, w.beta, mi, m, ar, lds, r0, r1);
-        if (w.a >= ia.level) special_inverse<LOGN>(r0, r1, u0, comp_words, ar, lds, w.tile);
+        special_result<LOGN>(ia, w, r0, r1, ar, lds);
     } else {
         const ArithInt ar = make_int(T, mi, LOGN);
         special_products<LOGN, MULT>(ia, oa, T, w.op, w.tile, w.a, w.g, w.beta, mi, m, ar, lds, r0, r1);
-        if (w.a >= ia.level) special_inverse<LOGN>(r0, r1, u0, comp_words, ar, lds, w.tile);
+        special_result<LOGN>(ia, w, r0, r1, ar, lds);
     }
-    if (w.a < ia.level) {
+}
+
+// The sums of a thread's pairs as in special_products, from digits in the NTT domain.
+template <int LOGN, bool MULT, class A>
+__device__ __forceinline__ void finished_products(const InnerArgs &ia, const OpArgs &oa, const DevTables &T, const InnerTile &w, unsigned mi,
+                                                  const ModConst &m, const A &ar, u64 (&r0)[4], u64 (&r1)[4])
+{
+    const int own = MULT && w.a < ia.level ? w.a / ia.alpha : -1, M = ia.L + ia.K, Ma = ia.level + ia.K;
+    const char *key0 = (const char *)((ia.per_op ? oa.evk[w.op] : ia.evk) + (((size_t)mi << LOGN) + ((size_t)w.tile << SPECIAL_TLOG)));
+    const char *dig0 = (const char *)(ia.raised + (((size_t)w.op * ia.raised_stride + w.a) << LOGN));
+    const size_t dig_step = ((size_t)Ma << LOGN) * 8, comp_step = ((size_t)M << LOGN) * 8, key_step = 2 * comp_step;
+    unsigned sr[2];
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        const unsigned pos = (w.tile << SPECIAL_TLOG) + 512u * i + 2u * threadIdx.x;
+        sr[i] = w.g == 1 ? pos : galois_index(pos, w.g, LOGN);
+    }
+    double f0[4], f1[4];
+    U128 s0[4], s1[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) f0[k] = f1[k] = 0.0, s0[k] = s1[k] = U128{0, 0};
+    for (int j = 0; j < w.beta; j++) {
+        const char *kj = key0 + (size_t)j * key_step;
 #pragma unroll
         for (int i = 0; i < 2; i++) {
-            char *o = (char *)(u0 + ((size_t)w.tile << SPECIAL_TLOG)) + 4096 * i + threadIdx.x * 16u;
-            __builtin_nontemporal_store(u64x2{r0[2 * i], r0[2 * i + 1]}, (u64x2 *)o);
-            __builtin_nontemporal_store(u64x2{r1[2 * i], r1[2 * i + 1]}, (u64x2 *)(o + comp_words * 8));
+            const u64x2 ka = ld_at<u64x2>(kj + 4096 * i, threadIdx.x * 16u), kb = ld_at<u64x2>(kj + comp_step + 4096 * i, threadIdx.x * 16u);
+            u64 x, y;
+            if (MULT && j == own) { // g = 1: the pair itself
+                const TensorPair p = tensor_pair<LOGN>(ia, w.op, w.a, sr[i]);
+                if constexpr (A::IS_FP) {
+                    const double P = T.dn_pmod_d[w.a];
+                    x = ar.store_final(tensor_mac(ar, p.a0.x, p.a1.x, p.b0.x, p.b1.x, P, f0[2 * i], f1[2 * i]));
+                    y = ar.store_final(tensor_mac(ar, p.a0.y, p.a1.y, p.b0.y, p.b1.y, P, f0[2 * i + 1], f1[2 * i + 1]));
+                } else {
+                    const u64 P = T.dn_pmod[w.a];
+                    x = tensor_mac(m, p.a0.x, p.a1.x, p.b0.x, p.b1.x, P, s0[2 * i], s1[2 * i]);
+                    y = tensor_mac(m, p.a0.y, p.a1.y, p.b0.y, p.b1.y, P, s0[2 * i + 1], s1[2 * i + 1]);
+                }
+            } else {
+                const u64x2 v = ld_at<u64x2>(dig0 + (size_t)j * dig_step, (sr[i] & ~1u) * 8u);
+                x = sr[i] & 1u ? v.y : v.x, y = sr[i] & 1u ? v.x : v.y;
+            }
+            if constexpr (A::IS_FP) { // key words are balanced doubles
+                const double xd = u2d(x), yd = u2d(y);
+                f0[2 * i] += ar.mulmod(xd, ar.load_mid(ka.x)), f0[2 * i + 1] += ar.mulmod(yd, ar.load_mid(ka.y));
+                f1[2 * i] += ar.mulmod(xd, ar.load_mid(kb.x)), f1[2 * i + 1] += ar.mulmod(yd, ar.load_mid(kb.y));
+            } else {
+                mac128(s0[2 * i], x, ka.x);
+                mac128(s0[2 * i + 1], y, ka.y);
+                mac128(s1[2 * i], x, kb.x);
+                mac128(s1[2 * i + 1], y, kb.y);
+            }
         }
+        if constexpr (A::IS_FP) {
+            if ((j & 3) == 3) {
+#pragma unroll
+                for (int k = 0; k < 4; k++) f0[k] = ar.reduce(f0[k]), f1[k] = ar.reduce(f1[k]);
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        if constexpr (A::IS_FP)
+            r0[k] = ar.store_final(f0[k]), r1[k] = ar.store_final(f1[k]);
+        else
+            r0[k] = reduce128(s0[k], m), r1[k] = reduce128(s1[k], m);
+    }
+}
+// The limbs of k_inner_special, in the same order.
+template <int LOGN, bool MULT> __global__ __launch_bounds__(SPECIAL_THREADS, 5) void k_inner_finished(InnerArgs ia, DevTables T, OpArgs oa)
+{
+    __shared__ u64 lds[2 * SPECIAL_DIGIT];
+    const InnerTile w = inner_tile<LOGN>(ia, oa, ia.level + ia.K - ia.first, ia.first);
+    if (w.none) return;
+    const int mi = active_mod(w.a, ia.level, ia.L);
+    const ModConst m = T.mod[mi];
+    u64 r0[4], r1[4];
+    if (m.qd != 0.0) {
+        const ArithFp ar = make_fp(T, mi, LOGN);
+        finished_products<LOGN, MULT>(ia, oa, T, w, mi, m, ar, r0, r1);
+        special_result<LOGN>(ia, w, r0, r1, ar, lds);
+    } else {
+        const ArithInt ar = make_int(T, mi, LOGN);
+        finished_products<LOGN, MULT>(ia, oa, T, w, mi, m, ar, r0, r1);
+        special_result<LOGN>(ia, w, r0, r1, ar, lds);
     }
 }
 

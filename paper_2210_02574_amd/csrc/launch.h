@@ -13,7 +13,7 @@
 enum KernelId {
     KID_FWD_COLS, KID_FWD_COLS_MODUP, KID_FWD_COLS_MODDOWN, KID_FWD_COLS_RESCALE, KID_FWD_COLS_MODDOWN_RS, KID_FWD_BLOCKS,
     KID_FWD_BLOCKS_FIN,
-    KID_INV_BLOCKS, KID_INV_COLS, KID_LIMBWISE, KID_CMULT, KID_INNER, KID_INNER_FIN, KID_COUNT
+    KID_INV_BLOCKS, KID_INV_COLS, KID_LIMBWISE, KID_CMULT, KID_INNER, KID_INNER_FINISHED, KID_INNER_FIN, KID_COUNT
 };
 
 // Creates the event pair of one profiled launch and appends it to the context's record list.
@@ -109,10 +109,18 @@ static void launch_inv_blocks(he_ctx *c, hipStream_t st, double bytes, const u64
 template <int LOGN>
 static void launch_inner(he_ctx *c, hipStream_t st, double bytes, unsigned grid, const InnerArgs &ia, const OpArgs &oa)
 {
-    if (ia.ta && ia.first < ia.level)
-        KLAUNCH_T(c, st, KID_INNER, bytes, (k_inner_special<LOGN, true>), grid, SPECIAL_THREADS, ia, c->dev, oa);
-    else
-        KLAUNCH_T(c, st, KID_INNER, bytes, (k_inner_special<LOGN, false>), grid, SPECIAL_THREADS, ia, c->dev, oa);
+    const bool mult = ia.ta && ia.first < ia.level; // the dropped limb of a Mult is among them
+    if (ia.finished) {
+        if (mult)
+            KLAUNCH_T(c, st, KID_INNER_FINISHED, bytes, (k_inner_finished<LOGN, true>), grid, SPECIAL_THREADS, ia, c->dev, oa);
+        else
+            KLAUNCH_T(c, st, KID_INNER_FINISHED, bytes, (k_inner_finished<LOGN, false>), grid, SPECIAL_THREADS, ia, c->dev, oa);
+    } else {
+        if (mult)
+            KLAUNCH_T(c, st, KID_INNER, bytes, (k_inner_special<LOGN, true>), grid, SPECIAL_THREADS, ia, c->dev, oa);
+        else
+            KLAUNCH_T(c, st, KID_INNER, bytes, (k_inner_special<LOGN, false>), grid, SPECIAL_THREADS, ia, c->dev, oa);
+    }
 }
 template <int LOGN, int MODE>
 static void launch_inner_fin_mode(he_ctx *c, hipStream_t st, double bytes, unsigned grid, int path, const InnerArgs &ia, const FinishArgs &fa,

@@ -118,3 +118,37 @@ def test_products_over_their_factors(env):
             factors()
             he.hmult_relin_batch(key, fa, fb, out=f)
             assert np.array_equal(he.to_host(f), prod), level
+
+
+# name -> (parameters, levels, counts): launches of the special limbs on both sides of the 1024 work-groups from which their digits are
+# finished ahead (64 per limb and operation at N = 2^16; one or two digits, or three with a dropped limb)
+BATCHES = {
+    "N16": (wl.N16, (4, 7), (3, 4)),
+    "mixed16": (SETS["mixed16"], (5, 6), (5, 8)),  # a dropped limb on either path
+    "float16": (wl.Params("float16", 16, wl.N16.q[:3], (wl.N16.q[3],), 3), (3,), (16,)),  # no special limb on the integer path
+}
+
+
+@pytest.mark.parametrize("name", BATCHES)
+def test_special_limbs_of_small_and_large_launches(oracle_mod, name):
+    import torch
+
+    import paper_2210_02574_amd as pkg
+
+    p, levels, counts = BATCHES[name]
+    he, o, evk = pkg.HE.from_params(p, device=0), oracle_mod.Oracle(p.logN, p.q, p.p, p.dnum), wl.uniform_evk(9, p)
+    relin, rot = he.evk_from_host(evk, 1), he.evk_from_host(evk, he.galois_element(3))
+    for level in levels:
+        host = [wl.uniform_ct(200 + 20 * level + i, p, level) for i in range(max(counts))]
+        dev = torch.stack([he.to_device(c) for c in host])
+        rotated = [o.hrot(c, evk, 3) for c in host]
+        products = [o.rescale(o.hmult_relin(host[i], host[i - 1], evk)) for i in range(len(host))]
+        for count in counts:
+            got = he.to_host(he.hrot_batch(rot, dev[:count]))
+            assert all(np.array_equal(got[i], rotated[i]) for i in range(count)), (level, count)
+            shifted = torch.roll(dev, 1, 0)[:count].contiguous()
+            got = he.to_host(he.hmult_relin_rescale_batch(relin, dev[:count], shifted))
+            assert all(np.array_equal(got[i], products[i]) for i in range(count)), (level, count)
+        for count in (2, 3):  # shared digits
+            for got in he.hrot_many([rot] * count, dev[0]):
+                assert np.array_equal(he.to_host(got), rotated[0]), (level, count)
