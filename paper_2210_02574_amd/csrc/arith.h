@@ -213,16 +213,16 @@ struct ArithFp {
     {
         fwd16_with(a, reduce_first, [&](int c) { return twf[step16_twiddle(s_base, G, (unsigned)c)]; });
     }
-    template <bool LAST> __device__ __forceinline__ void inv16(V (&a)[16], unsigned s_base, unsigned G) const
+    // tw(c) as in fwd16_with
+    template <bool LAST, class F> __device__ __forceinline__ void inv16_with(V (&a)[16], F tw) const
     {
 #pragma unroll
         for (int sp = 3; sp >= 0; sp--) {
             const int dist = 8 >> sp;
-            const unsigned idx0 = (1u << (s_base + sp)) + (G << sp);
 #pragma unroll
             for (int g = 0; g < (1 << sp); g++) {
                 const bool fin = LAST && sp == 0;
-                const double w = fin ? n1 : twi[idx0 + g];
+                const double w = fin ? n1 : tw((1 << sp) - 1 + g);
 #pragma unroll
                 for (int e = 0; e < dist; e++) {
                     const int k0 = g * 2 * dist + e, k1 = k0 + dist;
@@ -237,6 +237,10 @@ struct ArithFp {
                 }
             }
         }
+    }
+    template <bool LAST> __device__ __forceinline__ void inv16(V (&a)[16], unsigned s_base, unsigned G) const
+    {
+        inv16_with<LAST>(a, [&](int c) { return twi[step16_twiddle(s_base, G, (unsigned)c)]; });
     }
     // Three inverse stages on 8 elements (pairs 1, 2, 4 apart), tw as for fwd8_with; sums are reduced at the second and
     // third stage.  From |v| <= 1.6q it stays below 6.4q and ends below 1.6q.
@@ -374,16 +378,15 @@ struct ArithInt {
             }
         }
     }
-    template <bool LAST> __device__ __forceinline__ void inv16(V (&a)[16], unsigned s_base, unsigned G) const
+    template <bool LAST, class F> __device__ __forceinline__ void inv16_with(V (&a)[16], F tw) const
     {
 #pragma unroll
         for (int sp = 3; sp >= 0; sp--) {
             const int dist = 8 >> sp;
-            const unsigned idx0 = (1u << (s_base + sp)) + (G << sp);
 #pragma unroll
             for (int g = 0; g < (1 << sp); g++) {
                 const bool fin = LAST && sp == 0;
-                const ShoupConst w = fin ? n1 : twi[idx0 + g];
+                const ShoupConst w = fin ? n1 : tw((1 << sp) - 1 + g);
 #pragma unroll
                 for (int e = 0; e < dist; e++) {
                     const int k0 = g * 2 * dist + e, k1 = k0 + dist;
@@ -393,6 +396,10 @@ struct ArithInt {
                 }
             }
         }
+    }
+    template <bool LAST> __device__ __forceinline__ void inv16(V (&a)[16], unsigned s_base, unsigned G) const
+    {
+        inv16_with<LAST>(a, [&](int c) { return twi[step16_twiddle(s_base, G, (unsigned)c)]; });
     }
     __device__ __forceinline__ void fwd_stage0(V (&lo)[16], V (&hi)[16], bool) const
     {
