@@ -581,26 +581,29 @@ __device__ __forceinline__ void inv_cols_body(u64 *__restrict__ limb, unsigned c
     // each half of the rows: stages logN-9 .. logN-12 on 16 consecutive rows, exchange through the same 32 KiB of
     // LDS, then stages 3 .. 0 (N = 2^16) or 4 .. 1 (N = 2^17: stage 0 pairs the halves afterwards).  Written as two calls:
     // as a loop it is too large for the compiler to unroll, and the values, indexed by the half, go to scratch memory.
-    // N = 2^17 (two or three work-groups per compute unit): the twelve twiddles of the first two stages are loaded ahead of the
-    // values, and all are on their way before any is worked on (34 limbs: 41.3 us, 41.8 with the loads where the compiler puts them)
-    typename A::W tw[15];
-    const auto load_tw = [&](int h) __attribute__((always_inline)) {
+    // N = 2^17 (two or three work-groups per compute unit): the first step's twiddles are loaded by themselves, ahead of the
+    // first half's values, else they come late, and the limbs on the integer path with them (34 limbs, both passes: 40.5 us; 41.5 with
+    // the values of both halves on their way before the first is worked on)
+    const auto half = [&](V (&v)[16], int h) __attribute__((always_inline)) {
+        const unsigned g = rl + 16 * h;
+        typename A::W tw[15];
+        if (H == 2 && h == 0) {
 #pragma unroll
-        for (int t = 3; t < 15; t++) tw[t] = ar.twi[step16_twiddle(H + 3, rl + 16 * h, (unsigned)t)];
-    };
-    if (H == 2) load_tw(0);
-#pragma unroll
-    for (int h = 0; h < H; h++)
+            for (int t = 0; t < 15; t++) tw[t] = ar.twi[step16_twiddle(H + 3, g, (unsigned)t)];
+        }
 #pragma unroll
         for (int k = 0; k < 16; k++) {
-            const u64 *src = limb + (16 * (rl + 16 * h) + k) * 256 + col0 + c;
-            a[h][k] = ar.load_mid(STREAM ? __builtin_nontemporal_load(src) : *src);
+            const u64 *src = limb + (16 * g + k) * 256 + col0 + c;
+            v[k] = ar.load_mid(STREAM ? __builtin_nontemporal_load(src) : *src);
         }
-    if (H == 2) __builtin_amdgcn_sched_barrier(0);
-    const auto half = [&](V (&v)[16], int h) __attribute__((always_inline)) {
-        const auto twiddle = [&](int t) { return H == 2 && t >= 3 ? tw[t] : ar.twi[step16_twiddle(H + 3, rl + 16 * h, (unsigned)t)]; };
-        ar.template inv16_with<false>(v, twiddle);
-        if (H == 2 && h == 0) load_tw(1);
+        if (H == 2 && h == 1) {
+#pragma unroll
+            for (int t = 0; t < 15; t++) tw[t] = ar.twi[step16_twiddle(H + 3, g, (unsigned)t)];
+        }
+        if (H == 2)
+            ar.template inv16_with<false>(v, [&](int t) { return tw[t]; });
+        else
+            ar.template inv16<false>(v, H + 3, g);
         if (h > 0) __syncthreads(); // the previous half has been read back by every thread
 #pragma unroll
         for (int k = 0; k < 16; k++) lds[col_at(16 * rl + k, c)] = ar.store_mid(v[k]);
