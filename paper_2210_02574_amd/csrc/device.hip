@@ -327,12 +327,12 @@ static ConvArgs conv_args(const he_ctx *c, const u64 *src, int level, int dst_st
     return cv;
 }
 
-static const FinArgs kNoFin = {nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, 0, 1, 1 << 30, 0, 0, 0};
+static const FinArgs kNoFin = {nullptr, nullptr, nullptr, nullptr, 0, 0, 1, 1 << 30, 0, 0};
 static const OpArgs kNoOps = {};
 
 // Forward NTT of the listed limbs of `data`.  pro selects what the column pass transforms (the
 // limb's own content, or a base conversion of cv.src); with fin != nullptr the block pass writes
-// (u - ntt) * const + addend to fin->out instead of the transform itself.
+// (u - ntt) * const to fin->out instead of the transform itself.
 // src_limbs = number of source limbs the prologue reads in total (for the byte count).
 // blocks: the limbs whose block pass runs here (the others are finished by the kernel that consumes them): all, none, or
 // the ciphertext limbs on the integer path and every limb with a modulus index from finish_from on.
@@ -351,14 +351,13 @@ static int32_t ntt_forward(he_ctx *c, hipStream_t st, u64 *data, const LimbList 
                              : pro == PRO_MODDOWN_RS ? KID_FWD_COLS_MODDOWN_RS
                                                   : KID_FWD_COLS_RESCALE;
         if (dl.fwd_limb[pro]) { // the whole transform in one launch, on every limb
-            const double extra = fin ? (double)nb * N8 * (fin->add ? 2.0 : 1.0) : 0.0;
-            dl.fwd_limb[pro](c, st, kid_cols, cols_bytes + extra, wide, data, lb, nb, cv, fin);
+            dl.fwd_limb[pro](c, st, kid_cols, cols_bytes + (fin ? (double)nb * N8 : 0.0), wide, data, lb, nb, cv, fin);
             return;
         }
         (cv.exact && dl.fwd_cols_ex[pro] ? dl.fwd_cols_ex[pro] : dl.fwd_cols[pro])(c, st, kid_cols, cols_bytes, wide, data, lb, nb, cv);
         if (fin) {
-            // reads the transform's input, the minuend and the addend, writes the result
-            dl.fwd_blocks(c, st, (double)nb * N8 * (fin->add ? 4.0 : 3.0), true, data, lb, nb, *fin);
+            // reads the transform's input and the minuend, writes the result
+            dl.fwd_blocks(c, st, 3.0 * nb * N8, true, data, lb, nb, *fin);
         } else if (blocks == BLOCKS_ALL)
             dl.fwd_blocks(c, st, 2.0 * nb * N8, false, data, lb, nb, kNoFin);
     });
@@ -893,7 +892,7 @@ extern "C" int32_t he_hmult_relin_rescale_batch(he_ctx *ctx, const he_evk *relin
         LimbList last;
         for (int o = 0; o < count; o++)
             for (int cc = 0; cc < 2; cc++) last.add(o * W + cc * level + level - 1, level - 1);
-        const FinArgs fl = {ws + w.u * N, rbuf, nullptr, ctx->dev.dn_pinv, ctx->dev.dn_pinv_d, Ma, level, 0, level, W, W, W, 0};
+        const FinArgs fl = {ws + w.u * N, rbuf, ctx->dev.dn_pinv, ctx->dev.dn_pinv_d, Ma, level, level, W, W, W};
         if ((rc = ntt_forward(ctx, st, rbuf, last, PRO_MODDOWN, cv, &fl, 2 * K * count)) != HE_OK) return rc;
         if ((rc = ntt_inverse(ctx, st, rbuf, rbuf, last, SCALE_NONE, cv)) != HE_OK) return rc;
     }
@@ -1176,8 +1175,8 @@ extern "C" int32_t he_rescale_batch(he_ctx *ctx, const uint64_t *d_ct, uint64_t 
     for (int o = 0; o < count; o++)
         for (int c = 0; c < 2; c++)
             for (int i = 0; i < level - 1; i++) l.add(o * W + c * (level - 1) + i, i);
-    const FinArgs fa = {d_ct, d_out, nullptr, ctx->dev.rs_inv + (size_t)(level - 1) * ctx->L,
-                        ctx->dev.rs_inv_d + (size_t)(level - 1) * ctx->L, level, level - 1, 0, level - 1, W, 2 * level, 2 * (level - 1), 0};
+    const FinArgs fa = {d_ct, d_out, ctx->dev.rs_inv + (size_t)(level - 1) * ctx->L, ctx->dev.rs_inv_d + (size_t)(level - 1) * ctx->L,
+                        level, level - 1, level - 1, W, 2 * level, 2 * (level - 1)};
     return ntt_forward(ctx, st, r, l, PRO_RESCALE, cv, &fa, 2 * count);
 }
 

@@ -217,7 +217,7 @@ extern "C" int32_t he_ctx_create(const he_params *p, int32_t device, he_ctx **ou
         c->ninv.resize((size_t)M * 2);
         c->twd_fwd.assign((size_t)M * N, 0.0);
         c->twd_inv.assign((size_t)M * N, 0.0);
-        c->twd_blk.assign((size_t)M * N, 0.0);
+        if (device >= 0 && c->logN > 12) c->twd_blk.assign((size_t)M * N, 0.0); // for the device's inner product, which N = 2^12 does without
         c->ninvd.assign((size_t)M * 2, 0.0);
     } catch (...) {
         delete c;
@@ -261,7 +261,7 @@ extern "C" int32_t he_ctx_create(const he_params *p, int32_t device, he_ctx **ou
                 c->twd_inv[(size_t)i * N + e] = bal(c->tw_inv[(size_t)i * N + e].w);
             }
             const int s0 = c->logN - 8; // first stage of the block pass
-            for (u64 G = 0; G < N / 256; G++)
+            for (u64 G = 0; !c->twd_blk.empty() && G < N / 256; G++)
                 for (int m = 0; m < 8; m++)
                     for (u64 x = 0; x < ((u64)1 << m); x++)
                         c->twd_blk[(size_t)i * N + 256 * G + ((u64)1 << m) - 1 + x] =

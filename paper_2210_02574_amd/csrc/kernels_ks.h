@@ -558,13 +558,13 @@ __device__ __forceinline__ void special_inverse(const u64 (&r0)[4], const u64 (&
     for (int k = 0; k < 16; k++) limb[bg * 256 + il + 16 * k] = ar.store_mid(v[k]);
 }
 
-// What both forms do with their sums: u on a ciphertext limb, the inverse block pass on a special one.
-template <int LOGN, class A>
+// What both forms do with their sums: the inverse block pass on a special limb, u on a ciphertext limb (MULT: the dropped one).
+template <int LOGN, bool MULT, class A>
 __device__ __forceinline__ void special_result(const InnerArgs &ia, const InnerTile &w, const u64 (&r0)[4], const u64 (&r1)[4], const A &ar, u64 *lds)
 {
     u64 *u0 = ia.u + (((size_t)w.op * ia.u_stride + w.a) << LOGN);
     const size_t comp_words = (size_t)(ia.level + ia.K) << LOGN;
-    if (w.a >= ia.level) {
+    if (!MULT || w.a >= ia.level) {
         special_inverse<LOGN>(r0, r1, u0, comp_words, ar, lds, w.tile);
         return;
     }
@@ -591,11 +591,11 @@ template <int LOGN, bool MULT> __global__ __launch_bounds__(SPECIAL_THREADS, 2) 
     if (m.qd != 0.0) {
         const ArithFp ar = make_fp(T, mi, LOGN);
         special_products<LOGN, MULT>(ia, oa, T, w.op, w.tile, w.a, w.g, w.beta, mi, m, ar, lds, r0, r1);
-        special_result<LOGN>(ia, w, r0, r1, ar, lds);
+        special_result<LOGN, MULT>(ia, w, r0, r1, ar, lds);
     } else {
         const ArithInt ar = make_int(T, mi, LOGN);
         special_products<LOGN, MULT>(ia, oa, T, w.op, w.tile, w.a, w.g, w.beta, mi, m, ar, lds, r0, r1);
-        special_result<LOGN>(ia, w, r0, r1, ar, lds);
+        special_result<LOGN, MULT>(ia, w, r0, r1, ar, lds);
     }
 }
 
@@ -677,11 +677,11 @@ template <int LOGN, bool MULT> __global__ __launch_bounds__(SPECIAL_THREADS, 5) 
     if (m.qd != 0.0) {
         const ArithFp ar = make_fp(T, mi, LOGN);
         finished_products<LOGN, MULT>(ia, oa, T, w, mi, m, ar, r0, r1);
-        special_result<LOGN>(ia, w, r0, r1, ar, lds);
+        special_result<LOGN, MULT>(ia, w, r0, r1, ar, lds);
     } else {
         const ArithInt ar = make_int(T, mi, LOGN);
         finished_products<LOGN, MULT>(ia, oa, T, w, mi, m, ar, r0, r1);
-        special_result<LOGN>(ia, w, r0, r1, ar, lds);
+        special_result<LOGN, MULT>(ia, w, r0, r1, ar, lds);
     }
 }
 

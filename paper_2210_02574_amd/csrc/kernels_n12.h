@@ -171,10 +171,10 @@ __global__ __launch_bounds__(N12_THREADS, EPI == EPI_FIN ? 4 : 1) void k_ntt_fwd
     u64 *limb = data + ((size_t)slot << 12);
     const ModConst m = T.mod[mi];
     const ConvSetup<NSMAX> S = conv_setup<PRO, NSMAX, 12>(cv, T, slot, mi);
-    FinOperands fo[EPI == EPI_FIN ? 8 : 1];
+    u64 uv[EPI == EPI_FIN ? 8 : 1];
     if (EPI == EPI_FIN) {
 #pragma unroll
-        for (int k = 0; k < 8; k++) fo[k] = fin_load<12>(fa, slot, nb + 64 * k);
+        for (int k = 0; k < 8; k++) uv[k] = fin_load<12>(fa, slot, nb + 64 * k);
     }
     conv_variant12<PRO, NSMAX, EX, true>(T, mi, m, S.qld, [&](auto ar, auto split, auto tint) {
         typedef decltype(ar) A;
@@ -186,7 +186,7 @@ __global__ __launch_bounds__(N12_THREADS, EPI == EPI_FIN ? 4 : 1) void k_ntt_fwd
         for (int k = 0; k < 8; k++) {
             const unsigned pos = nb + 64 * k;
             if (EPI == EPI_FIN)
-                fin_store<12, A::IS_FP>(fa, T, slot, pos, v[k], fo[k]);
+                fin_store<12, A::IS_FP>(fa, T, slot, pos, v[k], uv[k]);
             else
                 limb[pos] = v[k];
         }

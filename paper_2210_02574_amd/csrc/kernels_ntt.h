@@ -16,10 +16,10 @@
 //    centred residue of a dropped limb (rescale);
 //  * the inverse column pass can fold (D/q_i)^-1 or (P/p_k)^-1 into its 1/N scaling, so it emits
 //    the y values those sums need;
-//  * the forward block pass can finish ModDown / rescale: out = (u - ntt) * const + addend;
+//  * the forward block pass can finish a rescale or the ModDown of one limb: out = (u - ntt) * const;
 //  * ModDown followed by rescale takes one transform per limb instead of two: with t the centred dropped
 //    limb of the ModDown result, NTT(r) P^-1 + NTT(t) = NTT(r + P t) P^-1, so the column pass transforms
-//    r + P t and the block pass finishes out = (u - ntt) (P q_l)^-1 + d q_l^-1.
+//    r + P t and the inner product finishes out = (u - ntt) (P q_l)^-1.
 #pragma once
 #include "arith.h"
 
@@ -72,16 +72,15 @@ __device__ __forceinline__ int conv_op_level(const ConvArgs &cv, unsigned slot)
     return l ? l : cv.level;
 }
 
-// Finishing epilogue of the block pass: out = (u - ntt) * cst + addend.  A limb's slot within its operation decodes
+// Finishing epilogue of the block pass: out = (u - ntt) * cst.  A limb's slot within its operation decodes
 // as component c = slot / nl, limb i = slot % nl.
 struct FinArgs {
     const u64 *u;   // minuend limbs, component stride u_cstride limbs
     u64 *out;       // component stride out_cstride limbs
-    const u64 *add; // addend limbs, component stride add_cstride limbs; null: no addend
     const ShoupConst *cst;
     const double *cst_d;
-    int u_cstride, out_cstride, add_cstride, nl;
-    int dst_stride, u_stride, out_stride, add_stride; // limbs between two operations in each buffer
+    int u_cstride, out_cstride, nl;
+    int dst_stride, u_stride, out_stride; // limbs between two operations in each buffer
 };
 
 __device__ __forceinline__ int active_mod(int a, int level, int L) { return a < level ? a : L + (a - level); }
@@ -316,26 +315,20 @@ __device__ __forceinline__ u64 conv_get(const ConvSetup<NSMAX> &S, const ArithIn
 
 // ---- epilogue: what the forward block pass does with a finished (canonical) NTT value ---------------------
 
-// Operands of the epilogue for one output: issued before the transform so that the loads overlap it.
-struct FinOperands {
-    u64 uv, av;
-};
+// The minuend of one output: issued before the transform so that the load overlaps it.
 template <int LOGN>
-__device__ __forceinline__ FinOperands fin_load(const FinArgs &fa, unsigned slot, unsigned pos)
+__device__ __forceinline__ u64 fin_load(const FinArgs &fa, unsigned slot, unsigned pos)
 {
     const unsigned op = slot / (unsigned)fa.dst_stride;
     slot -= op * (unsigned)fa.dst_stride;
     const unsigned c = slot / fa.nl, i = slot % fa.nl;
-    FinOperands o;
-    o.uv = __builtin_nontemporal_load(fa.u + ((((size_t)op * fa.u_stride + (size_t)c * fa.u_cstride + i) << LOGN) + pos));
-    o.av = fa.add ? fa.add[(((size_t)op * fa.add_stride + (size_t)c * fa.add_cstride + i) << LOGN) + pos] : 0;
-    return o;
+    return __builtin_nontemporal_load(fa.u + ((((size_t)op * fa.u_stride + (size_t)c * fa.u_cstride + i) << LOGN) + pos));
 }
 
 // FP: the limb's modulus is on the floating-point path (known from the transform's arithmetic at compile time)
 template <int LOGN, bool FP>
 __device__ __forceinline__ void fin_store(const FinArgs &fa, const DevTables &T, unsigned slot, unsigned pos, u64 rv,
-                                          const FinOperands &fo)
+                                          u64 uv)
 {
     const unsigned op = slot / (unsigned)fa.dst_stride;
     slot -= op * (unsigned)fa.dst_stride;
@@ -344,9 +337,9 @@ __device__ __forceinline__ void fin_store(const FinArgs &fa, const DevTables &T,
     const size_t o = (((size_t)op * fa.out_stride + (size_t)c * fa.out_cstride + i) << LOGN) + pos;
     u64 res;
     if (FP)
-        res = fp_canon(fp_mulmod(u2d(fo.uv) - u2d(rv), fa.cst_d[i], m.qd, m.qinvd) + u2d(fo.av), m.qd, m.qinvd);
+        res = fp_canon(fp_mulmod(u2d(uv) - u2d(rv), fa.cst_d[i], m.qd, m.qinvd), m.qd, m.qinvd);
     else
-        res = csub(mul_shoup(fo.uv + m.q - rv, fa.cst[i], m.q) + fo.av, m.q);
+        res = mul_shoup(uv + m.q - rv, fa.cst[i], m.q);
     __builtin_nontemporal_store(res, fa.out + o); // a result: nothing in this launch reads it
 }
 
@@ -383,13 +376,13 @@ __device__ __forceinline__ void fwd_blocks_body(u64 *__restrict__ limb, const A 
     const unsigned blk = threadIdx.x >> 4, il = threadIdx.x & 15;
     const unsigned bg = tile * BLK_PER_WG + blk; // block index within the limb
     typename A::V a[16];
-    FinOperands fo[EPI == EPI_FIN ? 16 : 1];
+    u64 uv[EPI == EPI_FIN ? 16 : 1];
 #pragma unroll
     for (int k = 0; k < 16; k++)
         a[k] = ar.load_mid(__builtin_nontemporal_load(limb + bg * 256 + il + 16 * k)); // read once: the column pass wrote it
     if (EPI == EPI_FIN) {
 #pragma unroll
-        for (int k = 0; k < 16; k++) fo[k] = fin_load<LOGN>(fa, slot, bg * 256 + il + 16 * k);
+        for (int k = 0; k < 16; k++) uv[k] = fin_load<LOGN>(fa, slot, bg * 256 + il + 16 * k);
     }
     ar.fwd16(a, LOGN - 8, bg, true);
 #pragma unroll
@@ -407,7 +400,7 @@ __device__ __forceinline__ void fwd_blocks_body(u64 *__restrict__ limb, const A 
         const unsigned pos = bg * 256 + il + 16 * k;
         const u64 v = lds[tile_at(blk, il + 16 * k)];
         if (EPI == EPI_FIN)
-            fin_store<LOGN, A::IS_FP>(fa, T, slot, pos, v, fo[k]);
+            fin_store<LOGN, A::IS_FP>(fa, T, slot, pos, v, uv[k]);
         else
             __builtin_nontemporal_store(v, limb + pos);
     }
@@ -570,8 +563,7 @@ __device__ __forceinline__ void fwd_cols_body(u64 *__restrict__ limb, unsigned c
     }
 }
 
-// STREAM: the input is the first half of a conversion's inverse transform, read this once only
-template <int LOGN, bool STREAM, class A>
+template <int LOGN, class A>
 __device__ __forceinline__ void inv_cols_body(u64 *__restrict__ limb, unsigned col0, const A &ar, u64 *lds)
 {
     constexpr int H = ColsGeom<LOGN>::HALVES;
@@ -594,7 +586,7 @@ __device__ __forceinline__ void inv_cols_body(u64 *__restrict__ limb, unsigned c
 #pragma unroll
         for (int k = 0; k < 16; k++) {
             const u64 *src = limb + (16 * g + k) * 256 + col0 + c;
-            v[k] = ar.load_mid(STREAM ? __builtin_nontemporal_load(src) : *src);
+            v[k] = ar.load_mid(__builtin_nontemporal_load(src)); // the block pass wrote it, read this once only
         }
         if (H == 2 && h == 1) {
 #pragma unroll
@@ -762,9 +754,9 @@ __device__ __forceinline__ void inv_cols_kernel(u64 *__restrict__ data, const De
     double cd;
     scale_consts(SCALE, cv, T, mi, lb.slot[b], ci, cd);
     if (T.mod[mi].qd != 0.0)
-        inv_cols_body<LOGN, true>(limb, tile * 16, make_fp(T, mi, LOGN, cd), lds);
+        inv_cols_body<LOGN>(limb, tile * 16, make_fp(T, mi, LOGN, cd), lds);
     else
-        inv_cols_body<LOGN, true>(limb, tile * 16, make_int(T, mi, LOGN, ci), lds);
+        inv_cols_body<LOGN>(limb, tile * 16, make_int(T, mi, LOGN, ci), lds);
 }
 template <int SCALE>
 __global__ __launch_bounds__(256) void k_ntt_inv_cols16(u64 *__restrict__ data, DevTables T, LimbBatch lb, ConvArgs cv)
