@@ -3,9 +3,10 @@
 #include "kernels_n12.h"
 
 template <int PRO, int NSMAX, bool EX>
-static void launch_fwd12(he_ctx *c, hipStream_t st, int kid, double bytes, u64 *data, const LimbBatch &lb, int nb, const ConvArgs &cv,
+static void launch_fwd12(he_ctx *c, hipStream_t st, double bytes, u64 *data, const LimbBatch &lb, int nb, const ConvArgs &cv,
                          const FinArgs *fin)
 {
+    constexpr int kid = PRO == PRO_MODUP ? KID_FWD12_MODUP : PRO == PRO_RESCALE ? KID_FWD12_RESCALE : KID_FWD12;
     if constexpr (PRO == PRO_RESCALE) { // the one prologue that the finishing epilogue follows here
         if (fin) {
             KLAUNCH_T(c, st, kid, bytes, (k_ntt_fwd12<PRO, NSMAX, EX, EPI_FIN>), nb, N12_THREADS, data, c->dev, lb, cv, *fin);
@@ -15,31 +16,31 @@ static void launch_fwd12(he_ctx *c, hipStream_t st, int kid, double bytes, u64 *
     KLAUNCH_T(c, st, kid, bytes, (k_ntt_fwd12<PRO, NSMAX, EX, EPI_STORE>), nb, N12_THREADS, data, c->dev, lb, cv, FinArgs{});
 }
 template <int PRO>
-static void fwd12(he_ctx *c, hipStream_t st, int kid, double bytes, bool wide, u64 *data, const LimbBatch &lb, int nb,
+static void fwd12(he_ctx *c, hipStream_t st, double bytes, bool wide, u64 *data, const LimbBatch &lb, int nb,
                   const ConvArgs &cv, const FinArgs *fin)
 {
     if constexpr (PRO == PRO_MODUP) {
         if (cv.exact)
-            (wide ? launch_fwd12<PRO, 8, true> : launch_fwd12<PRO, 4, true>)(c, st, kid, bytes, data, lb, nb, cv, fin);
+            (wide ? launch_fwd12<PRO, 8, true> : launch_fwd12<PRO, 4, true>)(c, st, bytes, data, lb, nb, cv, fin);
         else
-            (wide ? launch_fwd12<PRO, 8, false> : launch_fwd12<PRO, 4, false>)(c, st, kid, bytes, data, lb, nb, cv, fin);
+            (wide ? launch_fwd12<PRO, 8, false> : launch_fwd12<PRO, 4, false>)(c, st, bytes, data, lb, nb, cv, fin);
     } else
-        launch_fwd12<PRO, 4, false>(c, st, kid, bytes, data, lb, nb, cv, fin);
+        launch_fwd12<PRO, 4, false>(c, st, bytes, data, lb, nb, cv, fin);
 }
 static void inv12(he_ctx *c, hipStream_t st, double bytes, int scale, const u64 *src, const u64 *src2, u64 *dst, const LimbBatch &lb, int nb,
                   const ConvArgs &cv)
 {
     switch (scale) { // special limbs are scaled where they are produced
-    case SCALE_NONE: KLAUNCH_T(c, st, KID_INV_COLS, bytes, (k_ntt_inv12<SCALE_NONE>), nb, N12_THREADS, src, src2, dst, c->dev, lb, cv); break;
-    default: KLAUNCH_T(c, st, KID_INV_COLS, bytes, (k_ntt_inv12<SCALE_MODUP>), nb, N12_THREADS, src, src2, dst, c->dev, lb, cv); break;
+    case SCALE_NONE: KLAUNCH_T(c, st, KID_INV12, bytes, (k_ntt_inv12<SCALE_NONE>), nb, N12_THREADS, src, src2, dst, c->dev, lb, cv); break;
+    default: KLAUNCH_T(c, st, KID_INV12, bytes, (k_ntt_inv12<SCALE_MODUP>), nb, N12_THREADS, src, src2, dst, c->dev, lb, cv); break;
     }
 }
 static void inner12(he_ctx *c, hipStream_t st, double bytes, const InnerArgs &ia, const OpArgs &oa)
 {
     if (ia.ta)
-        KLAUNCH_T(c, st, KID_INNER, bytes, (k_inner12<true>), dim3(ia.level + ia.K, 2, ia.count), N12_THREADS, ia, c->dev, oa);
+        KLAUNCH_T(c, st, KID_INNER12, bytes, (k_inner12<true>), dim3(ia.level + ia.K, 2, ia.count), N12_THREADS, ia, c->dev, oa);
     else
-        KLAUNCH_T(c, st, KID_INNER, bytes, (k_inner12<false>), dim3(ia.level + 2 * ia.K, 1, ia.count), N12_THREADS, ia, c->dev, oa);
+        KLAUNCH_T(c, st, KID_INNER12, bytes, (k_inner12<false>), dim3(ia.level + 2 * ia.K, 1, ia.count), N12_THREADS, ia, c->dev, oa);
 }
 template <int PRO, bool DROP, bool INTS>
 static void launch_fin12(he_ctx *c, hipStream_t st, double bytes, bool wide, int mode, const InnerArgs &ia, const FinishArgs &fa,
@@ -48,14 +49,14 @@ static void launch_fin12(he_ctx *c, hipStream_t st, double bytes, bool wide, int
     const dim3 grid(DROP ? 1 : fa.nl, 2, ia.count);
     if (cv.exact) {
         if (wide)
-            KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 8, true, DROP, INTS>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
+            KLAUNCH_T(c, st, KID_FIN12, bytes, (k_fin12<PRO, 8, true, DROP, INTS>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
         else
-            KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 4, true, DROP, INTS>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
+            KLAUNCH_T(c, st, KID_FIN12, bytes, (k_fin12<PRO, 4, true, DROP, INTS>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
     } else {
         if (wide)
-            KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 8, false, DROP, INTS>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
+            KLAUNCH_T(c, st, KID_FIN12, bytes, (k_fin12<PRO, 8, false, DROP, INTS>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
         else
-            KLAUNCH_T(c, st, KID_INNER_FIN, bytes, (k_fin12<PRO, 4, false, DROP, INTS>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
+            KLAUNCH_T(c, st, KID_FIN12, bytes, (k_fin12<PRO, 4, false, DROP, INTS>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
     }
 }
 static void fin12(he_ctx *c, hipStream_t st, double bytes, bool wide, int pro, bool drop, int mode, const InnerArgs &ia,

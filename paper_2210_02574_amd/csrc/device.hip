@@ -177,7 +177,8 @@ extern "C" int32_t he_evk_to_host(const he_evk *evk, uint64_t *h_out)
 static const char *const kKernelNames[KID_COUNT] = {
     "k_ntt_fwd_cols", "k_ntt_fwd_cols_modup", "k_ntt_fwd_cols_moddown", "k_ntt_fwd_cols_rescale", "k_ntt_fwd_cols_moddown_rescale",
     "k_ntt_fwd_blocks",
-    "k_ntt_fwd_blocks_fin", "k_ntt_inv_blocks", "k_ntt_inv_cols", "k_limbwise", "k_cmult", "k_inner_blocks", "k_inner_finished", "k_inner_fin"};
+    "k_ntt_fwd_blocks_fin", "k_ntt_inv_blocks", "k_ntt_inv_cols", "k_limbwise", "k_cmult", "k_inner_special", "k_inner_finished",
+    "k_inner_fin", "k_ntt_fwd12", "k_ntt_fwd12_modup", "k_ntt_fwd12_rescale", "k_ntt_inv12", "k_inner12", "k_fin12"};
 
 bool prof_events(he_ctx *c, int kid, double bytes, ProfRecord &r)
 {
@@ -351,7 +352,7 @@ static int32_t ntt_forward(he_ctx *c, hipStream_t st, u64 *data, const LimbList 
                              : pro == PRO_MODDOWN_RS ? KID_FWD_COLS_MODDOWN_RS
                                                   : KID_FWD_COLS_RESCALE;
         if (dl.fwd_limb[pro]) { // the whole transform in one launch, on every limb
-            dl.fwd_limb[pro](c, st, kid_cols, cols_bytes + (fin ? (double)nb * N8 : 0.0), wide, data, lb, nb, cv, fin);
+            dl.fwd_limb[pro](c, st, cols_bytes + (fin ? (double)nb * N8 : 0.0), wide, data, lb, nb, cv, fin);
             return;
         }
         (cv.exact && dl.fwd_cols_ex[pro] ? dl.fwd_cols_ex[pro] : dl.fwd_cols[pro])(c, st, kid_cols, cols_bytes, wide, data, lb, nb, cv);

@@ -13,7 +13,9 @@
 enum KernelId {
     KID_FWD_COLS, KID_FWD_COLS_MODUP, KID_FWD_COLS_MODDOWN, KID_FWD_COLS_RESCALE, KID_FWD_COLS_MODDOWN_RS, KID_FWD_BLOCKS,
     KID_FWD_BLOCKS_FIN,
-    KID_INV_BLOCKS, KID_INV_COLS, KID_LIMBWISE, KID_CMULT, KID_INNER, KID_INNER_FINISHED, KID_INNER_FIN, KID_COUNT
+    KID_INV_BLOCKS, KID_INV_COLS, KID_LIMBWISE, KID_CMULT, KID_INNER_SPECIAL, KID_INNER_FINISHED, KID_INNER_FIN,
+    KID_FWD12, KID_FWD12_MODUP, KID_FWD12_RESCALE, KID_INV12, KID_INNER12, KID_FIN12, // N = 2^12
+    KID_COUNT
 };
 
 // Creates the event pair of one profiled launch and appends it to the context's record list.
@@ -40,7 +42,7 @@ struct DevLaunch {
     // place of the passes below: fwd_limb, with the finishing epilogue if fin is not null; inv_limb; the inner product, with
     // the special limbs' inverse transform; the finishing of the first fa.nl limbs (rescale: with the dropped limb's
     // share in the corrections; drop: of the dropped limb alone, into fa.r).
-    void (*fwd_limb[5])(he_ctx *c, hipStream_t st, int kid, double bytes, bool wide, u64 *data, const LimbBatch &lb, int nb,
+    void (*fwd_limb[5])(he_ctx *c, hipStream_t st, double bytes, bool wide, u64 *data, const LimbBatch &lb, int nb,
                         const ConvArgs &cv, const FinArgs *fin);
     void (*inv_limb)(he_ctx *c, hipStream_t st, double bytes, int scale, const u64 *src, const u64 *src2, u64 *dst, const LimbBatch &lb, int nb,
                      const ConvArgs &cv);
@@ -117,9 +119,9 @@ static void launch_inner(he_ctx *c, hipStream_t st, double bytes, unsigned grid,
             KLAUNCH_T(c, st, KID_INNER_FINISHED, bytes, (k_inner_finished<LOGN, false>), grid, SPECIAL_THREADS, ia, c->dev, oa);
     } else {
         if (mult)
-            KLAUNCH_T(c, st, KID_INNER, bytes, (k_inner_special<LOGN, true>), grid, SPECIAL_THREADS, ia, c->dev, oa);
+            KLAUNCH_T(c, st, KID_INNER_SPECIAL, bytes, (k_inner_special<LOGN, true>), grid, SPECIAL_THREADS, ia, c->dev, oa);
         else
-            KLAUNCH_T(c, st, KID_INNER, bytes, (k_inner_special<LOGN, false>), grid, SPECIAL_THREADS, ia, c->dev, oa);
+            KLAUNCH_T(c, st, KID_INNER_SPECIAL, bytes, (k_inner_special<LOGN, false>), grid, SPECIAL_THREADS, ia, c->dev, oa);
     }
 }
 template <int LOGN, int MODE>
