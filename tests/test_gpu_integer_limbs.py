@@ -152,3 +152,32 @@ def test_special_limbs_of_small_and_large_launches(oracle_mod, name):
         for count in (2, 3):  # shared digits
             for got in he.hrot_many([rot] * count, dev[0]):
                 assert np.array_equal(he.to_host(got), rotated[0]), (level, count)
+
+
+def test_product_over_a_factor_in_a_graph():
+    """The copy that such a result takes can be captured: three replays with eager work in between."""
+    import torch
+
+    import paper_2210_02574_amd as pkg
+
+    p = SETS["int16"]
+    he = pkg.HE.from_params(p, device=0)
+    relin = he.evk_from_host(wl.uniform_evk(9, p), 1)
+    a, b = [he.to_device(wl.uniform_ct(300 + k, p, p.L)) for k in range(2)]
+    want = he.hmult_relin_rescale(relin, a, b)
+    work = a.clone()
+    out = work.view(-1)[: want.numel()].view(want.shape)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        he.hmult_relin_rescale(relin, work, b, out=out)  # the workspace of the capture stream exists before the capture starts
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        he.hmult_relin_rescale(relin, work, b, out=out)
+    for replay in range(3):
+        work.copy_(a)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), replay
+        assert torch.equal(he.hmult_relin_rescale(relin, a, b), want)
