@@ -573,29 +573,33 @@ __device__ __forceinline__ void inv_cols_body(u64 *__restrict__ limb, unsigned c
     // each half of the rows: stages logN-9 .. logN-12 on 16 consecutive rows, exchange through the same 32 KiB of
     // LDS, then stages 3 .. 0 (N = 2^16) or 4 .. 1 (N = 2^17: stage 0 pairs the halves afterwards).  Written as two calls:
     // as a loop it is too large for the compiler to unroll, and the values, indexed by the half, go to scratch memory.
-    // N = 2^17 (two or three work-groups per compute unit): the first step's twiddles are loaded by themselves, ahead of the
-    // first half's values, else they come late, and the limbs on the integer path with them (34 limbs, both passes: 40.5 us; 41.5 with
-    // the values of both halves on their way before the first is worked on)
+    // N = 2^17 (two or three work-groups per compute unit): a step's twiddles are loaded by themselves, ahead of the values, else they come
+    // late, and the limbs on the integer path with them; the second half's values are on their way behind the first half's first
+    // step.  34 limbs, both passes: 40.0 us (41.6 with the values of both halves ahead of everything, 40.7 with the second half's in its
+    // turn); 4 limbs: 16.3 (16.8 in its turn)
+    const auto values = [&](V (&v)[16], int h) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < 16; k++) {
+            const u64 *src = limb + (16 * (rl + 16 * h) + k) * 256 + col0 + c;
+            v[k] = ar.load_mid(__builtin_nontemporal_load(src)); // the block pass wrote it, read this once only
+        }
+    };
     const auto half = [&](V (&v)[16], int h) __attribute__((always_inline)) {
         const unsigned g = rl + 16 * h;
         typename A::W tw[15];
-        if (H == 2 && h == 0) {
+        if (H == 2) {
 #pragma unroll
             for (int t = 0; t < 15; t++) tw[t] = ar.twi[step16_twiddle(H + 3, g, (unsigned)t)];
         }
-#pragma unroll
-        for (int k = 0; k < 16; k++) {
-            const u64 *src = limb + (16 * g + k) * 256 + col0 + c;
-            v[k] = ar.load_mid(__builtin_nontemporal_load(src)); // the block pass wrote it, read this once only
-        }
-        if (H == 2 && h == 1) {
-#pragma unroll
-            for (int t = 0; t < 15; t++) tw[t] = ar.twi[step16_twiddle(H + 3, g, (unsigned)t)];
-        }
+        if (h == 0) values(v, 0);
         if (H == 2)
             ar.template inv16_with<false>(v, [&](int t) { return tw[t]; });
         else
             ar.template inv16<false>(v, H + 3, g);
+        if (H == 2 && h == 0) {
+            values(a[H - 1], 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         if (h > 0) __syncthreads(); // the previous half has been read back by every thread
 #pragma unroll
         for (int k = 0; k < 16; k++) lds[col_at(16 * rl + k, c)] = ar.store_mid(v[k]);
