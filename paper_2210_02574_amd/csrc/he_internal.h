@@ -35,7 +35,7 @@ struct DevTables {
     // the same three tables as balanced residues in (-q/2, q/2) stored as doubles (moduli < 2^50)
     const double *twd_fwd;     // [M][N]
     // forward twiddles of the last eight stages by block of 256 elements: entry 256 G + 2^m - 1 + i is the one of
-    // block G, local stage m, group i < 2^m (entry 255 of a block is unused)
+    // block G, local stage m, group i < 2^m (entry 255 of a block is unused); none at N = 2^12
     const double *twd_blk;     // [M][N]
     const double *twd_inv;     // [M][N]
     const double *ninvd;       // [M][2]

@@ -2,16 +2,16 @@
 // threads, 8 elements each, runs a whole transform (four steps of three stages), and a key switch is four launches:
 //   1. inverse transform of the input limbs, scaled                                  (k_ntt_inv12<SCALE_MODUP>)
 //   2. ModUp and forward transform of every raised limb                                 (k_ntt_fwd12<PRO_MODUP>)
-//   3. per active limb and component: inner product u, for special limbs its inverse transform, scaled (k_inner12)
+//   3. per active limb (and component, but for a rotation's ciphertext limbs): inner product u, for special limbs its inverse transform, scaled (k_inner12)
 //   4. per ciphertext limb and component: ModDown correction, its forward transform, (u - r) * const + addend (k_fin12)
 // and one more for Mult with rescale, which finishes the dropped limb between 3 and 4 (k_fin12 with DROP).
 //
-// At this size nothing is bound by memory or by instructions: a launch is a chain of dependent steps on few
+// Single calls are bound neither by memory nor by instructions: a launch is a chain of dependent steps on few
 // work-groups, so what counts is the number of launches and the length of the chain in each.  With two launches per
 // transform (column pass, block pass) and the digits finished inside the inner product, one rotation (three primes, one
-// special prime) took seven launches of 4 to 10 us, 46 us in all; it takes 32 now (5.5, 8, 9.2 and 9.4), and eight
-// transforms 7.4 to 8.4 us, the host's time for one call, instead of 11.5.  The chain is kept short by fetching a step's
-// twiddles before the step ahead of it is worked on, by giving every component a work-group of its own, and by short
+// special prime) took seven launches of 4 to 10 us, 46 us in all; it takes 31 now, and eight
+// transforms 7.3 to 8.4 us, the host's time for one call, instead of 11.5.  The chain is kept short by fetching a step's
+// twiddles before the step ahead of it is worked on, by giving every component that is transformed a work-group of its own, and by short
 // code: a launch runs it once, and with 256 threads of 16 elements, twice the instructions, it took 37 us (the
 // finishing kernel 14.9).  Batches are bound by memory and by how many work-groups are resident: at most 128 registers keep two
 // per compute unit (64 rotations of 24 primes, with k_fin12 at 137 and the digits read once per component, took 572 us against
