@@ -23,6 +23,13 @@ __device__ __forceinline__ u64 negated(u64 q)
     const u64 nq = 0 - q;
     return (u64)(unsigned)__builtin_amdgcn_readfirstlane((int)(nq >> 32)) << 32 | (unsigned)__builtin_amdgcn_readfirstlane((int)nq);
 }
+// The same where the compiler would see through readfirstlane because it knows q to be uniform.
+__device__ __forceinline__ u64 negated_uniform(u64 q)
+{
+    u64 nq = negated(q);
+    asm("" : "+s"(nq));
+    return nq;
+}
 // x - q, or x where that is negative, for x < 2^63 + q, given nq = -q: the sign of the difference decides
 __device__ __forceinline__ u64 csub_neg(u64 x, u64 nq)
 {

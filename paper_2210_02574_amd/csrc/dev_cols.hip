@@ -25,9 +25,9 @@ static_assert(PRO_LOAD == 0 && PRO_MODUP == 1 && PRO_MODDOWN == 2 && PRO_RESCALE
 static void fwd_cols(he_ctx *c, hipStream_t st, int kid, double bytes, bool wide, u64 *data, const LimbBatch &lb, int nb,
                      const ConvArgs &cv)
 {
-#if HE_LOGN == 16 && HE_PRO == 1 /* PRO_MODUP */
+#if HE_LOGN == 16 && HE_PRO == 1 && HE_EX /* PRO_MODUP, corrected */
     if (!wide) {
-        KLAUNCH(c, st, kid, bytes, (k_ntt_fwd_cols16_modup2<4, HE_EX != 0>), 16 * ((nb + 1) / 2), data, c->dev, lb, cv, nb);
+        KLAUNCH(c, st, kid, bytes, (k_ntt_fwd_cols16_modup2<4>), 16 * ((nb + 1) / 2), data, c->dev, lb, cv, nb);
         return;
     }
 #endif

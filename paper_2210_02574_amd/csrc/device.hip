@@ -202,14 +202,14 @@ static const DevLaunch &dev_launch(const he_ctx *c)
         [] {
             DevLaunch t{};
             dev_launch_cols16_0(t), dev_launch_cols16_1(t), dev_launch_cols16_2(t), dev_launch_cols16_3(t);
-            dev_launch_cols16_4(t), dev_launch_cols16_5(t), dev_launch_n16_blocks(t);
+            dev_launch_cols16_4(t), dev_launch_cols16_5(t), dev_launch_n16_blocks(t), dev_launch_conv16(t);
             dev_launch_cols_ex16_1(t), dev_launch_cols_ex16_2(t), dev_launch_cols_ex16_4(t);
             return t;
         }(),
         [] {
             DevLaunch t{};
             dev_launch_cols17_0(t), dev_launch_cols17_1(t), dev_launch_cols17_2(t), dev_launch_cols17_3(t);
-            dev_launch_cols17_4(t), dev_launch_cols17_5(t), dev_launch_n17_blocks(t);
+            dev_launch_cols17_4(t), dev_launch_cols17_5(t), dev_launch_n17_blocks(t), dev_launch_conv17(t);
             dev_launch_cols_ex17_1(t), dev_launch_cols_ex17_2(t), dev_launch_cols_ex17_4(t);
             return t;
         }(),
@@ -358,9 +358,9 @@ static int32_t ntt_forward(he_ctx *c, hipStream_t st, u64 *data, const LimbList 
         (cv.exact && dl.fwd_cols_ex[pro] ? dl.fwd_cols_ex[pro] : dl.fwd_cols[pro])(c, st, kid_cols, cols_bytes, wide, data, lb, nb, cv);
         if (fin) {
             // reads the transform's input and the minuend, writes the result
-            dl.fwd_blocks(c, st, 3.0 * nb * N8, true, data, lb, nb, *fin);
+            dl.fwd_blocks(c, st, 3.0 * nb * N8, true, pro_pairs_rows(pro), data, lb, nb, *fin);
         } else if (blocks == BLOCKS_ALL)
-            dl.fwd_blocks(c, st, 2.0 * nb * N8, false, data, lb, nb, kNoFin);
+            dl.fwd_blocks(c, st, 2.0 * nb * N8, false, pro_pairs_rows(pro), data, lb, nb, kNoFin);
     });
     if (rc != HE_OK || blocks != BLOCKS_SOME || dl.fwd_limb[pro]) return rc;
     // after all column passes: few launches, each as large as possible
@@ -368,7 +368,7 @@ static int32_t ntt_forward(he_ctx *c, hipStream_t st, u64 *data, const LimbList 
     for (int b = 0; b < l.size(); b++)
         if (l.mod[b] >= finish_from || (c->modc[l.mod[b]].qd == 0.0 && l.mod[b] < c->L)) li.add(l.slot[b], l.src[b], l.mod[b]);
     return for_batches(c, li, [&](const LimbBatch &lb, int nb) {
-        dl.fwd_blocks(c, st, 2.0 * nb * N8, false, data, lb, nb, kNoFin);
+        dl.fwd_blocks(c, st, 2.0 * nb * N8, false, pro_pairs_rows(pro), data, lb, nb, kNoFin);
     });
 }
 
@@ -636,31 +636,71 @@ static bool special_finished(const he_ctx *c, int level, int first, int count, b
 // the modulus index from which on ks_raise finishes raised limbs
 static int finish_from(const he_ctx *c, int level, int first, bool finished) { return !finished ? c->M : first < level ? first : c->L; }
 
+// ModUp with the inverse column pass ahead of it in one kernel (k_ntt_fwd_cols_modup): the common case, N = 2^16 and 2^17, digits of up to four
+// limbs, all on the floating-point path, without the correction of the overshoot.
+static bool modup_fused(const he_ctx *c) { return dev_launch(c).modup && c->alpha <= 4 && !c->up_split && !c->exact_conv; }
+// The targets of a digit are shared out among so many work-groups that a launch of few operations puts one on every compute unit, and no
+// more, for each repeats the inverse column pass (N = 2^16: one rotation at level 13 93.5 us, with two on every unit 96.4; one product at level 6
+// 103.5 and 104.9).
+static int modup_chunks(int units, int targets) { return std::max(1, std::min(256 / (CONV_GROUPS * units), targets)); }
+
 // Steps 1-2 of the key switch for `count` polynomials (d_ntt2: products of two): operation o reads its NTT-domain input at
-// d_ntt + o*d_stride limbs and works in ws + o*w.total limbs.  Raised ciphertext limbs on the floating-point path
-// and special ones are left as the column pass wrote them (the inner-product kernels finish them), but for those of
-// modulus index finish_at and above.
-static int32_t ks_raise(he_ctx *c, const u64 *d_ntt, int d_stride, u64 *ws, const WsLayout &w, int level, int count,
+// d_ntt + from(o) limbs and works in ws + o*w.total limbs, laid out for `level`; levels: null, or the operations' own.  Raised ciphertext
+// limbs on the floating-point path and special ones are left as the column pass wrote them (the inner-product kernels finish
+// them), but for those of modulus index finish_at and above.
+template <class F>
+static int32_t ks_raise(he_ctx *c, const u64 *d_ntt, F from, u64 *ws, const WsLayout &w, int level, const int32_t *levels, int count,
                         hipStream_t st, int finish_at, const u64 *d_ntt2 = nullptr)
 {
     const size_t N = c->N;
-    const int K = c->K, Ma = level + K, beta = (level + c->alpha - 1) / c->alpha, W = (int)w.total;
+    const int K = c->K, Ma = level + K, W = (int)w.total;
+    const auto level_of = [&](int o) { return levels ? (int)levels[o] : level; };
     LimbList l;
-    for (int o = 0; o < count; o++)
-        for (int i = 0; i < level; i++) l.add(o * W + i, o * d_stride + i, i);
-    const ConvArgs cv = conv_args(c, ws + w.x * N, level, W, W);
-    int32_t rc = ntt_inverse(c, st, d_ntt, ws + w.x * N, l, SCALE_MODUP, cv, false, d_ntt2);
-    if (rc != HE_OK) return rc;
+    int src_limbs = 0, targets = 0;
+    for (int o = 0; o < count; o++) {
+        const int lo = level_of(o), beta = (lo + c->alpha - 1) / c->alpha;
+        for (int i = 0; i < lo; i++) l.add(o * W + i, from(o) + i, i);
+        src_limbs += lo, targets += beta * (lo + K) - lo;
+    }
+    ConvArgs cv = conv_args(c, ws + w.x * N, level, W, W);
+    for (int o = 0; levels && o < count; o++) cv.op_level[o] = (uint8_t)levels[o];
+    const bool fused = modup_fused(c);
+    // limbs that go through a column pass or a block pass of their own
     LimbList r;
-    for (int o = 0; o < count; o++)
+    for (int o = 0; o < count; o++) {
+        const int lo = level_of(o), beta = (lo + c->alpha - 1) / c->alpha;
         for (int j = 0; j < beta; j++) {
-            const int lo = j * c->alpha, hi = std::min(lo + c->alpha, level);
-            for (int a = 0; a < Ma; a++) {
-                if (a >= lo && a < hi) continue;
-                r.add(o * W + j * Ma + a, a < level ? a : c->L + (a - level));
+            const int dlo = j * c->alpha, dhi = std::min(dlo + c->alpha, lo);
+            for (int a = fused ? std::min(finish_at, level) : 0; a < Ma; a++) {
+                const int mi = active_mod(a, level, c->L);
+                if ((a >= dlo && a < dhi) || (a >= lo && a < level) || (fused && mi < finish_at)) continue;
+                r.add(o * W + j * Ma + a, mi);
             }
         }
-    return ntt_forward(c, st, ws + w.raised * N, r, PRO_MODUP, cv, nullptr, level * count, BLOCKS_SOME, finish_at);
+    }
+    int32_t rc;
+    if (!fused) {
+        if ((rc = ntt_inverse(c, st, d_ntt, ws + w.x * N, l, SCALE_MODUP, cv, false, d_ntt2)) != HE_OK) return rc;
+        return ntt_forward(c, st, ws + w.raised * N, r, PRO_MODUP, cv, nullptr, src_limbs, BLOCKS_SOME, finish_at);
+    }
+    const double N8 = (double)N * 8.0;
+    const DevLaunch &dl = dev_launch(c);
+    rc = for_batches(c, l, [&](const LimbBatch &lb, int nb) { dl.inv_blocks(c, st, (d_ntt2 ? 3.0 : 2.0) * nb * N8, d_ntt, d_ntt2, ws + w.x * N, lb, nb); });
+    if (rc != HE_OK) return rc;
+    ModUpArgs ua;
+    ua.x = ws + w.x * N, ua.raised = ws + w.raised * N;
+    ua.level = level, ua.L = c->L, ua.K = K, ua.alpha = c->alpha, ua.beta = (level + c->alpha - 1) / c->alpha, ua.stride = W;
+    ua.chunks = modup_chunks(ua.beta * count, Ma - c->alpha);
+    memcpy(ua.op_level, cv.op_level, sizeof(ua.op_level));
+    dl.modup(c, st, (double)(src_limbs + targets) * N8, count, ua);
+    if ((rc = launch_ok(c)) != HE_OK) return rc;
+    return for_batches(c, r, [&](const LimbBatch &lb, int nb) { dl.fwd_blocks(c, st, 2.0 * nb * N8, false, true, ws + w.raised * N, lb, nb, kNoFin); });
+}
+
+// limb offset of operation o's input where inputs are `stride` limbs apart
+static auto every(int stride)
+{
+    return [stride](int o) { return o * stride; };
 }
 
 static InnerArgs inner_args(const he_ctx *c, const he_evk *evk, const u64 *d_ntt, int d_stride, u64 *ws, const WsLayout &w,
@@ -836,7 +876,7 @@ extern "C" int32_t he_hmult_relin_batch(he_ctx *ctx, const he_evk *relin, const 
     const size_t N = ctx->N;
     const MultOut mo = mult_out(ctx, d_a, d_b, d_out, ws + w.tmp * N, (int)w.total, 2 * level, 2 * level, count);
     const bool finished = special_finished(ctx, level, level, count, false);
-    if ((rc = ks_raise(ctx, d_a + (size_t)level * N, 2 * level, ws, w, level, count, st, finish_from(ctx, level, level, finished),
+    if ((rc = ks_raise(ctx, d_a + (size_t)level * N, every(2 * level), ws, w, level, nullptr, count, st, finish_from(ctx, level, level, finished),
                        d_b + (size_t)level * N)) != HE_OK)
         return rc;
     if ((rc = ks_apply(ctx, mult_args(ctx, relin, d_a, d_b, ws, w, level, count, finished), nullptr, ws, w,
@@ -872,7 +912,7 @@ extern "C" int32_t he_hmult_relin_rescale_batch(he_ctx *ctx, const he_evk *relin
     const MultOut mo = mult_out(ctx, d_a, d_b, d_out, ws + w.tmp * N, W, 2 * level, 2 * (level - 1), count);
     const int first = level - 1; // the dropped limb goes with the special ones
     const bool finished = special_finished(ctx, level, first, count, false);
-    if ((rc = ks_raise(ctx, d_a + (size_t)level * N, 2 * level, ws, w, level, count, st, finish_from(ctx, level, first, finished),
+    if ((rc = ks_raise(ctx, d_a + (size_t)level * N, every(2 * level), ws, w, level, nullptr, count, st, finish_from(ctx, level, first, finished),
                        d_b + (size_t)level * N)) != HE_OK)
         return rc;
     InnerArgs ia = mult_args(ctx, relin, d_a, d_b, ws, w, level, count, finished);
@@ -926,7 +966,7 @@ extern "C" int32_t he_hrot_many(he_ctx *ctx, const he_evk *const *rots, int32_t 
     const WsLayout w = ws_layout(ctx, level);
     const u64 *c1 = d_ct + (size_t)level * ctx->N;
     const bool finished = special_finished(ctx, level, level, count, true);
-    if ((rc = ks_raise(ctx, c1, 0, ws, w, level, 1, st, finish_from(ctx, level, level, finished))) != HE_OK) return rc;
+    if ((rc = ks_raise(ctx, c1, every(0), ws, w, level, nullptr, 1, st, finish_from(ctx, level, level, finished))) != HE_OK) return rc;
     // With workspace for several operations the rotations share every launch: operation o keeps its inner
     // products and ModDown corrections in workspace o, all read the raised digits of workspace 0.
     int fit = (int)std::min<size_t>(ws_bytes / (w.total * ctx->N * sizeof(u64)), HE_OPS_MAX);
@@ -959,7 +999,7 @@ static int32_t hrot_batch_to(he_ctx *ctx, const he_evk *rot, const u64 *d_ct, in
     const WsLayout w = ws_layout(ctx, level);
     const u64 *c1 = d_ct + (size_t)level * ctx->N;
     const bool finished = special_finished(ctx, level, level, count, false);
-    if ((rc = ks_raise(ctx, c1, in_stride, ws, w, level, count, st, finish_from(ctx, level, level, finished))) != HE_OK) return rc;
+    if ((rc = ks_raise(ctx, c1, every(in_stride), ws, w, level, nullptr, count, st, finish_from(ctx, level, level, finished))) != HE_OK) return rc;
     return ks_apply(ctx, inner_args(ctx, rot, c1, in_stride, ws, w, level, count, nullptr, false, finished), nullptr, ws, w,
                     finish_args(ctx, d_out, out_stride, d_ct, in_stride, level, level), plus_input ? FIN_ROTSUM : FIN_ROT, st);
 }
@@ -1009,7 +1049,7 @@ extern "C" int32_t he_hrot_batch_keys(he_ctx *ctx, const he_evk *const *rots, co
         const int nb = std::min(fit, count - r);
         const u64 *in = d_ct + (size_t)r * ct_limbs * N, *c1 = in + (size_t)level * N;
         const bool finished = special_finished(ctx, level, level, nb, false);
-        if ((rc = ks_raise(ctx, c1, ct_limbs, ws, w, level, nb, st, finish_from(ctx, level, level, finished))) != HE_OK) return rc;
+        if ((rc = ks_raise(ctx, c1, every(ct_limbs), ws, w, level, nullptr, nb, st, finish_from(ctx, level, level, finished))) != HE_OK) return rc;
         OpArgs oa = {};
         for (int o = 0; o < nb; o++) {
             oa.evk[o] = rots[r + o]->dev, oa.g[o] = (unsigned)rots[r + o]->galois;
@@ -1044,7 +1084,6 @@ extern "C" int32_t he_hrot_batch_levels(he_ctx *ctx, const he_evk *const *rots, 
     hipStream_t st = (hipStream_t)stream;
     u64 *ws = (u64 *)d_ws;
     const size_t N = ctx->N;
-    const int K = ctx->K, alpha = ctx->alpha, L = ctx->L;
     size_t done_limbs = 0; // limbs of the operations already processed (inputs and outputs are packed alike)
     for (int r = 0; r < count;) {
         // group: as many operations as the workspace holds at the layout of their largest level
@@ -1057,43 +1096,24 @@ extern "C" int32_t he_hrot_batch_levels(he_ctx *ctx, const he_evk *const *rots, 
         }
         if (nb == 0) return HE_EWORKSPACE;
         const WsLayout w = ws_layout(ctx, lmax);
-        const int W = (int)w.total, Ma = lmax + K;
         const u64 *in0 = d_ct + done_limbs * N;
         u64 *out0 = d_out + done_limbs * N;
         std::vector<size_t> off(nb + 1, 0); // limb offset of operation o within the group
         for (int o = 0; o < nb; o++) off[o + 1] = off[o] + 2 * (size_t)h_levels[r + o];
         if (off[nb] > 65535) return HE_EINVAL;
-        ConvArgs cv = conv_args(ctx, ws + w.x * N, lmax, W, W);
         OpArgs oa = {};
         for (int o = 0; o < nb; o++) {
             const int lo = h_levels[r + o];
-            cv.op_level[o] = oa.level[o] = (uint8_t)lo;
+            oa.level[o] = (uint8_t)lo;
             oa.evk[o] = rots[r + o]->dev, oa.g[o] = (unsigned)rots[r + o]->galois;
             oa.d[o] = in0 + (off[o] + lo) * N; // c1
             oa.add[o] = in0 + off[o] * N;      // c0
             oa.out[o] = out0 + off[o] * N;
         }
-        // 1. inverse transform of every c1 limb, scaled for its digit's conversion
-        LimbList l;
-        for (int o = 0; o < nb; o++)
-            for (int i = 0; i < h_levels[r + o]; i++) l.add(o * W + i, (int)(off[o] + h_levels[r + o] + i), i);
-        if ((rc = ntt_inverse(ctx, st, in0, ws + w.x * N, l, SCALE_MODUP, cv)) != HE_OK) return rc;
-        // 2. raised digits
+        // 1 - 2
         const bool finished = special_finished(ctx, lmax, lmax, nb, false);
-        LimbList rl;
-        int src_limbs = 0;
-        for (int o = 0; o < nb; o++) {
-            const int lo = h_levels[r + o], beta = (lo + alpha - 1) / alpha;
-            src_limbs += lo;
-            for (int j = 0; j < beta; j++) {
-                const int dlo = j * alpha, dhi = std::min(dlo + alpha, lo);
-                for (int a = 0; a < Ma; a++) {
-                    if ((a >= dlo && a < dhi) || (a >= lo && a < lmax)) continue;
-                    rl.add(o * W + j * Ma + a, a < lmax ? a : L + (a - lmax));
-                }
-            }
-        }
-        if ((rc = ntt_forward(ctx, st, ws + w.raised * N, rl, PRO_MODUP, cv, nullptr, src_limbs, BLOCKS_SOME, finish_from(ctx, lmax, lmax, finished))) != HE_OK)
+        if ((rc = ks_raise(ctx, in0, [&](int o) { return (int)off[o] + h_levels[r + o]; }, ws, w, lmax, h_levels + r, nb, st,
+                           finish_from(ctx, lmax, lmax, finished))) != HE_OK)
             return rc;
         // 3 - 6
         if (misaligned16(ws)) return HE_EINVAL;

@@ -1,6 +1,6 @@
 // The inner product of key switching with the evaluation key.
 #pragma once
-#include "kernels_ntt.h"
+#include "kernels_conv.h"
 
 // ---- inner product with the evaluation key, fused with the transforms on both sides of it -----------------------
 //
@@ -21,7 +21,6 @@
 // memory either.  As one inner product over all limbs and a finishing block pass, u was written and read back:
 // 4 level limbs of traffic per operation, a tenth of a key switch's total.
 
-typedef u64 u64x2 __attribute__((ext_vector_type(2)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
 struct InnerArgs {
@@ -69,7 +68,6 @@ struct FinishArgs {
 // eight XCDs round-robin by index, and each XCD has its own L2: index 8 s + x runs on XCD x, and the `count`
 // operations of one (tile, limb) take consecutive s there, so the key slice they share is fetched from
 // memory once per XCD visit instead of once per operation.
-#define XCDS 8u
 __host__ __device__ inline unsigned inner_grid(unsigned tiles, unsigned limbs, unsigned count)
 {
     return (tiles * limbs + XCDS - 1) / XCDS * XCDS * count;
@@ -138,6 +136,21 @@ __device__ __forceinline__ BlockLane block_lane(u64 *lds, const double *tws)
     b.l3 = lds + b.blk * TILE_GROUP + 4 * b.t + (b.t >> 2);
     b.tw = tws + b.blk * 256;
     return b;
+}
+// This thread's eight values, t + 32 k of its block, from the two blocks in LDS as the column pass left them, rows interleaved.  A lane reads
+// four elements of both rows, 16 bytes at a time, the lower half of the wave k < 4 and the upper one k >= 4, and the halves swap what belongs to
+// the other's row: read one row at a time, every access would hit half of the banks only.
+__device__ __forceinline__ void mid_pairs8(const ArithFp &ar, double (&dv)[8], const u64 *pre, const BlockLane &b)
+{
+    const u64x2 *p = (const u64x2 *)pre + b.t + 128 * b.blk;
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        const u64x2 v = p[32 * k];
+        const auto l = __builtin_amdgcn_permlane32_swap((unsigned)v.x, (unsigned)v.y, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(v.x >> 32), (unsigned)(v.y >> 32), false, false);
+        dv[k] = ar.load_mid((u64)h[0] << 32 | l[0]);
+        dv[k + 4] = ar.load_mid((u64)h[1] << 32 | l[1]);
+    }
 }
 // Block pass of the eight values dv of this thread (pattern of step 1); the result is left in the wave's LDS, element e
 // of block b at tile_at(b, e), for the caller to read after a block_sync.  tw(m, i): twiddle of local stage m, group i of the block.
@@ -302,9 +315,7 @@ __device__ __forceinline__ void inner_products8(const InnerArgs &ia, const OpArg
             // this digit has arrived (nothing else of this wave is in flight here); once it is in registers the
             // buffer is free for the next one
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            const u64 *pw = pre + b.blk * 256 + b.t;
-#pragma unroll
-            for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(pw[32 * k]);
+            mid_pairs8(ar, dv, pre, b);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             {
                 const int jn = j + 1 == own ? j + 2 : j + 1;
@@ -453,11 +464,12 @@ __device__ __forceinline__ void special_products(const InnerArgs &ia, const OpAr
     for (int j0 = 0; j0 < beta; j0 += SPECIAL_WAVES) {
         const int jw = j0 + (int)wave;
         if (jw < beta && jw != own) {
-            const u64 *in = raised0 + (size_t)jw * raised_step + blk * 256 + il;
+            const u64 *in = raised0 + (size_t)jw * raised_step + (finished ? mid_at<false>(blk, il) : mid_at<true>(blk, il));
+            const unsigned step = finished ? 16 : 32;
             u64 *dig = lds + wave * SPECIAL_DIGIT;
             u64 x[16];
 #pragma unroll
-            for (int k = 0; k < 16; k++) x[k] = __builtin_nontemporal_load(in + 16 * k);
+            for (int k = 0; k < 16; k++) x[k] = __builtin_nontemporal_load(in + step * k);
             if (finished) {
 #pragma unroll
                 for (int k = 0; k < 16; k++) dig[tile_at(blk, il + 16 * k)] = x[k];
@@ -726,10 +738,10 @@ __device__ __forceinline__ void inner_fin_int(const InnerArgs &ia, const FinishA
 #pragma unroll 1
     for (int c = 0; c < 2; c++) {
         const BlockLane b = block_lane(lds + c * WAVE_BLOCKS * TILE_GROUP, nullptr);
-        const u64 *in = r_grp + c * ((size_t)ia.level << LOGN) + b.blk * 256 + b.t;
+        const u64 *in = r_grp + c * ((size_t)ia.level << LOGN) + mid_at<true>(b.blk, b.t);
         u64 v[8];
 #pragma unroll
-        for (int k = 0; k < 8; k++) v[k] = __builtin_nontemporal_load(in + 32 * k);
+        for (int k = 0; k < 8; k++) v[k] = __builtin_nontemporal_load(in + 64 * k);
         const unsigned G = w.grp * WAVE_BLOCKS + b.blk;
         block_pass8(ar, v, b, [&](int st, unsigned i) { return ar.twf[(1u << (LOGN - 8 + st)) + (G << st) + i]; });
     }
@@ -782,9 +794,7 @@ __device__ __forceinline__ void inner_fin_fp(const InnerArgs &ia, const FinishAr
         double dv[8];
         u64x2 av[4];
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        const u64 *pw = pre + b.blk * 256 + b.t;
-#pragma unroll
-        for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(pw[32 * k]);
+        mid_pairs8(ar, dv, pre, b);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         if (c == 0) wave_copy_4k<true>(r_lane + r_step, (char *)pre);
 #pragma unroll

@@ -23,6 +23,10 @@
 #pragma once
 #include "arith.h"
 
+typedef u64 u64x2 __attribute__((ext_vector_type(2)));
+// Work-groups go to the eight XCDs round-robin by index, and each XCD has its own L2.
+#define XCDS 8u
+
 // limbs per launch: the table below travels as a kernel argument (10 KiB); large launches matter, halving this
 // costs the conversion passes 11-14 %
 #ifndef HE_MAXB
@@ -42,6 +46,13 @@ struct LimbBatch {
 
 enum { PRO_LOAD = 0, PRO_MODUP = 1, PRO_MODDOWN = 2, PRO_RESCALE = 3, PRO_MODDOWN_RS = 4 };
 __host__ __device__ constexpr bool pro_is_moddown(int pro) { return pro == PRO_MODDOWN || pro == PRO_MODDOWN_RS; }
+// A column pass behind a conversion of the key switch (N = 2^16 and 2^17) leaves the limb with its rows, the blocks of 256 of the block pass,
+// interleaved by two: element e of block b at mid_at<true>(b, e).  A plain transform works in place and cannot.
+__host__ __device__ constexpr bool pro_pairs_rows(int pro) { return pro == PRO_MODUP || pro_is_moddown(pro); }
+template <bool PAIR> __device__ __forceinline__ unsigned mid_at(unsigned b, unsigned e)
+{
+    return PAIR ? (b >> 1) * 512u + 2u * e + (b & 1u) : b * 256u + e;
+}
 enum { SCALE_NONE = 0, SCALE_MODUP = 1, SCALE_MODDOWN = 2 };
 enum { EPI_STORE = 0, EPI_FIN = 1 };
 
@@ -83,7 +94,7 @@ struct FinArgs {
     int dst_stride, u_stride, out_stride; // limbs between two operations in each buffer
 };
 
-__device__ __forceinline__ int active_mod(int a, int level, int L) { return a < level ? a : L + (a - level); }
+__host__ __device__ __forceinline__ int active_mod(int a, int level, int L) { return a < level ? a : L + (a - level); }
 
 // NTT-domain index of the automorphism sigma_g: out[k] = in[k'] with
 // 2 brv(k') + 1 = (2 brv(k) + 1) g mod 2N.
@@ -369,7 +380,8 @@ __device__ __forceinline__ unsigned col_at(unsigned r, unsigned c) { return (r >
 
 // ---- block pass ---------------------------------------------------------------------------------------------
 
-template <int LOGN, int EPI, class A>
+// PAIR: the column pass has interleaved the rows; a wave's four blocks are two pairs, so that the result may still go in their place
+template <int LOGN, int EPI, bool PAIR, class A>
 __device__ __forceinline__ void fwd_blocks_body(u64 *__restrict__ limb, const A &ar, u64 *lds, unsigned tile,
                                                 const FinArgs &fa, const DevTables &T, unsigned slot)
 {
@@ -379,7 +391,7 @@ __device__ __forceinline__ void fwd_blocks_body(u64 *__restrict__ limb, const A 
     u64 uv[EPI == EPI_FIN ? 16 : 1];
 #pragma unroll
     for (int k = 0; k < 16; k++)
-        a[k] = ar.load_mid(__builtin_nontemporal_load(limb + bg * 256 + il + 16 * k)); // read once: the column pass wrote it
+        a[k] = ar.load_mid(__builtin_nontemporal_load(limb + mid_at<PAIR>(bg, il + 16 * k))); // read once: the column pass wrote it
     if (EPI == EPI_FIN) {
 #pragma unroll
         for (int k = 0; k < 16; k++) uv[k] = fin_load<LOGN>(fa, slot, bg * 256 + il + 16 * k);
@@ -452,7 +464,7 @@ __device__ __forceinline__ void inv_blocks_body(const u64 *in, const u64 *in2, u
 }
 
 // grid.x = (N/4096) * batch
-template <int LOGN, int EPI>
+template <int LOGN, int EPI, bool PAIR>
 __global__ __launch_bounds__(BLK_THREADS, EPI == EPI_FIN ? 4 : 1) void k_ntt_fwd_blocks(u64 *__restrict__ data, DevTables T, LimbBatch lb, FinArgs fa)
 {
     __shared__ u64 lds[BLK_PER_WG * TILE_GROUP];
@@ -461,9 +473,9 @@ __global__ __launch_bounds__(BLK_THREADS, EPI == EPI_FIN ? 4 : 1) void k_ntt_fwd
     const unsigned mi = lb.mod[b], slot = lb.slot[b];
     u64 *limb = data + ((size_t)slot << LOGN);
     if (T.mod[mi].qd != 0.0)
-        fwd_blocks_body<LOGN, EPI>(limb, make_fp(T, mi, LOGN), lds, tile, fa, T, slot);
+        fwd_blocks_body<LOGN, EPI, PAIR>(limb, make_fp(T, mi, LOGN), lds, tile, fa, T, slot);
     else
-        fwd_blocks_body<LOGN, EPI>(limb, make_int(T, mi, LOGN), lds, tile, fa, T, slot);
+        fwd_blocks_body<LOGN, EPI, PAIR>(limb, make_int(T, mi, LOGN), lds, tile, fa, T, slot);
 }
 
 // src2: with PROD, the second factor, at the same limbs as src
@@ -508,9 +520,9 @@ __device__ __forceinline__ void cols_inputs(typename A::V (&a)[16], const u64 *_
         a[k] = PRO == PRO_LOAD ? ar.load(__builtin_nontemporal_load(limb + pos)) : conv_get<PRO, SPLIT, TINT, EX>(S, ar, m, pos);
     }
 }
-// second phase of the forward column pass for rows 16 g .. 16 g + 15, held in LDS as group gl.  STREAM: the
+// second phase of the forward column pass for rows 16 g .. 16 g + 15, held in LDS as group gl.  With a prologue the
 // output is a new buffer that a later kernel reads, so it is stored past the sources that stay in L2
-template <int S_BASE, bool STREAM, class A>
+template <int S_BASE, int PRO, class A>
 __device__ __forceinline__ void cols_finish_group(typename A::V (&a)[16], u64 *__restrict__ limb, unsigned col0, unsigned g,
                                                   unsigned gl, const A &ar, const u64 *lds)
 {
@@ -518,10 +530,16 @@ __device__ __forceinline__ void cols_finish_group(typename A::V (&a)[16], u64 *_
 #pragma unroll
     for (int k = 0; k < 16; k++) a[k] = ar.load_mid(lds[col_at(16 * gl + k, c)]);
     ar.fwd16(a, S_BASE, g, true);
+    if constexpr (pro_pairs_rows(PRO)) {
+#pragma unroll
+        for (int k = 0; k < 16; k += 2)
+            __builtin_nontemporal_store(u64x2{ar.store_mid(a[k]), ar.store_mid(a[k + 1])}, (u64x2 *)(limb + mid_at<true>(16 * g + k, col0 + c)));
+        return;
+    }
 #pragma unroll
     for (int k = 0; k < 16; k++) { // the block pass finishes
         u64 *dst = limb + (16 * g + k) * 256 + col0 + c;
-        if (STREAM)
+        if (PRO != PRO_LOAD)
             __builtin_nontemporal_store(ar.store_mid(a[k]), dst);
         else
             *dst = ar.store_mid(a[k]);
@@ -541,7 +559,7 @@ __device__ __forceinline__ void fwd_cols_body(u64 *__restrict__ limb, unsigned c
 #pragma unroll
         for (int k = 0; k < 16; k++) lds[col_at(rl + 16 * k, c)] = ar.store_mid(a0[k]);
         __syncthreads();
-        cols_finish_group<4, PRO != PRO_LOAD>(a0, limb, col0, rl, rl, ar, lds);
+        cols_finish_group<4, PRO>(a0, limb, col0, rl, rl, ar, lds);
     } else {
         typename A::V a1[16];
         // one half's source loads at a time: 32 outputs x up to 8 sources in flight would not fit the registers
@@ -554,12 +572,12 @@ __device__ __forceinline__ void fwd_cols_body(u64 *__restrict__ limb, unsigned c
 #pragma unroll
         for (int k = 0; k < 16; k++) lds[col_at(rl + 16 * k, c)] = ar.store_mid(a0[k]);
         __syncthreads();
-        cols_finish_group<5, PRO != PRO_LOAD>(a0, limb, col0, rl, rl, ar, lds);
+        cols_finish_group<5, PRO>(a0, limb, col0, rl, rl, ar, lds);
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < 16; k++) lds[col_at(rl + 16 * k, c)] = ar.store_mid(a1[k]);
         __syncthreads();
-        cols_finish_group<5, PRO != PRO_LOAD>(a1, limb, col0, rl + 16, rl, ar, lds);
+        cols_finish_group<5, PRO>(a1, limb, col0, rl + 16, rl, ar, lds);
     }
 }
 
@@ -654,19 +672,19 @@ __device__ __forceinline__ void fwd_cols_kernel(u64 *__restrict__ data, const De
     fwd_cols_limb<LOGN, PRO, NSMAX, EX>(data, T, lb, cv, blockIdx.x & 15, blockIdx.x >> 4, lds);
 }
 
-// ModUp column pass for two limbs per work-group (N = 2^16; grid.x = 16 * ceil(batch / 2)): limbs 2i and 2i+1 of
+// ModUp column pass of the corrected conversion for two limbs per work-group (N = 2^16; grid.x = 16 * ceil(batch / 2)): limbs 2i and 2i+1 of
 // the launch.  When both are floating-point targets of the same digit of the same operation (the usual case:
 // the targets of a digit follow each other in a launch), the digit's source limbs are read and converted to
 // doubles once and both base conversions are formed from them, term by term as in conv_get; every target
 // otherwise re-reads the same source tile through L2.  Any other pair is processed one limb after the other.
-template <int NSMAX, bool EX>
+template <int NSMAX>
 __global__ __launch_bounds__(256) void k_ntt_fwd_cols16_modup2(u64 *__restrict__ data, DevTables T, LimbBatch lb,
                                                                 ConvArgs cv, int nb)
 {
     __shared__ u64 lds[ColsGeom<16>::LDS_WORDS];
     const unsigned tile = blockIdx.x & 15, b0 = (blockIdx.x >> 4) * 2, b1 = b0 + 1;
     if (b1 >= (unsigned)nb) {
-        fwd_cols_limb<16, PRO_MODUP, NSMAX, EX>(data, T, lb, cv, tile, b0, lds);
+        fwd_cols_limb<16, PRO_MODUP, NSMAX, true>(data, T, lb, cv, tile, b0, lds);
         return;
     }
     const unsigned mi0 = lb.mod[b0], mi1 = lb.mod[b1], slot0 = lb.slot[b0], slot1 = lb.slot[b1];
@@ -676,9 +694,9 @@ __global__ __launch_bounds__(256) void k_ntt_fwd_cols16_modup2(u64 *__restrict__
 #pragma unroll
     for (int s = 0; s < NSMAX; s++) same = same && S0.sp[s] == S1.sp[s];
     if (!same) {
-        fwd_cols_limb<16, PRO_MODUP, NSMAX, EX>(data, T, lb, cv, tile, b0, lds);
+        fwd_cols_limb<16, PRO_MODUP, NSMAX, true>(data, T, lb, cv, tile, b0, lds);
         __syncthreads(); // the first limb's second phase has read the tile
-        fwd_cols_limb<16, PRO_MODUP, NSMAX, EX>(data, T, lb, cv, tile, b1, lds);
+        fwd_cols_limb<16, PRO_MODUP, NSMAX, true>(data, T, lb, cv, tile, b1, lds);
         return;
     }
     const ArithFp ar0 = make_fp(T, mi0, 16), ar1 = make_fp(T, mi1, 16);
@@ -691,29 +709,26 @@ __global__ __launch_bounds__(256) void k_ntt_fwd_cols16_modup2(u64 *__restrict__
 #pragma unroll
         for (int s = 0; s < NSMAX; s++) {
             const double y = u2d(S0.sp[s][pos]);
-            if (EX) sv = sv + y * S0.rq[s];
+            sv = sv + y * S0.rq[s];
             acc0 += ar0.mulmod(y, S0.cd[s]);
             acc1 += ar1.mulmod(y, S1.cd[s]);
             if ((s & 3) == 3 && s + 1 < NSMAX) acc0 = ar0.reduce(acc0), acc1 = ar1.reduce(acc1);
         }
-        if (EX) { // one estimate of the multiple of D for both targets
-            const double v = __builtin_floor(sv);
-            acc0 -= v * S0.dm_d, acc1 -= v * S1.dm_d;
-        }
-        a0[k] = acc0, a1[k] = acc1;
+        const double v = __builtin_floor(sv); // one estimate of the multiple of D for both targets
+        a0[k] = acc0 - v * S0.dm_d, a1[k] = acc1 - v * S1.dm_d;
     }
     u64 *limb0 = data + ((size_t)slot0 << 16), *limb1 = data + ((size_t)slot1 << 16);
     ar0.fwd16(a0, 0, 0, true);
 #pragma unroll
     for (int k = 0; k < 16; k++) lds[col_at(rl + 16 * k, c)] = ar0.store_mid(a0[k]);
     __syncthreads();
-    cols_finish_group<4, true>(a0, limb0, col0, rl, rl, ar0, lds);
+    cols_finish_group<4, PRO_MODUP>(a0, limb0, col0, rl, rl, ar0, lds);
     __syncthreads();
     ar1.fwd16(a1, 0, 0, true);
 #pragma unroll
     for (int k = 0; k < 16; k++) lds[col_at(rl + 16 * k, c)] = ar1.store_mid(a1[k]);
     __syncthreads();
-    cols_finish_group<4, true>(a1, limb1, col0, rl, rl, ar1, lds);
+    cols_finish_group<4, PRO_MODUP>(a1, limb1, col0, rl, rl, ar1, lds);
 }
 // grid.x = 16 * batch
 // EX: the corrected conversions (a kernel of its own: their extra registers would cost the default form waves)

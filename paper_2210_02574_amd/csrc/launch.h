@@ -55,13 +55,15 @@ struct DevLaunch {
     // the same with the corrected base conversions (entries of prologues without a conversion stay null)
     void (*fwd_cols_ex[5])(he_ctx *c, hipStream_t st, int kid, double bytes, bool wide, u64 *data, const LimbBatch &lb, int nb,
                            const ConvArgs &cv);
-    // forward block pass of the first nb limbs of lb; fin: with the finishing epilogue
-    void (*fwd_blocks)(he_ctx *c, hipStream_t st, double bytes, bool fin, u64 *data, const LimbBatch &lb, int nb,
+    // forward block pass of the first nb limbs of lb; fin: with the finishing epilogue; pairs: their rows are interleaved
+    void (*fwd_blocks)(he_ctx *c, hipStream_t st, double bytes, bool fin, bool pairs, u64 *data, const LimbBatch &lb, int nb,
                        const FinArgs &fa);
     // src2: null, or a second factor of the transform's input
     void (*inv_blocks)(he_ctx *c, hipStream_t st, double bytes, const u64 *src, const u64 *src2, u64 *dst, const LimbBatch &lb, int nb);
     void (*inv_cols)(he_ctx *c, hipStream_t st, double bytes, int scale, u64 *dst, const LimbBatch &lb, int nb,
                      const ConvArgs &cv);
+    // ModUp of `count` operations with the inverse column pass ahead of it: digits of up to four limbs on the floating-point path
+    void (*modup)(he_ctx *c, hipStream_t st, double bytes, int count, const ModUpArgs &ua);
     // inner product on the limbs ia.first .. level + K - 1, and the finishing one on the first fa.nl limbs (path: FIN_FP, ..)
     void (*inner)(he_ctx *c, hipStream_t st, double bytes, unsigned grid, const InnerArgs &ia, const OpArgs &oa);
     void (*inner_fin)(he_ctx *c, hipStream_t st, double bytes, unsigned grid, int mode, int path, const InnerArgs &ia, const FinishArgs &fa,
@@ -72,6 +74,8 @@ struct DevLaunch {
 void dev_launch_n12(DevLaunch &t);
 void dev_launch_n16_blocks(DevLaunch &t);
 void dev_launch_n17_blocks(DevLaunch &t);
+void dev_launch_conv16(DevLaunch &t);
+void dev_launch_conv17(DevLaunch &t);
 #define HE_DECL_COLS(n)                                                                                              \
     void dev_launch_cols##n##_0(DevLaunch &t);                                                                       \
     void dev_launch_cols##n##_1(DevLaunch &t);                                                                       \
@@ -88,16 +92,22 @@ HE_DECL_COLS(17)
 
 // ---- launcher bodies, instantiated by the per-ring-size translation units ------------------------------
 
-template <int LOGN>
-static void launch_fwd_blocks(he_ctx *c, hipStream_t st, double bytes, bool fin, u64 *data, const LimbBatch &lb, int nb,
-                              const FinArgs &fa)
+template <int LOGN, bool PAIR>
+static void launch_fwd_blocks_layout(he_ctx *c, hipStream_t st, double bytes, bool fin, u64 *data, const LimbBatch &lb, int nb,
+                                     const FinArgs &fa)
 {
     if (fin)
-        KLAUNCH_T(c, st, KID_FWD_BLOCKS_FIN, bytes, (k_ntt_fwd_blocks<LOGN, EPI_FIN>), BLK_TILES(c) * nb, BLK_THREADS, data,
+        KLAUNCH_T(c, st, KID_FWD_BLOCKS_FIN, bytes, (k_ntt_fwd_blocks<LOGN, EPI_FIN, PAIR>), BLK_TILES(c) * nb, BLK_THREADS, data,
                   c->dev, lb, fa);
     else
-        KLAUNCH_T(c, st, KID_FWD_BLOCKS, bytes, (k_ntt_fwd_blocks<LOGN, EPI_STORE>), BLK_TILES(c) * nb, BLK_THREADS, data,
+        KLAUNCH_T(c, st, KID_FWD_BLOCKS, bytes, (k_ntt_fwd_blocks<LOGN, EPI_STORE, PAIR>), BLK_TILES(c) * nb, BLK_THREADS, data,
                   c->dev, lb, fa);
+}
+template <int LOGN>
+static void launch_fwd_blocks(he_ctx *c, hipStream_t st, double bytes, bool fin, bool pairs, u64 *data, const LimbBatch &lb, int nb,
+                              const FinArgs &fa)
+{
+    (pairs ? launch_fwd_blocks_layout<LOGN, true> : launch_fwd_blocks_layout<LOGN, false>)(c, st, bytes, fin, data, lb, nb, fa);
 }
 template <int LOGN>
 static void launch_inv_blocks(he_ctx *c, hipStream_t st, double bytes, const u64 *src, const u64 *src2, u64 *dst,

@@ -1,0 +1,60 @@
+"""Base conversions of the key switch at N = 2^16 and 2^17 against the oracle, bit for bit: digits of one to four limbs and a last digit
+that is shorter, special primes on either arithmetic path, operations of several levels in one launch, one operation (its targets
+shared out among several work-groups) and a few, uniform residues and the largest ones."""
+import numpy as np
+import pytest
+
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+SETS = {
+    "three16": wl.Params("three16", 16, wl.N16.q[:7], wl.N16.p[:2], 3),  # digits of 3, 3, 1
+    "two16": wl.Params("two16", 16, wl.N16.q[:6], wl.N16.q[10:13], 3),  # special primes below 2^50
+    "one16": wl.Params("one16", 16, wl.N16.q[:3], (wl.N16.p[0],), 3),  # digits of 1
+    "four17": wl.Params("four17", 17, wl.P17.q[:6], wl.P17.p[:3], 2),  # digits of 3, 3
+    "mixed17": wl.Params("mixed17", 17, wl.P17.q[:5], (wl.P17.p[0], wl.P17.q[9]), 2),  # special primes of both kinds
+}
+
+
+@pytest.fixture(scope="module", params=sorted(SETS))
+def env(request, oracle_mod):
+    import paper_2210_02574_amd as pkg
+
+    p = SETS[request.param]
+    he, o = pkg.HE.from_params(p, device=0), oracle_mod.Oracle(p.logN, p.q, p.p, p.dnum)
+    return he, o, p, wl.uniform_evk(11, p)
+
+
+def _largest(p, level):
+    """Every NTT value of both components is q - 1."""
+    return np.stack([np.stack([np.full(p.N, p.q[i] - 1, dtype=np.uint64) for i in range(level)])] * 2)
+
+
+def test_rotations_of_every_level(env):
+    he, o, p, evk = env
+    key = he.evk_from_host(evk, he.galois_element(3))
+    levels = list(range(1, p.L + 1))
+    cts = [wl.uniform_ct(60 + lv, p, lv) for lv in levels]
+    want = [o.hrot(ct, evk, 3) for ct in cts]
+    for ct, w in zip(cts, want):
+        assert np.array_equal(he.to_host(he.hrot(key, he.to_device(ct))), w)
+    # in one launch, the buffers laid out for the largest level
+    packed = he.to_device(np.concatenate([ct.reshape(-1, p.N) for ct in cts]))
+    got = he.to_host(he.hrot_batch_levels([key] * len(levels), levels, packed))
+    assert np.array_equal(got, np.concatenate([w.reshape(-1, p.N) for w in want]))
+
+
+def test_products(env):
+    he, o, p, evk = env
+    key, count = he.evk_from_host(evk, 1), 3
+    for level in (2, p.L):
+        a = np.stack([wl.uniform_ct(80 + level, p, level), _largest(p, level), wl.uniform_ct(81 + level, p, level)])
+        b = np.stack([wl.uniform_ct(90 + level, p, level), _largest(p, level), a[2]])
+        prod = [o.hmult_relin(x, y, evk) for x, y in zip(a, b)]
+        da, db = he.to_device(a), he.to_device(b)
+        assert np.array_equal(he.to_host(he.hmult_relin_batch(key, da, db)), np.stack(prod))
+        resc = np.stack([o.rescale(x) for x in prod])
+        assert np.array_equal(he.to_host(he.hmult_relin_rescale_batch(key, da, db)), resc)
+        for i in range(count):
+            assert np.array_equal(he.to_host(he.hmult_relin_rescale(key, da[i], db[i])), resc[i])
