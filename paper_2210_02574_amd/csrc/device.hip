@@ -639,10 +639,15 @@ static int finish_from(const he_ctx *c, int level, int first, bool finished) { r
 // ModUp with the inverse column pass ahead of it in one kernel (k_ntt_fwd_cols_modup): the common case, N = 2^16 and 2^17, digits of up to four
 // limbs, all on the floating-point path, without the correction of the overshoot.
 static bool modup_fused(const he_ctx *c) { return dev_launch(c).modup && c->alpha <= 4 && !c->up_split && !c->exact_conv; }
+// The same for ModDown's corrections (k_ntt_fwd_cols_moddown): up to four special primes, ciphertext limbs on the floating-point path.
+static bool moddown_fused(const he_ctx *c)
+{
+    return dev_launch(c).moddown && c->K <= 4 && !c->up_split && (!c->dn_split || c->dn_fold) && !c->exact_conv;
+}
 // The targets of a digit are shared out among so many work-groups that a launch of few operations puts one on every compute unit, and no
 // more, for each repeats the inverse column pass (N = 2^16: one rotation at level 13 93.5 us, with two on every unit 96.4; one product at level 6
 // 103.5 and 104.9).
-static int modup_chunks(int units, int targets) { return std::max(1, std::min(256 / (CONV_GROUPS * units), targets)); }
+static int conv_chunks(int units, int targets) { return std::max(1, std::min(256 / (CONV_GROUPS * units), targets)); }
 
 // Steps 1-2 of the key switch for `count` polynomials (d_ntt2: products of two): operation o reads its NTT-domain input at
 // d_ntt + from(o) limbs and works in ws + o*w.total limbs, laid out for `level`; levels: null, or the operations' own.  Raised ciphertext
@@ -690,7 +695,7 @@ static int32_t ks_raise(he_ctx *c, const u64 *d_ntt, F from, u64 *ws, const WsLa
     ModUpArgs ua;
     ua.x = ws + w.x * N, ua.raised = ws + w.raised * N;
     ua.level = level, ua.L = c->L, ua.K = K, ua.alpha = c->alpha, ua.beta = (level + c->alpha - 1) / c->alpha, ua.stride = W;
-    ua.chunks = modup_chunks(ua.beta * count, Ma - c->alpha);
+    ua.chunks = conv_chunks(ua.beta * count, Ma - c->alpha);
     memcpy(ua.op_level, cv.op_level, sizeof(ua.op_level));
     dl.modup(c, st, (double)(src_limbs + targets) * N8, count, ua);
     if ((rc = launch_ok(c)) != HE_OK) return rc;
@@ -739,8 +744,8 @@ static double inner_words(const he_ctx *c, const InnerArgs &ia, const OpArgs *oa
     return words;
 }
 
-// Steps 3 and 4: the scaled coefficient-domain digits of the special limbs, in u.  ia.first < level: also u on the
-// limbs from there on.
+// Steps 3 and 4: the scaled coefficient-domain digits of the special limbs, in u (where ModDown's kernel makes them itself, what the inverse block
+// pass leaves).  ia.first < level: also u on the limbs from there on.
 static int32_t ks_special(he_ctx *c, const InnerArgs &ia, const OpArgs *oa, const WsLayout &w, hipStream_t st)
 {
     const size_t N = c->N;
@@ -754,13 +759,33 @@ static int32_t ks_special(he_ctx *c, const InnerArgs &ia, const OpArgs *oa, cons
     dev_launch(c).inner(c, st, bytes, inner_grid((unsigned)(N / INNER_TILE), (unsigned)(Ma - ia.first), (unsigned)ia.count), ia,
                         oa ? *oa : kNoOps);
     int32_t rc = launch_ok(c);
-    if (rc != HE_OK) return rc;
+    if (rc != HE_OK || moddown_fused(c)) return rc;
     LimbList sp;
     for (int o = 0; o < ia.count; o++)
         for (int cc = 0; cc < 2; cc++)
             for (int k = 0; k < K; k++) sp.add(o * W + cc * Ma + ia.level + k, c->L + k);
     const ConvArgs cv = conv_args(c, ia.u, ia.level, W, W);
     return ntt_inverse(c, st, ia.u, ia.u, sp, SCALE_MODDOWN, cv, true);
+}
+
+// ModDown's corrections of the ciphertext limbs [first, first + limbs) into ws, step 5 with the inverse column pass of step 4.
+static int32_t ks_corrections(he_ctx *c, const InnerArgs &ia, const OpArgs *oa, const WsLayout &w, u64 *ws, int first, int limbs, bool rs, bool keep,
+                              hipStream_t st)
+{
+    ModDownArgs da;
+    da.u = ia.u, da.r = ws + w.r * c->N;
+    da.level = ia.level, da.L = c->L, da.K = c->K, da.stride = (int)w.total;
+    da.first = first, da.limbs = limbs, da.keep = keep ? 1 : 0;
+    da.chunks = conv_chunks(2 * ia.count, limbs);
+    memset(da.op_level, 0, sizeof(da.op_level));
+    double moved = (2.0 * c->K + (rs ? 2.0 : keep ? 2.0 * c->K : 0.0)) * ia.count;
+    for (int o = 0; o < ia.count; o++) {
+        const int level = oa && oa->level[o] ? oa->level[o] : ia.level;
+        if (oa) da.op_level[o] = oa->level[o];
+        moved += 2.0 * std::max(0, std::min(first + limbs, level) - first);
+    }
+    dev_launch(c).moddown(c, st, moved * c->N * 8.0, rs, ia.count, da);
+    return launch_ok(c);
 }
 
 // Steps 5 and 6 on the first fa.nl limbs of every operation (those that it has): pro is the prologue of the
@@ -785,7 +810,8 @@ static int32_t ks_finish(he_ctx *c, const InnerArgs &ia, const OpArgs *oa, const
         dev_launch(c).fin_limb(c, st, words * N * 8.0, std::max(c->alpha, c->K) > 4, pro, false, mode, ia, fa, oa ? *oa : kNoOps, cv);
         return launch_ok(c);
     }
-    int32_t rc = ntt_forward(c, st, r, l, pro, cv, nullptr, 2 * c->K * ia.count + extra, BLOCKS_NONE);
+    int32_t rc = moddown_fused(c) ? ks_corrections(c, ia, oa, w, ws, 0, fa.nl, pro == PRO_MODDOWN_RS, false, st)
+                                  : ntt_forward(c, st, r, l, pro, cv, nullptr, 2 * c->K * ia.count + extra, BLOCKS_NONE);
     if (rc != HE_OK) return rc;
     const unsigned grid = inner_grid((unsigned)(N / INNER_TILE), (unsigned)fa.nl, (unsigned)ia.count);
     int n_int = 0;
@@ -934,8 +960,19 @@ extern "C" int32_t he_hmult_relin_rescale_batch(he_ctx *ctx, const he_evk *relin
         for (int o = 0; o < count; o++)
             for (int cc = 0; cc < 2; cc++) last.add(o * W + cc * level + level - 1, level - 1);
         const FinArgs fl = {ws + w.u * N, rbuf, ctx->dev.dn_pinv, ctx->dev.dn_pinv_d, Ma, level, level, W, W, W};
-        if ((rc = ntt_forward(ctx, st, rbuf, last, PRO_MODDOWN, cv, &fl, 2 * K * count)) != HE_OK) return rc;
-        if ((rc = ntt_inverse(ctx, st, rbuf, rbuf, last, SCALE_NONE, cv)) != HE_OK) return rc;
+        if (moddown_fused(ctx)) { // the dropped limb's inverse column pass is part of the last conversion
+            const double N8 = (double)N * 8.0;
+            const DevLaunch &dl = dev_launch(ctx);
+            if ((rc = ks_corrections(ctx, ia, nullptr, w, ws, first, 1, false, true, st)) != HE_OK) return rc;
+            rc = for_batches(ctx, last, [&](const LimbBatch &lb, int nb) {
+                dl.fwd_blocks(ctx, st, 3.0 * nb * N8, true, true, rbuf, lb, nb, fl);
+                dl.inv_blocks(ctx, st, 2.0 * nb * N8, rbuf, nullptr, rbuf, lb, nb);
+            });
+            if (rc != HE_OK) return rc;
+        } else {
+            if ((rc = ntt_forward(ctx, st, rbuf, last, PRO_MODDOWN, cv, &fl, 2 * K * count)) != HE_OK) return rc;
+            if ((rc = ntt_inverse(ctx, st, rbuf, rbuf, last, SCALE_NONE, cv)) != HE_OK) return rc;
+        }
     }
     // every other limb: ModDown and rescale corrections in one transform
     fa.nl = fa.out_cstride = level - 1;

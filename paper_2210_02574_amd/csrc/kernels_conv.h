@@ -5,6 +5,10 @@
 // targets, 56 instead of 72 FP64 instructions per output: one rotation at level 13 7.5 + 24.4 -> 19.7 us, eight at level 24
 // 41 + 290 -> 285 us, four at N = 2^17, level 30, 57 + 584 -> 490 us; 16 products with rescale 1827 -> 1695 us as a call.
 //
+// ModDown's corrections, one rotation at level 13: 10.0 + 13.2 -> 19.4 us (inverse column pass of the special limbs and column pass of the
+// corrections before), eight at level 24 32 + 142 -> 132, four at N = 2^17, level 30, 35 + 168 -> 186 (the centring and splitting of a digit
+// is done once, not once per target).  A product with rescale at level 6 takes three launches fewer, 102 -> 95 us as a call.
+//
 // A conversion reads a few source limbs (a digit's, or the special ones) and makes many target limbs of them.  One work-group
 // takes CONV_COLS columns of all rows: its waves run the inverse column pass of one source each and leave the scaled coefficients
 // in LDS, then each wave makes one target after the other: conversion, forward column pass, store.  Sources are read once
@@ -30,6 +34,8 @@ template <int LOGN> struct ConvGeom {
     // two work-groups per compute unit, four waves per SIMD; N = 2^17, with twice the values per lane and sources of twice the
     // size, one of three waves per SIMD (at four, 31 registers go to scratch memory)
     static constexpr int WAVES = LOGN == 16 ? 8 : 12, BOUND = LOGN == 16 ? 4 : 3;
+    // ModDown, whose inverse column pass is on the integer path as a rule: two waves per SIMD at N = 2^17
+    static constexpr int DOWN_WAVES = 8, DOWN_BOUND = LOGN == 16 ? 4 : 2;
 };
 // A lane's place: in the strided pattern it holds rows (lane >> 2) + 16 k of column lane & 3, in the consecutive one rows
 // 16 (lane >> 2) + k.
@@ -67,20 +73,24 @@ __device__ __forceinline__ void conv_inverse(typename A::V (&v)[ConvGeom<LOGN>::
     for (int h = 0; h < H; h++)
 #pragma unroll
         for (int k = 0; k < 16; k++) v[h][k] = ar.load_mid(col[(16 * (g + 16 * h) + k) * 256]);
-#pragma unroll
-    for (int h = 0; h < H; h++) {
-        ar.template inv16<false>(v[h], H + 3, g + 16 * h);
-        conv_exchange<false>(v[h], ar, ex);
+    // written out: as a loop it is too large for the compiler to unroll, and the values, indexed by the half, go to scratch memory
+    const auto half = [&](typename A::V (&a)[16], int h) __attribute__((always_inline)) {
+        ar.template inv16<false>(a, H + 3, g + 16 * h);
+        conv_exchange<false>(a, ar, ex);
         if (H == 1)
-            ar.template inv16<true>(v[h], 0, 0);
+            ar.template inv16<true>(a, 0, 0);
         else
-            ar.template inv16<false>(v[h], 1, h);
+            ar.template inv16<false>(a, 1, h);
+    };
+    half(v[0], 0);
+    if constexpr (H == 2) {
+        half(v[1], 1);
+        ar.inv_stage0_last(v[0], v[1]);
     }
-    if constexpr (H == 2) ar.inv_stage0_last(v[0], v[1]);
 }
 
-// Forward column pass of the values of conv_inverse's pattern (floating point: within 1.25 q of zero; the first five stages then stay
-// below 6.6 q), stored with the rows interleaved by two.
+// Forward column pass of the values of conv_inverse's pattern (floating point: within 1.5 q of zero; the first five stages then stay
+// below 7.2 q), stored with the rows interleaved by two.
 template <int LOGN, class A>
 __device__ __forceinline__ void conv_forward(typename A::V (&v)[ConvGeom<LOGN>::HALVES][16], u64 *limb, unsigned col, const A &ar, unsigned *ex)
 {
@@ -93,25 +103,26 @@ __device__ __forceinline__ void conv_forward(typename A::V (&v)[ConvGeom<LOGN>::
         ar.fwd16(v[0], 1, 0, false);
         ar.fwd16(v[1], 1, 1, false);
     }
-#pragma unroll
-    for (int h = 0; h < H; h++) {
-        conv_exchange<true>(v[h], ar, ex);
-        ar.fwd16(v[h], H + 3, g + 16 * h, true);
+    const auto half = [&](typename A::V (&a)[16], int h) __attribute__((always_inline)) {
+        conv_exchange<true>(a, ar, ex);
+        ar.fwd16(a, H + 3, g + 16 * h, true);
         u64 *o = limb + (size_t)(g + 16 * h) * 4096 + 2 * col;
 #pragma unroll
         for (int p = 0; p < 8; p++) // read by a later kernel
-            __builtin_nontemporal_store(u64x2{ar.store_mid(v[h][2 * p]), ar.store_mid(v[h][2 * p + 1])}, (u64x2 *)(o + 512 * p));
-    }
+            __builtin_nontemporal_store(u64x2{ar.store_mid(a[2 * p]), ar.store_mid(a[2 * p + 1])}, (u64x2 *)(o + 512 * p));
+    };
+    half(v[0], 0);
+    if constexpr (H == 2) half(v[1], 1);
 }
 
-// Sum of up to four products y c modulo q, |y| < 2^50, |c| <= q/2, q < 2^50: 21 instructions for four.  The running sum is
-// kept on the grid of multiples of 2^50 (ulp of the bias), which every step's rounding error, an integer below 2^49, completes exactly; one
-// quotient then serves all products.  The result is within 1.25 q of zero.
-#define CONV_BIAS 7605903601369376408980219232256.0 // 1.5 * 2^102
+// Sum of up to five products y c modulo q, |y| <= 2^50 (of a fifth one 2^49), |c| <= q/2, q < 2^50: 21 instructions for four.  The
+// running sum is kept on the grid of multiples of 2^50 (2^51 for five), the ulp of the bias; every step's rounding error, an integer of at most half
+// a grid step, completes it exactly, and one quotient serves all products.  The result is within 1.25 q of zero (1.5 q for five).
 template <int NS> __device__ __forceinline__ double conv_sum_fp(const double (&y)[NS], const double (&c)[NS], double q, double qinv)
 {
-    static_assert(NS <= 4, "the bias leaves room for four products");
-    double acc = CONV_BIAS, low = 0.0;
+    static_assert(NS <= 5, "the bias leaves room for five products");
+    constexpr double BIAS = (NS <= 4 ? 1.0 : 2.0) * 7605903601369376408980219232256.0; // 1.5 * 2^102, 1.5 * 2^103
+    double acc = BIAS, low = 0.0;
 #pragma unroll
     for (int s = 0; s < NS; s++) {
         const double next = __builtin_fma(y[s], c[s], acc);
@@ -119,7 +130,7 @@ template <int NS> __device__ __forceinline__ double conv_sum_fp(const double (&y
         low = s == 0 ? l : low + l;
         acc = next;
     }
-    const double h = acc - CONV_BIAS;
+    const double h = acc - BIAS;
     const double quo = __builtin_rint(__builtin_fma(low, qinv, h * qinv));
     return __builtin_fma(-quo, q, h) + low;
 }
@@ -241,5 +252,128 @@ __global__ __launch_bounds__(64 * ConvGeom<LOGN>::WAVES, ConvGeom<LOGN>::BOUND) 
                 }
             conv_forward<LOGN>(v, limb, col, ar, ex);
         }
+    }
+}
+
+// ModDown's corrections r of both components: operation o's special limbs come from u + o * stride limbs, component c's limb k at
+// c * (level + K) + level + k, and the corrections go to r + o * stride limbs, component c's limb i at c * level + i.  For ciphertext limbs on
+// the floating-point path and special primes below 2^50, or above with 2^50 mod q_i small for every i (DevTables.dn_fold).
+struct ModDownArgs {
+    u64 *u, *r;
+    int level, L, K, chunks, stride;
+    int first, limbs; // ciphertext limbs first .. first + limbs - 1 are made (of an operation at a lower level those that it has)
+    int keep;         // the centred digits replace the special limbs in u, for a second launch that takes them from there
+    uint8_t op_level[HE_OPS_MAX];
+};
+// A centred digit y, |y| < 2^59, in LDS: y + 2^49.  Its low 50 bits are yl + 2^49 with |yl| <= 2^49, what is above them is yh = (y - yl) / 2^50, and
+// y = yh (2^50 mod q) + yl modulo q, within 2^50 of zero.
+#define CONV_HALF (1ull << 49)
+__device__ __forceinline__ double conv_digit(u64 z, double r50)
+{
+    const double yl = __longlong_as_double((long long)((z & 0x3FFFFFFFFFFFFull) | 0x4330000000000000ull)) - (4503599627370496.0 + 562949953421312.0);
+    return __builtin_fma((double)((int)(z >> 32) >> 18), r50, yl);
+}
+
+// grid: CONV_GROUPS * operations * 2 * chunks, work-groups and waves as in k_ntt_fwd_cols_modup; the digits come from the inverse column
+// pass of the special limbs.  RS: with a rescale, after a launch for the dropped limb, level - 1, with `keep`: the
+// digits are in u, and the dropped limb, as the inverse block pass left it in r, is one more source with P for its constant.
+template <int LOGN, bool RS>
+__global__ __launch_bounds__(64 * ConvGeom<LOGN>::DOWN_WAVES, ConvGeom<LOGN>::DOWN_BOUND) void k_ntt_fwd_cols_moddown(ModDownArgs da, DevTables T)
+{
+    typedef ConvGeom<LOGN> G;
+    constexpr int KMAX = 4, NS = KMAX + (RS ? 1 : 0), W = G::DOWN_WAVES, H = G::HALVES;
+    __shared__ u64 src[NS * G::TILE];
+    __shared__ unsigned exch[W][CONV_EXCH];
+    __shared__ int next;
+    const unsigned s8 = blockIdx.x / XCDS, cg = blockIdx.x % XCDS * (CONV_GROUPS / XCDS) + s8 % (CONV_GROUPS / XCDS);
+    unsigned unit = s8 / (CONV_GROUPS / XCDS);
+    const int chunk = unit % (unsigned)da.chunks;
+    unit /= (unsigned)da.chunks;
+    const int comp = unit & 1u;
+    const unsigned op = unit >> 1;
+    const int ol = op < HE_OPS_MAX ? da.op_level[op] : 0, level = ol ? ol : da.level;
+    const unsigned lane = threadIdx.x & 63u, col = CONV_COLS * cg + (lane & 3u);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    unsigned *ex = exch[wave];
+    u64 *special = da.u + (((size_t)op * da.stride + (size_t)comp * (da.level + da.K) + da.level) << LOGN);
+    u64 *corr = da.r + (((size_t)op * da.stride + (size_t)comp * da.level) << LOGN);
+    if (threadIdx.x == 0) next = 0;
+    // row (lane >> 2) + 16 k + 256 h of this lane's column, in the limb; in LDS it sits at 1024 h + 64 k + lane
+    const auto place = [&](int h, int k) { return ((lane >> 2) + 16 * k + 256 * h) * 256 + col; };
+    u64 *mine = src + wave * G::TILE + lane;
+    if (wave < da.K) {
+        u64 *limb = special + ((size_t)wave << LOGN);
+        const ModConst m = T.mod[da.L + wave];
+        if (RS) {
+#pragma unroll
+            for (int h = 0; h < H; h++)
+#pragma unroll
+                for (int k = 0; k < 16; k++) mine[1024 * h + 64 * k] = limb[place(h, k)];
+        } else {
+            const u64 half = (m.q - 1) / 2;
+            const auto put = [&](int h, int k, u64 y) {
+                const u64 z = (y > half ? y - m.q : y) + CONV_HALF;
+                mine[1024 * h + 64 * k] = z;
+                if (da.keep) limb[place(h, k)] = z;
+            };
+            if (m.qd != 0.0) {
+                const ArithFp ar = make_fp(T, da.L + wave, LOGN, T.dn_inv_d[wave]);
+                double v[H][16];
+                conv_inverse<LOGN>(v, limb + col, ar, ex);
+#pragma unroll
+                for (int h = 0; h < H; h++)
+#pragma unroll
+                    for (int k = 0; k < 16; k++) put(h, k, ar.store_final(v[h][k]));
+            } else {
+                const ArithInt ar = conv_int<LOGN>(T, da.L + wave, T.dn_inv[wave]);
+                u64 v[H][16];
+                conv_inverse<LOGN>(v, limb + col, ar, ex);
+#pragma unroll
+                for (int h = 0; h < H; h++)
+#pragma unroll
+                    for (int k = 0; k < 16; k++) put(h, k, ar.store_final(v[h][k]));
+            }
+        }
+    } else if (wave < KMAX) { // fewer special primes: digits of zero
+#pragma unroll
+        for (int k = 0; k < 16 * H; k++) mine[64 * k] = CONV_HALF;
+    } else if (RS && wave == KMAX) {
+        const ArithFp ar = make_fp(T, da.level - 1, LOGN);
+        double v[H][16];
+        conv_inverse<LOGN>(v, corr + ((size_t)(da.level - 1) << LOGN) + col, ar, ex);
+        const double half = (ar.q - 1.0) * 0.5;
+#pragma unroll
+        for (int h = 0; h < H; h++)
+#pragma unroll
+            for (int k = 0; k < 16; k++) { // centred; the reduction may end on the wrong side of half by one
+                const double r = ar.reduce(v[h][k]);
+                mine[1024 * h + 64 * k] = ar.store_mid(r > half ? r - ar.q : r < -half ? r + ar.q : r);
+            }
+    }
+    __syncthreads();
+    const int end = min(da.first + da.limbs, level);
+    const u64 *sp = src + lane;
+    for (;;) {
+        int t = 0;
+        if (lane == 0) t = atomicAdd(&next, 1);
+        const int i = da.first + chunk + da.chunks * __builtin_amdgcn_readfirstlane(t);
+        if (i >= end) break;
+        const ArithFp ar = make_fp(T, i, LOGN);
+        const double r50 = T.dn_r50_d[i];
+        double c[NS], v[H][16];
+#pragma unroll
+        for (int s = 0; s < KMAX; s++) c[s] = s < da.K ? T.dn_hat_d[s * da.L + i] : 0.0;
+        if (RS) c[NS - 1] = T.dn_pmod_d[i];
+#pragma unroll
+        for (int h = 0; h < H; h++)
+#pragma unroll
+            for (int k = 0; k < 16; k++) {
+                double y[NS];
+#pragma unroll
+                for (int s = 0; s < KMAX; s++) y[s] = conv_digit(sp[s * G::TILE + 1024 * h + 64 * k], r50);
+                if (RS) y[NS - 1] = ar.load_mid(sp[(NS - 1) * G::TILE + 1024 * h + 64 * k]);
+                v[h][k] = conv_sum_fp(y, c, ar.q, ar.qinv);
+            }
+        conv_forward<LOGN>(v, corr + ((size_t)i << LOGN), col, ar, ex);
     }
 }

@@ -64,6 +64,8 @@ struct DevLaunch {
                      const ConvArgs &cv);
     // ModUp of `count` operations with the inverse column pass ahead of it: digits of up to four limbs on the floating-point path
     void (*modup)(he_ctx *c, hipStream_t st, double bytes, int count, const ModUpArgs &ua);
+    // ModDown's corrections of `count` operations with the inverse column pass ahead of it; rs: with a rescale
+    void (*moddown)(he_ctx *c, hipStream_t st, double bytes, bool rs, int count, const ModDownArgs &da);
     // inner product on the limbs ia.first .. level + K - 1, and the finishing one on the first fa.nl limbs (path: FIN_FP, ..)
     void (*inner)(he_ctx *c, hipStream_t st, double bytes, unsigned grid, const InnerArgs &ia, const OpArgs &oa);
     void (*inner_fin)(he_ctx *c, hipStream_t st, double bytes, unsigned grid, int mode, int path, const InnerArgs &ia, const FinishArgs &fa,
