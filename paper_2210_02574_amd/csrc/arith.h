@@ -270,6 +270,29 @@ struct ArithFp {
             }
         }
     }
+    // Two inverse stages on each of the two groups a[0..3], a[4..7] (pairs 1, 2 apart), tw as for fwd4x2_with.  From canonical
+    // residues it stays below 4q and ends below 1.3q.
+    template <class F> __device__ __forceinline__ void inv4x2_with(V (&a)[8], F tw) const
+    {
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+#pragma unroll
+            for (int sp = 1; sp >= 0; sp--) {
+                const int dist = 2 >> sp;
+#pragma unroll
+                for (int g = 0; g < (1 << sp); g++) {
+                    const double w = tw(h, sp, g);
+#pragma unroll
+                    for (int e = 0; e < dist; e++) {
+                        const int k0 = 4 * h + g * 2 * dist + e, k1 = k0 + dist;
+                        const double u = a[k0], v = a[k1], t = u + v;
+                        a[k0] = sp == 0 ? reduce(t) : t;
+                        a[k1] = mulmod(u - v, w);
+                    }
+                }
+            }
+        }
+    }
     // Stage 0 of a 32-element column step (N = 2^17): pairs (lo[k], hi[k]) are N/2 apart, twiddle index 1.
     // Forward: inputs within 1q of zero (reduced or canonical).  Inverse: last stage, with the 1/N factors.
     __device__ __forceinline__ void fwd_stage0(V (&lo)[16], V (&hi)[16], bool reduce_first) const
@@ -367,6 +390,27 @@ struct ArithInt {
                     const u64 u = a[k0], v = a[k1];
                     a[k0] = fin ? mul_shoup_sloppy(u + v, n0, nq) : csub_neg(u + v, nq4);
                     a[k1] = mul_shoup_sloppy(u - v + q4, w, nq);
+                }
+            }
+        }
+    }
+    template <class F> __device__ __forceinline__ void inv4x2_with(V (&a)[8], F tw) const
+    {
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+#pragma unroll
+            for (int sp = 1; sp >= 0; sp--) {
+                const int dist = 2 >> sp;
+#pragma unroll
+                for (int g = 0; g < (1 << sp); g++) {
+                    const ShoupConst w = tw(h, sp, g);
+#pragma unroll
+                    for (int e = 0; e < dist; e++) {
+                        const int k0 = 4 * h + g * 2 * dist + e, k1 = k0 + dist;
+                        const u64 u = a[k0], v = a[k1];
+                        a[k0] = csub_neg(u + v, nq4);
+                        a[k1] = mul_shoup_sloppy(u - v + q4, w, nq);
+                    }
                 }
             }
         }

@@ -617,11 +617,11 @@ static bool batch_fits(const WsLayout &w, int count) { return count >= 1 && w.to
 
 // Whether the block pass of the raised limbs from active limb `first` on runs ahead of the first inner-product launch
 // (k_inner_finished), rather than inside it (k_inner_special).  Digits that three or more rotations share: yes (N = 2^16, 15 rotations at
-// level 24 1106 -> 1029 us, 4 at level 6 129 -> 126, 2 99 -> 102).  Otherwise k_inner_special is the faster one as long as its launch leaves
-// the chip part empty or its four waves have a digit each in every round: at level 13 (four digits) 8 rotations take 445 us, not
-// 460, at level 24 (six) 852, not 859.  It loses in launches of four and more work-groups per compute unit where half of the waves
-// have none (one or two digits: 8 rotations at level 4 170 -> 162 us, at level 8 259 -> 255, 4 at level 4 of N = 2^17 172 -> 165), and in a Mult
-// with rescale, whose dropped limb takes its registers for the tensor product, where a quarter has none (16 at level 24 1861 -> 1840).
+// level 24 983 us, not 1048, 4 at level 12 155, not 158).  Otherwise k_inner_special is the faster one as long as its launch leaves
+// the chip part empty or more than half of its four waves have a digit in every round: 16 products with rescale at level 24 (six digits) take
+// 1676 us, not 1693, 4 take 460, not 467.  It loses in launches of four and more work-groups per compute unit where half of the waves
+// have none (one or two digits: 8 rotations at level 4 144 us, not 151, 8 products with rescale at level 6 253, not 260, 4 rotations at
+// level 4 of N = 2^17 175, not 182).
 // Special limbs on the floating-point path (none of 2^50 or above) are cheap to finish: k_inner_special (8 rotations 267 us, not 282).
 static bool special_finished(const he_ctx *c, int level, int first, int count, bool shared)
 {
@@ -629,9 +629,9 @@ static bool special_finished(const he_ctx *c, int level, int first, int count, b
     if (shared) return count > 2;
     bool ints = false;
     for (int k = 0; k < c->K; k++) ints |= c->modc[c->L + k].qd == 0.0;
-    const size_t groups = (size_t)(level + c->K - first) * count * (c->N / SPECIAL_TILE);
+    const size_t groups = (size_t)(level + c->K - first) * count * (c->N >> FINISHED_TLOG);
     const int beta = (level + c->alpha - 1) / c->alpha, rounds = (beta + SPECIAL_WAVES - 1) / SPECIAL_WAVES, idle = rounds * SPECIAL_WAVES - beta;
-    return ints && groups >= 1024 && idle * (first < level ? 4 : 2) >= rounds * SPECIAL_WAVES;
+    return ints && groups >= 1024 && idle * 2 >= rounds * SPECIAL_WAVES;
 }
 // the modulus index from which on ks_raise finishes raised limbs
 static int finish_from(const he_ctx *c, int level, int first, bool finished) { return !finished ? c->M : first < level ? first : c->L; }
@@ -756,7 +756,8 @@ static int32_t ks_special(he_ctx *c, const InnerArgs &ia, const OpArgs *oa, cons
         return launch_ok(c);
     }
     const double bytes = (inner_words(c, ia, oa, ia.first, Ma) + 2.0 * ia.count * (Ma - ia.first)) * N * 8.0;
-    dev_launch(c).inner(c, st, bytes, inner_grid((unsigned)(N / INNER_TILE), (unsigned)(Ma - ia.first), (unsigned)ia.count), ia,
+    const unsigned tile = ia.finished ? 1u << FINISHED_TLOG : SPECIAL_TILE;
+    dev_launch(c).inner(c, st, bytes, inner_grid((unsigned)N / tile, (unsigned)(Ma - ia.first), (unsigned)ia.count), ia,
                         oa ? *oa : kNoOps);
     int32_t rc = launch_ok(c);
     if (rc != HE_OK || moddown_fused(c)) return rc;

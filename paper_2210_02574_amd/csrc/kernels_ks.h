@@ -137,17 +137,19 @@ __device__ __forceinline__ BlockLane block_lane(u64 *lds, const double *tws)
     b.tw = tws + b.blk * 256;
     return b;
 }
-// This thread's eight values, t + 32 k of its block, from the two blocks in LDS as the column pass left them, rows interleaved.  A lane reads
-// four elements of both rows, 16 bytes at a time, the lower half of the wave k < 4 and the upper one k >= 4, and the halves swap what belongs to
-// the other's row: read one row at a time, every access would hit half of the banks only.
-__device__ __forceinline__ void mid_pairs8(const ArithFp &ar, double (&dv)[8], const u64 *pre, const BlockLane &b)
+// This thread's eight values, t + 32 k of its block, from the two blocks at `pair` (in LDS or in memory) as the column pass left them, rows
+// interleaved.  A lane reads four elements of both rows, 16 bytes at a time, the lower half of the wave k < 4 and the upper one k >= 4, and
+// the halves swap what belongs to the other's row: read one row at a time, every access would hit half of the banks only.
+template <class A> __device__ __forceinline__ void mid_pairs8(const A &ar, typename A::V (&dv)[8], const u64 *pair, const BlockLane &b)
 {
-    const u64x2 *p = (const u64x2 *)pre + b.t + 128 * b.blk;
+    const u64x2 *p = (const u64x2 *)pair + b.t + 128 * b.blk;
+    u64x2 v[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) v[k] = p[32 * k];
 #pragma unroll
     for (int k = 0; k < 4; k++) {
-        const u64x2 v = p[32 * k];
-        const auto l = __builtin_amdgcn_permlane32_swap((unsigned)v.x, (unsigned)v.y, false, false);
-        const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(v.x >> 32), (unsigned)(v.y >> 32), false, false);
+        const auto l = __builtin_amdgcn_permlane32_swap((unsigned)v[k].x, (unsigned)v[k].y, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(v[k].x >> 32), (unsigned)(v[k].y >> 32), false, false);
         dv[k] = ar.load_mid((u64)h[0] << 32 | l[0]);
         dv[k + 4] = ar.load_mid((u64)h[1] << 32 | l[1]);
     }
@@ -174,7 +176,29 @@ template <class A, class F> __device__ __forceinline__ void block_pass8(const A 
 #pragma unroll
     for (int k = 0; k < 8; k++) b.l3[136 * (k >> 2) + (k & 3)] = ar.store_mid(dv[k]);
 }
-// the same with the twiddles in LDS
+// The inverse block pass of canonical residues in the wave's LDS (element e of block b at tile_at(b, e)), which it leaves as the inverse column pass
+// takes them; dv: elements t + 32 k.
+template <class A, class F> __device__ __forceinline__ void inv_block_pass8(const A &ar, typename A::V (&dv)[8], const BlockLane &b, F tw)
+{
+#pragma unroll
+    for (int k = 0; k < 8; k++) dv[k] = ar.load(b.l3[136 * (k >> 2) + (k & 3)]);
+    ar.inv4x2_with(dv, [&](int h, int sp, int gg) { return tw(6 + sp, ((b.t + 32 * h) << sp) + gg); });
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 8; k++) b.l3[136 * (k >> 2) + (k & 3)] = ar.store_mid(dv[k]);
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(b.l2[4 * k + (k >> 2)]);
+    ar.template inv8_with<false>(dv, [&](int sp, int gg) { return tw(3 + sp, (b.g2 << sp) + gg); });
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 8; k++) b.l2[4 * k + (k >> 2)] = ar.store_mid(dv[k]);
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(b.l1[34 * k]);
+    ar.template inv8_with<false>(dv, [&](int sp, int gg) { return tw(sp, (unsigned)gg); });
+}
+// the same as block_pass8 with the twiddles in LDS
 __device__ __forceinline__ void block_pass8(const ArithFp &ar, double (&dv)[8], const BlockLane &b)
 {
     block_pass8(ar, dv, b, [&](int m, unsigned i) { return b.tw[(1u << m) - 1 + i]; });
@@ -188,11 +212,11 @@ struct InnerTile {
     int level, beta; // of the operation
     bool none;
 };
-template <int LOGN>
+template <int LOGN, int TLOG>
 __device__ __forceinline__ InnerTile inner_tile(const InnerArgs &ia, const OpArgs &oa, int limbs, int first)
 {
     InnerTile w;
-    const unsigned ntile = 1u << (LOGN - INNER_TLOG);
+    const unsigned ntile = 1u << (LOGN - TLOG);
     const unsigned slot = blockIdx.x / XCDS;
     w.op = slot % (unsigned)ia.count;
     const unsigned tl = slot / (unsigned)ia.count * XCDS + blockIdx.x % XCDS;
@@ -404,284 +428,235 @@ __device__ __forceinline__ void inner_products_int(const InnerArgs &ia, const Op
 //
 // k_inner_special, for launches that leave the chip part empty: what a wave of k_inner_fin does alone is shared
 // out: a work-group of four waves makes SPECIAL_TILE outputs of both components, and in each round every wave finishes
-// the transform of another digit (16 lanes a block of 256, 16 elements per lane, the steps of k_ntt_fwd_blocks) into LDS;
+// the transform of another digit (the steps of k_inner_fin's block pass) into LDS;
 // then all threads multiply the digits of the round, read through the index map, with the key.  One operation
 // alone then has four digits in work at a time, and the finished digits never travel to memory.
-// Bound by the chain of a round (load, two steps with their twiddles, exchange, products): at N = 2^16 it
-// takes 19 us for one operation, where the block pass as a launch of its own and the products after it took 10 + 17.
+// Bound by the chain of a round (load, three steps with their twiddles, exchanges, products): one rotation at N = 2^16, level 13, takes
+// 15.3 us, with tiles of 1024 outputs and 16 elements per lane 18.3; eight at level 24 128 us, 137 (105 registers instead of 148, four waves per
+// SIMD instead of three).
 //
 // k_inner_finished, for launches that fill it and for digits that several operations share: k_ntt_fwd_blocks finishes the
 // digits, each thread reads them through the index map straight into its sums, without LDS and without a barrier.
-// Of 16 products at level 24 (the dropped limb among them) the two launches take 143 + 142 us; with k_inner_special 293.  32 rotations of mixed
-// levels take 359 us in k_inner_special, as much as in two launches of this form (170 + 183); with 168 registers and some of them in
-// scratch memory it was 407.
 //
 // The result leaves either with the block pass of its inverse transform applied.
 #define SPECIAL_THREADS 256
 #define SPECIAL_WAVES (SPECIAL_THREADS / 64)
-#define SPECIAL_TLOG 10
-#define SPECIAL_TILE (1 << SPECIAL_TLOG)                    // outputs per work-group: four blocks, 16 elements per lane of a wave
-#define SPECIAL_DIGIT (SPECIAL_TILE / 256 * TILE_GROUP)     // LDS words of one digit
+#define SPECIAL_TLOG 9
+#define SPECIAL_TILE (1 << SPECIAL_TLOG)           // outputs per work-group: two blocks, 8 elements per lane of a wave
+#define SPECIAL_DIGIT (WAVE_BLOCKS * TILE_GROUP)   // LDS words of 512 elements
+#define FINISHED_TLOG 10
 
-// Element p of the tile in LDS.
-__device__ __forceinline__ unsigned special_at(unsigned p) { return tile_at(p >> 8, p & 255u); }
-
-// limb a of one operation; the results of the thread's pairs (512 i + 2 thread, + 1), i < 2, of both components
-template <int LOGN, bool MULT, class A>
-__device__ __forceinline__ void special_products(const InnerArgs &ia, const OpArgs &oa, const DevTables &T, unsigned op, unsigned tile,
-                                                 int a, unsigned g, int beta, unsigned mi, const ModConst &m, const A &ar, u64 *lds,
-                                                 u64 (&r0)[4], u64 (&r1)[4])
+// Twiddles of local stage m, group i of block G, forward or inverse.
+template <int LOGN, class Tv> __device__ __forceinline__ Tv block_twiddle(const Tv *tw, unsigned G, int m, unsigned i)
 {
-    const int own = MULT && a < ia.level ? a / ia.alpha : -1, M = ia.L + ia.K, Ma = ia.level + ia.K; // the dropped limb of a Mult
-    const unsigned tile_in = g == 1 ? tile : galois_index(tile << SPECIAL_TLOG, g, LOGN) >> SPECIAL_TLOG;
-    const char *key0 = (const char *)((ia.per_op ? oa.evk[op] : ia.evk) + (((size_t)mi << LOGN) + ((size_t)tile << SPECIAL_TLOG)));
-    const u64 *raised0 = ia.raised + ((((size_t)op * ia.raised_stride + a) << LOGN) + ((size_t)tile_in << SPECIAL_TLOG));
+    return tw[(1u << (LOGN - 8 + m)) + (G << m) + i];
+}
+
+// The pair of digit values at `key`-order position: floating point, within 1.9 q of zero; integer, below 8q.
+__device__ __forceinline__ void special_mac(const ArithFp &ar, double x, u64 k0, u64 k1, double &s0, double &s1)
+{
+    s0 += ar.mulmod(x, ar.load_mid(k0)), s1 += ar.mulmod(x, ar.load_mid(k1)); // key words are balanced doubles
+}
+__device__ __forceinline__ void special_mac(const ArithInt &, u64 x, u64 k0, u64 k1, U128 &s0, U128 &s1) { mac128(s0, x, k0), mac128(s1, x, k1); }
+template <class A> struct SpecialSum;
+template <> struct SpecialSum<ArithFp> {
+    typedef double S;
+    static __device__ __forceinline__ double zero() { return 0.0; }
+    static __device__ __forceinline__ double fold(const ModConst &m, double s) { return fp_reduce(s, m.qd, m.qinvd); }
+    static __device__ __forceinline__ u64 result(const ArithFp &ar, const ModConst &, double s) { return ar.store_final(s); }
+    static __device__ __forceinline__ double product(const DevTables &T, const ModConst &, const ArithFp &ar, int a, u64 a0, u64 a1, u64 b0, u64 b1, double &s0, double &s1)
+    {
+        return tensor_mac(ar, a0, a1, b0, b1, T.dn_pmod_d[a], s0, s1);
+    }
+};
+template <> struct SpecialSum<ArithInt> {
+    typedef U128 S;
+    static __device__ __forceinline__ U128 zero() { return U128{0, 0}; }
+    static __device__ __forceinline__ U128 fold(const ModConst &m, U128 s) { return U128{reduce128(s, m), 0}; }
+    static __device__ __forceinline__ u64 result(const ArithInt &, const ModConst &m, U128 s) { return reduce128(s, m); }
+    static __device__ __forceinline__ u64 product(const DevTables &T, const ModConst &m, const ArithInt &, int a, u64 a0, u64 a1, u64 b0, u64 b1, U128 &s0, U128 &s1)
+    {
+        return tensor_mac(m, a0, a1, b0, b1, T.dn_pmod[a], s0, s1);
+    }
+};
+
+// limb w.a of one operation; the results of the thread's pair (2 thread, + 1) of both components
+template <int LOGN, bool MULT, class A>
+__device__ __forceinline__ void special_products(const InnerArgs &ia, const OpArgs &oa, const DevTables &T, const InnerTile &w, unsigned mi,
+                                                 const ModConst &m, const A &ar, u64 *lds, u64 (&r0)[2], u64 (&r1)[2])
+{
+    typedef SpecialSum<A> Sum;
+    const int a = w.a, own = MULT && a < ia.level ? a / ia.alpha : -1, M = ia.L + ia.K, Ma = ia.level + ia.K; // own: the dropped limb of a Mult
+    const unsigned tile_in = w.g == 1 ? w.tile : galois_index(w.tile << SPECIAL_TLOG, w.g, LOGN) >> SPECIAL_TLOG;
+    const char *key0 = (const char *)((ia.per_op ? oa.evk[w.op] : ia.evk) + (((size_t)mi << LOGN) + ((size_t)w.tile << SPECIAL_TLOG)));
+    const u64 *raised0 = ia.raised + ((((size_t)w.op * ia.raised_stride + a) << LOGN) + ((size_t)tile_in << SPECIAL_TLOG));
     const size_t raised_step = (size_t)Ma << LOGN, comp_step = ((size_t)M << LOGN) * 8, key_step = 2 * comp_step;
-    const unsigned wave = wave_id(), lane = threadIdx.x & 63u, blk = lane >> 4, il = lane & 15u, bg = tile_in * 4 + blk;
+    const int wave = wave_id();
     // an integer-path ciphertext limb (the one a rescale drops) has been finished with the other ciphertext limbs
     const bool finished = MULT && !A::IS_FP && a < ia.level;
-    unsigned sr[2], lx[2], ly[2]; // sources of the pairs: index in the limb, LDS words of the even and the odd element
+    // source of the pair: index in the limb, LDS words of the even and the odd element
+    const unsigned pos = (w.tile << SPECIAL_TLOG) + 2u * threadIdx.x, sr = w.g == 1 ? pos : galois_index(pos, w.g, LOGN);
+    const unsigned sl = sr & (SPECIAL_TILE - 2u), sw = sr & 1u, wd = tile_at(sl >> 8, sl & 255u);
+    typename Sum::S s0[2], s1[2];
 #pragma unroll
-    for (int i = 0; i < 2; i++) {
-        const unsigned pos = (tile << SPECIAL_TLOG) + 512u * i + 2u * threadIdx.x;
-        sr[i] = g == 1 ? pos : galois_index(pos, g, LOGN);
-        const unsigned sl = sr[i] & (SPECIAL_TILE - 2u), sw = sr[i] & 1u;
-        lx[i] = special_at(sl) + sw, ly[i] = special_at(sl) + 1 - sw;
-    }
-    double f0[4], f1[4];
-    U128 s0[4], s1[4];
-#pragma unroll
-    for (int k = 0; k < 4; k++) f0[k] = f1[k] = 0.0, s0[k] = s1[k] = U128{0, 0};
+    for (int e = 0; e < 2; e++) s0[e] = s1[e] = Sum::zero();
     // the key words of the digit after the one at hand are on their way, those of a round's first through the transforms
-    u64x2 ka[2], kb[2];
+    u64x2 ka, kb;
     const auto load_key = [&](int j) {
         const char *kj = key0 + (size_t)j * key_step;
-#pragma unroll
-        for (int i = 0; i < 2; i++)
-            ka[i] = ld_at<u64x2>(kj + 4096 * i, threadIdx.x * 16u), kb[i] = ld_at<u64x2>(kj + comp_step + 4096 * i, threadIdx.x * 16u);
+        ka = ld_at<u64x2>(kj, threadIdx.x * 16u), kb = ld_at<u64x2>(kj + comp_step, threadIdx.x * 16u);
     };
     load_key(0);
-    for (int j0 = 0; j0 < beta; j0 += SPECIAL_WAVES) {
-        const int jw = j0 + (int)wave;
-        if (jw < beta && jw != own) {
-            const u64 *in = raised0 + (size_t)jw * raised_step + (finished ? mid_at<false>(blk, il) : mid_at<true>(blk, il));
-            const unsigned step = finished ? 16 : 32;
+    for (int j0 = 0; j0 < w.beta; j0 += SPECIAL_WAVES) {
+        const int jw = j0 + wave;
+        if (jw < w.beta && jw != own) {
+            const u64 *in = raised0 + (size_t)jw * raised_step;
             u64 *dig = lds + wave * SPECIAL_DIGIT;
-            u64 x[16];
-#pragma unroll
-            for (int k = 0; k < 16; k++) x[k] = __builtin_nontemporal_load(in + step * k);
+            const BlockLane b = block_lane(dig, nullptr);
             if (finished) {
 #pragma unroll
-                for (int k = 0; k < 16; k++) dig[tile_at(blk, il + 16 * k)] = x[k];
+                for (int k = 0; k < 8; k++) b.l1[34 * k] = in[b.blk * 256 + b.t + 32 * k];
             } else {
-                typename A::V v[16];
-#pragma unroll
-                for (int k = 0; k < 16; k++) v[k] = ar.load_mid(x[k]);
-                ar.fwd16(v, LOGN - 8, bg, true);
-#pragma unroll
-                for (int k = 0; k < 16; k++) dig[tile_at(blk, il + 16 * k)] = ar.store_mid(v[k]);
-                block_sync();
-#pragma unroll
-                for (int k = 0; k < 16; k++) v[k] = ar.load_mid(dig[tile_at(blk, 16 * il + k)]);
-                ar.fwd16(v, LOGN - 4, bg * 16 + il, true);
-                block_sync();
-#pragma unroll
-                for (int k = 0; k < 16; k++) dig[tile_at(blk, 16 * il + k)] = ar.store_final(v[k]);
+                typename A::V v[8];
+                mid_pairs8(ar, v, in, b);
+                const unsigned G = tile_in * WAVE_BLOCKS + b.blk;
+                block_pass8(ar, v, b, [&](int st, unsigned i) { return block_twiddle<LOGN>(ar.twf, G, st, i); });
             }
         }
         __syncthreads();
 #pragma unroll 1
-        for (int jj = 0; jj < SPECIAL_WAVES && j0 + jj < beta; jj++) {
+        for (int jj = 0; jj < SPECIAL_WAVES && j0 + jj < w.beta; jj++) {
             const int j = j0 + jj;
             const u64 *dig = lds + jj * SPECIAL_DIGIT;
-            const u64x2 ca[2] = {ka[0], ka[1]}, cb[2] = {kb[0], kb[1]};
-            if (j + 1 < beta) load_key(j + 1);
-#pragma unroll
-            for (int i = 0; i < 2; i++) {
-                u64 x, y;
-                if (MULT && j == own) { // g = 1: the pair itself
-                    const TensorPair p = tensor_pair<LOGN>(ia, op, a, sr[i]);
-                    if constexpr (A::IS_FP) {
-                        const double P = T.dn_pmod_d[a];
-                        x = ar.store_final(tensor_mac(ar, p.a0.x, p.a1.x, p.b0.x, p.b1.x, P, f0[2 * i], f1[2 * i]));
-                        y = ar.store_final(tensor_mac(ar, p.a0.y, p.a1.y, p.b0.y, p.b1.y, P, f0[2 * i + 1], f1[2 * i + 1]));
-                    } else {
-                        const u64 P = T.dn_pmod[a];
-                        x = tensor_mac(m, p.a0.x, p.a1.x, p.b0.x, p.b1.x, P, s0[2 * i], s1[2 * i]);
-                        y = tensor_mac(m, p.a0.y, p.a1.y, p.b0.y, p.b1.y, P, s0[2 * i + 1], s1[2 * i + 1]);
-                    }
-                } else
-                    x = dig[lx[i]], y = dig[ly[i]];
-                if constexpr (A::IS_FP) { // key words are balanced doubles
-                    const double xd = u2d(x), yd = u2d(y);
-                    f0[2 * i] += ar.mulmod(xd, ar.load_mid(ca[i].x)), f0[2 * i + 1] += ar.mulmod(yd, ar.load_mid(ca[i].y));
-                    f1[2 * i] += ar.mulmod(xd, ar.load_mid(cb[i].x)), f1[2 * i + 1] += ar.mulmod(yd, ar.load_mid(cb[i].y));
-                } else {
-                    mac128(s0[2 * i], x, ca[i].x);
-                    mac128(s0[2 * i + 1], y, ca[i].y);
-                    mac128(s1[2 * i], x, cb[i].x);
-                    mac128(s1[2 * i + 1], y, cb[i].y);
-                }
-            }
+            const u64x2 ca = ka, cb = kb;
+            if (j + 1 < w.beta) load_key(j + 1);
+            typename A::V x, y;
+            if (MULT && j == own) { // g = 1: the pair itself
+                const TensorPair p = tensor_pair<LOGN>(ia, w.op, a, sr);
+                x = Sum::product(T, m, ar, a, p.a0.x, p.a1.x, p.b0.x, p.b1.x, s0[0], s1[0]);
+                y = Sum::product(T, m, ar, a, p.a0.y, p.a1.y, p.b0.y, p.b1.y, s0[1], s1[1]);
+            } else
+                x = ar.load_mid(dig[wd + sw]), y = ar.load_mid(dig[wd + 1 - sw]);
+            special_mac(ar, x, ca.x, cb.x, s0[0], s1[0]);
+            special_mac(ar, y, ca.y, cb.y, s0[1], s1[1]);
         }
-        if constexpr (A::IS_FP) { // after at most four products
+        if (A::IS_FP || w.beta > 28) { // floating point: after at most four products; integer: 28 below 2^123 fit, with the two of d0 and d1
 #pragma unroll
-            for (int k = 0; k < 4; k++) f0[k] = ar.reduce(f0[k]), f1[k] = ar.reduce(f1[k]);
+            for (int e = 0; e < 2; e++) s0[e] = Sum::fold(m, s0[e]), s1[e] = Sum::fold(m, s1[e]);
         }
         __syncthreads(); // the digits have been read
     }
 #pragma unroll
-    for (int k = 0; k < 4; k++) {
-        if constexpr (A::IS_FP)
-            r0[k] = ar.store_final(f0[k]), r1[k] = ar.store_final(f1[k]);
-        else
-            r0[k] = reduce128(s0[k], m), r1[k] = reduce128(s1[k], m);
-    }
+    for (int e = 0; e < 2; e++) r0[e] = Sum::result(ar, m, s0[e]), r1[e] = Sum::result(ar, m, s1[e]);
 }
 
-// Inverse block pass of both components from the pairs of special_products, through LDS (which nothing reads any more) to
-// one component per wave; u: component 0, component 1 comp_words further on.
-template <int LOGN, class A>
-__device__ __forceinline__ void special_inverse(const u64 (&r0)[4], const u64 (&r1)[4], u64 *u, size_t comp_words, const A &ar, u64 *lds,
-                                                unsigned tile)
-{
-#pragma unroll
-    for (int i = 0; i < 2; i++) {
-        const unsigned wd = special_at(512u * i + 2u * threadIdx.x);
-        lds[wd] = r0[2 * i], lds[wd + 1] = r0[2 * i + 1];
-        lds[SPECIAL_DIGIT + wd] = r1[2 * i], lds[SPECIAL_DIGIT + wd + 1] = r1[2 * i + 1];
-    }
-    __syncthreads();
-    const unsigned comp = wave_id(), lane = threadIdx.x & 63u, blk = lane >> 4, il = lane & 15u, bg = tile * 4 + blk;
-    if (comp > 1) return;
-    u64 *limb = u + comp * comp_words, *w = lds + comp * SPECIAL_DIGIT;
-    typename A::V v[16];
-#pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = ar.load(w[tile_at(blk, 16 * il + k)]);
-    ar.template inv16<false>(v, LOGN - 4, bg * 16 + il);
-    block_sync();
-#pragma unroll
-    for (int k = 0; k < 16; k++) w[tile_at(blk, 16 * il + k)] = ar.store_mid(v[k]);
-    block_sync();
-#pragma unroll
-    for (int k = 0; k < 16; k++) v[k] = ar.load_mid(w[tile_at(blk, il + 16 * k)]);
-    ar.template inv16<false>(v, LOGN - 8, bg);
-#pragma unroll
-    for (int k = 0; k < 16; k++) limb[bg * 256 + il + 16 * k] = ar.store_mid(v[k]);
-}
-
-// What both forms do with their sums: the inverse block pass on a special limb, u on a ciphertext limb (MULT: the dropped one).
-template <int LOGN, bool MULT, class A>
-__device__ __forceinline__ void special_result(const InnerArgs &ia, const InnerTile &w, const u64 (&r0)[4], const u64 (&r1)[4], const A &ar, u64 *lds)
+// What both forms do with their sums, PAIRS pairs (512 i + 2 thread, + 1) of a thread and component, groups of 512 outputs from `tile` on: the inverse block
+// pass on a special limb, one group of one component per wave, through LDS (which nothing reads any more); u on a ciphertext limb (MULT: the dropped one).
+template <int LOGN, bool MULT, int PAIRS, class A>
+__device__ __forceinline__ void special_result(const InnerArgs &ia, const InnerTile &w, const u64 (&r0)[2 * PAIRS], const u64 (&r1)[2 * PAIRS], const A &ar, u64 *lds)
 {
     u64 *u0 = ia.u + (((size_t)w.op * ia.u_stride + w.a) << LOGN);
     const size_t comp_words = (size_t)(ia.level + ia.K) << LOGN;
-    if (!MULT || w.a >= ia.level) {
-        special_inverse<LOGN>(r0, r1, u0, comp_words, ar, lds, w.tile);
+    const unsigned group0 = w.tile * PAIRS;
+    if (MULT && w.a < ia.level) {
+#pragma unroll
+        for (int i = 0; i < PAIRS; i++) {
+            char *o = (char *)(u0 + ((size_t)(group0 + i) << WAVE_LOG)) + threadIdx.x * 16u;
+            __builtin_nontemporal_store(u64x2{r0[2 * i], r0[2 * i + 1]}, (u64x2 *)o);
+            __builtin_nontemporal_store(u64x2{r1[2 * i], r1[2 * i + 1]}, (u64x2 *)(o + comp_words * 8));
+        }
         return;
     }
 #pragma unroll
-    for (int i = 0; i < 2; i++) {
-        char *o = (char *)(u0 + ((size_t)w.tile << SPECIAL_TLOG)) + 4096 * i + threadIdx.x * 16u;
-        __builtin_nontemporal_store(u64x2{r0[2 * i], r0[2 * i + 1]}, (u64x2 *)o);
-        __builtin_nontemporal_store(u64x2{r1[2 * i], r1[2 * i + 1]}, (u64x2 *)(o + comp_words * 8));
+    for (int i = 0; i < PAIRS; i++) {
+        const unsigned p = 2u * threadIdx.x, wd = tile_at(p >> 8, p & 255u);
+        u64 *d0 = lds + (2 * i) * SPECIAL_DIGIT + wd, *d1 = d0 + SPECIAL_DIGIT;
+        d0[0] = r0[2 * i], d0[1] = r0[2 * i + 1];
+        d1[0] = r1[2 * i], d1[1] = r1[2 * i + 1];
     }
+    __syncthreads();
+    const unsigned wave = wave_id(), comp = wave & 1u, group = group0 + (wave >> 1);
+    if (wave >= 2 * PAIRS) return;
+    const BlockLane b = block_lane(lds + wave * SPECIAL_DIGIT, nullptr);
+    const unsigned G = group * WAVE_BLOCKS + b.blk;
+    typename A::V v[8];
+    inv_block_pass8(ar, v, b, [&](int st, unsigned i) { return block_twiddle<LOGN>(ar.twi, G, st, i); });
+    u64 *o = u0 + comp * comp_words + (size_t)G * 256 + b.t;
+#pragma unroll
+    for (int k = 0; k < 8; k++) o[32 * k] = ar.store_mid(v[k]);
 }
 
 // Active limbs ia.first .. level + K - 1 of every operation.  The same order of work-groups as k_inner_fin.
 // MULT: of a Mult with rescale, whose dropped limb takes d0, d1 and d2 (a kernel of its own: with their code in every launch
 // 32 mixed rotations at N = 2^16 took 2388 us instead of 2342)
-template <int LOGN, bool MULT> __global__ __launch_bounds__(SPECIAL_THREADS, 2) void k_inner_special(InnerArgs ia, DevTables T, OpArgs oa)
+template <int LOGN, bool MULT> __global__ __launch_bounds__(SPECIAL_THREADS, MULT ? 3 : 4) void k_inner_special(InnerArgs ia, DevTables T, OpArgs oa)
 {
-    __shared__ u64 lds[SPECIAL_WAVES * SPECIAL_DIGIT];
-    static_assert(SPECIAL_TILE == INNER_TILE, "inner_grid and inner_tile serve both kernels");
-    const InnerTile w = inner_tile<LOGN>(ia, oa, ia.level + ia.K - ia.first, ia.first);
+    __shared__ __align__(16) u64 lds[SPECIAL_WAVES * SPECIAL_DIGIT];
+    const InnerTile w = inner_tile<LOGN, SPECIAL_TLOG>(ia, oa, ia.level + ia.K - ia.first, ia.first);
     if (w.none) return;
     const int mi = active_mod(w.a, ia.level, ia.L);
     const ModConst m = T.mod[mi];
-    u64 r0[4], r1[4];
+    u64 r0[2], r1[2];
     if (m.qd != 0.0) {
         const ArithFp ar = make_fp(T, mi, LOGN);
-        special_products<LOGN, MULT>(ia, oa, T, w.op, w.tile, w.a, w.g, w.beta, mi, m, ar, lds, r0, r1);
-        special_result<LOGN, MULT>(ia, w, r0, r1, ar, lds);
+        special_products<LOGN, MULT>(ia, oa, T, w, mi, m, ar, lds, r0, r1);
+        special_result<LOGN, MULT, 1>(ia, w, r0, r1, ar, lds);
     } else {
         const ArithInt ar = make_int(T, mi, LOGN);
-        special_products<LOGN, MULT>(ia, oa, T, w.op, w.tile, w.a, w.g, w.beta, mi, m, ar, lds, r0, r1);
-        special_result<LOGN, MULT>(ia, w, r0, r1, ar, lds);
+        special_products<LOGN, MULT>(ia, oa, T, w, mi, m, ar, lds, r0, r1);
+        special_result<LOGN, MULT, 1>(ia, w, r0, r1, ar, lds);
     }
 }
 
-// The sums of a thread's pairs as in special_products, from digits in the NTT domain.
+// The sums of a thread's pairs (512 i + 2 thread, + 1), i < 2, from digits in the NTT domain.
 template <int LOGN, bool MULT, class A>
 __device__ __forceinline__ void finished_products(const InnerArgs &ia, const OpArgs &oa, const DevTables &T, const InnerTile &w, unsigned mi,
                                                   const ModConst &m, const A &ar, u64 (&r0)[4], u64 (&r1)[4])
 {
+    typedef SpecialSum<A> Sum;
     const int own = MULT && w.a < ia.level ? w.a / ia.alpha : -1, M = ia.L + ia.K, Ma = ia.level + ia.K;
-    const char *key0 = (const char *)((ia.per_op ? oa.evk[w.op] : ia.evk) + (((size_t)mi << LOGN) + ((size_t)w.tile << SPECIAL_TLOG)));
+    const char *key0 = (const char *)((ia.per_op ? oa.evk[w.op] : ia.evk) + (((size_t)mi << LOGN) + ((size_t)w.tile << FINISHED_TLOG)));
     const char *dig0 = (const char *)(ia.raised + (((size_t)w.op * ia.raised_stride + w.a) << LOGN));
     const size_t dig_step = ((size_t)Ma << LOGN) * 8, comp_step = ((size_t)M << LOGN) * 8, key_step = 2 * comp_step;
     unsigned sr[2];
 #pragma unroll
     for (int i = 0; i < 2; i++) {
-        const unsigned pos = (w.tile << SPECIAL_TLOG) + 512u * i + 2u * threadIdx.x;
+        const unsigned pos = (w.tile << FINISHED_TLOG) + 512u * i + 2u * threadIdx.x;
         sr[i] = w.g == 1 ? pos : galois_index(pos, w.g, LOGN);
     }
-    double f0[4], f1[4];
-    U128 s0[4], s1[4];
+    typename Sum::S s0[4], s1[4];
 #pragma unroll
-    for (int k = 0; k < 4; k++) f0[k] = f1[k] = 0.0, s0[k] = s1[k] = U128{0, 0};
+    for (int k = 0; k < 4; k++) s0[k] = s1[k] = Sum::zero();
     for (int j = 0; j < w.beta; j++) {
         const char *kj = key0 + (size_t)j * key_step;
 #pragma unroll
         for (int i = 0; i < 2; i++) {
             const u64x2 ka = ld_at<u64x2>(kj + 4096 * i, threadIdx.x * 16u), kb = ld_at<u64x2>(kj + comp_step + 4096 * i, threadIdx.x * 16u);
-            u64 x, y;
+            typename A::V x, y;
             if (MULT && j == own) { // g = 1: the pair itself
                 const TensorPair p = tensor_pair<LOGN>(ia, w.op, w.a, sr[i]);
-                if constexpr (A::IS_FP) {
-                    const double P = T.dn_pmod_d[w.a];
-                    x = ar.store_final(tensor_mac(ar, p.a0.x, p.a1.x, p.b0.x, p.b1.x, P, f0[2 * i], f1[2 * i]));
-                    y = ar.store_final(tensor_mac(ar, p.a0.y, p.a1.y, p.b0.y, p.b1.y, P, f0[2 * i + 1], f1[2 * i + 1]));
-                } else {
-                    const u64 P = T.dn_pmod[w.a];
-                    x = tensor_mac(m, p.a0.x, p.a1.x, p.b0.x, p.b1.x, P, s0[2 * i], s1[2 * i]);
-                    y = tensor_mac(m, p.a0.y, p.a1.y, p.b0.y, p.b1.y, P, s0[2 * i + 1], s1[2 * i + 1]);
-                }
+                x = Sum::product(T, m, ar, w.a, p.a0.x, p.a1.x, p.b0.x, p.b1.x, s0[2 * i], s1[2 * i]);
+                y = Sum::product(T, m, ar, w.a, p.a0.y, p.a1.y, p.b0.y, p.b1.y, s0[2 * i + 1], s1[2 * i + 1]);
             } else {
                 const u64x2 v = ld_at<u64x2>(dig0 + (size_t)j * dig_step, (sr[i] & ~1u) * 8u);
-                x = sr[i] & 1u ? v.y : v.x, y = sr[i] & 1u ? v.x : v.y;
+                x = ar.load(sr[i] & 1u ? v.y : v.x), y = ar.load(sr[i] & 1u ? v.x : v.y);
             }
-            if constexpr (A::IS_FP) { // key words are balanced doubles
-                const double xd = u2d(x), yd = u2d(y);
-                f0[2 * i] += ar.mulmod(xd, ar.load_mid(ka.x)), f0[2 * i + 1] += ar.mulmod(yd, ar.load_mid(ka.y));
-                f1[2 * i] += ar.mulmod(xd, ar.load_mid(kb.x)), f1[2 * i + 1] += ar.mulmod(yd, ar.load_mid(kb.y));
-            } else {
-                mac128(s0[2 * i], x, ka.x);
-                mac128(s0[2 * i + 1], y, ka.y);
-                mac128(s1[2 * i], x, kb.x);
-                mac128(s1[2 * i + 1], y, kb.y);
-            }
+            special_mac(ar, x, ka.x, kb.x, s0[2 * i], s1[2 * i]);
+            special_mac(ar, y, ka.y, kb.y, s0[2 * i + 1], s1[2 * i + 1]);
         }
-        if constexpr (A::IS_FP) {
-            if ((j & 3) == 3) {
+        if (A::IS_FP && (j & 3) == 3) {
 #pragma unroll
-                for (int k = 0; k < 4; k++) f0[k] = ar.reduce(f0[k]), f1[k] = ar.reduce(f1[k]);
-            }
+            for (int k = 0; k < 4; k++) s0[k] = Sum::fold(m, s0[k]), s1[k] = Sum::fold(m, s1[k]);
         }
     }
 #pragma unroll
-    for (int k = 0; k < 4; k++) {
-        if constexpr (A::IS_FP)
-            r0[k] = ar.store_final(f0[k]), r1[k] = ar.store_final(f1[k]);
-        else
-            r0[k] = reduce128(s0[k], m), r1[k] = reduce128(s1[k], m);
-    }
+    for (int k = 0; k < 4; k++) r0[k] = Sum::result(ar, m, s0[k]), r1[k] = Sum::result(ar, m, s1[k]);
 }
 // The limbs of k_inner_special, in the same order.
 template <int LOGN, bool MULT> __global__ __launch_bounds__(SPECIAL_THREADS, 5) void k_inner_finished(InnerArgs ia, DevTables T, OpArgs oa)
 {
-    __shared__ u64 lds[2 * SPECIAL_DIGIT];
-    const InnerTile w = inner_tile<LOGN>(ia, oa, ia.level + ia.K - ia.first, ia.first);
+    __shared__ __align__(16) u64 lds[4 * SPECIAL_DIGIT];
+    const InnerTile w = inner_tile<LOGN, FINISHED_TLOG>(ia, oa, ia.level + ia.K - ia.first, ia.first);
     if (w.none) return;
     const int mi = active_mod(w.a, ia.level, ia.L);
     const ModConst m = T.mod[mi];
@@ -689,11 +664,11 @@ template <int LOGN, bool MULT> __global__ __launch_bounds__(SPECIAL_THREADS, 5) 
     if (m.qd != 0.0) {
         const ArithFp ar = make_fp(T, mi, LOGN);
         finished_products<LOGN, MULT>(ia, oa, T, w, mi, m, ar, r0, r1);
-        special_result<LOGN, MULT>(ia, w, r0, r1, ar, lds);
+        special_result<LOGN, MULT, 2>(ia, w, r0, r1, ar, lds);
     } else {
         const ArithInt ar = make_int(T, mi, LOGN);
         finished_products<LOGN, MULT>(ia, oa, T, w, mi, m, ar, r0, r1);
-        special_result<LOGN, MULT>(ia, w, r0, r1, ar, lds);
+        special_result<LOGN, MULT, 2>(ia, w, r0, r1, ar, lds);
     }
 }
 
@@ -824,7 +799,7 @@ template <int LOGN, int MODE, int PATH>
 __global__ __launch_bounds__(INNER_THREADS, PATH != FIN_INT ? 6 : MODE == FIN_MULT ? 3 : 4) void k_inner_fin(InnerArgs ia, FinishArgs fa, DevTables T, OpArgs oa)
 {
     __shared__ __align__(16) u64 wave_lds[INNER_THREADS / 64][PATH == FIN_INT ? 2 * WAVE_BLOCKS * TILE_GROUP : WAVE_LDS];
-    const InnerTile w = inner_tile<LOGN>(ia, oa, fa.nl, 0);
+    const InnerTile w = inner_tile<LOGN, INNER_TLOG>(ia, oa, fa.nl, 0);
     if (w.none) return;
     const ModConst m = T.mod[w.a];
     const u64 *r_grp = fa.r + (((size_t)w.op * fa.r_stride + w.a) << LOGN) + ((size_t)w.grp << WAVE_LOG);
