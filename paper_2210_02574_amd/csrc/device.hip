@@ -636,13 +636,26 @@ static bool special_finished(const he_ctx *c, int level, int first, int count, b
 // the modulus index from which on ks_raise finishes raised limbs
 static int finish_from(const he_ctx *c, int level, int first, bool finished) { return !finished ? c->M : first < level ? first : c->L; }
 
-// ModUp with the inverse column pass ahead of it in one kernel (k_ntt_fwd_cols_modup): the common case, N = 2^16 and 2^17, digits of up to four
-// limbs, all on the floating-point path, without the correction of the overshoot.
-static bool modup_fused(const he_ctx *c) { return dev_launch(c).modup && c->alpha <= 4 && !c->up_split && !c->exact_conv; }
-// The same for ModDown's corrections (k_ntt_fwd_cols_moddown): up to four special primes, ciphertext limbs on the floating-point path.
-static bool moddown_fused(const he_ctx *c)
+// The conversion kernels with the inverse column pass ahead of them make `targets` limbs per unit (a digit, or a component's special limbs).
+// Each work-group waits for the inverse pass of its sources, half of its waves without work, so it has to have some targets to
+// make, unless all work-groups of the launch are resident at once and what counts is that there is one launch less.  N = 2^16, two work-groups per
+// compute unit: the dropped limb of 16 products 90 us, 68 with the passes apart, 8 rotations at level 4 46 and 52; N = 2^17, one per compute
+// unit: 4 rotations at level 4 65 and 58, at level 6 the same, 4 products at level 6 49 and 51.
+static bool conv_pays(const he_ctx *c, int units, int targets)
 {
-    return dev_launch(c).moddown && c->K <= 4 && !c->up_split && (!c->dn_split || c->dn_fold) && !c->exact_conv;
+    return CONV_GROUPS * units <= (c->logN == 16 ? 512 : 256) || targets >= (c->logN == 16 ? 4 : 8);
+}
+// ModUp so (k_ntt_fwd_cols_modup): the common case, N = 2^16 and 2^17, digits of up to four limbs, all on the floating-point path, without the
+// correction of the overshoot.
+static bool modup_fused(const he_ctx *c, int level, int count)
+{
+    return dev_launch(c).modup && c->alpha <= 4 && !c->up_split && !c->exact_conv &&
+           conv_pays(c, (level + c->alpha - 1) / c->alpha * count, std::max(level - c->alpha, 0) + c->K);
+}
+// The same for ModDown's corrections of `targets` limbs (k_ntt_fwd_cols_moddown): up to four special primes, ciphertext limbs on the floating-point path.
+static bool moddown_fused(const he_ctx *c, int targets, int count)
+{
+    return dev_launch(c).moddown && c->K <= 4 && !c->up_split && (!c->dn_split || c->dn_fold) && !c->exact_conv && conv_pays(c, 2 * count, targets);
 }
 // The targets of a digit are shared out among so many work-groups that a launch of few operations puts one on every compute unit, and no
 // more, for each repeats the inverse column pass (N = 2^16: one rotation at level 13 93.5 us, with two on every unit 96.4; one product at level 6
@@ -669,7 +682,7 @@ static int32_t ks_raise(he_ctx *c, const u64 *d_ntt, F from, u64 *ws, const WsLa
     }
     ConvArgs cv = conv_args(c, ws + w.x * N, level, W, W);
     for (int o = 0; levels && o < count; o++) cv.op_level[o] = (uint8_t)levels[o];
-    const bool fused = modup_fused(c);
+    const bool fused = modup_fused(c, level, count);
     // limbs that go through a column pass or a block pass of their own
     LimbList r;
     for (int o = 0; o < count; o++) {
@@ -744,9 +757,9 @@ static double inner_words(const he_ctx *c, const InnerArgs &ia, const OpArgs *oa
     return words;
 }
 
-// Steps 3 and 4: the scaled coefficient-domain digits of the special limbs, in u (where ModDown's kernel makes them itself, what the inverse block
-// pass leaves).  ia.first < level: also u on the limbs from there on.
-static int32_t ks_special(he_ctx *c, const InnerArgs &ia, const OpArgs *oa, const WsLayout &w, hipStream_t st)
+// Steps 3 and 4: the scaled coefficient-domain digits of the special limbs, in u (cols false: what the inverse block pass leaves, for a kernel that
+// makes them itself).  ia.first < level: also u on the limbs from there on.
+static int32_t ks_special(he_ctx *c, const InnerArgs &ia, const OpArgs *oa, const WsLayout &w, bool cols, hipStream_t st)
 {
     const size_t N = c->N;
     const int K = c->K, Ma = ia.level + K, W = (int)w.total;
@@ -760,7 +773,7 @@ static int32_t ks_special(he_ctx *c, const InnerArgs &ia, const OpArgs *oa, cons
     dev_launch(c).inner(c, st, bytes, inner_grid((unsigned)N / tile, (unsigned)(Ma - ia.first), (unsigned)ia.count), ia,
                         oa ? *oa : kNoOps);
     int32_t rc = launch_ok(c);
-    if (rc != HE_OK || moddown_fused(c)) return rc;
+    if (rc != HE_OK || !cols) return rc;
     LimbList sp;
     for (int o = 0; o < ia.count; o++)
         for (int cc = 0; cc < 2; cc++)
@@ -790,9 +803,9 @@ static int32_t ks_corrections(he_ctx *c, const InnerArgs &ia, const OpArgs *oa, 
 }
 
 // Steps 5 and 6 on the first fa.nl limbs of every operation (those that it has): pro is the prologue of the
-// corrections' column pass, `extra` the source limbs it reads besides the special ones.
+// corrections' column pass, `extra` the source limbs it reads besides the special ones; fused: k_ntt_fwd_cols_moddown makes them.
 static int32_t ks_finish(he_ctx *c, const InnerArgs &ia, const OpArgs *oa, const WsLayout &w, u64 *ws, FinishArgs fa, int mode, int pro,
-                         const ConvArgs &cv, int extra, hipStream_t st)
+                         const ConvArgs &cv, int extra, bool fused, hipStream_t st)
 {
     const size_t N = c->N;
     const int W = (int)w.total;
@@ -811,7 +824,7 @@ static int32_t ks_finish(he_ctx *c, const InnerArgs &ia, const OpArgs *oa, const
         dev_launch(c).fin_limb(c, st, words * N * 8.0, std::max(c->alpha, c->K) > 4, pro, false, mode, ia, fa, oa ? *oa : kNoOps, cv);
         return launch_ok(c);
     }
-    int32_t rc = moddown_fused(c) ? ks_corrections(c, ia, oa, w, ws, 0, fa.nl, pro == PRO_MODDOWN_RS, false, st)
+    int32_t rc = fused ? ks_corrections(c, ia, oa, w, ws, 0, fa.nl, pro == PRO_MODDOWN_RS, false, st)
                                   : ntt_forward(c, st, r, l, pro, cv, nullptr, 2 * c->K * ia.count + extra, BLOCKS_NONE);
     if (rc != HE_OK) return rc;
     const unsigned grid = inner_grid((unsigned)(N / INNER_TILE), (unsigned)fa.nl, (unsigned)ia.count);
@@ -836,10 +849,11 @@ static int32_t ks_apply(he_ctx *c, const InnerArgs &ia, const OpArgs *oa, u64 *w
                         hipStream_t st)
 {
     const int W = (int)w.total;
-    int32_t rc = ks_special(c, ia, oa, w, st);
+    const bool fused = moddown_fused(c, fa.nl, ia.count);
+    int32_t rc = ks_special(c, ia, oa, w, !fused, st);
     if (rc != HE_OK) return rc;
     const ConvArgs cv = conv_args(c, ws + w.u * c->N, ia.level, W, W);
-    return ks_finish(c, ia, oa, w, ws, fa, mode, PRO_MODDOWN, cv, 0, st);
+    return ks_finish(c, ia, oa, w, ws, fa, mode, PRO_MODDOWN, cv, 0, fused, st);
 }
 
 static int32_t ks_guard(he_ctx *c, const he_evk *evk, int level, int count, void *ws, size_t ws_bytes)
@@ -944,7 +958,8 @@ extern "C" int32_t he_hmult_relin_rescale_batch(he_ctx *ctx, const he_evk *relin
         return rc;
     InnerArgs ia = mult_args(ctx, relin, d_a, d_b, ws, w, level, count, finished);
     ia.first = first;
-    if ((rc = ks_special(ctx, ia, nullptr, w, st)) != HE_OK) return rc;
+    const bool fused_drop = moddown_fused(ctx, 1, count), fused = moddown_fused(ctx, level - 1, count);
+    if ((rc = ks_special(ctx, ia, nullptr, w, !fused_drop, st)) != HE_OK) return rc;
     u64 *rbuf = ws + w.r * N;
     ConvArgs cv = conv_args(ctx, ws + w.u * N, level, W, W);
     cv.src2 = rbuf;
@@ -961,24 +976,23 @@ extern "C" int32_t he_hmult_relin_rescale_batch(he_ctx *ctx, const he_evk *relin
         for (int o = 0; o < count; o++)
             for (int cc = 0; cc < 2; cc++) last.add(o * W + cc * level + level - 1, level - 1);
         const FinArgs fl = {ws + w.u * N, rbuf, ctx->dev.dn_pinv, ctx->dev.dn_pinv_d, Ma, level, level, W, W, W};
-        if (moddown_fused(ctx)) { // the dropped limb's inverse column pass is part of the last conversion
-            const double N8 = (double)N * 8.0;
-            const DevLaunch &dl = dev_launch(ctx);
+        if (fused_drop) {
             if ((rc = ks_corrections(ctx, ia, nullptr, w, ws, first, 1, false, true, st)) != HE_OK) return rc;
-            rc = for_batches(ctx, last, [&](const LimbBatch &lb, int nb) {
-                dl.fwd_blocks(ctx, st, 3.0 * nb * N8, true, true, rbuf, lb, nb, fl);
-                dl.inv_blocks(ctx, st, 2.0 * nb * N8, rbuf, nullptr, rbuf, lb, nb);
-            });
-            if (rc != HE_OK) return rc;
-        } else {
-            if ((rc = ntt_forward(ctx, st, rbuf, last, PRO_MODDOWN, cv, &fl, 2 * K * count)) != HE_OK) return rc;
-            if ((rc = ntt_inverse(ctx, st, rbuf, rbuf, last, SCALE_NONE, cv)) != HE_OK) return rc;
-        }
+        } else if ((rc = ntt_forward(ctx, st, rbuf, last, PRO_MODDOWN, cv, nullptr, 2 * K * count, BLOCKS_NONE)) != HE_OK)
+            return rc;
+        const double N8 = (double)N * 8.0;
+        const DevLaunch &dl = dev_launch(ctx);
+        rc = for_batches(ctx, last, [&](const LimbBatch &lb, int nb) {
+            dl.fwd_blocks(ctx, st, 3.0 * nb * N8, true, true, rbuf, lb, nb, fl);
+            dl.inv_blocks(ctx, st, 2.0 * nb * N8, rbuf, nullptr, rbuf, lb, nb);
+            if (!fused) dl.inv_cols(ctx, st, 2.0 * nb * N8, SCALE_NONE, rbuf, lb, nb, cv); // else part of the last conversion
+        });
+        if (rc != HE_OK) return rc;
     }
     // every other limb: ModDown and rescale corrections in one transform
     fa.nl = fa.out_cstride = level - 1;
     fa.cst = ctx->dev.rsp_inv + (size_t)(level - 1) * L, fa.cst_d = ctx->dev.rsp_inv_d + (size_t)(level - 1) * L;
-    if ((rc = ks_finish(ctx, ia, nullptr, w, ws, fa, FIN_MULT, PRO_MODDOWN_RS, cv, 2 * count, st)) != HE_OK) return rc;
+    if ((rc = ks_finish(ctx, ia, nullptr, w, ws, fa, FIN_MULT, PRO_MODDOWN_RS, cv, 2 * count, fused, st)) != HE_OK) return rc;
     return mult_copy(ctx, mo, d_out, 2 * (level - 1), count, st);
 }
 

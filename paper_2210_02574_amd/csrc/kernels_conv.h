@@ -262,7 +262,7 @@ struct ModDownArgs {
     u64 *u, *r;
     int level, L, K, chunks, stride;
     int first, limbs; // ciphertext limbs first .. first + limbs - 1 are made (of an operation at a lower level those that it has)
-    int keep;         // the centred digits replace the special limbs in u, for a second launch that takes them from there
+    int keep;         // the digits, as residues, replace the special limbs in u, for a second launch that takes them from there
     uint8_t op_level[HE_OPS_MAX];
 };
 // A centred digit y, |y| < 2^59, in LDS: y + 2^49.  Its low 50 bits are yl + 2^49 with |yl| <= 2^49, what is above them is yh = (y - yl) / 2^50, and
@@ -275,8 +275,8 @@ __device__ __forceinline__ double conv_digit(u64 z, double r50)
 }
 
 // grid: CONV_GROUPS * operations * 2 * chunks, work-groups and waves as in k_ntt_fwd_cols_modup; the digits come from the inverse column
-// pass of the special limbs.  RS: with a rescale, after a launch for the dropped limb, level - 1, with `keep`: the
-// digits are in u, and the dropped limb, as the inverse block pass left it in r, is one more source with P for its constant.
+// pass of the special limbs.  RS: with a rescale, after the dropped limb, level - 1, has been through ModDown: the digits are
+// in u, and the dropped limb, as the inverse block pass left it in r, is one more source with P for its constant.
 template <int LOGN, bool RS>
 __global__ __launch_bounds__(64 * ConvGeom<LOGN>::DOWN_WAVES, ConvGeom<LOGN>::DOWN_BOUND) void k_ntt_fwd_cols_moddown(ModDownArgs da, DevTables T)
 {
@@ -304,35 +304,33 @@ __global__ __launch_bounds__(64 * ConvGeom<LOGN>::DOWN_WAVES, ConvGeom<LOGN>::DO
     if (wave < da.K) {
         u64 *limb = special + ((size_t)wave << LOGN);
         const ModConst m = T.mod[da.L + wave];
+        const u64 half = (m.q - 1) / 2;
+        const auto put = [&](int h, int k, u64 y) { mine[1024 * h + 64 * k] = (y > half ? y - m.q : y) + CONV_HALF; };
+        const auto put_keep = [&](int h, int k, u64 y) {
+            put(h, k, y);
+            if (da.keep) limb[place(h, k)] = y;
+        };
         if (RS) {
 #pragma unroll
             for (int h = 0; h < H; h++)
 #pragma unroll
-                for (int k = 0; k < 16; k++) mine[1024 * h + 64 * k] = limb[place(h, k)];
+                for (int k = 0; k < 16; k++) put(h, k, limb[place(h, k)]);
+        } else if (m.qd != 0.0) {
+            const ArithFp ar = make_fp(T, da.L + wave, LOGN, T.dn_inv_d[wave]);
+            double v[H][16];
+            conv_inverse<LOGN>(v, limb + col, ar, ex);
+#pragma unroll
+            for (int h = 0; h < H; h++)
+#pragma unroll
+                for (int k = 0; k < 16; k++) put_keep(h, k, ar.store_final(v[h][k]));
         } else {
-            const u64 half = (m.q - 1) / 2;
-            const auto put = [&](int h, int k, u64 y) {
-                const u64 z = (y > half ? y - m.q : y) + CONV_HALF;
-                mine[1024 * h + 64 * k] = z;
-                if (da.keep) limb[place(h, k)] = z;
-            };
-            if (m.qd != 0.0) {
-                const ArithFp ar = make_fp(T, da.L + wave, LOGN, T.dn_inv_d[wave]);
-                double v[H][16];
-                conv_inverse<LOGN>(v, limb + col, ar, ex);
+            const ArithInt ar = conv_int<LOGN>(T, da.L + wave, T.dn_inv[wave]);
+            u64 v[H][16];
+            conv_inverse<LOGN>(v, limb + col, ar, ex);
 #pragma unroll
-                for (int h = 0; h < H; h++)
+            for (int h = 0; h < H; h++)
 #pragma unroll
-                    for (int k = 0; k < 16; k++) put(h, k, ar.store_final(v[h][k]));
-            } else {
-                const ArithInt ar = conv_int<LOGN>(T, da.L + wave, T.dn_inv[wave]);
-                u64 v[H][16];
-                conv_inverse<LOGN>(v, limb + col, ar, ex);
-#pragma unroll
-                for (int h = 0; h < H; h++)
-#pragma unroll
-                    for (int k = 0; k < 16; k++) put(h, k, ar.store_final(v[h][k]));
-            }
+                for (int k = 0; k < 16; k++) put_keep(h, k, ar.store_final(v[h][k]));
         }
     } else if (wave < KMAX) { // fewer special primes: digits of zero
 #pragma unroll
