@@ -358,9 +358,9 @@ static int32_t ntt_forward(he_ctx *c, hipStream_t st, u64 *data, const LimbList 
         (cv.exact && dl.fwd_cols_ex[pro] ? dl.fwd_cols_ex[pro] : dl.fwd_cols[pro])(c, st, kid_cols, cols_bytes, wide, data, lb, nb, cv);
         if (fin) {
             // reads the transform's input and the minuend, writes the result
-            dl.fwd_blocks(c, st, 3.0 * nb * N8, true, pro_pairs_rows(pro), data, lb, nb, *fin);
+            dl.fwd_blocks(c, st, 3.0 * nb * N8, EPI_FIN, false, data, lb, nb, *fin);
         } else if (blocks == BLOCKS_ALL)
-            dl.fwd_blocks(c, st, 2.0 * nb * N8, false, pro_pairs_rows(pro), data, lb, nb, kNoFin);
+            dl.fwd_blocks(c, st, 2.0 * nb * N8, EPI_STORE, pro_pairs_rows(pro), data, lb, nb, kNoFin);
     });
     if (rc != HE_OK || blocks != BLOCKS_SOME || dl.fwd_limb[pro]) return rc;
     // after all column passes: few launches, each as large as possible
@@ -368,7 +368,7 @@ static int32_t ntt_forward(he_ctx *c, hipStream_t st, u64 *data, const LimbList 
     for (int b = 0; b < l.size(); b++)
         if (l.mod[b] >= finish_from || (c->modc[l.mod[b]].qd == 0.0 && l.mod[b] < c->L)) li.add(l.slot[b], l.src[b], l.mod[b]);
     return for_batches(c, li, [&](const LimbBatch &lb, int nb) {
-        dl.fwd_blocks(c, st, 2.0 * nb * N8, false, pro_pairs_rows(pro), data, lb, nb, kNoFin);
+        dl.fwd_blocks(c, st, 2.0 * nb * N8, EPI_STORE, pro_pairs_rows(pro), data, lb, nb, kNoFin);
     });
 }
 
@@ -712,7 +712,7 @@ static int32_t ks_raise(he_ctx *c, const u64 *d_ntt, F from, u64 *ws, const WsLa
     memcpy(ua.op_level, cv.op_level, sizeof(ua.op_level));
     dl.modup(c, st, (double)(src_limbs + targets) * N8, count, ua);
     if ((rc = launch_ok(c)) != HE_OK) return rc;
-    return for_batches(c, r, [&](const LimbBatch &lb, int nb) { dl.fwd_blocks(c, st, 2.0 * nb * N8, false, true, ws + w.raised * N, lb, nb, kNoFin); });
+    return for_batches(c, r, [&](const LimbBatch &lb, int nb) { dl.fwd_blocks(c, st, 2.0 * nb * N8, EPI_STORE, true, ws + w.raised * N, lb, nb, kNoFin); });
 }
 
 // limb offset of operation o's input where inputs are `stride` limbs apart
@@ -983,8 +983,7 @@ extern "C" int32_t he_hmult_relin_rescale_batch(he_ctx *ctx, const he_evk *relin
         const double N8 = (double)N * 8.0;
         const DevLaunch &dl = dev_launch(ctx);
         rc = for_batches(ctx, last, [&](const LimbBatch &lb, int nb) {
-            dl.fwd_blocks(ctx, st, 3.0 * nb * N8, true, true, rbuf, lb, nb, fl);
-            dl.inv_blocks(ctx, st, 2.0 * nb * N8, rbuf, nullptr, rbuf, lb, nb);
+            dl.fwd_blocks(ctx, st, 3.0 * nb * N8, EPI_FIN_INV, true, rbuf, lb, nb, fl);
             if (!fused) dl.inv_cols(ctx, st, 2.0 * nb * N8, SCALE_NONE, rbuf, lb, nb, cv); // else part of the last conversion
         });
         if (rc != HE_OK) return rc;

@@ -96,9 +96,7 @@ __host__ __device__ inline unsigned inner_grid(unsigned tiles, unsigned limbs, u
 #define INNER_TLOG 10
 #define WAVE_OUT 512u                       // outputs per wave
 #define WAVE_LOG 9
-#define WAVE_BLOCKS 2                       // 256-element blocks per wave
 #define WAVE_LDS (WAVE_BLOCKS * (TILE_GROUP + 512)) // LDS words per wave: exchange tile, twiddles, the next digit
-__device__ __forceinline__ unsigned wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 __device__ __forceinline__ unsigned pair8_at(unsigned i) { return WAVE_OUT * wave_id() + 128u * i + 2u * (threadIdx.x & 63u); }
 
 // Addresses are formed as a wave-uniform base plus a 32-bit lane offset so that they stay in scalar registers;
@@ -119,89 +117,6 @@ template <bool NT> __device__ __forceinline__ void wave_copy_4k(const char *src,
     for (int c = 0; c < 4; c++)
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + 1024 * c),
                                          (__attribute__((address_space(3))) void *)(dst + 1024 * c), 16, 0, NT ? 2 : 0);
-}
-
-// This thread's place in the block pass and the LDS addresses of its three exchange patterns.
-struct BlockLane {
-    unsigned blk, t, g2;
-    u64 *l1, *l2, *l3;
-    const double *tw; // the block's 255 twiddles in LDS
-};
-__device__ __forceinline__ BlockLane block_lane(u64 *lds, const double *tws)
-{
-    BlockLane b;
-    b.blk = (threadIdx.x >> 5) & 1u, b.t = threadIdx.x & 31, b.g2 = b.t & 7;
-    b.l1 = lds + b.blk * TILE_GROUP + b.t + (b.t >> 4);
-    b.l2 = lds + b.blk * TILE_GROUP + 34 * b.g2 + (b.t >> 3);
-    b.l3 = lds + b.blk * TILE_GROUP + 4 * b.t + (b.t >> 2);
-    b.tw = tws + b.blk * 256;
-    return b;
-}
-// This thread's eight values, t + 32 k of its block, from the two blocks at `pair` (in LDS or in memory) as the column pass left them, rows
-// interleaved.  A lane reads four elements of both rows, 16 bytes at a time, the lower half of the wave k < 4 and the upper one k >= 4, and
-// the halves swap what belongs to the other's row: read one row at a time, every access would hit half of the banks only.
-template <class A> __device__ __forceinline__ void mid_pairs8(const A &ar, typename A::V (&dv)[8], const u64 *pair, const BlockLane &b)
-{
-    const u64x2 *p = (const u64x2 *)pair + b.t + 128 * b.blk;
-    u64x2 v[4];
-#pragma unroll
-    for (int k = 0; k < 4; k++) v[k] = p[32 * k];
-#pragma unroll
-    for (int k = 0; k < 4; k++) {
-        const auto l = __builtin_amdgcn_permlane32_swap((unsigned)v[k].x, (unsigned)v[k].y, false, false);
-        const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(v[k].x >> 32), (unsigned)(v[k].y >> 32), false, false);
-        dv[k] = ar.load_mid((u64)h[0] << 32 | l[0]);
-        dv[k + 4] = ar.load_mid((u64)h[1] << 32 | l[1]);
-    }
-}
-// Block pass of the eight values dv of this thread (pattern of step 1); the result is left in the wave's LDS, element e
-// of block b at tile_at(b, e), for the caller to read after a block_sync.  tw(m, i): twiddle of local stage m, group i of the block.
-// Ranges (in units of q): floating point: the column pass leaves up to 3.7; reduced, step 1 ends below 2.7 and step 2 below 6.3;
-// reduced again, step 3 ends below 1.9, small enough for exact products.  Integer: in [0, 8) throughout.
-template <class A, class F> __device__ __forceinline__ void block_pass8(const A &ar, typename A::V (&dv)[8], const BlockLane &b, F tw)
-{
-    ar.fwd8_with(dv, true, [&](int sp, int gg) { return tw(sp, (unsigned)gg); });
-#pragma unroll
-    for (int k = 0; k < 8; k++) b.l1[34 * k] = ar.store_mid(dv[k]);
-    block_sync();
-#pragma unroll
-    for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(b.l2[4 * k + (k >> 2)]);
-    ar.fwd8_with(dv, false, [&](int sp, int gg) { return tw(3 + sp, (b.g2 << sp) + gg); });
-#pragma unroll
-    for (int k = 0; k < 8; k++) b.l2[4 * k + (k >> 2)] = ar.store_mid(dv[k]);
-    block_sync();
-#pragma unroll
-    for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(b.l3[136 * (k >> 2) + (k & 3)]);
-    ar.fwd4x2_with(dv, true, [&](int h, int sp, int gg) { return tw(6 + sp, ((b.t + 32 * h) << sp) + gg); });
-#pragma unroll
-    for (int k = 0; k < 8; k++) b.l3[136 * (k >> 2) + (k & 3)] = ar.store_mid(dv[k]);
-}
-// The inverse block pass of canonical residues in the wave's LDS (element e of block b at tile_at(b, e)), which it leaves as the inverse column pass
-// takes them; dv: elements t + 32 k.
-template <class A, class F> __device__ __forceinline__ void inv_block_pass8(const A &ar, typename A::V (&dv)[8], const BlockLane &b, F tw)
-{
-#pragma unroll
-    for (int k = 0; k < 8; k++) dv[k] = ar.load(b.l3[136 * (k >> 2) + (k & 3)]);
-    ar.inv4x2_with(dv, [&](int h, int sp, int gg) { return tw(6 + sp, ((b.t + 32 * h) << sp) + gg); });
-    block_sync();
-#pragma unroll
-    for (int k = 0; k < 8; k++) b.l3[136 * (k >> 2) + (k & 3)] = ar.store_mid(dv[k]);
-    block_sync();
-#pragma unroll
-    for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(b.l2[4 * k + (k >> 2)]);
-    ar.template inv8_with<false>(dv, [&](int sp, int gg) { return tw(3 + sp, (b.g2 << sp) + gg); });
-    block_sync();
-#pragma unroll
-    for (int k = 0; k < 8; k++) b.l2[4 * k + (k >> 2)] = ar.store_mid(dv[k]);
-    block_sync();
-#pragma unroll
-    for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(b.l1[34 * k]);
-    ar.template inv8_with<false>(dv, [&](int sp, int gg) { return tw(sp, (unsigned)gg); });
-}
-// the same as block_pass8 with the twiddles in LDS
-__device__ __forceinline__ void block_pass8(const ArithFp &ar, double (&dv)[8], const BlockLane &b)
-{
-    block_pass8(ar, dv, b, [&](int m, unsigned i) { return b.tw[(1u << m) - 1 + i]; });
 }
 
 // What one work-group works on.
@@ -445,12 +360,6 @@ __device__ __forceinline__ void inner_products_int(const InnerArgs &ia, const Op
 #define SPECIAL_TILE (1 << SPECIAL_TLOG)           // outputs per work-group: two blocks, 8 elements per lane of a wave
 #define SPECIAL_DIGIT (WAVE_BLOCKS * TILE_GROUP)   // LDS words of 512 elements
 #define FINISHED_TLOG 10
-
-// Twiddles of local stage m, group i of block G, forward or inverse.
-template <int LOGN, class Tv> __device__ __forceinline__ Tv block_twiddle(const Tv *tw, unsigned G, int m, unsigned i)
-{
-    return tw[(1u << (LOGN - 8 + m)) + (G << m) + i];
-}
 
 // The pair of digit values at `key`-order position: floating point, within 1.9 q of zero; integer, below 8q.
 __device__ __forceinline__ void special_mac(const ArithFp &ar, double x, u64 k0, u64 k1, double &s0, double &s1)

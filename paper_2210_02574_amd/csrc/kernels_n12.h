@@ -174,7 +174,7 @@ __global__ __launch_bounds__(N12_THREADS, EPI == EPI_FIN ? 4 : 1) void k_ntt_fwd
     u64 uv[EPI == EPI_FIN ? 8 : 1];
     if (EPI == EPI_FIN) {
 #pragma unroll
-        for (int k = 0; k < 8; k++) uv[k] = fin_load<12>(fa, slot, nb + 64 * k);
+        for (int k = 0; k < 8; k++) uv[k] = __builtin_nontemporal_load(fa.u + (((size_t)fin_limb(fa, slot, fa.u_stride, fa.u_cstride) << 12) + nb + 64 * k));
     }
     conv_variant12<PRO, NSMAX, EX, true>(T, mi, m, S.qld, [&](auto ar, auto split, auto tint) {
         typedef decltype(ar) A;
@@ -186,7 +186,7 @@ __global__ __launch_bounds__(N12_THREADS, EPI == EPI_FIN ? 4 : 1) void k_ntt_fwd
         for (int k = 0; k < 8; k++) {
             const unsigned pos = nb + 64 * k;
             if (EPI == EPI_FIN)
-                fin_store<12, A::IS_FP>(fa, T, slot, pos, v[k], uv[k]);
+                fin_store<12>(fa, slot, pos, fin_value<A::IS_FP>(fa, T, slot, v[k], uv[k]));
             else
                 limb[pos] = v[k];
         }

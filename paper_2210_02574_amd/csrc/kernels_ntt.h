@@ -24,6 +24,7 @@
 #include "arith.h"
 
 typedef u64 u64x2 __attribute__((ext_vector_type(2)));
+typedef u64 u64x2u __attribute__((ext_vector_type(2), aligned(8))); // in buffers of a caller, which are aligned to words
 // Work-groups go to the eight XCDs round-robin by index, and each XCD has its own L2.
 #define XCDS 8u
 
@@ -54,7 +55,8 @@ template <bool PAIR> __device__ __forceinline__ unsigned mid_at(unsigned b, unsi
     return PAIR ? (b >> 1) * 512u + 2u * e + (b & 1u) : b * 256u + e;
 }
 enum { SCALE_NONE = 0, SCALE_MODUP = 1, SCALE_MODDOWN = 2 };
-enum { EPI_STORE = 0, EPI_FIN = 1 };
+// Epilogues of the block pass: the transform; a finished rescale; the finished limb that a rescale drops, through its inverse block pass.
+enum { EPI_STORE = 0, EPI_FIN = 1, EPI_FIN_INV = 2 };
 
 // Batches: `count` independent ciphertexts are laid out with fixed strides (in limbs); a limb's slot
 // is op * stride + local index, so op = slot / stride and the local index keeps its single-op meaning.
@@ -326,97 +328,162 @@ __device__ __forceinline__ u64 conv_get(const ConvSetup<NSMAX> &S, const ArithIn
 
 // ---- epilogue: what the forward block pass does with a finished (canonical) NTT value ---------------------
 
-// The minuend of one output: issued before the transform so that the load overlaps it.
-template <int LOGN>
-__device__ __forceinline__ u64 fin_load(const FinArgs &fa, unsigned slot, unsigned pos)
+// Limb of destination slot `slot` in a buffer with these strides.
+__device__ __forceinline__ unsigned fin_limb(const FinArgs &fa, unsigned slot, int stride, int cstride)
 {
     const unsigned op = slot / (unsigned)fa.dst_stride;
     slot -= op * (unsigned)fa.dst_stride;
-    const unsigned c = slot / fa.nl, i = slot % fa.nl;
-    return __builtin_nontemporal_load(fa.u + ((((size_t)op * fa.u_stride + (size_t)c * fa.u_cstride + i) << LOGN) + pos));
+    return op * (unsigned)stride + slot / (unsigned)fa.nl * (unsigned)cstride + slot % (unsigned)fa.nl;
 }
-
+// modulus index: the limb within its component
+__device__ __forceinline__ unsigned fin_mod(const FinArgs &fa, unsigned slot) { return slot % (unsigned)fa.dst_stride % (unsigned)fa.nl; }
+// The minuends of two neighbouring outputs: issued before the transform so that the load overlaps it.
+template <int LOGN> __device__ __forceinline__ u64x2 fin_load(const FinArgs &fa, unsigned slot, unsigned pos)
+{
+    return __builtin_nontemporal_load((const u64x2u *)(fa.u + (((size_t)fin_limb(fa, slot, fa.u_stride, fa.u_cstride) << LOGN) + pos)));
+}
 // FP: the limb's modulus is on the floating-point path (known from the transform's arithmetic at compile time)
-template <int LOGN, bool FP>
-__device__ __forceinline__ void fin_store(const FinArgs &fa, const DevTables &T, unsigned slot, unsigned pos, u64 rv,
-                                          u64 uv)
+template <bool FP> __device__ __forceinline__ u64 fin_value(const FinArgs &fa, const DevTables &T, unsigned slot, u64 rv, u64 uv)
 {
-    const unsigned op = slot / (unsigned)fa.dst_stride;
-    slot -= op * (unsigned)fa.dst_stride;
-    const unsigned c = slot / fa.nl, i = slot % fa.nl;
+    const unsigned i = fin_mod(fa, slot);
     const ModConst m = T.mod[i];
-    const size_t o = (((size_t)op * fa.out_stride + (size_t)c * fa.out_cstride + i) << LOGN) + pos;
-    u64 res;
-    if (FP)
-        res = fp_canon(fp_mulmod(u2d(uv) - u2d(rv), fa.cst_d[i], m.qd, m.qinvd), m.qd, m.qinvd);
-    else
-        res = mul_shoup(uv + m.q - rv, fa.cst[i], m.q);
-    __builtin_nontemporal_store(res, fa.out + o); // a result: nothing in this launch reads it
+    if (FP) return fp_canon(fp_mulmod(u2d(uv) - u2d(rv), fa.cst_d[i], m.qd, m.qinvd), m.qd, m.qinvd);
+    return mul_shoup(uv + m.q - rv, fa.cst[i], m.q);
+}
+template <bool FP> __device__ __forceinline__ u64x2 fin_value(const FinArgs &fa, const DevTables &T, unsigned slot, u64x2 rv, u64x2 uv)
+{
+    return u64x2{fin_value<FP>(fa, T, slot, (u64)rv.x, (u64)uv.x), fin_value<FP>(fa, T, slot, (u64)rv.y, (u64)uv.y)};
+}
+template <int LOGN, class Tv> __device__ __forceinline__ void fin_store(const FinArgs &fa, unsigned slot, unsigned pos, Tv res) // Tv: u64 or u64x2u
+{
+    // a result: nothing in this launch reads it
+    __builtin_nontemporal_store(res, (Tv *)(fa.out + (((size_t)fin_limb(fa, slot, fa.out_stride, fa.out_cstride) << LOGN) + pos)));
 }
 
-// LDS tile of the block pass: 16 groups x 256 elements; one pad word per 16 elements and 16 pad words per
-// group keep both the "stride-16" and the "16 consecutive" access patterns free of bank conflicts.
+// LDS of the block pass, element i of block grp: one pad word per 16 elements and 16 per block keep all its patterns free of bank conflicts.
 #define TILE_GROUP 272
-// threads per work-group of the block pass: 16 threads per 256-element block
-#ifndef BLK_THREADS
-#define BLK_THREADS 256
-#endif
-#define BLK_PER_WG (BLK_THREADS / 16)
 __device__ __forceinline__ unsigned tile_at(unsigned grp, unsigned i) { return grp * TILE_GROUP + i + (i >> 4); }
-// Exchange through LDS among the 16 lanes that own one 256-element block.  They belong to one wave, and a wave's
-// LDS operations execute in order, so no work-group barrier is needed: only the compiler has to be kept from
-// moving LDS accesses across this point.
+// Exchange through LDS among the lanes of one wave.  A wave's LDS operations execute in order, so no work-group barrier is
+// needed: only the compiler has to be kept from moving LDS accesses across this point.
 __device__ __forceinline__ void block_sync()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
-static_assert(BLK_THREADS % 64 == 0, "a block's 16 lanes must not straddle two waves");
 // column pass: row r of column c (0..15).  The 16 lanes of a column group always touch 16 consecutive words,
 // so this tile needs no padding: 32 KiB at N = 2^16, five work-groups per compute unit.
 #define COL_GROUP 256
 __device__ __forceinline__ unsigned col_at(unsigned r, unsigned c) { return (r >> 4) * COL_GROUP + (r & 15) * 16 + c; }
 
 // ---- block pass ---------------------------------------------------------------------------------------------
-
-// PAIR: the column pass has interleaved the rows; a wave's four blocks are two pairs, so that the result may still go in their place
-template <int LOGN, int EPI, bool PAIR, class A>
-__device__ __forceinline__ void fwd_blocks_body(u64 *__restrict__ limb, const A &ar, u64 *lds, unsigned tile,
-                                                const FinArgs &fa, const DevTables &T, unsigned slot)
+//
+// A wave takes two blocks of 256 elements, eight per lane, 32 lanes a block, and runs their stages as three register steps, stages 0-2, 3-5
+// and 6-7 of the block, with two exchanges through LDS among those lanes:
+//   step 1: lane t holds e = t + 32 k;   step 2: lane (g = t & 7, r = t >> 3) holds e = 32 g + r + 4 k;
+//   step 3: lane t holds e = 4 t + k' and 128 + 4 t + k' (k' < 4).
+// With one pad word per 16 elements every 16 consecutive lanes of each pattern hit 16 different 8-byte banks.  The three patterns are
+// one base each plus compile-time offsets (t + 32 k sits at t + (t >> 4) + 34 k, 32 g + r + 4 k at 34 g + r + 4 k + (k >> 2), and
+// 128 h + 4 t + k' at 4 t + (t >> 2) + 136 h + k').
+//
+// Bound by memory in large launches, by the chain of one wave in small ones.  With 16 elements per lane, 16 lanes a block, two steps of four stages
+// and one exchange, the kernels took 79 to 118 registers and four waves per SIMD; now 59 to 64 (with an epilogue 85 and 100) and eight.  Transforms of
+// 64 limbs at N = 2^16 33.0 -> 30.6 us, of 34 at N = 2^17 41.5 -> 40.2, of 256 109 -> 104 (with plain loads and stores, whose lines the other pass
+// finds in the last-level cache, in place of nontemporal ones; both passes).
+#define WAVE_BLOCKS 2
+#define BLK_THREADS 256
+#define BLK_PER_WG (BLK_THREADS / 64 * WAVE_BLOCKS)
+#define BLK_LDS (BLK_PER_WG * TILE_GROUP)
+__device__ __forceinline__ unsigned wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+// This thread's place in the block pass and the LDS addresses of its three exchange patterns.
+struct BlockLane {
+    unsigned blk, t, g2;
+    u64 *l1, *l2, *l3;
+    const double *tw; // the block's 255 twiddles in LDS
+};
+__device__ __forceinline__ BlockLane block_lane(u64 *lds, const double *tws)
 {
-    const unsigned blk = threadIdx.x >> 4, il = threadIdx.x & 15;
-    const unsigned bg = tile * BLK_PER_WG + blk; // block index within the limb
-    typename A::V a[16];
-    u64 uv[EPI == EPI_FIN ? 16 : 1];
+    BlockLane b;
+    b.blk = (threadIdx.x >> 5) & 1u, b.t = threadIdx.x & 31, b.g2 = b.t & 7;
+    b.l1 = lds + b.blk * TILE_GROUP + b.t + (b.t >> 4);
+    b.l2 = lds + b.blk * TILE_GROUP + 34 * b.g2 + (b.t >> 3);
+    b.l3 = lds + b.blk * TILE_GROUP + 4 * b.t + (b.t >> 2);
+    b.tw = tws + b.blk * 256;
+    return b;
+}
+// This thread's eight values, t + 32 k of its block, from the two blocks at `pair` (in LDS or in memory) as the column pass left them, rows
+// interleaved.  A lane reads four elements of both rows, 16 bytes at a time, the lower half of the wave k < 4 and the upper one k >= 4, and
+// the halves swap what belongs to the other's row: read one row at a time, every access would hit half of the banks only.
+template <class A> __device__ __forceinline__ void mid_pairs8(const A &ar, typename A::V (&dv)[8], const u64 *pair, const BlockLane &b)
+{
+    const u64x2 *p = (const u64x2 *)pair + b.t + 128 * b.blk;
+    u64x2 v[4];
 #pragma unroll
-    for (int k = 0; k < 16; k++)
-        a[k] = ar.load_mid(__builtin_nontemporal_load(limb + mid_at<PAIR>(bg, il + 16 * k))); // read once: the column pass wrote it
-    if (EPI == EPI_FIN) {
+    for (int k = 0; k < 4; k++) v[k] = p[32 * k];
 #pragma unroll
-        for (int k = 0; k < 16; k++) uv[k] = fin_load<LOGN>(fa, slot, bg * 256 + il + 16 * k);
-    }
-    ar.fwd16(a, LOGN - 8, bg, true);
-#pragma unroll
-    for (int k = 0; k < 16; k++) lds[tile_at(blk, il + 16 * k)] = ar.store_mid(a[k]);
-    block_sync();
-#pragma unroll
-    for (int k = 0; k < 16; k++) a[k] = ar.load_mid(lds[tile_at(blk, 16 * il + k)]);
-    ar.fwd16(a, LOGN - 4, bg * 16 + il, true);
-    block_sync();
-#pragma unroll
-    for (int k = 0; k < 16; k++) lds[tile_at(blk, 16 * il + k)] = ar.store_final(a[k]);
-    block_sync();
-#pragma unroll
-    for (int k = 0; k < 16; k++) {
-        const unsigned pos = bg * 256 + il + 16 * k;
-        const u64 v = lds[tile_at(blk, il + 16 * k)];
-        if (EPI == EPI_FIN)
-            fin_store<LOGN, A::IS_FP>(fa, T, slot, pos, v, uv[k]);
-        else
-            __builtin_nontemporal_store(v, limb + pos);
+    for (int k = 0; k < 4; k++) {
+        const auto l = __builtin_amdgcn_permlane32_swap((unsigned)v[k].x, (unsigned)v[k].y, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(v[k].x >> 32), (unsigned)(v[k].y >> 32), false, false);
+        dv[k] = ar.load_mid((u64)h[0] << 32 | l[0]);
+        dv[k + 4] = ar.load_mid((u64)h[1] << 32 | l[1]);
     }
 }
+// Block pass of the eight values dv of this thread (pattern of step 1); the result is left in the wave's LDS, element e
+// of block b at tile_at(b, e), for the caller to read after a block_sync.  tw(m, i): twiddle of local stage m, group i of the block.
+// Ranges (in units of q): floating point: the column pass leaves up to 3.7; reduced, step 1 ends below 2.7 and step 2 below 6.3;
+// reduced again, step 3 ends below 1.9, small enough for exact products.  Integer: in [0, 8) throughout.
+template <class A, class F> __device__ __forceinline__ void block_pass8(const A &ar, typename A::V (&dv)[8], const BlockLane &b, F tw)
+{
+    ar.fwd8_with(dv, true, [&](int sp, int gg) { return tw(sp, (unsigned)gg); });
+#pragma unroll
+    for (int k = 0; k < 8; k++) b.l1[34 * k] = ar.store_mid(dv[k]);
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(b.l2[4 * k + (k >> 2)]);
+    ar.fwd8_with(dv, false, [&](int sp, int gg) { return tw(3 + sp, (b.g2 << sp) + gg); });
+#pragma unroll
+    for (int k = 0; k < 8; k++) b.l2[4 * k + (k >> 2)] = ar.store_mid(dv[k]);
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(b.l3[136 * (k >> 2) + (k & 3)]);
+    ar.fwd4x2_with(dv, true, [&](int h, int sp, int gg) { return tw(6 + sp, ((b.t + 32 * h) << sp) + gg); });
+#pragma unroll
+    for (int k = 0; k < 8; k++) b.l3[136 * (k >> 2) + (k & 3)] = ar.store_mid(dv[k]);
+}
+// The inverse block pass of canonical residues in the wave's LDS (element e of block b at tile_at(b, e)), which it leaves as the inverse column pass
+// takes them; dv: elements t + 32 k.
+template <class A, class F> __device__ __forceinline__ void inv_block_pass8(const A &ar, typename A::V (&dv)[8], const BlockLane &b, F tw)
+{
+#pragma unroll
+    for (int k = 0; k < 8; k++) dv[k] = ar.load(b.l3[136 * (k >> 2) + (k & 3)]);
+    ar.inv4x2_with(dv, [&](int h, int sp, int gg) { return tw(6 + sp, ((b.t + 32 * h) << sp) + gg); });
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 8; k++) b.l3[136 * (k >> 2) + (k & 3)] = ar.store_mid(dv[k]);
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(b.l2[4 * k + (k >> 2)]);
+    ar.template inv8_with<false>(dv, [&](int sp, int gg) { return tw(3 + sp, (b.g2 << sp) + gg); });
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 8; k++) b.l2[4 * k + (k >> 2)] = ar.store_mid(dv[k]);
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(b.l1[34 * k]);
+    ar.template inv8_with<false>(dv, [&](int sp, int gg) { return tw(sp, (unsigned)gg); });
+}
+// the same as block_pass8 with the twiddles in LDS
+__device__ __forceinline__ void block_pass8(const ArithFp &ar, double (&dv)[8], const BlockLane &b)
+{
+    block_pass8(ar, dv, b, [&](int m, unsigned i) { return b.tw[(1u << m) - 1 + i]; });
+}
+
+// Twiddles of local stage m, group i of block G, forward or inverse.
+template <int LOGN, class Tv> __device__ __forceinline__ Tv block_twiddle(const Tv *tw, unsigned G, int m, unsigned i)
+{
+    return tw[(1u << (LOGN - 8 + m)) + (G << m) + i];
+}
+
 
 // Product of two residues, canonical.
 __device__ __forceinline__ u64 mul_residues(u64 x, u64 y, const ModConst &m, const ArithFp &)
@@ -425,49 +492,100 @@ __device__ __forceinline__ u64 mul_residues(u64 x, u64 y, const ModConst &m, con
 }
 __device__ __forceinline__ u64 mul_residues(u64 x, u64 y, const ModConst &m, const ArithInt &) { return mul_mod(x, y, m); }
 
+// Where a wave's pairs of neighbouring elements, 128 i + 2 lane and + 1 of its 512, i < 4, sit in its LDS.
+__device__ __forceinline__ unsigned wave_pair_at(int i)
+{
+    const unsigned p = 128u * i + 2u * (threadIdx.x & 63u);
+    return tile_at(p >> 8, p & 255u);
+}
+// The wave's inverse block pass from canonical residues in its LDS, stored to `limb` as the inverse column pass takes them.  stream: the batch is part
+// of a conversion and far larger than the caches; in place (a plain inverse transform) the column pass that follows finds the
+// stores in the last-level cache
+template <int LOGN, class A> __device__ __forceinline__ void inv_blocks_wave(u64 *limb, unsigned bg, const A &ar, const BlockLane &b, bool stream)
+{
+    typename A::V v[8];
+    inv_block_pass8(ar, v, b, [&](int m, unsigned i) { return block_twiddle<LOGN>(ar.twi, bg, m, i); });
+    u64 *o = limb + bg * 256 + b.t;
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+        if (stream)
+            __builtin_nontemporal_store(ar.store_mid(v[k]), o + 32 * k);
+        else
+            o[32 * k] = ar.store_mid(v[k]);
+    }
+}
+// PAIR: the column pass has interleaved the rows; a wave's two blocks are a pair, so that the result may still go in their place
+template <int LOGN, int EPI, bool PAIR, class A>
+__device__ __forceinline__ void fwd_blocks_body(u64 *__restrict__ limb, const A &ar, u64 *lds, unsigned tile,
+                                                const FinArgs &fa, const DevTables &T, unsigned slot)
+{
+    u64 *wlds = lds + wave_id() * WAVE_BLOCKS * TILE_GROUP;
+    const BlockLane b = block_lane(wlds, nullptr);
+    const unsigned b0 = tile * BLK_PER_WG + wave_id() * WAVE_BLOCKS, bg = b0 + b.blk; // block index within the limb
+    typename A::V a[8];
+    u64x2 uv[EPI == EPI_STORE ? 1 : 4];
+    const unsigned pos = b0 * 256 + 2u * (threadIdx.x & 63u); // of the first of this lane's pairs, 128 apart
+    if (PAIR)
+        mid_pairs8(ar, a, limb + b0 * 256, b);
+    else {
+#pragma unroll
+        for (int k = 0; k < 8; k++) a[k] = ar.load_mid(limb[bg * 256 + b.t + 32 * k]);
+    }
+    if (EPI != EPI_STORE) {
+#pragma unroll
+        for (int i = 0; i < 4; i++) uv[i] = fin_load<LOGN>(fa, slot, pos + 128 * i);
+    }
+    block_pass8(ar, a, b, [&](int m, unsigned i) { return block_twiddle<LOGN>(ar.twf, bg, m, i); });
+    block_sync();
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        u64 *w = wlds + wave_pair_at(i);
+        const u64x2 v = {ar.store_final(ar.load_mid(w[0])), ar.store_final(ar.load_mid(w[1]))};
+        if (EPI == EPI_STORE)
+            *(u64x2u *)(limb + pos + 128 * i) = v;
+        else {
+            const u64x2 res = fin_value<A::IS_FP>(fa, T, slot, v, uv[i]);
+            if (EPI == EPI_FIN)
+                fin_store<LOGN, u64x2u>(fa, slot, pos + 128 * i, res);
+            else
+                w[0] = res.x, w[1] = res.y;
+        }
+    }
+    if constexpr (EPI == EPI_FIN_INV) {
+        block_sync();
+        inv_blocks_wave<LOGN>(fa.out + ((size_t)fin_limb(fa, slot, fa.out_stride, fa.out_cstride) << LOGN), bg, ar, b, false);
+    }
+}
+
 // PROD: the input is the product of `in` and `in2` (d2 = a1 b1 of a Mult, which is stored nowhere)
 template <int LOGN, bool PROD, class A>
 __device__ __forceinline__ void inv_blocks_body(const u64 *in, const u64 *in2, u64 *limb, const ModConst &m, const A &ar,
                                                 u64 *lds, unsigned tile)
 {
-    // out of place: part of a conversion, whose batch is far larger than the caches; in place (a plain inverse
-    // transform) the column pass that follows finds the stores in the last-level cache
-    const bool stream = in != limb;
-    const unsigned blk = threadIdx.x >> 4, il = threadIdx.x & 15;
-    const unsigned bg = tile * BLK_PER_WG + blk;
-    typename A::V a[16];
+    u64 *wlds = lds + wave_id() * WAVE_BLOCKS * TILE_GROUP;
+    const BlockLane b = block_lane(wlds, nullptr);
+    const unsigned b0 = tile * BLK_PER_WG + wave_id() * WAVE_BLOCKS, pos = b0 * 256 + 2u * (threadIdx.x & 63u);
+    u64x2 x[4], y[PROD ? 4 : 1];
 #pragma unroll
-    for (int k = 0; k < 16; k++) {
-        const unsigned pos = bg * 256 + il + 16 * k;
-        const u64 x = __builtin_nontemporal_load(in + pos); // read once
-        lds[tile_at(blk, il + 16 * k)] = PROD ? mul_residues(x, __builtin_nontemporal_load(in2 + pos), m, ar) : x;
+    for (int i = 0; i < 4; i++) {
+        x[i] = __builtin_nontemporal_load((const u64x2u *)(in + pos + 128 * i)); // read once
+        if (PROD) y[i] = __builtin_nontemporal_load((const u64x2u *)(in2 + pos + 128 * i));
+    }
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        if (PROD) x[i] = u64x2{mul_residues(x[i].x, y[i].x, m, ar), mul_residues(x[i].y, y[i].y, m, ar)};
+        u64 *w = wlds + wave_pair_at(i);
+        w[0] = x[i].x, w[1] = x[i].y;
     }
     block_sync();
-#pragma unroll
-    for (int k = 0; k < 16; k++) a[k] = ar.load(lds[tile_at(blk, 16 * il + k)]);
-    ar.template inv16<false>(a, LOGN - 4, bg * 16 + il);
-    block_sync();
-#pragma unroll
-    for (int k = 0; k < 16; k++) lds[tile_at(blk, 16 * il + k)] = ar.store_mid(a[k]);
-    block_sync();
-#pragma unroll
-    for (int k = 0; k < 16; k++) a[k] = ar.load_mid(lds[tile_at(blk, il + 16 * k)]);
-    ar.template inv16<false>(a, LOGN - 8, bg);
-#pragma unroll
-    for (int k = 0; k < 16; k++) { // the column pass finishes
-        u64 *dst = limb + bg * 256 + il + 16 * k;
-        if (stream)
-            __builtin_nontemporal_store(ar.store_mid(a[k]), dst);
-        else
-            *dst = ar.store_mid(a[k]);
-    }
+    inv_blocks_wave<LOGN>(limb, b0 + b.blk, ar, b, in != limb);
 }
 
-// grid.x = (N/4096) * batch
+// grid.x = (N / (256 BLK_PER_WG)) * batch
 template <int LOGN, int EPI, bool PAIR>
-__global__ __launch_bounds__(BLK_THREADS, EPI == EPI_FIN ? 4 : 1) void k_ntt_fwd_blocks(u64 *__restrict__ data, DevTables T, LimbBatch lb, FinArgs fa)
+__global__ __launch_bounds__(BLK_THREADS, 4) void k_ntt_fwd_blocks(u64 *__restrict__ data, DevTables T, LimbBatch lb, FinArgs fa)
 {
-    __shared__ u64 lds[BLK_PER_WG * TILE_GROUP];
+    __shared__ __align__(16) u64 lds[BLK_LDS];
     constexpr unsigned TILES = (1u << LOGN) / (256 * BLK_PER_WG);
     const unsigned tile = blockIdx.x % TILES, b = blockIdx.x / TILES;
     const unsigned mi = lb.mod[b], slot = lb.slot[b];
@@ -480,10 +598,10 @@ __global__ __launch_bounds__(BLK_THREADS, EPI == EPI_FIN ? 4 : 1) void k_ntt_fwd
 
 // src2: with PROD, the second factor, at the same limbs as src
 template <int LOGN, bool PROD>
-__global__ __launch_bounds__(BLK_THREADS) void k_ntt_inv_blocks(const u64 *src, const u64 *src2, u64 *dst,
+__global__ __launch_bounds__(BLK_THREADS, 4) void k_ntt_inv_blocks(const u64 *src, const u64 *src2, u64 *dst,
                                                         DevTables T, LimbBatch lb)
 {
-    __shared__ u64 lds[BLK_PER_WG * TILE_GROUP];
+    __shared__ __align__(16) u64 lds[BLK_LDS];
     constexpr unsigned TILES = (1u << LOGN) / (256 * BLK_PER_WG);
     const unsigned tile = blockIdx.x % TILES, b = blockIdx.x / TILES;
     const unsigned mi = lb.mod[b];
@@ -517,7 +635,7 @@ __device__ __forceinline__ void cols_inputs(typename A::V (&a)[16], const u64 *_
 #pragma unroll
     for (int k = 0; k < 16; k++) {
         const unsigned pos = (rl + 16 * k + 256 * h) * 256 + col0 + c;
-        a[k] = PRO == PRO_LOAD ? ar.load(__builtin_nontemporal_load(limb + pos)) : conv_get<PRO, SPLIT, TINT, EX>(S, ar, m, pos);
+        a[k] = PRO == PRO_LOAD ? ar.load(limb[pos]) : conv_get<PRO, SPLIT, TINT, EX>(S, ar, m, pos);
     }
 }
 // second phase of the forward column pass for rows 16 g .. 16 g + 15, held in LDS as group gl.  With a prologue the
@@ -599,7 +717,7 @@ __device__ __forceinline__ void inv_cols_body(u64 *__restrict__ limb, unsigned c
 #pragma unroll
         for (int k = 0; k < 16; k++) {
             const u64 *src = limb + (16 * (rl + 16 * h) + k) * 256 + col0 + c;
-            v[k] = ar.load_mid(__builtin_nontemporal_load(src)); // the block pass wrote it, read this once only
+            v[k] = ar.load_mid(*src); // the block pass wrote it
         }
     };
     const auto half = [&](V (&v)[16], int h) __attribute__((always_inline)) {

@@ -55,8 +55,8 @@ struct DevLaunch {
     // the same with the corrected base conversions (entries of prologues without a conversion stay null)
     void (*fwd_cols_ex[5])(he_ctx *c, hipStream_t st, int kid, double bytes, bool wide, u64 *data, const LimbBatch &lb, int nb,
                            const ConvArgs &cv);
-    // forward block pass of the first nb limbs of lb; fin: with the finishing epilogue; pairs: their rows are interleaved
-    void (*fwd_blocks)(he_ctx *c, hipStream_t st, double bytes, bool fin, bool pairs, u64 *data, const LimbBatch &lb, int nb,
+    // forward block pass of the first nb limbs of lb with epilogue epi; pairs: their rows are interleaved (EPI_FIN: never, EPI_FIN_INV: always)
+    void (*fwd_blocks)(he_ctx *c, hipStream_t st, double bytes, int epi, bool pairs, u64 *data, const LimbBatch &lb, int nb,
                        const FinArgs &fa);
     // src2: null, or a second factor of the transform's input
     void (*inv_blocks)(he_ctx *c, hipStream_t st, double bytes, const u64 *src, const u64 *src2, u64 *dst, const LimbBatch &lb, int nb);
@@ -94,22 +94,18 @@ HE_DECL_COLS(17)
 
 // ---- launcher bodies, instantiated by the per-ring-size translation units ------------------------------
 
-template <int LOGN, bool PAIR>
-static void launch_fwd_blocks_layout(he_ctx *c, hipStream_t st, double bytes, bool fin, u64 *data, const LimbBatch &lb, int nb,
-                                     const FinArgs &fa)
-{
-    if (fin)
-        KLAUNCH_T(c, st, KID_FWD_BLOCKS_FIN, bytes, (k_ntt_fwd_blocks<LOGN, EPI_FIN, PAIR>), BLK_TILES(c) * nb, BLK_THREADS, data,
-                  c->dev, lb, fa);
-    else
-        KLAUNCH_T(c, st, KID_FWD_BLOCKS, bytes, (k_ntt_fwd_blocks<LOGN, EPI_STORE, PAIR>), BLK_TILES(c) * nb, BLK_THREADS, data,
-                  c->dev, lb, fa);
-}
 template <int LOGN>
-static void launch_fwd_blocks(he_ctx *c, hipStream_t st, double bytes, bool fin, bool pairs, u64 *data, const LimbBatch &lb, int nb,
-                              const FinArgs &fa)
+static void launch_fwd_blocks(he_ctx *c, hipStream_t st, double bytes, int epi, bool pairs, u64 *data, const LimbBatch &lb, int nb, const FinArgs &fa)
 {
-    (pairs ? launch_fwd_blocks_layout<LOGN, true> : launch_fwd_blocks_layout<LOGN, false>)(c, st, bytes, fin, data, lb, nb, fa);
+    const int grid = BLK_TILES(c) * nb;
+    if (epi == EPI_FIN_INV) // of a Mult's dropped limb, behind its ModDown
+        KLAUNCH_T(c, st, KID_FWD_BLOCKS_FIN, bytes, (k_ntt_fwd_blocks<LOGN, EPI_FIN_INV, true>), grid, BLK_THREADS, data, c->dev, lb, fa);
+    else if (epi == EPI_FIN) // of a rescale
+        KLAUNCH_T(c, st, KID_FWD_BLOCKS_FIN, bytes, (k_ntt_fwd_blocks<LOGN, EPI_FIN, false>), grid, BLK_THREADS, data, c->dev, lb, fa);
+    else if (pairs)
+        KLAUNCH_T(c, st, KID_FWD_BLOCKS, bytes, (k_ntt_fwd_blocks<LOGN, EPI_STORE, true>), grid, BLK_THREADS, data, c->dev, lb, fa);
+    else
+        KLAUNCH_T(c, st, KID_FWD_BLOCKS, bytes, (k_ntt_fwd_blocks<LOGN, EPI_STORE, false>), grid, BLK_THREADS, data, c->dev, lb, fa);
 }
 template <int LOGN>
 static void launch_inv_blocks(he_ctx *c, hipStream_t st, double bytes, const u64 *src, const u64 *src2, u64 *dst,

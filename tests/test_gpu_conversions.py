@@ -58,3 +58,29 @@ def test_products(env):
         assert np.array_equal(he.to_host(he.hmult_relin_rescale_batch(key, da, db)), resc)
         for i in range(count):
             assert np.array_equal(he.to_host(he.hmult_relin_rescale(key, da[i], db[i])), resc[i])
+
+
+@pytest.mark.parametrize("params", ["N16", "P17"])
+def test_buffers_that_start_at_an_odd_word(params, oracle_mod):
+    """Transforms and rescales take buffers aligned to words, not to the 16 bytes that a pair of them has."""
+    import torch
+
+    import paper_2210_02574_amd as pkg
+
+    p = getattr(wl, params)
+    he, o = pkg.HE.from_params(p, device=0), oracle_mod.Oracle(p.logN, p.q, p.p, p.dnum)
+
+    def odd(x):
+        t = he.to_device(np.concatenate([np.zeros(1, dtype=np.uint64), x.reshape(-1)]))[1:].view(x.shape)
+        assert t.data_ptr() % 16 == 8 and t.is_contiguous()
+        return t
+
+    mods = [0, p.L]  # one limb on either arithmetic path
+    x = np.stack([wl.rng(5).integers(0, p.moduli[i], size=p.N, dtype=np.uint64) for i in mods])
+    want = o.ntt(x, mods)
+    d = odd(x)
+    assert np.array_equal(he.to_host(he.ntt(d, mods)), want)
+    assert np.array_equal(he.to_host(he.intt(d, mods)), x)
+    ct = wl.uniform_ct(6, p, 3)
+    out = torch.zeros(2 * 2 * p.N + 1, dtype=torch.int64, device="cuda:0")[1:].view(2, 2, p.N)
+    assert np.array_equal(he.to_host(he.rescale(odd(ct), out=out)), o.rescale(ct))
