@@ -640,22 +640,27 @@ static int finish_from(const he_ctx *c, int level, int first, bool finished) { r
 // Each work-group waits for the inverse pass of its sources, half of its waves without work, so it has to have some targets to
 // make, unless all work-groups of the launch are resident at once and what counts is that there is one launch less.  N = 2^16, two work-groups per
 // compute unit: the dropped limb of 16 products 90 us, 68 with the passes apart, 8 rotations at level 4 46 and 52; N = 2^17, one per compute
-// unit: 4 rotations at level 4 65 and 58, at level 6 the same, 4 products at level 6 49 and 51.
-static bool conv_pays(const he_ctx *c, int units, int targets)
+// unit: 4 rotations at level 4 65 and 58, at level 6 the same, 4 products at level 6 49 and 51; more than four sources, one per compute unit: 16
+// rotations at level 6 429 us as a call, 366 with the passes apart, at level 12 665 and 714.
+static bool conv_pays(const he_ctx *c, int sources, int units, int targets)
 {
-    return CONV_GROUPS * units <= (c->logN == 16 ? 512 : 256) || targets >= (c->logN == 16 ? 4 : 8);
+    const bool two = c->logN == 16 && sources <= 4; // work-groups per compute unit
+    return CONV_GROUPS * units <= (two ? 512 : 256) || targets >= (two ? 4 : 8);
 }
-// ModUp so (k_ntt_fwd_cols_modup): the common case, N = 2^16 and 2^17, digits of up to four limbs, all on the floating-point path, without the
-// correction of the overshoot.
+// ModUp so (k_ntt_fwd_cols_modup): N = 2^16 and 2^17, digits whose limbs are all on the floating-point path, without the correction of the
+// overshoot.
 static bool modup_fused(const he_ctx *c, int level, int count)
 {
-    return dev_launch(c).modup && c->alpha <= 4 && !c->up_split && !c->exact_conv &&
-           conv_pays(c, (level + c->alpha - 1) / c->alpha * count, std::max(level - c->alpha, 0) + c->K);
+    return dev_launch(c).modup && !c->up_split && !c->exact_conv &&
+           conv_pays(c, c->alpha, (level + c->alpha - 1) / c->alpha * count, std::max(level - c->alpha, 0) + c->K);
 }
-// The same for ModDown's corrections of `targets` limbs (k_ntt_fwd_cols_moddown): up to four special primes, ciphertext limbs on the floating-point path.
-static bool moddown_fused(const he_ctx *c, int targets, int count)
+// The same for ModDown's corrections of `targets` limbs (k_ntt_fwd_cols_moddown): ciphertext limbs on the floating-point path.  With a rescale and more
+// than four special primes from two targets on: the pass of its own splits every digit at bit 31 (16 products of wide digits at level 3 388 us as a
+// call, 468 with it).
+static bool moddown_fused(const he_ctx *c, int targets, int count, bool rs)
 {
-    return dev_launch(c).moddown && c->K <= 4 && !c->up_split && (!c->dn_split || c->dn_fold) && !c->exact_conv && conv_pays(c, 2 * count, targets);
+    return dev_launch(c).moddown && !c->up_split && (!c->dn_split || c->dn_fold) && !c->exact_conv &&
+           (conv_pays(c, c->K, 2 * count, targets) || (rs && c->K > 4 && targets > 1));
 }
 // The targets of a digit are shared out among so many work-groups that a launch of few operations puts one on every compute unit, and no
 // more, for each repeats the inverse column pass (N = 2^16: one rotation at level 13 93.5 us, with two on every unit 96.4; one product at level 6
@@ -849,7 +854,7 @@ static int32_t ks_apply(he_ctx *c, const InnerArgs &ia, const OpArgs *oa, u64 *w
                         hipStream_t st)
 {
     const int W = (int)w.total;
-    const bool fused = moddown_fused(c, fa.nl, ia.count);
+    const bool fused = moddown_fused(c, fa.nl, ia.count, false);
     int32_t rc = ks_special(c, ia, oa, w, !fused, st);
     if (rc != HE_OK) return rc;
     const ConvArgs cv = conv_args(c, ws + w.u * c->N, ia.level, W, W);
@@ -958,7 +963,7 @@ extern "C" int32_t he_hmult_relin_rescale_batch(he_ctx *ctx, const he_evk *relin
         return rc;
     InnerArgs ia = mult_args(ctx, relin, d_a, d_b, ws, w, level, count, finished);
     ia.first = first;
-    const bool fused_drop = moddown_fused(ctx, 1, count), fused = moddown_fused(ctx, level - 1, count);
+    const bool fused_drop = moddown_fused(ctx, 1, count, false), fused = moddown_fused(ctx, level - 1, count, true);
     if ((rc = ks_special(ctx, ia, nullptr, w, !fused_drop, st)) != HE_OK) return rc;
     u64 *rbuf = ws + w.r * N;
     ConvArgs cv = conv_args(ctx, ws + w.u * N, level, W, W);

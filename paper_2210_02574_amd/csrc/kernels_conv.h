@@ -27,15 +27,17 @@
 // free of bank conflicts; the low and the high halves of the values go through it in turn
 #define CONV_EXCH (16 * 68)
 
-template <int LOGN> struct ConvGeom {
+// SOURCES: the most that a conversion has (an eighth of the LDS of a compute unit each at N = 2^17, a twentieth at N = 2^16).
+template <int LOGN, int SOURCES = 4> struct ConvGeom {
     static constexpr int ROWS = 1 << (LOGN - 8);
     static constexpr int HALVES = ROWS / 256;       // 16-element register steps per lane
     static constexpr int TILE = ROWS * CONV_COLS;   // words of one source
     // two work-groups per compute unit, four waves per SIMD; N = 2^17, with twice the values per lane and sources of twice the
-    // size, one of three waves per SIMD (at four, 31 registers go to scratch memory)
-    static constexpr int WAVES = LOGN == 16 ? 8 : 12, BOUND = LOGN == 16 ? 4 : 3;
-    // ModDown, whose inverse column pass is on the integer path as a rule: two waves per SIMD at N = 2^17
-    static constexpr int DOWN_WAVES = 8, DOWN_BOUND = LOGN == 16 ? 4 : 2;
+    // size, one of three waves per SIMD (at four, 31 registers go to scratch memory), as with more than five sources at N = 2^16; ModDown, whose
+    // inverse column pass is on the integer path as a rule, two waves per SIMD at N = 2^17
+    static constexpr bool WIDE = SOURCES > 5;
+    static constexpr int WAVES = LOGN == 16 && !WIDE ? 8 : 12, BOUND = LOGN == 16 && !WIDE ? 4 : 3;
+    static constexpr int DOWN_WAVES = WIDE ? 12 : 8, DOWN_BOUND = WIDE ? 3 : LOGN == 16 ? 4 : 2;
 };
 // A lane's place: in the strided pattern it holds rows (lane >> 2) + 16 k of column lane & 3, in the consecutive one rows
 // 16 (lane >> 2) + k.
@@ -134,6 +136,20 @@ template <int NS> __device__ __forceinline__ double conv_sum_fp(const double (&y
     const double quo = __builtin_rint(__builtin_fma(low, qinv, h * qinv));
     return __builtin_fma(-quo, q, h) + low;
 }
+// All sources of a conversion: up to five at once, more in two sums, reduced.
+template <int NS> __device__ __forceinline__ double conv_value(const ArithFp &ar, const double (&y)[NS], const double (&c)[NS])
+{
+    if constexpr (NS <= 5)
+        return conv_sum_fp(y, c, ar.q, ar.qinv);
+    else {
+        double y0[4], c0[4], y1[NS - 4], c1[NS - 4];
+#pragma unroll
+        for (int s = 0; s < 4; s++) y0[s] = y[s], c0[s] = c[s];
+#pragma unroll
+        for (int s = 4; s < NS; s++) y1[s - 4] = y[s], c1[s - 4] = c[s];
+        return ar.reduce(conv_sum_fp(y0, c0, ar.q, ar.qinv) + conv_sum_fp(y1, c1, ar.q, ar.qinv));
+    }
+}
 // The same on the integer path, 0 <= y < 2^50 - 1, rho[s] = c[s] / q: the quotient is summed in floating point (at most four off: half a
 // unit for each of four roundings, less for the errors of rho) and the remainder modulo 2^64.  The result is in (0, 8q).
 template <int NS> __device__ __forceinline__ u64 conv_sum_int(const double (&y)[NS], const u64 (&c)[NS], const double (&rho)[NS], u64 q4, u64 nq)
@@ -157,6 +173,21 @@ template <int LOGN> __device__ __forceinline__ ArithInt conv_int(const DevTables
     return ar;
 }
 
+template <int NS>
+__device__ __forceinline__ u64 conv_value(const ArithInt &ar, const double (&y)[NS], const u64 (&c)[NS], const double (&rho)[NS])
+{
+    if constexpr (NS <= 4)
+        return conv_sum_int(y, c, rho, ar.q4, ar.nq);
+    else {
+        static_assert(NS == 8, "two sums of four");
+        double y0[4], y1[4], r0[4], r1[4];
+        u64 c0[4], c1[4];
+#pragma unroll
+        for (int s = 0; s < 4; s++) y0[s] = y[s], c0[s] = c[s], r0[s] = rho[s], y1[s] = y[s + 4], c1[s] = c[s + 4], r1[s] = rho[s + 4];
+        return csub(conv_sum_int(y0, c0, r0, ar.q4, ar.nq) + conv_sum_int(y1, c1, r1, ar.q4, ar.nq), 2 * ar.q4); // below 16q < 2^64
+    }
+}
+
 // ModUp.  Operation o's scaled digits come from x + o * stride limbs, as the inverse block pass left them, and its raised
 // digits go to raised + o * stride limbs, digit j's limb a (active index) at j * (level + K) + a.
 struct ModUpArgs {
@@ -168,11 +199,11 @@ struct ModUpArgs {
 
 // grid: CONV_GROUPS * operations * beta * chunks, the column groups of an XCD adjacent (four of them share every line that is read).  A
 // work-group makes every chunks'th target of its digit, the special limbs (the longest) first; its waves take them one by one.
-template <int LOGN>
-__global__ __launch_bounds__(64 * ConvGeom<LOGN>::WAVES, ConvGeom<LOGN>::BOUND) void k_ntt_fwd_cols_modup(ModUpArgs ua, DevTables T)
+template <int LOGN, int NS>
+__global__ __launch_bounds__((64 * ConvGeom<LOGN, NS>::WAVES), (ConvGeom<LOGN, NS>::BOUND)) void k_ntt_fwd_cols_modup(ModUpArgs ua, DevTables T)
 {
-    typedef ConvGeom<LOGN> G;
-    constexpr int NS = 4, W = G::WAVES, H = G::HALVES;
+    typedef ConvGeom<LOGN, NS> G;
+    constexpr int W = G::WAVES, H = G::HALVES;
     __shared__ double src[NS * G::TILE];
     __shared__ unsigned exch[W][CONV_EXCH];
     __shared__ int next;
@@ -229,7 +260,7 @@ __global__ __launch_bounds__(64 * ConvGeom<LOGN>::WAVES, ConvGeom<LOGN>::BOUND) 
                     double y[NS];
 #pragma unroll
                     for (int s = 0; s < NS; s++) y[s] = sp[s * G::TILE + 1024 * h + 64 * k];
-                    v[h][k] = conv_sum_fp(y, c, ar.q, ar.qinv);
+                    v[h][k] = conv_value(ar, y, c);
                 }
             conv_forward<LOGN>(v, limb, col, ar, ex);
         } else {
@@ -248,7 +279,7 @@ __global__ __launch_bounds__(64 * ConvGeom<LOGN>::WAVES, ConvGeom<LOGN>::BOUND) 
                     double y[NS];
 #pragma unroll
                     for (int s = 0; s < NS; s++) y[s] = sp[s * G::TILE + 1024 * h + 64 * k];
-                    v[h][k] = conv_sum_int(y, c, rho, ar.q4, ar.nq);
+                    v[h][k] = conv_value(ar, y, c, rho);
                 }
             conv_forward<LOGN>(v, limb, col, ar, ex);
         }
@@ -277,11 +308,11 @@ __device__ __forceinline__ double conv_digit(u64 z, double r50)
 // grid: CONV_GROUPS * operations * 2 * chunks, work-groups and waves as in k_ntt_fwd_cols_modup; the digits come from the inverse column
 // pass of the special limbs.  RS: with a rescale, after the dropped limb, level - 1, has been through ModDown: the digits are
 // in u, and the dropped limb, as the inverse block pass left it in r, is one more source with P for its constant.
-template <int LOGN, bool RS>
-__global__ __launch_bounds__(64 * ConvGeom<LOGN>::DOWN_WAVES, ConvGeom<LOGN>::DOWN_BOUND) void k_ntt_fwd_cols_moddown(ModDownArgs da, DevTables T)
+template <int LOGN, bool RS, int KMAX>
+__global__ __launch_bounds__((64 * ConvGeom<LOGN, KMAX>::DOWN_WAVES), (ConvGeom<LOGN, KMAX>::DOWN_BOUND)) void k_ntt_fwd_cols_moddown(ModDownArgs da, DevTables T)
 {
-    typedef ConvGeom<LOGN> G;
-    constexpr int KMAX = 4, NS = KMAX + (RS ? 1 : 0), W = G::DOWN_WAVES, H = G::HALVES;
+    typedef ConvGeom<LOGN, KMAX> G;
+    constexpr int NS = KMAX + (RS ? 1 : 0), W = G::DOWN_WAVES, H = G::HALVES;
     __shared__ u64 src[NS * G::TILE];
     __shared__ unsigned exch[W][CONV_EXCH];
     __shared__ int next;
@@ -370,7 +401,7 @@ __global__ __launch_bounds__(64 * ConvGeom<LOGN>::DOWN_WAVES, ConvGeom<LOGN>::DO
 #pragma unroll
                 for (int s = 0; s < KMAX; s++) y[s] = conv_digit(sp[s * G::TILE + 1024 * h + 64 * k], r50);
                 if (RS) y[NS - 1] = ar.load_mid(sp[(NS - 1) * G::TILE + 1024 * h + 64 * k]);
-                v[h][k] = conv_sum_fp(y, c, ar.q, ar.qinv);
+                v[h][k] = conv_value(ar, y, c);
             }
         conv_forward<LOGN>(v, corr + ((size_t)i << LOGN), col, ar, ex);
     }

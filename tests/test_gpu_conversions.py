@@ -1,4 +1,4 @@
-"""Base conversions of the key switch at N = 2^16 and 2^17 against the oracle, bit for bit: digits of one to four limbs and a last digit
+"""Base conversions of the key switch at N = 2^16 and 2^17 against the oracle, bit for bit: digits of one to eight limbs and a last digit
 that is shorter, special primes on either arithmetic path, operations of several levels in one launch, one operation (its targets
 shared out among several work-groups) and a few, uniform residues and the largest ones."""
 import numpy as np
@@ -12,6 +12,8 @@ SETS = {
     "three16": wl.Params("three16", 16, wl.N16.q[:7], wl.N16.p[:2], 3),  # digits of 3, 3, 1
     "two16": wl.Params("two16", 16, wl.N16.q[:6], wl.N16.q[10:13], 3),  # special primes below 2^50
     "one16": wl.Params("one16", 16, wl.N16.q[:3], (wl.N16.p[0],), 3),  # digits of 1
+    "five16": wl.Params("five16", 16, wl.N16.q[:9], wl.W16.p, 2),  # digits of 5, 4; five special primes
+    "eight16": wl.Params("eight16", 16, wl.N16.q[:8], wl.N16.p + wl.N16.q[10:14], 1),  # one digit of 8, special primes of both kinds
     "four17": wl.Params("four17", 17, wl.P17.q[:6], wl.P17.p[:3], 2),  # digits of 3, 3
     "mixed17": wl.Params("mixed17", 17, wl.P17.q[:5], (wl.P17.p[0], wl.P17.q[9]), 2),  # special primes of both kinds
 }
