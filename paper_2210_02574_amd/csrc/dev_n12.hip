@@ -2,6 +2,9 @@
 #include "launch.h"
 #include "kernels_n12.h"
 
+// The conversions, but for the corrected ones, are instantiated for up to one, two, four and eight sources: a source past the real count costs its
+// product, and single calls are as long as one work-group's chain (one rotation of three primes, digits and special primes of one:
+// 30.0 us, 32.5 with four sources everywhere; two digits of two primes 47.8 -> 45.0).
 template <int PRO, int NSMAX, bool EX>
 static void launch_fwd12(he_ctx *c, hipStream_t st, double bytes, u64 *data, const LimbBatch &lb, int nb, const ConvArgs &cv,
                          const FinArgs *fin)
@@ -23,7 +26,10 @@ static void fwd12(he_ctx *c, hipStream_t st, double bytes, bool wide, u64 *data,
         if (cv.exact)
             (wide ? launch_fwd12<PRO, 8, true> : launch_fwd12<PRO, 4, true>)(c, st, bytes, data, lb, nb, cv, fin);
         else
-            (wide ? launch_fwd12<PRO, 8, false> : launch_fwd12<PRO, 4, false>)(c, st, bytes, data, lb, nb, cv, fin);
+            (wide           ? launch_fwd12<PRO, 8, false>
+             : c->alpha > 2 ? launch_fwd12<PRO, 4, false>
+             : c->alpha > 1 ? launch_fwd12<PRO, 2, false>
+                            : launch_fwd12<PRO, 1, false>)(c, st, bytes, data, lb, nb, cv, fin);
     } else
         launch_fwd12<PRO, 4, false>(c, st, bytes, data, lb, nb, cv, fin);
 }
@@ -55,8 +61,12 @@ static void launch_fin12(he_ctx *c, hipStream_t st, double bytes, bool wide, int
     } else {
         if (wide)
             KLAUNCH_T(c, st, KID_FIN12, bytes, (k_fin12<PRO, 8, false, DROP, INTS>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
-        else
+        else if (c->K > 2)
             KLAUNCH_T(c, st, KID_FIN12, bytes, (k_fin12<PRO, 4, false, DROP, INTS>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
+        else if (c->K > 1)
+            KLAUNCH_T(c, st, KID_FIN12, bytes, (k_fin12<PRO, 2, false, DROP, INTS>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
+        else
+            KLAUNCH_T(c, st, KID_FIN12, bytes, (k_fin12<PRO, 1, false, DROP, INTS>), grid, N12_THREADS, ia, fa, c->dev, oa, cv, mode);
     }
 }
 static void fin12(he_ctx *c, hipStream_t st, double bytes, bool wide, int pro, bool drop, int mode, const InnerArgs &ia,
