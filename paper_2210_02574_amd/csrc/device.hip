@@ -177,7 +177,7 @@ extern "C" int32_t he_evk_to_host(const he_evk *evk, uint64_t *h_out)
 static const char *const kKernelNames[KID_COUNT] = {
     "k_ntt_fwd_cols", "k_ntt_fwd_cols_modup", "k_ntt_fwd_cols_moddown", "k_ntt_fwd_cols_rescale", "k_ntt_fwd_cols_moddown_rescale",
     "k_ntt_fwd_blocks",
-    "k_ntt_fwd_blocks_fin", "k_ntt_inv_blocks", "k_ntt_inv_cols", "k_limbwise", "k_cmult", "k_inner_special", "k_inner_finished",
+    "k_ntt_fwd_blocks_fin", "k_ntt_inv_blocks", "k_ntt_inv_cols", "k_limbwise", "k_cmult", "k_copy_limbs", "k_inner_special", "k_inner_finished",
     "k_inner_fin", "k_ntt_fwd12", "k_ntt_fwd12_modup", "k_ntt_fwd12_rescale", "k_ntt_inv12", "k_inner12", "k_fin12"};
 
 bool prof_events(he_ctx *c, int kid, double bytes, ProfRecord &r)
@@ -558,6 +558,14 @@ extern "C" int32_t he_add_const(he_ctx *ctx, const uint64_t *d_ct, const uint64_
     return he_add_const_batch(ctx, d_ct, h_scalar, d_out, level, 1, stream);
 }
 
+// Rows of `width` limbs, src_stride and dst_stride limbs apart.
+static int32_t copy_limbs(he_ctx *c, const u64 *src, int src_stride, u64 *dst, int dst_stride, int width, int rows, hipStream_t st)
+{
+    const dim3 grid((unsigned)(c->N / 512), (unsigned)width, (unsigned)std::min(rows, 65535));
+    KLAUNCH(c, st, KID_COPY, 2.0 * rows * width * c->N * 8.0, (k_copy_limbs), grid, src, dst, src_stride, dst_stride, rows, c->logN);
+    return launch_ok(c);
+}
+
 extern "C" int32_t he_moddrop_batch(he_ctx *ctx, const uint64_t *d_ct, int32_t in_level, uint64_t *d_out,
                                     int32_t out_level, int32_t count, void *stream)
 {
@@ -565,16 +573,8 @@ extern "C" int32_t he_moddrop_batch(he_ctx *ctx, const uint64_t *d_ct, int32_t i
     if (rc != HE_OK) return rc;
     if (out_level < 1 || out_level > in_level) return HE_ELEVEL;
     if (!d_ct || !d_out || d_ct == d_out || count < 1) return HE_EINVAL;
-    const size_t N = ctx->N;
     // one row per (operation, component): the first out_level limbs of in_level
-    hipError_t e = hipMemcpy2DAsync(d_out, (size_t)out_level * N * sizeof(u64), d_ct, (size_t)in_level * N * sizeof(u64),
-                                    (size_t)out_level * N * sizeof(u64), (size_t)count * 2, hipMemcpyDeviceToDevice,
-                                    (hipStream_t)stream);
-    if (e != hipSuccess) {
-        ctx->hip_err = std::string("hipMemcpy2DAsync: ") + hipGetErrorString(e);
-        return HE_EHIP;
-    }
-    return HE_OK;
+    return copy_limbs(ctx, d_ct, in_level, d_out, out_level, out_level, count * 2, (hipStream_t)stream);
 }
 extern "C" int32_t he_moddrop(he_ctx *ctx, const uint64_t *d_ct, int32_t in_level, uint64_t *d_out, int32_t out_level,
                               void *stream)
@@ -896,9 +896,7 @@ static MultOut mult_out(const he_ctx *c, const u64 *a, const u64 *b, u64 *out, u
 static int32_t mult_copy(he_ctx *c, const MultOut &mo, u64 *out, int out_limbs, int count, hipStream_t st)
 {
     if (!mo.copy) return HE_OK;
-    const size_t row = (size_t)out_limbs * c->N * sizeof(u64);
-    HIP_TRY(c, hipMemcpy2DAsync(out, row, mo.out, (size_t)mo.stride * c->N * sizeof(u64), row, (size_t)count, hipMemcpyDeviceToDevice, st));
-    return HE_OK;
+    return copy_limbs(c, mo.out, mo.stride, out, out_limbs, out_limbs, count, st);
 }
 static InnerArgs mult_args(const he_ctx *c, const he_evk *relin, const u64 *a, const u64 *b, u64 *ws, const WsLayout &w, int level, int count,
                            bool finished)
@@ -1209,16 +1207,7 @@ extern "C" int32_t he_rotate_sum_batch(he_ctx *ctx, const he_evk *const *rots, i
         if (rc != HE_OK) return rc;
         in_tmp = !in_tmp;
     }
-    if (in_tmp) {
-        const size_t row = (size_t)2 * level * ctx->N * sizeof(u64);
-        hipError_t e = hipMemcpy2DAsync(d_ct, row, tmp, (size_t)W * ctx->N * sizeof(u64), row, (size_t)count,
-                                        hipMemcpyDeviceToDevice, st);
-        if (e != hipSuccess) {
-            ctx->hip_err = std::string("hipMemcpy2DAsync: ") + hipGetErrorString(e);
-            return HE_EHIP;
-        }
-    }
-    return HE_OK;
+    return in_tmp ? copy_limbs(ctx, tmp, W, d_ct, 2 * level, 2 * level, count, st) : HE_OK;
 }
 
 extern "C" int32_t he_rotate_sum(he_ctx *ctx, const he_evk *const *rots, int32_t count, uint64_t *d_ct, int32_t level,
@@ -1284,13 +1273,7 @@ extern "C" int32_t he_modraise(he_ctx *ctx, const uint64_t *d_ct, uint64_t *d_ou
         for (int i = 1; i < level_out; i++) l.add(c * level_out + i, i);
     if ((rc = ntt_forward(ctx, st, d_out, l, PRO_RESCALE, cv, nullptr, 2)) != HE_OK) return rc;
     // limb 0 of both components is the input itself
-    hipError_t e = hipMemcpy2DAsync(d_out, (size_t)level_out * N * sizeof(u64), d_ct, N * sizeof(u64), N * sizeof(u64), 2,
-                                    hipMemcpyDeviceToDevice, st);
-    if (e != hipSuccess) {
-        ctx->hip_err = std::string("hipMemcpy2DAsync: ") + hipGetErrorString(e);
-        return HE_EHIP;
-    }
-    return HE_OK;
+    return copy_limbs(ctx, d_ct, 1, d_out, level_out, 1, 2, st);
 }
 
 extern "C" int32_t he_rescale(he_ctx *ctx, const uint64_t *d_ct, uint64_t *d_out, int32_t level, void *d_ws,

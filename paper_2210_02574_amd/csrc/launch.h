@@ -13,7 +13,7 @@
 enum KernelId {
     KID_FWD_COLS, KID_FWD_COLS_MODUP, KID_FWD_COLS_MODDOWN, KID_FWD_COLS_RESCALE, KID_FWD_COLS_MODDOWN_RS, KID_FWD_BLOCKS,
     KID_FWD_BLOCKS_FIN,
-    KID_INV_BLOCKS, KID_INV_COLS, KID_LIMBWISE, KID_CMULT, KID_INNER_SPECIAL, KID_INNER_FINISHED, KID_INNER_FIN,
+    KID_INV_BLOCKS, KID_INV_COLS, KID_LIMBWISE, KID_CMULT, KID_COPY, KID_INNER_SPECIAL, KID_INNER_FINISHED, KID_INNER_FIN,
     KID_FWD12, KID_FWD12_MODUP, KID_FWD12_RESCALE, KID_INV12, KID_INNER12, KID_FIN12, // N = 2^12
     KID_COUNT
 };
