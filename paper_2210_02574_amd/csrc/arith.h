@@ -119,8 +119,9 @@ __device__ __forceinline__ u64 fp_canon(double v, double q, double qinv)
 // same stages backwards, and with LAST also folds the factors n0 = 1/N (times an optional extra
 // constant) and n1 = n0 * twiddle into stage 0.
 //
-// ArithFp ranges: values are signed; a forward phase entered with |v| <= 1q (canonical input) or
-// after reduce_first (|v| <= q/2) ends below 4.7q; an inverse phase reduces the sum path at its
+// ArithFp ranges: values are signed; a stage takes |v| to at most 1.1875 |v| + q/2.  A forward phase of four stages entered with |v| <= 1q
+// (canonical input) ends below 4.7q; with reduce_first the first half, which its first stage does not multiply, is reduced, and from |v| <= 7.2q it
+// ends below 5.8q (reducing both halves took 24 instructions more of about 950 for a target of ModUp); an inverse phase reduces the sum path at its
 // second and fourth stage and never exceeds 7.4q.  Everything stays below 8q < 2^53.
 
 // index of twiddle c (stage sp's at c = 2^sp - 1 .. 2^(sp+1) - 2) of the 16-element step that starts at stage s_base in group G
@@ -145,9 +146,9 @@ struct ArithFp {
     // tw(c): twiddle c of the 15 this step uses, stage sp's at c = 2^sp - 1 .. 2^(sp+1) - 2
     template <class F> __device__ __forceinline__ void fwd16_with(V (&a)[16], bool reduce_first, F tw) const
     {
-        if (reduce_first) {
+        if (reduce_first) { // the values that are multiplied may be any exact integer
 #pragma unroll
-            for (int k = 0; k < 16; k++) a[k] = reduce(a[k]);
+            for (int k = 0; k < 8; k++) a[k] = reduce(a[k]);
         }
 #pragma unroll
         for (int sp = 0; sp < 4; sp++) {

@@ -430,7 +430,7 @@ template <class A> __device__ __forceinline__ void mid_pairs8(const A &ar, typen
 }
 // Block pass of the eight values dv of this thread (pattern of step 1); the result is left in the wave's LDS, element e
 // of block b at tile_at(b, e), for the caller to read after a block_sync.  tw(m, i): twiddle of local stage m, group i of the block.
-// Ranges (in units of q): floating point: the column pass leaves up to 3.7; reduced, step 1 ends below 2.7 and step 2 below 6.3;
+// Ranges (in units of q): floating point: the column pass leaves up to 5.8; reduced, step 1 ends below 2.7 and step 2 below 6.3;
 // reduced again, step 3 ends below 1.9, small enough for exact products.  Integer: in [0, 8) throughout.
 template <class A, class F> __device__ __forceinline__ void block_pass8(const A &ar, typename A::V (&dv)[8], const BlockLane &b, F tw)
 {
