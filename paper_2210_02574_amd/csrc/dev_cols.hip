@@ -50,9 +50,14 @@ static void inv_cols(he_ctx *c, hipStream_t st, double bytes, int scale, u64 *ds
                      const ConvArgs &cv)
 {
     switch (scale) {
-    case SCALE_NONE: KLAUNCH(c, st, KID_INV_COLS, bytes, (INV_KERNEL<SCALE_NONE>), 16 * nb, dst, c->dev, lb, cv); break;
-    case SCALE_MODUP: KLAUNCH(c, st, KID_INV_COLS, bytes, (INV_KERNEL<SCALE_MODUP>), 16 * nb, dst, c->dev, lb, cv); break;
-    default: KLAUNCH(c, st, KID_INV_COLS, bytes, (INV_KERNEL<SCALE_MODDOWN>), 16 * nb, dst, c->dev, lb, cv); break;
+    case SCALE_NONE:
+        if (nb * c->N * sizeof(u64) <= INV_CACHED)
+            KLAUNCH(c, st, KID_INV_COLS, bytes, (INV_KERNEL<SCALE_NONE, true>), 16 * nb, dst, c->dev, lb, cv);
+        else
+            KLAUNCH(c, st, KID_INV_COLS, bytes, (INV_KERNEL<SCALE_NONE, false>), 16 * nb, dst, c->dev, lb, cv);
+        break;
+    case SCALE_MODUP: KLAUNCH(c, st, KID_INV_COLS, bytes, (INV_KERNEL<SCALE_MODUP, false>), 16 * nb, dst, c->dev, lb, cv); break;
+    default: KLAUNCH(c, st, KID_INV_COLS, bytes, (INV_KERNEL<SCALE_MODDOWN, false>), 16 * nb, dst, c->dev, lb, cv); break;
     }
 }
 void PASTE3(dev_launch_cols, HE_LOGN, HE_PRO)(DevLaunch &t) { t.inv_cols = inv_cols; }

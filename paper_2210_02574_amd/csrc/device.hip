@@ -1,6 +1,6 @@
 // Device-side entry points of the RNS-CKKS library: table upload, kernel launch sequences of
 // NTT, Mult (tensor product + relinearisation), Rotate (hybrid key switching), rescale and
-// rotate-and-sum.  The kernels are in kernels_ntt.h, kernels_ks.h and kernels_elem.h.
+// rotate-and-sum.  The kernels are in kernels_ntt.h, kernels_conv.h, kernels_ks.h, kernels_n12.h and kernels_elem.h.
 //
 // Key switch of a polynomial d (NTT domain, `level` limbs) with key evk, Galois element g:
 //   1. inverse NTT of d, its column pass also multiplying limb i by (D/q_i)^-1      -> y  (ws.x)
@@ -12,6 +12,8 @@
 //      y_k (P/p_k mod q_i) over centred digits y_k                                     -> r
 //   6. inner product on the ciphertext limbs (the digit's own limbs straight from d), block pass of r and
 //      out = (u - r) P^-1 + addend, in one kernel                                      -> out
+// N = 2^16 and 2^17: the inverse column passes of steps 1 and 4 are part of the kernels of steps 2 and 5 (kernels_conv.h) where conv_pays() says
+// so, five launches in all; the coefficients then stay in LDS.
 // Hoisted rotations share steps 1-2.
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>

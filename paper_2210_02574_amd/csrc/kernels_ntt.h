@@ -2,13 +2,13 @@
 //
 // Forward transform = decimation in time with the powers of psi in bit-reversed order; stage s
 // (s = 0 .. logN-1) pairs elements N/2^(s+1) apart and uses twiddle index 2^s + (j >> (logN-s)).
-// Each thread keeps 16 elements in registers and runs four stages on them (a radix-16 step);
-// between steps the 256-thread work-group exchanges data through LDS.  A limb of N = 2^16 takes
-// two kernels: the column pass (stages 0-7 on 16 columns x 256 rows, row stride 256 elements,
-// 128-byte global segments) and the block pass (stages 8-15 on 16 contiguous blocks of 256).
+// A limb of N = 2^16 takes two kernels: the column pass (stages 0-7 on 16 columns x 256 rows, row stride 256 elements,
+// 128-byte global segments; 16 elements per thread, four stages on them at a time, a radix-16 step, and one exchange through LDS between the
+// 256 threads) and the block pass (stages 8-15 on contiguous blocks of 256, eight elements per lane, two blocks to a wave).
 // N = 2^17 keeps the two kernels: its column pass runs nine stages on 512 rows (32 elements per thread).
-// N = 2^12 has kernels of its own (kernels_n12.h).
-// The inverse runs the block pass first and the column pass last.
+// N = 2^12 has kernels of its own (kernels_n12.h).  The inverse runs the block pass first and the column pass last.
+// The key switch's base conversions have column passes of their own (kernels_conv.h); the forms here serve what those leave out: the corrected
+// conversions, primes of 2^50 and above among the sources, launches with few targets to a source.
 //
 // Fusions, all bit-identical to the unfused steps:
 //  * the forward column pass can build its input on the fly: ModUp (sum over the digit's limbs of
@@ -16,7 +16,8 @@
 //    centred residue of a dropped limb (rescale);
 //  * the inverse column pass can fold (D/q_i)^-1 or (P/p_k)^-1 into its 1/N scaling, so it emits
 //    the y values those sums need;
-//  * the forward block pass can finish a rescale or the ModDown of one limb: out = (u - ntt) * const;
+//  * the forward block pass can finish a rescale, out = (u - ntt) * const, or the ModDown of the limb that a rescale drops, which goes
+//    through its inverse block pass at once;
 //  * ModDown followed by rescale takes one transform per limb instead of two: with t the centred dropped
 //    limb of the ModDown result, NTT(r) P^-1 + NTT(t) = NTT(r + P t) P^-1, so the column pass transforms
 //    r + P t and the inner product finishes out = (u - ntt) (P q_l)^-1.
@@ -388,8 +389,7 @@ __device__ __forceinline__ unsigned col_at(unsigned r, unsigned c) { return (r >
 //
 // Bound by memory in large launches, by the chain of one wave in small ones.  With 16 elements per lane, 16 lanes a block, two steps of four stages
 // and one exchange, the kernels took 79 to 118 registers and four waves per SIMD; now 59 to 64 (with an epilogue 85 and 100) and eight.  Transforms of
-// 64 limbs at N = 2^16 33.0 -> 30.6 us, of 34 at N = 2^17 41.5 -> 40.2, of 256 109 -> 104 (with plain loads and stores, whose lines the other pass
-// finds in the last-level cache, in place of nontemporal ones; both passes).
+// 64 limbs at N = 2^16 34.0 -> 30.8 us, of 256 103 -> 101, of 34 at N = 2^17 40.5 -> 39.8.
 #define WAVE_BLOCKS 2
 #define BLK_THREADS 256
 #define BLK_PER_WG (BLK_THREADS / 64 * WAVE_BLOCKS)
@@ -529,7 +529,7 @@ __device__ __forceinline__ void fwd_blocks_body(u64 *__restrict__ limb, const A 
         mid_pairs8(ar, a, limb + b0 * 256, b);
     else {
 #pragma unroll
-        for (int k = 0; k < 8; k++) a[k] = ar.load_mid(limb[bg * 256 + b.t + 32 * k]);
+        for (int k = 0; k < 8; k++) a[k] = ar.load_mid(__builtin_nontemporal_load(limb + bg * 256 + b.t + 32 * k)); // read once: the column pass wrote it
     }
     if (EPI != EPI_STORE) {
 #pragma unroll
@@ -542,7 +542,7 @@ __device__ __forceinline__ void fwd_blocks_body(u64 *__restrict__ limb, const A 
         u64 *w = wlds + wave_pair_at(i);
         const u64x2 v = {ar.store_final(ar.load_mid(w[0])), ar.store_final(ar.load_mid(w[1]))};
         if (EPI == EPI_STORE)
-            *(u64x2u *)(limb + pos + 128 * i) = v;
+            __builtin_nontemporal_store((u64x2u)v, (u64x2u *)(limb + pos + 128 * i));
         else {
             const u64x2 res = fin_value<A::IS_FP>(fa, T, slot, v, uv[i]);
             if (EPI == EPI_FIN)
@@ -635,7 +635,7 @@ __device__ __forceinline__ void cols_inputs(typename A::V (&a)[16], const u64 *_
 #pragma unroll
     for (int k = 0; k < 16; k++) {
         const unsigned pos = (rl + 16 * k + 256 * h) * 256 + col0 + c;
-        a[k] = PRO == PRO_LOAD ? ar.load(limb[pos]) : conv_get<PRO, SPLIT, TINT, EX>(S, ar, m, pos);
+        a[k] = PRO == PRO_LOAD ? ar.load(__builtin_nontemporal_load(limb + pos)) : conv_get<PRO, SPLIT, TINT, EX>(S, ar, m, pos);
     }
 }
 // second phase of the forward column pass for rows 16 g .. 16 g + 15, held in LDS as group gl.  With a prologue the
@@ -699,7 +699,11 @@ __device__ __forceinline__ void fwd_cols_body(u64 *__restrict__ limb, unsigned c
     }
 }
 
-template <int LOGN, class A>
+// CACHED: a plain transform of at most INV_CACHED bytes, whose values the block pass has left in the last-level cache; a plain load keeps them
+// there for the stores.  Larger launches stream through it (64 limbs of N = 2^16 32.8 us with plain loads, 34.0 with nontemporal ones, 150 66.2 and
+// 64.8, 256 115 and 106; 34 of N = 2^17 40.3 and 42.0, 80 78.7 and 77.2).
+#define INV_CACHED (64ull << 20)
+template <int LOGN, bool CACHED, class A>
 __device__ __forceinline__ void inv_cols_body(u64 *__restrict__ limb, unsigned col0, const A &ar, u64 *lds)
 {
     constexpr int H = ColsGeom<LOGN>::HALVES;
@@ -717,7 +721,7 @@ __device__ __forceinline__ void inv_cols_body(u64 *__restrict__ limb, unsigned c
 #pragma unroll
         for (int k = 0; k < 16; k++) {
             const u64 *src = limb + (16 * (rl + 16 * h) + k) * 256 + col0 + c;
-            v[k] = ar.load_mid(*src); // the block pass wrote it
+            v[k] = ar.load_mid(CACHED ? *src : __builtin_nontemporal_load(src)); // the block pass wrote it
         }
     };
     const auto half = [&](V (&v)[16], int h) __attribute__((always_inline)) {
@@ -879,7 +883,7 @@ __device__ __forceinline__ void scale_consts(int scale, const ConvArgs &cv, cons
     }
 }
 
-template <int LOGN, int SCALE>
+template <int LOGN, int SCALE, bool CACHED>
 __device__ __forceinline__ void inv_cols_kernel(u64 *__restrict__ data, const DevTables &T, const LimbBatch &lb,
                                                 const ConvArgs &cv)
 {
@@ -891,17 +895,17 @@ __device__ __forceinline__ void inv_cols_kernel(u64 *__restrict__ data, const De
     double cd;
     scale_consts(SCALE, cv, T, mi, lb.slot[b], ci, cd);
     if (T.mod[mi].qd != 0.0)
-        inv_cols_body<LOGN>(limb, tile * 16, make_fp(T, mi, LOGN, cd), lds);
+        inv_cols_body<LOGN, CACHED>(limb, tile * 16, make_fp(T, mi, LOGN, cd), lds);
     else
-        inv_cols_body<LOGN>(limb, tile * 16, make_int(T, mi, LOGN, ci), lds);
+        inv_cols_body<LOGN, CACHED>(limb, tile * 16, make_int(T, mi, LOGN, ci), lds);
 }
-template <int SCALE>
+template <int SCALE, bool CACHED>
 __global__ __launch_bounds__(256) void k_ntt_inv_cols16(u64 *__restrict__ data, DevTables T, LimbBatch lb, ConvArgs cv)
 {
-    inv_cols_kernel<16, SCALE>(data, T, lb, cv);
+    inv_cols_kernel<16, SCALE, CACHED>(data, T, lb, cv);
 }
-template <int SCALE>
+template <int SCALE, bool CACHED>
 __global__ __launch_bounds__(256, 3) void k_ntt_inv_cols17(u64 *__restrict__ data, DevTables T, LimbBatch lb, ConvArgs cv)
 {
-    inv_cols_kernel<17, SCALE>(data, T, lb, cv);
+    inv_cols_kernel<17, SCALE, CACHED>(data, T, lb, cv);
 }
