@@ -9,7 +9,7 @@
 // Single calls are bound neither by memory nor by instructions: a launch is a chain of dependent steps on few
 // work-groups, so what counts is the number of launches and the length of the chain in each.  With two launches per
 // transform (column pass, block pass) and the digits finished inside the inner product, one rotation (three primes, one
-// special prime) took seven launches of 4 to 10 us, 46 us in all; it takes 31 now, and eight
+// special prime) took seven launches of 4 to 10 us, 46 us in all; it takes 28 now, and eight
 // transforms 7.3 to 8.4 us, the host's time for one call, instead of 11.5.  The chain is kept short by fetching a step's
 // twiddles before the step ahead of it is worked on, by giving every component that is transformed a work-group of its own, and by short
 // code: a launch runs it once, and with 256 threads of 16 elements, twice the instructions, it took 37 us (the

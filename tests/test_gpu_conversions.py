@@ -86,3 +86,16 @@ def test_buffers_that_start_at_an_odd_word(params, oracle_mod):
     ct = wl.uniform_ct(6, p, 3)
     out = torch.zeros(2 * 2 * p.N + 1, dtype=torch.int64, device="cuda:0")[1:].view(2, 2, p.N)
     assert np.array_equal(he.to_host(he.rescale(odd(ct), out=out)), o.rescale(ct))
+
+
+def test_more_digits_than_unreduced_sums_hold(oracle_mod):
+    """29 digits: the special limb's 128-bit sums of values below 8q are folded on the way (28 and fewer fit)."""
+    import paper_2210_02574_amd as pkg
+
+    p = wl.Params("many16", 16, wl.P17.q[:29], (wl.P17.p[0],), 29)
+    he, o = pkg.HE.from_params(p, device=0), oracle_mod.Oracle(p.logN, p.q, p.p, p.dnum)
+    evk = wl.uniform_evk(12, p)
+    key = he.evk_from_host(evk, he.galois_element(5))
+    for level in (28, 29):
+        ct = wl.uniform_ct(40 + level, p, level)
+        assert np.array_equal(he.to_host(he.hrot(key, he.to_device(ct))), o.hrot(ct, evk, 5))
