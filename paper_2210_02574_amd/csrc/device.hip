@@ -638,31 +638,48 @@ static bool special_finished(const he_ctx *c, int level, int first, int count, b
 // the modulus index from which on ks_raise finishes raised limbs
 static int finish_from(const he_ctx *c, int level, int first, bool finished) { return !finished ? c->M : first < level ? first : c->L; }
 
-// The conversion kernels with the inverse column pass ahead of them make `targets` limbs per unit (a digit, or a component's special limbs).
-// Each work-group waits for the inverse pass of its sources, half of its waves without work, so it has to have some targets to
-// make, unless all work-groups of the launch are resident at once and what counts is that there is one launch less.  N = 2^16, two work-groups per
-// compute unit: the dropped limb of 16 products 90 us, 68 with the passes apart, 8 rotations at level 4 46 and 52; N = 2^17, one per compute
-// unit: 4 rotations at level 4 65 and 58, at level 6 the same, 4 products at level 6 49 and 51; more than four sources, one per compute unit: 16
-// rotations at level 6 429 us as a call, 366 with the passes apart, at level 12 665 and 714.
-static bool conv_pays(const he_ctx *c, int sources, int units, int targets)
+// What a launch of conversions has to do: units (a digit, or a component's special limbs), their source limbs and the limbs made of them, over
+// operations that may be at levels of their own.
+struct ConvWork {
+    int units = 0, sources = 0, targets = 0;
+};
+enum ConvKind { CONV_UP, CONV_DOWN, CONV_DOWN_RS };
+// Whether a conversion goes through the kernels with the inverse column pass ahead of it (kernels_conv.h) or through passes of their own.  A work-group
+// of those kernels waits for the inverse pass of its sources, the waves that have none without work, so its unit has to have some targets to make:
+// the more, the fewer sources each of them reads.  Where all work-groups are resident at once what counts is that there is one launch less.  With one
+// work-group per compute unit, a last round that is nearly empty counts against it too.  Gain of the call as a whole, in per cent, N = 2^16 unless stated:
+//   digits of one limb, 16 to 64 of them, 4 targets each: -5 to 0, 6: +1 to +2, 12: +6 to +11; of two, 4: -3 to +2, 6: +2 to +4; of three,
+//   4: -1 to +4; of four, 4: 0 to +5, 24: +9 to +14; of five and more, 5: -2 to +1, 8: 0 to +5; N = 2^17, four limbs, 8: -3, 10: +1 to +2 (12 units),
+//   -3 to -4 (6, a round and a half), 30: +5 to +8; two limbs, 8: -3 to -8, 12: -1 to +2
+//   corrections of one special limb, 32 units, 6 targets: -3, 8: -1 to 0, 12: +1 to +2; of two, 4: -1, 8: +2; of three, 3: -1, 4: 0; of four,
+//   2: +1, 24: +3; of five, 16 units, 8: -1, 10: +2, 32 units, 9: -3, 11: +2; N = 2^17, four, 8 units, 6: -1, 8: +2, 16 units, 12: 0, 16: 0;
+//   two, 8 to 16 units, 8: -1 to -3, 12: -1
+//   with a rescale, 32 units, 3 targets -1 to -2 (one to four special limbs), 5: 0, 7: +1 to +4; N = 2^17, 8 units, 5: -1 to +1, 7: +2 to +4.
+//   Where digits or special primes are more than four, its pass apart is the one for eight sources: with one target +7, with more +20 to +85.
+static bool conv_pays(const he_ctx *c, ConvKind kind, const ConvWork &w)
 {
-    const bool two = c->logN == 16 && sources <= 4; // work-groups per compute unit
-    return CONV_GROUPS * units <= (two ? 512 : 256) || targets >= (two ? 4 : 8);
+    const bool two = c->logN == 16 && (kind == CONV_UP ? c->alpha : c->K) <= 4; // work-groups per compute unit
+    const int units = std::max(w.units, 1), groups = CONV_GROUPS * units;
+    if (groups <= (two ? 512 : 256)) return true;
+    if (kind == CONV_DOWN_RS && std::max(c->alpha, c->K) > 4) return true;
+    const int s = (w.sources + units - 1) / units; // per unit
+    const int up = c->logN == 17 ? 13 - s : two ? std::max(4, 7 - s) : 6;
+    const int down = c->logN == 17 ? (s >= 3 && units < 16 ? 8 : 14) : two ? 10 - 2 * s : 12 + std::min(units, 32) / 8 - s;
+    const int rs = c->logN == 17 ? 7 : 5;
+    const int need = kind == CONV_UP ? up : kind == CONV_DOWN ? down : rs;
+    const int rounds = two ? units : (groups + 255) / 256 * (256 / CONV_GROUPS); // in units: of whole rounds
+    return w.targets >= need * rounds;
 }
 // ModUp so (k_ntt_fwd_cols_modup): N = 2^16 and 2^17, digits whose limbs are all on the floating-point path, without the correction of the
 // overshoot.
-static bool modup_fused(const he_ctx *c, int level, int count)
+static bool modup_fused(const he_ctx *c, const ConvWork &w) { return dev_launch(c).modup && !c->up_split && !c->exact_conv && conv_pays(c, CONV_UP, w); }
+// The same for ModDown's corrections of both components of `count` operations, `limbs` of each component in all (k_ntt_fwd_cols_moddown): ciphertext limbs
+// on the floating-point path.
+static bool moddown_fused(const he_ctx *c, int limbs, int count, bool rs)
 {
-    return dev_launch(c).modup && !c->up_split && !c->exact_conv &&
-           conv_pays(c, c->alpha, (level + c->alpha - 1) / c->alpha * count, std::max(level - c->alpha, 0) + c->K);
-}
-// The same for ModDown's corrections of `targets` limbs (k_ntt_fwd_cols_moddown): ciphertext limbs on the floating-point path.  With a rescale and more
-// than four special primes from two targets on: the pass of its own splits every digit at bit 31 (16 products of wide digits at level 3 388 us as a
-// call, 468 with it).
-static bool moddown_fused(const he_ctx *c, int targets, int count, bool rs)
-{
-    return dev_launch(c).moddown && !c->up_split && (!c->dn_split || c->dn_fold) && !c->exact_conv &&
-           (conv_pays(c, c->K, 2 * count, targets) || (rs && c->K > 4 && targets > 1));
+    ConvWork w;
+    w.units = 2 * count, w.sources = w.units * c->K, w.targets = 2 * limbs;
+    return dev_launch(c).moddown && !c->up_split && (!c->dn_split || c->dn_fold) && !c->exact_conv && conv_pays(c, rs ? CONV_DOWN_RS : CONV_DOWN, w);
 }
 // The targets of a digit are shared out among so many work-groups that a launch of few operations puts one on every compute unit, and no
 // more, for each repeats the inverse column pass (N = 2^16: one rotation at level 13 93.5 us, with two on every unit 96.4; one product at level 6
@@ -681,15 +698,15 @@ static int32_t ks_raise(he_ctx *c, const u64 *d_ntt, F from, u64 *ws, const WsLa
     const int K = c->K, Ma = level + K, W = (int)w.total;
     const auto level_of = [&](int o) { return levels ? (int)levels[o] : level; };
     LimbList l;
-    int src_limbs = 0, targets = 0;
+    ConvWork cw;
     for (int o = 0; o < count; o++) {
         const int lo = level_of(o), beta = (lo + c->alpha - 1) / c->alpha;
         for (int i = 0; i < lo; i++) l.add(o * W + i, from(o) + i, i);
-        src_limbs += lo, targets += beta * (lo + K) - lo;
+        cw.units += beta, cw.sources += lo, cw.targets += beta * (lo + K) - lo;
     }
     ConvArgs cv = conv_args(c, ws + w.x * N, level, W, W);
     for (int o = 0; levels && o < count; o++) cv.op_level[o] = (uint8_t)levels[o];
-    const bool fused = modup_fused(c, level, count);
+    const bool fused = modup_fused(c, cw);
     // limbs that go through a column pass or a block pass of their own
     LimbList r;
     for (int o = 0; o < count; o++) {
@@ -706,7 +723,7 @@ static int32_t ks_raise(he_ctx *c, const u64 *d_ntt, F from, u64 *ws, const WsLa
     int32_t rc;
     if (!fused) {
         if ((rc = ntt_inverse(c, st, d_ntt, ws + w.x * N, l, SCALE_MODUP, cv, false, d_ntt2)) != HE_OK) return rc;
-        return ntt_forward(c, st, ws + w.raised * N, r, PRO_MODUP, cv, nullptr, src_limbs, BLOCKS_SOME, finish_at);
+        return ntt_forward(c, st, ws + w.raised * N, r, PRO_MODUP, cv, nullptr, cw.sources, BLOCKS_SOME, finish_at);
     }
     const double N8 = (double)N * 8.0;
     const DevLaunch &dl = dev_launch(c);
@@ -717,7 +734,7 @@ static int32_t ks_raise(he_ctx *c, const u64 *d_ntt, F from, u64 *ws, const WsLa
     ua.level = level, ua.L = c->L, ua.K = K, ua.alpha = c->alpha, ua.beta = (level + c->alpha - 1) / c->alpha, ua.stride = W;
     ua.chunks = conv_chunks(ua.beta * count, Ma - c->alpha);
     memcpy(ua.op_level, cv.op_level, sizeof(ua.op_level));
-    dl.modup(c, st, (double)(src_limbs + targets) * N8, count, ua);
+    dl.modup(c, st, (double)(cw.sources + cw.targets) * N8, count, ua);
     if ((rc = launch_ok(c)) != HE_OK) return rc;
     return for_batches(c, r, [&](const LimbBatch &lb, int nb) { dl.fwd_blocks(c, st, 2.0 * nb * N8, EPI_STORE, true, ws + w.raised * N, lb, nb, kNoFin); });
 }
@@ -856,7 +873,9 @@ static int32_t ks_apply(he_ctx *c, const InnerArgs &ia, const OpArgs *oa, u64 *w
                         hipStream_t st)
 {
     const int W = (int)w.total;
-    const bool fused = moddown_fused(c, fa.nl, ia.count, false);
+    int limbs = 0;
+    for (int o = 0; o < ia.count; o++) limbs += std::min(oa && oa->level[o] ? (int)oa->level[o] : ia.level, fa.nl);
+    const bool fused = moddown_fused(c, limbs, ia.count, false);
     int32_t rc = ks_special(c, ia, oa, w, !fused, st);
     if (rc != HE_OK) return rc;
     const ConvArgs cv = conv_args(c, ws + w.u * c->N, ia.level, W, W);
@@ -963,7 +982,7 @@ extern "C" int32_t he_hmult_relin_rescale_batch(he_ctx *ctx, const he_evk *relin
         return rc;
     InnerArgs ia = mult_args(ctx, relin, d_a, d_b, ws, w, level, count, finished);
     ia.first = first;
-    const bool fused_drop = moddown_fused(ctx, 1, count, false), fused = moddown_fused(ctx, level - 1, count, true);
+    const bool fused_drop = moddown_fused(ctx, count, count, false), fused = moddown_fused(ctx, (level - 1) * count, count, true);
     if ((rc = ks_special(ctx, ia, nullptr, w, !fused_drop, st)) != HE_OK) return rc;
     u64 *rbuf = ws + w.r * N;
     ConvArgs cv = conv_args(ctx, ws + w.u * N, level, W, W);

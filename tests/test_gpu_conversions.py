@@ -99,3 +99,43 @@ def test_more_digits_than_unreduced_sums_hold(oracle_mod):
     for level in (28, 29):
         ct = wl.uniform_ct(40 + level, p, level)
         assert np.array_equal(he.to_host(he.hrot(key, he.to_device(ct))), o.hrot(ct, evk, 5))
+
+
+# name -> (parameters, levels of the operations of one call, whether the inverse column passes run apart from the conversions)
+_ONES16 = wl.Params("ones16", 16, wl.N16.q[:5], wl.N16.p[:1], 5)  # digits of 1, one special prime
+FORMS = {
+    "few targets on average": (wl.W16, [12] + [2] * 15, True),  # by its largest level it would have many
+    "many targets on average": (wl.W16, [12] * 8 + [2], False),
+    "wide digits": (wl.W16, [5] * 8, True),
+    "one source": (_ONES16, [5] * 16, True),
+    "one source, one round": (_ONES16, [1] * 4, False),
+}
+
+
+@pytest.mark.parametrize("name", FORMS)
+def test_batches_in_either_form(name, oracle_mod):
+    import torch
+
+    import paper_2210_02574_amd as pkg
+
+    p, levels, apart = FORMS[name]
+    he, o, evk = pkg.HE.from_params(p, device=0), oracle_mod.Oracle(p.logN, p.q, p.p, p.dnum), wl.uniform_evk(13, p)
+    key, relin = he.evk_from_host(evk, he.galois_element(3)), he.evk_from_host(evk, 1)
+    cts = {lv: [wl.uniform_ct(70 + 2 * lv + k, p, lv) for k in range(2)] for lv in set(levels)}
+    want = {lv: [o.hrot(ct, evk, 3) for ct in pair] for lv, pair in cts.items()}
+    packed = he.to_device(np.concatenate([cts[lv][i % 2].reshape(-1, p.N) for i, lv in enumerate(levels)]))
+    he.profile_start()
+    got = he.to_host(he.hrot_batch_levels([key] * len(levels), levels, packed))
+    assert ("k_ntt_inv_cols" in he.profile_stop()) == apart
+    assert np.array_equal(got, np.concatenate([want[lv][i % 2].reshape(-1, p.N) for i, lv in enumerate(levels)]))
+    lv = levels[0]
+    if set(levels) != {lv} or lv < 2:
+        return
+    a = np.stack([cts[lv][i % 2] for i in range(len(levels))])
+    da, db = he.to_device(a), torch.roll(he.to_device(a), 1, 0).contiguous()
+    assert np.array_equal(he.to_host(he.hrot_batch(key, da)), np.stack([want[lv][i % 2] for i in range(len(levels))]))
+    prod = o.hmult_relin(cts[lv][0], cts[lv][1], evk)
+    got = he.to_host(he.hmult_relin_batch(relin, da, db))
+    assert all(np.array_equal(g, prod) for g in got)
+    got, resc = he.to_host(he.hmult_relin_rescale_batch(relin, da, db)), o.rescale(prod)
+    assert all(np.array_equal(g, resc) for g in got)
