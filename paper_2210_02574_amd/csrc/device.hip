@@ -707,22 +707,25 @@ static int32_t ks_raise(he_ctx *c, const u64 *d_ntt, F from, u64 *ws, const WsLa
     ConvArgs cv = conv_args(c, ws + w.x * N, level, W, W);
     for (int o = 0; levels && o < count; o++) cv.op_level[o] = (uint8_t)levels[o];
     const bool fused = modup_fused(c, cw);
-    // limbs that go through a column pass or a block pass of their own
+    // limbs that go through a column pass or a block pass of their own; listed once the first launches are on their way
     LimbList r;
-    for (int o = 0; o < count; o++) {
-        const int lo = level_of(o), beta = (lo + c->alpha - 1) / c->alpha;
-        for (int j = 0; j < beta; j++) {
-            const int dlo = j * c->alpha, dhi = std::min(dlo + c->alpha, lo);
-            for (int a = fused ? std::min(finish_at, level) : 0; a < Ma; a++) {
-                const int mi = active_mod(a, level, c->L);
-                if ((a >= dlo && a < dhi) || (a >= lo && a < level) || (fused && mi < finish_at)) continue;
-                r.add(o * W + j * Ma + a, mi);
+    const auto list_raised = [&] {
+        for (int o = 0; o < count; o++) {
+            const int lo = level_of(o), beta = (lo + c->alpha - 1) / c->alpha;
+            for (int j = 0; j < beta; j++) {
+                const int dlo = j * c->alpha, dhi = std::min(dlo + c->alpha, lo);
+                for (int a = fused ? std::min(finish_at, level) : 0; a < Ma; a++) {
+                    const int mi = active_mod(a, level, c->L);
+                    if ((a >= dlo && a < dhi) || (a >= lo && a < level) || (fused && mi < finish_at)) continue;
+                    r.add(o * W + j * Ma + a, mi);
+                }
             }
         }
-    }
+    };
     int32_t rc;
     if (!fused) {
         if ((rc = ntt_inverse(c, st, d_ntt, ws + w.x * N, l, SCALE_MODUP, cv, false, d_ntt2)) != HE_OK) return rc;
+        list_raised();
         return ntt_forward(c, st, ws + w.raised * N, r, PRO_MODUP, cv, nullptr, cw.sources, BLOCKS_SOME, finish_at);
     }
     const double N8 = (double)N * 8.0;
@@ -736,6 +739,7 @@ static int32_t ks_raise(he_ctx *c, const u64 *d_ntt, F from, u64 *ws, const WsLa
     memcpy(ua.op_level, cv.op_level, sizeof(ua.op_level));
     dl.modup(c, st, (double)(cw.sources + cw.targets) * N8, count, ua);
     if ((rc = launch_ok(c)) != HE_OK) return rc;
+    list_raised();
     return for_batches(c, r, [&](const LimbBatch &lb, int nb) { dl.fwd_blocks(c, st, 2.0 * nb * N8, EPI_STORE, true, ws + w.raised * N, lb, nb, kNoFin); });
 }
 
