@@ -19,6 +19,7 @@ SOURCES = (
     # the corrected base conversions: kernels of their own
     + [("dev_cols.hip", ["-DHE_LOGN=%d" % n, "-DHE_PRO=%d" % p, "-DHE_EX=1"], "dev_cols_ex%d_%d" % (n, p)) for n in (17, 16) for p in (4, 2, 1)]
     + [("dev_conv.hip", ["-DHE_LOGN=%d" % n], "dev_conv%d" % n) for n in (17, 16)]
+    + [("dev_n12.hip", ["-DHE_FEW=1"], "dev_n12_few")]  # its conversions of one and two sources
     + [(s, [], os.path.splitext(s)[0]) for s in ("dev_n12.hip", "dev_n16_blocks.hip", "dev_n17_blocks.hip", "device.hip", "host.cpp")]
 )
 OBJDIR = os.path.join(HERE, "_build")

@@ -1,7 +1,7 @@
 // Kernel launch plumbing shared by the translation units of the device library.
 //
 // The kernels are templates over the ring size; each ring size is instantiated in a translation unit of
-// its own (dev_n12.hip, dev_n16_blocks.hip, dev_n17_blocks.hip, dev_conv.hip once per larger ring size, and dev_cols.hip once per larger
+// its own (dev_n12.hip twice, dev_n16_blocks.hip, dev_n17_blocks.hip, dev_conv.hip once per larger ring size, and dev_cols.hip once per larger
 // ring size and prologue) so that the library builds in parallel, and device.hip reaches them through one table of launchers per ring size.
 #pragma once
 #include <hip/hip_runtime.h>
