@@ -172,9 +172,11 @@ __global__ __launch_bounds__(N12_THREADS, EPI == EPI_FIN ? 4 : 1) void k_ntt_fwd
     const ModConst m = T.mod[mi];
     const ConvSetup<NSMAX> S = conv_setup<PRO, NSMAX, 12>(cv, T, slot, mi);
     u64 uv[EPI == EPI_FIN ? 8 : 1];
+    FinAt at = {0, 0, 0};
     if (EPI == EPI_FIN) {
+        at = fin_at<12>(fa, slot);
 #pragma unroll
-        for (int k = 0; k < 8; k++) uv[k] = __builtin_nontemporal_load(fa.u + (((size_t)fin_limb(fa, slot, fa.u_stride, fa.u_cstride) << 12) + nb + 64 * k));
+        for (int k = 0; k < 8; k++) uv[k] = __builtin_nontemporal_load(fa.u + at.u + nb + 64 * k);
     }
     conv_variant12<PRO, NSMAX, EX, true>(T, mi, m, S.qld, [&](auto ar, auto split, auto tint) {
         typedef decltype(ar) A;
@@ -186,7 +188,7 @@ __global__ __launch_bounds__(N12_THREADS, EPI == EPI_FIN ? 4 : 1) void k_ntt_fwd
         for (int k = 0; k < 8; k++) {
             const unsigned pos = nb + 64 * k;
             if (EPI == EPI_FIN)
-                fin_store<12>(fa, slot, pos, fin_value<A::IS_FP>(fa, T, slot, v[k], uv[k]));
+                fin_store(fa, at, pos, fin_value<A::IS_FP>(fa, T, at, v[k], uv[k]));
             else
                 limb[pos] = v[k];
         }

@@ -329,36 +329,37 @@ __device__ __forceinline__ u64 conv_get(const ConvSetup<NSMAX> &S, const ArithIn
 
 // ---- epilogue: what the forward block pass does with a finished (canonical) NTT value ---------------------
 
-// Limb of destination slot `slot` in a buffer with these strides.
-__device__ __forceinline__ unsigned fin_limb(const FinArgs &fa, unsigned slot, int stride, int cstride)
+// The limb of destination slot `slot`: where its minuend and its result lie (words), its modulus index (the limb within its component).
+struct FinAt {
+    size_t u, out;
+    unsigned i;
+};
+template <int LOGN> __device__ __forceinline__ FinAt fin_at(const FinArgs &fa, unsigned slot)
 {
     const unsigned op = slot / (unsigned)fa.dst_stride;
     slot -= op * (unsigned)fa.dst_stride;
-    return op * (unsigned)stride + slot / (unsigned)fa.nl * (unsigned)cstride + slot % (unsigned)fa.nl;
+    const unsigned c = slot / (unsigned)fa.nl, i = slot % (unsigned)fa.nl;
+    return {(size_t)(op * fa.u_stride + c * fa.u_cstride + i) << LOGN, (size_t)(op * fa.out_stride + c * fa.out_cstride + i) << LOGN, i};
 }
-// modulus index: the limb within its component
-__device__ __forceinline__ unsigned fin_mod(const FinArgs &fa, unsigned slot) { return slot % (unsigned)fa.dst_stride % (unsigned)fa.nl; }
 // The minuends of two neighbouring outputs: issued before the transform so that the load overlaps it.
-template <int LOGN> __device__ __forceinline__ u64x2 fin_load(const FinArgs &fa, unsigned slot, unsigned pos)
+__device__ __forceinline__ u64x2 fin_load(const FinArgs &fa, const FinAt &at, unsigned pos)
 {
-    return __builtin_nontemporal_load((const u64x2u *)(fa.u + (((size_t)fin_limb(fa, slot, fa.u_stride, fa.u_cstride) << LOGN) + pos)));
+    return __builtin_nontemporal_load((const u64x2u *)(fa.u + at.u + pos));
 }
 // FP: the limb's modulus is on the floating-point path (known from the transform's arithmetic at compile time)
-template <bool FP> __device__ __forceinline__ u64 fin_value(const FinArgs &fa, const DevTables &T, unsigned slot, u64 rv, u64 uv)
+template <bool FP> __device__ __forceinline__ u64 fin_value(const FinArgs &fa, const DevTables &T, const FinAt &at, u64 rv, u64 uv)
 {
-    const unsigned i = fin_mod(fa, slot);
-    const ModConst m = T.mod[i];
-    if (FP) return fp_canon(fp_mulmod(u2d(uv) - u2d(rv), fa.cst_d[i], m.qd, m.qinvd), m.qd, m.qinvd);
-    return mul_shoup(uv + m.q - rv, fa.cst[i], m.q);
+    const ModConst m = T.mod[at.i];
+    if (FP) return fp_canon(fp_mulmod(u2d(uv) - u2d(rv), fa.cst_d[at.i], m.qd, m.qinvd), m.qd, m.qinvd);
+    return mul_shoup(uv + m.q - rv, fa.cst[at.i], m.q);
 }
-template <bool FP> __device__ __forceinline__ u64x2 fin_value(const FinArgs &fa, const DevTables &T, unsigned slot, u64x2 rv, u64x2 uv)
+template <bool FP> __device__ __forceinline__ u64x2 fin_value(const FinArgs &fa, const DevTables &T, const FinAt &at, u64x2 rv, u64x2 uv)
 {
-    return u64x2{fin_value<FP>(fa, T, slot, (u64)rv.x, (u64)uv.x), fin_value<FP>(fa, T, slot, (u64)rv.y, (u64)uv.y)};
+    return u64x2{fin_value<FP>(fa, T, at, (u64)rv.x, (u64)uv.x), fin_value<FP>(fa, T, at, (u64)rv.y, (u64)uv.y)};
 }
-template <int LOGN, class Tv> __device__ __forceinline__ void fin_store(const FinArgs &fa, unsigned slot, unsigned pos, Tv res) // Tv: u64 or u64x2u
+template <class Tv> __device__ __forceinline__ void fin_store(const FinArgs &fa, const FinAt &at, unsigned pos, Tv res) // Tv: u64 or u64x2u
 {
-    // a result: nothing in this launch reads it
-    __builtin_nontemporal_store(res, (Tv *)(fa.out + (((size_t)fin_limb(fa, slot, fa.out_stride, fa.out_cstride) << LOGN) + pos)));
+    __builtin_nontemporal_store(res, (Tv *)(fa.out + at.out + pos)); // a result: nothing in this launch reads it
 }
 
 // LDS of the block pass, element i of block grp: one pad word per 16 elements and 16 per block keep all its patterns free of bank conflicts.
@@ -531,9 +532,11 @@ __device__ __forceinline__ void fwd_blocks_body(u64 *__restrict__ limb, const A 
 #pragma unroll
         for (int k = 0; k < 8; k++) a[k] = ar.load_mid(__builtin_nontemporal_load(limb + bg * 256 + b.t + 32 * k)); // read once: the column pass wrote it
     }
+    FinAt at = {0, 0, 0};
     if (EPI != EPI_STORE) {
+        at = fin_at<LOGN>(fa, slot);
 #pragma unroll
-        for (int i = 0; i < 4; i++) uv[i] = fin_load<LOGN>(fa, slot, pos + 128 * i);
+        for (int i = 0; i < 4; i++) uv[i] = fin_load(fa, at, pos + 128 * i);
     }
     block_pass8(ar, a, b, [&](int m, unsigned i) { return block_twiddle<LOGN>(ar.twf, bg, m, i); });
     block_sync();
@@ -544,16 +547,16 @@ __device__ __forceinline__ void fwd_blocks_body(u64 *__restrict__ limb, const A 
         if (EPI == EPI_STORE)
             __builtin_nontemporal_store((u64x2u)v, (u64x2u *)(limb + pos + 128 * i));
         else {
-            const u64x2 res = fin_value<A::IS_FP>(fa, T, slot, v, uv[i]);
+            const u64x2 res = fin_value<A::IS_FP>(fa, T, at, v, uv[i]);
             if (EPI == EPI_FIN)
-                fin_store<LOGN, u64x2u>(fa, slot, pos + 128 * i, res);
+                fin_store<u64x2u>(fa, at, pos + 128 * i, res);
             else
                 w[0] = res.x, w[1] = res.y;
         }
     }
     if constexpr (EPI == EPI_FIN_INV) {
         block_sync();
-        inv_blocks_wave<LOGN>(fa.out + ((size_t)fin_limb(fa, slot, fa.out_stride, fa.out_cstride) << LOGN), bg, ar, b, false);
+        inv_blocks_wave<LOGN>(fa.out + at.out, bg, ar, b, false);
     }
 }
 
