@@ -485,6 +485,51 @@ template <int LOGN, class Tv> __device__ __forceinline__ Tv block_twiddle(const 
     return tw[(1u << (LOGN - 8 + m)) + (G << m) + i];
 }
 
+// block_pass8 with the twiddles requested ahead: those of the first two steps before the values are waited for (`first`), those of the third behind the
+// first step.  For the epilogues, which take more than 64 registers in any case: launches whose waves are all resident at once run the three waits in
+// step (a rescale of 46 limbs at N = 2^16: 17.9 -> 16.5 us); the plain pass, eight waves per SIMD without, loses by it (34 limbs 21.6 -> 22.8 with the column pass).
+template <int LOGN> struct BlockTwiddles {
+    double w1[7], w2[7], w3[6];
+    __device__ __forceinline__ void first(const double *tw, const BlockLane &b, unsigned G)
+    {
+#pragma unroll
+        for (int sp = 0; sp < 3; sp++)
+#pragma unroll
+            for (int g = 0; g < (1 << sp); g++) {
+                w1[(1 << sp) - 1 + g] = block_twiddle<LOGN>(tw, G, sp, (unsigned)g);
+                w2[(1 << sp) - 1 + g] = block_twiddle<LOGN>(tw, G, 3 + sp, (b.g2 << sp) + g);
+            }
+    }
+    __device__ __forceinline__ void third(const double *tw, const BlockLane &b, unsigned G)
+    {
+#pragma unroll
+        for (int h = 0; h < 2; h++)
+#pragma unroll
+            for (int sp = 0; sp < 2; sp++)
+#pragma unroll
+                for (int g = 0; g < (1 << sp); g++) w3[3 * h + (1 << sp) - 1 + g] = block_twiddle<LOGN>(tw, G, 6 + sp, ((b.t + 32 * h) << sp) + g);
+    }
+};
+template <int LOGN> __device__ __forceinline__ void block_pass8(const ArithFp &ar, double (&dv)[8], const BlockLane &b, unsigned G, BlockTwiddles<LOGN> &w)
+{
+    ar.fwd8_with(dv, true, [&](int sp, int g) { return w.w1[(1 << sp) - 1 + g]; });
+    w.third(ar.twf, b, G);
+    __builtin_amdgcn_sched_barrier(0); // or the compiler asks for them where they are used
+#pragma unroll
+    for (int k = 0; k < 8; k++) b.l1[34 * k] = ar.store_mid(dv[k]);
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(b.l2[4 * k + (k >> 2)]);
+    ar.fwd8_with(dv, false, [&](int sp, int g) { return w.w2[(1 << sp) - 1 + g]; });
+#pragma unroll
+    for (int k = 0; k < 8; k++) b.l2[4 * k + (k >> 2)] = ar.store_mid(dv[k]);
+    block_sync();
+#pragma unroll
+    for (int k = 0; k < 8; k++) dv[k] = ar.load_mid(b.l3[136 * (k >> 2) + (k & 3)]);
+    ar.fwd4x2_with(dv, true, [&](int h, int sp, int g) { return w.w3[3 * h + (1 << sp) - 1 + g]; });
+#pragma unroll
+    for (int k = 0; k < 8; k++) b.l3[136 * (k >> 2) + (k & 3)] = ar.store_mid(dv[k]);
+}
 
 // Product of two residues, canonical.
 __device__ __forceinline__ u64 mul_residues(u64 x, u64 y, const ModConst &m, const ArithFp &)
@@ -523,6 +568,8 @@ __device__ __forceinline__ void fwd_blocks_body(u64 *__restrict__ limb, const A 
     u64 *wlds = lds + wave_id() * WAVE_BLOCKS * TILE_GROUP;
     const BlockLane b = block_lane(wlds, nullptr);
     const unsigned b0 = tile * BLK_PER_WG + wave_id() * WAVE_BLOCKS, bg = b0 + b.blk; // block index within the limb
+    BlockTwiddles<LOGN> tw;
+    if constexpr (A::IS_FP && EPI != EPI_STORE) tw.first(ar.twf, b, bg);
     typename A::V a[8];
     u64x2 uv[EPI == EPI_STORE ? 1 : 4];
     const unsigned pos = b0 * 256 + 2u * (threadIdx.x & 63u); // of the first of this lane's pairs, 128 apart
@@ -538,7 +585,11 @@ __device__ __forceinline__ void fwd_blocks_body(u64 *__restrict__ limb, const A 
 #pragma unroll
         for (int i = 0; i < 4; i++) uv[i] = fin_load(fa, at, pos + 128 * i);
     }
-    block_pass8(ar, a, b, [&](int m, unsigned i) { return block_twiddle<LOGN>(ar.twf, bg, m, i); });
+    if constexpr (A::IS_FP && EPI != EPI_STORE) __builtin_amdgcn_sched_barrier(0);
+    if constexpr (A::IS_FP && EPI != EPI_STORE)
+        block_pass8(ar, a, b, bg, tw);
+    else
+        block_pass8(ar, a, b, [&](int m, unsigned i) { return block_twiddle<LOGN>(ar.twf, bg, m, i); });
     block_sync();
 #pragma unroll
     for (int i = 0; i < 4; i++) {
