@@ -110,6 +110,7 @@ struct he_ctx {
     DevTables dev{};
     std::vector<void *> dev_allocs;
     u64 *static_scratch = nullptr; // address, on this context's device, of the library's file-scope scratch array
+    void *copy_kernel = nullptr;   // hipFunction_t of k_copy_limbs on that device
     mutable std::string hip_err;
     bool prof_on = false;
     std::vector<ProfRecord> prof;
