@@ -120,12 +120,13 @@ def test_products_over_their_factors(env):
             assert np.array_equal(he.to_host(f), prod), level
 
 
-# name -> (parameters, levels, counts): launches of the special limbs on both sides of the 1024 work-groups from which their digits are
-# finished ahead (64 per limb and operation at N = 2^16; one or two digits, or three with a dropped limb)
+# name -> (parameters, levels, counts, levels whose digits are finished ahead in the larger count's products with rescale): launches of the special
+# limbs on both sides of the 1024 work-groups from which one or two digits are finished ahead (64 per limb and operation at N = 2^16); three keep three
+# of the four waves busy and are not
 BATCHES = {
-    "N16": (wl.N16, (4, 7), (3, 4)),
-    "mixed16": (SETS["mixed16"], (5, 6), (5, 8)),  # a dropped limb on either path
-    "float16": (wl.Params("float16", 16, wl.N16.q[:3], (wl.N16.q[3],), 3), (3,), (16,)),  # no special limb on the integer path
+    "N16": (wl.N16, (4, 7), (3, 4), (4, 7)),
+    "mixed16": (SETS["mixed16"], (3, 4, 5, 6), (5, 8), (3, 4)),  # a dropped limb on either path
+    "float16": (wl.Params("float16", 16, wl.N16.q[:3], (wl.N16.q[3],), 3), (3,), (16,), ()),  # no special limb on the integer path
 }
 
 
@@ -135,7 +136,7 @@ def test_special_limbs_of_small_and_large_launches(oracle_mod, name):
 
     import paper_2210_02574_amd as pkg
 
-    p, levels, counts = BATCHES[name]
+    p, levels, counts, ahead = BATCHES[name]
     he, o, evk = pkg.HE.from_params(p, device=0), oracle_mod.Oracle(p.logN, p.q, p.p, p.dnum), wl.uniform_evk(9, p)
     relin, rot = he.evk_from_host(evk, 1), he.evk_from_host(evk, he.galois_element(3))
     for level in levels:
@@ -147,7 +148,9 @@ def test_special_limbs_of_small_and_large_launches(oracle_mod, name):
             got = he.to_host(he.hrot_batch(rot, dev[:count]))
             assert all(np.array_equal(got[i], rotated[i]) for i in range(count)), (level, count)
             shifted = torch.roll(dev, 1, 0)[:count].contiguous()
+            he.profile_start()
             got = he.to_host(he.hmult_relin_rescale_batch(relin, dev[:count], shifted))
+            assert ("k_inner_finished" in he.profile_stop()) == (count == counts[-1] and level in ahead), (level, count)
             assert all(np.array_equal(got[i], products[i]) for i in range(count)), (level, count)
         for count in (2, 3):  # shared digits
             for got in he.hrot_many([rot] * count, dev[0]):
