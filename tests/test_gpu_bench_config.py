@@ -47,10 +47,9 @@ def test_bench_step_outputs_match_oracle(oracle_mod, n_streams):
         assert np.array_equal(got, o.hrot(he.to_host(w.single_in[i]), evk, w.offsets[k])), i
 
 
-def test_full_batches_span_several_launches(oracle_mod):
-    """The batch sizes that bench.py times: 16 products per call (2304 raised limbs, more than one launch of the
-    conversion passes can carry, so the list is split) and 32 mixed-level rotations per call.  Operations on both sides
-    of every split, the first and the last are compared with the oracle bit for bit."""
+def test_full_batches(oracle_mod):
+    """The batch sizes that bench.py times: 16 products per call and 32 mixed-level rotations per call.  The first operation, the last and some in
+    between are compared with the oracle bit for bit."""
     import torch
 
     import bench
@@ -76,3 +75,44 @@ def test_full_batches_span_several_launches(oracle_mod):
         got = he.to_host(w.single_out[i])
         assert got.shape[1] == w.single_levels[i]
         assert np.array_equal(got, o.hrot(he.to_host(w.single_in[i]), evk, w.offsets[k])), (pos, i)
+
+
+# name -> (parameters, corrected conversion, the kernel whose limbs are listed): calls whose raised limbs, 144 per operation, are more than the
+# 2048 that one launch's list holds, so that they are split, within operation 7
+SPLITS = {
+    "N12": (wl.B12, False, "k_ntt_fwd12_modup"),
+    "N16 corrected": (wl.N16, True, "k_ntt_fwd_cols_modup"),
+}
+
+
+@pytest.mark.parametrize("name", SPLITS)
+def test_lists_of_limbs_span_several_launches(name, oracle_mod):
+    import torch
+
+    import paper_2210_02574_amd as pkg
+
+    p, exact, kernel = SPLITS[name]
+    count, level = 15, p.L
+    he, o, evk = pkg.HE.from_params(p, device=0), oracle_mod.Oracle(p.logN, p.q, p.p, p.dnum), wl.uniform_evk(21, p)
+    he.set_exact_conversion(exact)
+    rot, relin = he.evk_from_host(evk, he.galois_element(3)), he.evk_from_host(evk, 1)
+    host = [wl.uniform_ct(400 + i, p, level) for i in range(count)]
+    dev = torch.stack([he.to_device(ct) for ct in host])
+    some = [0, 6, 7, 8, count - 1] if p.logN > 12 else range(count)  # on both sides of the split
+
+    def split(call):
+        he.profile_start()
+        out = he.to_host(call())
+        assert he.profile_stop()[kernel][0] == 2
+        return out
+
+    o.set_exact(exact)
+    try:
+        got = split(lambda: he.hrot_batch(rot, dev))
+        for i in some:
+            assert np.array_equal(got[i], o.hrot(host[i], evk, 3)), i
+        got = split(lambda: he.hmult_relin_rescale_batch(relin, dev, torch.roll(dev, 1, 0).contiguous()))
+        for i in some:
+            assert np.array_equal(got[i], o.rescale(o.hmult_relin(host[i], host[i - 1], evk))), i
+    finally:
+        o.set_exact(False)
