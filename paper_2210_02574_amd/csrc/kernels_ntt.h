@@ -389,7 +389,7 @@ __device__ __forceinline__ unsigned col_at(unsigned r, unsigned c) { return (r >
 // 128 h + 4 t + k' at 4 t + (t >> 2) + 136 h + k').
 //
 // Bound by memory in large launches, by the chain of one wave in small ones.  With 16 elements per lane, 16 lanes a block, two steps of four stages
-// and one exchange, the kernels took 79 to 118 registers and four waves per SIMD; now 59 to 64 (with an epilogue 85 and 100) and eight.  Transforms of
+// and one exchange, the kernels took 79 to 118 registers and four waves per SIMD; now 59 to 64 (with an epilogue 62 to 98, five to eight waves) and eight.  Transforms of
 // 64 limbs at N = 2^16 34.0 -> 30.8 us, of 256 103 -> 101, of 34 at N = 2^17 40.5 -> 39.8.
 #define WAVE_BLOCKS 2
 #define BLK_THREADS 256
@@ -560,8 +560,13 @@ template <int LOGN, class A> __device__ __forceinline__ void inv_blocks_wave(u64
             o[32 * k] = ar.store_mid(v[k]);
     }
 }
-// PAIR: the column pass has interleaved the rows; a wave's two blocks are a pair, so that the result may still go in their place
-template <int LOGN, int EPI, bool PAIR, class A>
+// PAIR: the column pass has interleaved the rows; a wave's two blocks are a pair, so that the result may still go in their place.
+// AHEAD (with an epilogue): twiddles and minuends are requested ahead of where they are used, which takes 88 registers, five waves per SIMD.  A rescale's
+// launch that needs more waves than that to be resident at once asks for the minuends behind the transform, in 62 registers, eight waves.  N = 2^16, the
+// kernel and a rescale that is waited for: 24 limbs 8.5 us ahead, 9.9 behind (43.8, 45.0), 38 13.4 and 13.3 (48.7, 48.8), 42 15.0 and 15.0 (50.4, 50.3), 48
+// 17.4 and 15.3 (53.7, 52.2), 56 19.4 and 17.4 (56.7, 54.0), 736 193.5 and 191.3 (341, 339).  (16 elements per lane, four waves: 24 limbs 9.9, 48 14.1, 56 19.4, 736 195.)
+#define FIN_AHEAD_GROUPS (5 * 256)
+template <int LOGN, int EPI, bool PAIR, bool AHEAD, class A>
 __device__ __forceinline__ void fwd_blocks_body(u64 *__restrict__ limb, const A &ar, u64 *lds, unsigned tile,
                                                 const FinArgs &fa, const DevTables &T, unsigned slot)
 {
@@ -569,7 +574,7 @@ __device__ __forceinline__ void fwd_blocks_body(u64 *__restrict__ limb, const A 
     const BlockLane b = block_lane(wlds, nullptr);
     const unsigned b0 = tile * BLK_PER_WG + wave_id() * WAVE_BLOCKS, bg = b0 + b.blk; // block index within the limb
     BlockTwiddles<LOGN> tw;
-    if constexpr (A::IS_FP && EPI != EPI_STORE) tw.first(ar.twf, b, bg);
+    if constexpr (A::IS_FP && AHEAD) tw.first(ar.twf, b, bg);
     typename A::V a[8];
     u64x2 uv[EPI == EPI_STORE ? 1 : 4];
     const unsigned pos = b0 * 256 + 2u * (threadIdx.x & 63u); // of the first of this lane's pairs, 128 apart
@@ -580,16 +585,21 @@ __device__ __forceinline__ void fwd_blocks_body(u64 *__restrict__ limb, const A 
         for (int k = 0; k < 8; k++) a[k] = ar.load_mid(__builtin_nontemporal_load(limb + bg * 256 + b.t + 32 * k)); // read once: the column pass wrote it
     }
     FinAt at = {0, 0, 0};
-    if (EPI != EPI_STORE) {
+    const auto minuends = [&] {
         at = fin_at<LOGN>(fa, slot);
 #pragma unroll
         for (int i = 0; i < 4; i++) uv[i] = fin_load(fa, at, pos + 128 * i);
-    }
-    if constexpr (A::IS_FP && EPI != EPI_STORE) __builtin_amdgcn_sched_barrier(0);
-    if constexpr (A::IS_FP && EPI != EPI_STORE)
+    };
+    if (EPI != EPI_STORE && AHEAD) minuends();
+    if constexpr (A::IS_FP && AHEAD) {
+        __builtin_amdgcn_sched_barrier(0);
         block_pass8(ar, a, b, bg, tw);
-    else
+    } else
         block_pass8(ar, a, b, [&](int m, unsigned i) { return block_twiddle<LOGN>(ar.twf, bg, m, i); });
+    if (EPI != EPI_STORE && !AHEAD) {
+        __builtin_amdgcn_sched_barrier(0);
+        minuends();
+    }
     block_sync();
 #pragma unroll
     for (int i = 0; i < 4; i++) {
@@ -636,7 +646,7 @@ __device__ __forceinline__ void inv_blocks_body(const u64 *in, const u64 *in2, u
 }
 
 // grid.x = (N / (256 BLK_PER_WG)) * batch
-template <int LOGN, int EPI, bool PAIR>
+template <int LOGN, int EPI, bool PAIR, bool AHEAD>
 __global__ __launch_bounds__(BLK_THREADS, 4) void k_ntt_fwd_blocks(u64 *__restrict__ data, DevTables T, LimbBatch lb, FinArgs fa)
 {
     __shared__ __align__(16) u64 lds[BLK_LDS];
@@ -645,9 +655,9 @@ __global__ __launch_bounds__(BLK_THREADS, 4) void k_ntt_fwd_blocks(u64 *__restri
     const unsigned mi = lb.mod[b], slot = lb.slot[b];
     u64 *limb = data + ((size_t)slot << LOGN);
     if (T.mod[mi].qd != 0.0)
-        fwd_blocks_body<LOGN, EPI, PAIR>(limb, make_fp(T, mi, LOGN), lds, tile, fa, T, slot);
+        fwd_blocks_body<LOGN, EPI, PAIR, AHEAD>(limb, make_fp(T, mi, LOGN), lds, tile, fa, T, slot);
     else
-        fwd_blocks_body<LOGN, EPI, PAIR>(limb, make_int(T, mi, LOGN), lds, tile, fa, T, slot);
+        fwd_blocks_body<LOGN, EPI, PAIR, AHEAD>(limb, make_int(T, mi, LOGN), lds, tile, fa, T, slot);
 }
 
 // src2: with PROD, the second factor, at the same limbs as src

@@ -99,13 +99,15 @@ static void launch_fwd_blocks(he_ctx *c, hipStream_t st, double bytes, int epi, 
 {
     const int grid = BLK_TILES(c) * nb;
     if (epi == EPI_FIN_INV) // of a Mult's dropped limb, behind its ModDown
-        KLAUNCH_T(c, st, KID_FWD_BLOCKS_FIN, bytes, (k_ntt_fwd_blocks<LOGN, EPI_FIN_INV, true>), grid, BLK_THREADS, data, c->dev, lb, fa);
-    else if (epi == EPI_FIN) // of a rescale
-        KLAUNCH_T(c, st, KID_FWD_BLOCKS_FIN, bytes, (k_ntt_fwd_blocks<LOGN, EPI_FIN, false>), grid, BLK_THREADS, data, c->dev, lb, fa);
+        KLAUNCH_T(c, st, KID_FWD_BLOCKS_FIN, bytes, (k_ntt_fwd_blocks<LOGN, EPI_FIN_INV, true, true>), grid, BLK_THREADS, data, c->dev, lb, fa);
+    else if (epi == EPI_FIN && grid <= FIN_AHEAD_GROUPS) // of a rescale
+        KLAUNCH_T(c, st, KID_FWD_BLOCKS_FIN, bytes, (k_ntt_fwd_blocks<LOGN, EPI_FIN, false, true>), grid, BLK_THREADS, data, c->dev, lb, fa);
+    else if (epi == EPI_FIN)
+        KLAUNCH_T(c, st, KID_FWD_BLOCKS_FIN, bytes, (k_ntt_fwd_blocks<LOGN, EPI_FIN, false, false>), grid, BLK_THREADS, data, c->dev, lb, fa);
     else if (pairs)
-        KLAUNCH_T(c, st, KID_FWD_BLOCKS, bytes, (k_ntt_fwd_blocks<LOGN, EPI_STORE, true>), grid, BLK_THREADS, data, c->dev, lb, fa);
+        KLAUNCH_T(c, st, KID_FWD_BLOCKS, bytes, (k_ntt_fwd_blocks<LOGN, EPI_STORE, true, false>), grid, BLK_THREADS, data, c->dev, lb, fa);
     else
-        KLAUNCH_T(c, st, KID_FWD_BLOCKS, bytes, (k_ntt_fwd_blocks<LOGN, EPI_STORE, false>), grid, BLK_THREADS, data, c->dev, lb, fa);
+        KLAUNCH_T(c, st, KID_FWD_BLOCKS, bytes, (k_ntt_fwd_blocks<LOGN, EPI_STORE, false, false>), grid, BLK_THREADS, data, c->dev, lb, fa);
 }
 template <int LOGN>
 static void launch_inv_blocks(he_ctx *c, hipStream_t st, double bytes, const u64 *src, const u64 *src2, u64 *dst,

@@ -157,6 +157,19 @@ def test_special_limbs_of_small_and_large_launches(oracle_mod, name):
                 assert np.array_equal(he.to_host(got), rotated[0]), (level, count)
 
 
+# launches of up to 1280 work-groups of a rescale's last pass (40 limbs at N = 2^16, 20 at 2^17) and larger ones, on either arithmetic path
+@pytest.mark.parametrize("params,level,count", [(wl.N16, 21, 1), (wl.N16, 22, 1), (SETS["mixed16"], 6, 4), (SETS["mixed16"], 6, 5), (wl.P17, 11, 1), (wl.P17, 12, 1)],
+                         ids=lambda v: getattr(v, "name", v))
+def test_rescales_of_small_and_large_launches(oracle_mod, params, level, count):
+    import paper_2210_02574_amd as pkg
+
+    he, o = pkg.HE.from_params(params, device=0), oracle_mod.Oracle(params.logN, params.q, params.p, params.dnum)
+    cts = np.stack([wl.uniform_ct(350 + i, params, level) for i in range(count)])
+    cts[0, 0] = np.array(params.q[:level], dtype=np.uint64)[:, None] - 1  # the largest residues
+    got = he.to_host(he.rescale_batch(he.to_device(cts)))
+    assert all(np.array_equal(got[i], o.rescale(cts[i])) for i in range(count))
+
+
 def test_product_over_a_factor_in_a_graph():
     """The copy that such a result takes can be captured: three replays with eager work in between."""
     import torch
