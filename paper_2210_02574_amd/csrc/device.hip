@@ -281,6 +281,7 @@ struct LimbList {
     std::vector<int> slot, src, mod;
     void add(int s, int m) { slot.push_back(s), src.push_back(s), mod.push_back(m); }
     void add(int s, int from, int m) { slot.push_back(s), src.push_back(from), mod.push_back(m); }
+    void reserve(int n) { slot.reserve(n), src.reserve(n), mod.reserve(n); }
     int size() const { return (int)slot.size(); }
 };
 
@@ -717,15 +718,15 @@ static int32_t ks_raise(he_ctx *c, const u64 *d_ntt, F from, u64 *ws, const WsLa
     // limbs that go through a column pass or a block pass of their own; listed once the first launches are on their way
     LimbList r;
     const auto list_raised = [&] {
+        const int from = fused ? finish_at : 0; // modulus index
+        if (from < c->M) r.reserve(cw.targets);
         for (int o = 0; o < count; o++) {
             const int lo = level_of(o), beta = (lo + c->alpha - 1) / c->alpha;
             for (int j = 0; j < beta; j++) {
-                const int dlo = j * c->alpha, dhi = std::min(dlo + c->alpha, lo);
-                for (int a = fused ? std::min(finish_at, level) : 0; a < Ma; a++) {
-                    const int mi = active_mod(a, level, c->L);
-                    if ((a >= dlo && a < dhi) || (a >= lo && a < level) || (fused && mi < finish_at)) continue;
-                    r.add(o * W + j * Ma + a, mi);
-                }
+                const int dlo = j * c->alpha, dhi = std::min(dlo + c->alpha, lo), slot = o * W + j * Ma;
+                for (int i = from; i < dlo; i++) r.add(slot + i, i);
+                for (int i = std::max(from, dhi); i < lo; i++) r.add(slot + i, i);
+                for (int k = std::max(from - c->L, 0); k < K; k++) r.add(slot + level + k, c->L + k);
             }
         }
     };
