@@ -120,9 +120,11 @@ __device__ __forceinline__ u64 fp_canon(double v, double q, double qinv)
 // constant) and n1 = n0 * twiddle into stage 0.
 //
 // ArithFp ranges: values are signed; a stage takes |v| to at most 1.1875 |v| + q/2.  A forward phase of four stages entered with |v| <= 1q
-// (canonical input) ends below 4.7q; with reduce_first the first half, which its first stage does not multiply, is reduced, and from |v| <= 7.2q it
-// ends below 5.8q (reducing both halves took 24 instructions more of about 950 for a target of ModUp); an inverse phase reduces the sum path at its
-// second and fourth stage and never exceeds 7.4q.  Everything stays below 8q < 2^53.
+// (canonical input) ends below 4.7q, with |v| <= 1.5q (a conversion's sum) below 5.7q; with reduce_first the first half, which its first stage does not
+// multiply, is reduced, and from |v| <= 7.2q it ends below 5.8q, from 8q, the most that a conversion makes (ModUp of eight sources split at bit 31: half a q
+// from the first four, 4q from the others, less 7 times the digit's product for the overshoot, 3.5q), below 6q (reducing both halves took 24 instructions
+// more of about 950 for a target of ModUp); an inverse phase reduces the sum path at its second and fourth stage and never exceeds 7.4q.  Nothing exceeds
+// 8q <= 2^53, so that values are exact, and a product's quotient 4q <= 2^52, so that it is rounded to an integer.
 
 // index of twiddle c (stage sp's at c = 2^sp - 1 .. 2^(sp+1) - 2) of the 16-element step that starts at stage s_base in group G
 __device__ __forceinline__ unsigned step16_twiddle(unsigned s_base, unsigned G, unsigned c)
@@ -295,7 +297,7 @@ struct ArithFp {
         }
     }
     // Stage 0 of a 32-element column step (N = 2^17): pairs (lo[k], hi[k]) are N/2 apart, twiddle index 1.
-    // Forward: inputs within 1q of zero (reduced or canonical).  Inverse: last stage, with the 1/N factors.
+    // Forward: inputs within 1.5q of zero (reduced, canonical or a conversion's sum) unless reduce_first.  Inverse: last stage, with the 1/N factors.
     __device__ __forceinline__ void fwd_stage0(V (&lo)[16], V (&hi)[16], bool reduce_first) const
     {
         const double w = twf[1];

@@ -3,7 +3,8 @@
 // Bound by the arithmetic units (0.81 of their issue slots for eight rotations at N = 2^16, level 24) at the clock that the power
 // limit leaves them.  Against a column pass of its own for the inverse transform and a ModUp pass that read a digit's sources through L2 for every two
 // targets, 56 instead of 72 FP64 instructions per output: one rotation at level 13 7.5 + 24.4 -> 19.7 us, eight at level 24
-// 41 + 290 -> 285 us, four at N = 2^17, level 30, 57 + 584 -> 490 us; 16 products with rescale 1827 -> 1695 us as a call.
+// 41 + 290 -> 285 us, four at N = 2^17, level 30, 57 + 584 -> 490 us; 16 products with rescale 1827 -> 1695 us as a call (by this
+// kernel alone; later steps took them further).
 //
 // ModDown's corrections, one rotation at level 13: 10.0 + 13.2 -> 19.4 us (inverse column pass of the special limbs and column pass of the
 // corrections before), eight at level 24 32 + 142 -> 132, four at N = 2^17, level 30, 35 + 168 -> 186 (the centring and splitting of a digit
@@ -27,7 +28,7 @@
 // free of bank conflicts; the low and the high halves of the values go through it in turn
 #define CONV_EXCH (16 * 68)
 
-// SOURCES: the most that a conversion has (an eighth of the LDS of a compute unit each at N = 2^17, a twentieth at N = 2^16).
+// SOURCES: the most that a conversion has (a tenth of the LDS of a compute unit each at N = 2^17, a twentieth at N = 2^16).
 template <int LOGN, int SOURCES = 4> struct ConvGeom {
     static constexpr int ROWS = 1 << (LOGN - 8);
     static constexpr int HALVES = ROWS / 256;       // 16-element register steps per lane

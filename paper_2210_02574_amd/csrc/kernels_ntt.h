@@ -97,7 +97,7 @@ struct FinArgs {
     int dst_stride, u_stride, out_stride; // limbs between two operations in each buffer
 };
 
-__host__ __device__ __forceinline__ int active_mod(int a, int level, int L) { return a < level ? a : L + (a - level); }
+__device__ __forceinline__ int active_mod(int a, int level, int L) { return a < level ? a : L + (a - level); }
 
 // NTT-domain index of the automorphism sigma_g: out[k] = in[k'] with
 // 2 brv(k') + 1 = (2 brv(k) + 1) g mod 2N.
@@ -544,9 +544,9 @@ __device__ __forceinline__ unsigned wave_pair_at(int i)
     const unsigned p = 128u * i + 2u * (threadIdx.x & 63u);
     return tile_at(p >> 8, p & 255u);
 }
-// The wave's inverse block pass from canonical residues in its LDS, stored to `limb` as the inverse column pass takes them.  stream: the batch is part
-// of a conversion and far larger than the caches; in place (a plain inverse transform) the column pass that follows finds the
-// stores in the last-level cache
+// The wave's inverse block pass from canonical residues in its LDS, stored to `limb` as the inverse column pass takes them.  stream: out of place, as
+// part of a conversion, whose batch is far larger than the caches as a rule (the few limbs of a single call are stored past them too); in place (a plain
+// inverse transform) the column pass that follows finds the stores in the last-level cache
 template <int LOGN, class A> __device__ __forceinline__ void inv_blocks_wave(u64 *limb, unsigned bg, const A &ar, const BlockLane &b, bool stream)
 {
     typename A::V v[8];
@@ -765,7 +765,8 @@ __device__ __forceinline__ void fwd_cols_body(u64 *__restrict__ limb, unsigned c
 
 // CACHED: a plain transform of at most INV_CACHED bytes, whose values the block pass has left in the last-level cache; a plain load keeps them
 // there for the stores.  Larger launches stream through it (64 limbs of N = 2^16 32.8 us with plain loads, 34.0 with nontemporal ones, 150 66.2 and
-// 64.8, 256 115 and 106; 34 of N = 2^17 40.3 and 42.0, 80 78.7 and 77.2).
+// 64.8, 256 115 and 106; 34 of N = 2^17 40.3 and 42.0, 80 78.7 and 77.2; on buffers in turn, 1.5 GiB of them, 28 limbs of N = 2^16 22.3 and 22.8,
+// 64 34.3 and 35.4, 120 57.2 and 58.0, 34 of N = 2^17 43.0 and 43.6, 60 62.4 and 63.4, 20 and fewer the same).
 #define INV_CACHED (64ull << 20)
 template <int LOGN, bool CACHED, class A>
 __device__ __forceinline__ void inv_cols_body(u64 *__restrict__ limb, unsigned col0, const A &ar, u64 *lds)

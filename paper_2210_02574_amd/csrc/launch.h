@@ -62,7 +62,7 @@ struct DevLaunch {
     void (*inv_blocks)(he_ctx *c, hipStream_t st, double bytes, const u64 *src, const u64 *src2, u64 *dst, const LimbBatch &lb, int nb);
     void (*inv_cols)(he_ctx *c, hipStream_t st, double bytes, int scale, u64 *dst, const LimbBatch &lb, int nb,
                      const ConvArgs &cv);
-    // ModUp of `count` operations with the inverse column pass ahead of it: digits of up to four limbs on the floating-point path
+    // ModUp of `count` operations with the inverse column pass ahead of it: digits of up to eight limbs (N = 2^17: four) on the floating-point path
     void (*modup)(he_ctx *c, hipStream_t st, double bytes, int count, const ModUpArgs &ua);
     // ModDown's corrections of `count` operations with the inverse column pass ahead of it; rs: with a rescale
     void (*moddown)(he_ctx *c, hipStream_t st, double bytes, bool rs, int count, const ModDownArgs &da);
