@@ -766,7 +766,8 @@ __device__ __forceinline__ void fwd_cols_body(u64 *__restrict__ limb, unsigned c
 // CACHED: a plain transform of at most INV_CACHED bytes, whose values the block pass has left in the last-level cache; a plain load keeps them
 // there for the stores.  Larger launches stream through it (64 limbs of N = 2^16 32.8 us with plain loads, 34.0 with nontemporal ones, 150 66.2 and
 // 64.8, 256 115 and 106; 34 of N = 2^17 40.3 and 42.0, 80 78.7 and 77.2; on buffers in turn, 1.5 GiB of them, 28 limbs of N = 2^16 22.3 and 22.8,
-// 64 34.3 and 35.4, 120 57.2 and 58.0, 34 of N = 2^17 43.0 and 43.6, 60 62.4 and 63.4, 20 and fewer the same).
+// 64 34.3 and 35.4, 120 57.2 and 58.0, 34 of N = 2^17 43.0 and 43.6, 60 62.4 and 63.4, 20 and fewer the same; limbs met for the first time, waited
+// for, 34 of N = 2^17 60.8 and 63.1).
 #define INV_CACHED (64ull << 20)
 template <int LOGN, bool CACHED, class A>
 __device__ __forceinline__ void inv_cols_body(u64 *__restrict__ limb, unsigned col0, const A &ar, u64 *lds)
